@@ -1,4 +1,4 @@
-// MFMA paged prefill (chunked prefill) attention kernel for gfx950 (head_dim 128, all four KV formats).
+// MFMA paged prefill (chunked prefill) attention kernel for gfx950 (head_dim 64, 128 and 256, all four KV formats).
 //
 // FineServe Sec. 2.1: the prefill phase processes the prompt's tokens, each attending to the tokens up to
 // itself; Sec. 2.3: it is the compute-intensive phase; Sec. 4.2 schedules it in chunks.  Here a chunk's
@@ -218,16 +218,17 @@ __device__ void prefill_item(const PrefillArgs& P, int seq, int head, int qt, ui
 // tile loop; left pending until there, the compiler's wait-count bookkeeping must assume at the loop head that
 // they may still be in flight, and its wait for them also waits for the K/V loads issued just before -- the
 // very loads the loop is arranged to keep in flight across a whole step.
-__device__ __forceinline__ void settle_q(u32x4 (&q)[4]) {
+template <int KS>
+__device__ __forceinline__ void settle_q(u32x4 (&q)[KS]) {
   uint32_t any = 0;
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) any |= q[ks][0] | q[ks][1] | q[ks][2] | q[ks][3];
+  for (int ks = 0; ks < KS; ++ks) any |= q[ks][0] | q[ks][1] | q[ks][2] | q[ks][3];
   asm volatile("" ::"v"(any));
 }
 
-template <int NCB>
+template <int NCB, int HD = kD>
 struct WideState {
-  float4v acc[NCB][8];
+  float4v acc[NCB][HD / 16];
   float m[NCB], l[NCB], zc[NCB];
 };
 
@@ -241,8 +242,8 @@ struct WideState {
 
 // Moves the reference of column block cb (see the lazy online softmax of fs_mfma_tiles.h): tmax = this lane's
 // largest logit of the tile for its column.
-template <int DT, int NCB>
-__device__ __forceinline__ void wide_move_reference(WideState<NCB>& st, int cb, float tmax, int j) {
+template <int DT, int NCB, int HD>
+__device__ __forceinline__ void wide_move_reference(WideState<NCB, HD>& st, int cb, float tmax, int j) {
   tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
   tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
   const float m_new = fmaxf(st.m[cb], tmax);  // finite: token 0 is seen by every column
@@ -257,7 +258,7 @@ __device__ __forceinline__ void wide_move_reference(WideState<NCB>& st, int cb, 
   for (int r = 0; r < 4; ++r) {
     const float cr = __shfl(corr, 4 * j + r, 64);  // column h keeps its factor in lane c = h
 #pragma unroll
-    for (int e = 0; e < 8; ++e) st.acc[cb][e][r] *= cr;
+    for (int e = 0; e < HD / 16; ++e) st.acc[cb][e][r] *= cr;
   }
   st.m[cb] = m_new;
 }
@@ -354,7 +355,7 @@ __device__ __forceinline__ void wide_tile(const ItemCtx& X, const DevGeom& g, Ti
   }
   if (__any(need)) {
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT, NCB>(st, cb, tmax[cb], j);
+    for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT>(st, cb, tmax[cb], j);
   }
   // ---- weights ----
   u32x4 pk[NCB];
@@ -616,26 +617,29 @@ __global__ __launch_bounds__(kThreads, WPS) void prefill_wide_kernel(PrefillArgs
 // Stage layout: K fragments [sub-tile][u][k-step][lane] 16 B, V fragments [sub-tile][e][lane] 16 B, per-token
 // parameters [sub-tile][lane] 4 B.
 constexpr uint32_t kFrag = 64 * 16;  // one operand fragment of a wave
-// a stage of SUBS sub-tiles: K fragments, V fragments (8 KiB per sub-tile each), parameters
-constexpr uint32_t stage_v(int subs) { return (uint32_t)subs * 8 * kFrag; }
-constexpr uint32_t stage_par(int subs) { return 2 * (uint32_t)subs * 8 * kFrag; }
-constexpr uint32_t stage_bytes(int subs) { return stage_par(subs) + (uint32_t)subs * 256; }
+// K (and V) fragments of a sub-tile: two 16-token halves x HD / 32 k-steps (HD / 16 groups of 16 output columns)
+constexpr int frags(int hd) { return hd / 16; }
+// a stage of SUBS sub-tiles: K fragments, V fragments (8 KiB per sub-tile each at head_dim 128), parameters
+constexpr uint32_t stage_v(int subs, int hd = kD) { return (uint32_t)(subs * frags(hd)) * kFrag; }
+constexpr uint32_t stage_par(int subs, int hd = kD) { return 2 * stage_v(subs, hd); }
+constexpr uint32_t stage_bytes(int subs, int hd = kD) { return stage_par(subs, hd) + (uint32_t)subs * 256; }
 constexpr uint32_t kWgCtlBytes = 16;
 
-template <int DT>
-__device__ __forceinline__ void stage_k(uint8_t* stage, int sub, int lane, Tile<DT, 16>& t) {  // (K fragments lead the stage)
+template <int DT, int HD>
+__device__ __forceinline__ void stage_k(uint8_t* stage, int sub, int lane, Tile<DT, 16, HD>& t) {  // (K fragments lead the stage)
+  constexpr int KS = HD / 32;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    u32x4 a[4];
-    k_operands<DT>(t.k[u], a);
+    u32x4 a[KS];
+    k_operands<DT, HD>(t.k[u], a);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      *reinterpret_cast<u32x4*>(stage + (uint32_t)((sub * 8 + u * 4 + ks) * kFrag) + lane * 16) = a[ks];
+    for (int ks = 0; ks < KS; ++ks)
+      *reinterpret_cast<u32x4*>(stage + (uint32_t)(((sub * 2 + u) * KS + ks) * kFrag) + lane * 16) = a[ks];
   }
 }
-template <int DT, int SUBS>
-__device__ __forceinline__ void stage_v(uint8_t* stage, int sub, int lane, int j, Tile<DT, 16>& t, const ItemCtx& X, int vb) {
-  using F = Fmt<DT>;
+template <int DT, int SUBS, int HD>
+__device__ __forceinline__ void stage_v(uint8_t* stage, int sub, int lane, int j, Tile<DT, 16, HD>& t, const ItemCtx& X, int vb) {
+  using F = Fmt<DT, HD>;
   if constexpr (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3) {
     // slots past the sequence's end may hold NaN/Inf bit patterns; 0 * NaN would poison the MFMA
     const RunLoc L = locate(X, vb + j);
@@ -643,22 +647,22 @@ __device__ __forceinline__ void stage_v(uint8_t* stage, int sub, int lane, int j
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int q = 0; q < F::kVBytes / 4; ++q) t.v[i][q] = i < L.hi_u ? t.v[i][q] : 0u;
+        for (int q = 0; q < F::kVWords; ++q) t.v[i][q] = i < L.hi_u ? t.v[i][q] : 0u;
     }
   }
-  uint32_t vx[8][4];
+  uint32_t vx[8][F::kVRegs];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) v_unpack<DT>(t.v[i], vx[i]);
+  for (int i = 0; i < 8; ++i) v_unpack<DT, HD>(t.v[i], vx[i]);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int reg = DT == FS_KV_INT4 ? (e & 3) : (e >> 1);
-    const uint32_t sel = (DT == FS_KV_INT4 ? (e >> 2) : (e & 1)) ? 0x07060302u : 0x05040100u;
+  for (int e = 0; e < F::kNE; ++e) {
+    const int reg = DT == FS_KV_INT4 ? 4 * (e >> 3) + (e & 3) : (e >> 1);
+    const uint32_t sel = (DT == FS_KV_INT4 ? ((e >> 2) & 1) : (e & 1)) ? 0x07060302u : 0x05040100u;
     u32x4 b;
 #pragma unroll
     for (int q = 0; q < 4; ++q) b[q] = __builtin_amdgcn_perm(vx[2 * q + 1][reg], vx[2 * q][reg], sel);
-    *reinterpret_cast<u32x4*>(stage + stage_v(SUBS) + (uint32_t)((sub * 8 + e) * kFrag) + lane * 16) = b;
+    *reinterpret_cast<u32x4*>(stage + stage_v(SUBS, HD) + (uint32_t)((sub * F::kNE + e) * kFrag) + lane * 16) = b;
   }
-  if constexpr (F::kParBytes != 0) *reinterpret_cast<uint32_t*>(stage + stage_par(SUBS) + sub * 256 + lane * 4) = t.par[0];
+  if constexpr (F::kParBytes != 0) *reinterpret_cast<uint32_t*>(stage + stage_par(SUBS, HD) + sub * 256 + lane * 4) = t.par[0];
 }
 
 // ---- Staged dequantization (INT8 / INT4) ----------------------------------------------------------------------
@@ -788,26 +792,27 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
 
 // One staged 32-token sub-tile for the wave's column blocks: wide_tile with the operands read from LDS.
 // VPRE: V fragments requested in front of the softmax (registers permitting)
-template <int DT, int NCB, int SUBS, int VPRE = 0>
-__device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const ItemCtx& X, const u32x4 (&qb)[NCB][4],
+template <int DT, int NCB, int SUBS, int VPRE, int HD>
+__device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const ItemCtx& X, const u32x4 (&qb)[NCB][HD / 32],
                                         const float (&qsum)[NCB], const int (&len_cb)[NCB], float alpha, int first_pos,
-                                        int vb, int lane, int j, int c, WideState<NCB>& st, bool whole_runs = false) {
-  using F = Fmt<DT>;
+                                        int vb, int lane, int j, int c, WideState<NCB, HD>& st, bool whole_runs = false) {
+  using F = Fmt<DT, HD>;
+  constexpr int KS = HD / 32;
   float4v s[NCB][2];
   // The wave raises its priority for its MFMA sections and drops it for the softmax: of the two waves of a SIMD
   // the one that feeds the matrix pipe goes first, the other's vector work fills in (+ 2.4-3.5 % measured).
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    u32x4 a[4];
+    u32x4 a[KS];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      a[ks] = *reinterpret_cast<const u32x4*>(stage + (uint32_t)((sub * 8 + u * 4 + ks) * kFrag) + lane * 16);
+    for (int ks = 0; ks < KS; ++ks)
+      a[ks] = *reinterpret_cast<const u32x4*>(stage + (uint32_t)(((sub * 2 + u) * KS + ks) * kFrag) + lane * 16);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
       float4v acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) acc = mfma(a[ks], qb[cb][ks], acc);
+      for (int ks = 0; ks < KS; ++ks) acc = mfma(a[ks], qb[cb][ks], acc);
       s[cb][u] = acc;
     }
   }
@@ -817,7 +822,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
   u32x4 vpre[VPRE > 0 ? VPRE : 1];
 #pragma unroll
   for (int e = 0; e < VPRE; ++e)
-    vpre[e] = *reinterpret_cast<const u32x4*>(stage + stage_v(SUBS) + (uint32_t)((sub * 8 + e) * kFrag) + lane * 16);
+    vpre[e] = *reinterpret_cast<const u32x4*>(stage + stage_v(SUBS, HD) + (uint32_t)((sub * F::kNE + e) * kFrag) + lane * 16);
   // interior (wave-uniform): every token of the sub-tile lies at or before the wave's first query token and no run
   // is a shifted one -- nothing to mask.  With whole runs per block the test is scalar arithmetic and the run's
   // location is needed on the mask path only.
@@ -832,7 +837,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
   }
   float ka[8], kb[8], va[8], vb2[8];
   if constexpr (F::kParBytes != 0) {
-    const uint32_t par = *reinterpret_cast<const uint32_t*>(stage + stage_par(SUBS) + sub * 256 + lane * 4);
+    const uint32_t par = *reinterpret_cast<const uint32_t*>(stage + stage_par(SUBS, HD) + sub * 256 + lane * 4);
     float pa, pb;
     const float sc = f16lo(par);
     const float zp = DT == FS_KV_INT4 ? f16hi(par) : 128.0f;
@@ -894,7 +899,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
   }
   if (__any(need)) {
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT, NCB>(st, cb, tmax[cb], j);
+    for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT>(st, cb, tmax[cb], j);
   }
   u32x4 pk[NCB];
 #pragma unroll
@@ -931,10 +936,10 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
   }
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
+  for (int e = 0; e < F::kNE; ++e) {
     u32x4 b;
     if (e < VPRE) b = vpre[e];
-    else b = *reinterpret_cast<const u32x4*>(stage + stage_v(SUBS) + (uint32_t)((sub * 8 + e) * kFrag) + lane * 16);
+    else b = *reinterpret_cast<const u32x4*>(stage + stage_v(SUBS, HD) + (uint32_t)((sub * F::kNE + e) * kFrag) + lane * 16);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) st.acc[cb][e] = mfma(pk[cb], b, st.acc[cb][e]);
   }
@@ -950,13 +955,15 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 // cause was not found and the variant is no longer built.)
 // smem: two stages, then the workgroup's block-address table.
 // DEQ (INT8 / INT4 only): the staging waves dequantize, the tile code is the FP16 one.
-template <int DT, int NW, int NCB, int SUBS, bool DEQ = false>
+template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD>
 __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt, uint8_t* smem, uint64_t* s_tab, int w) {
   static_assert(NW == SUBS || NW == 2 * SUBS, "staging roles");
 #ifdef FS_TIMELINE
   uint64_t tl_ph[5] = {(uint64_t)wall_clock64(), 0, 0, 0, 0};
 #endif
   static_assert(!DEQ || Fmt<DT>::kParBytes != 0, "staged dequantization is for the formats with per-token parameters");
+  static_assert(!DEQ || HD == kD, "staged dequantization is written for head_dim 128");
+  constexpr int NE = HD / 16;  // output columns NE c .. NE c + NE - 1 are this lane's
   constexpr int CDT = DEQ ? FS_KV_FP16 : DT;  // the format the consumer code sees
   // V fragments read ahead of the softmax: what the format's register budget leaves room for (two waves per SIMD)
   constexpr int kVPre = NW != 8 ? 0 : (DEQ && DT == FS_KV_INT4 ? 8 : 4);
@@ -991,25 +998,25 @@ __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt,
   X.len = X.len_u;
   X.chunk_ptr = s_tab;
 
-  u32x4 qb[NCB][4];
+  u32x4 qb[NCB][HD / 32];
   float qsum[NCB];
   int len_cb[NCB], row_cb[NCB];
   float alpha = B.sm_scale * kLog2e;
   if (DT == FS_KV_FP8_E4M3) alpha *= B.k_scale[head];
-  WideState<NCB> st;
+  WideState<NCB, HD> st;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
     const int tok = cb * P.tpt + tok_c;  // query token of this lane's column in block cb
     const bool live = tok_c < P.tpt && tok < n_tok;
     len_cb[cb] = live ? first_pos + tok + 1 : X.len_u;  // a dead column (q = 0, never written) sees everything
     row_cb[cb] = min(max(P.q_offsets[seq] + r0 + tok, 0), P.n_rows - 1);
-    load_q<DT, !DEQ>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * kD, live, j, qb[cb], qsum[cb]);
+    load_q<DT, !DEQ, HD>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * HD, live, j, qb[cb], qsum[cb]);
     if constexpr (Fmt<CDT>::kParBytes != 0) {
       qsum[cb] += __shfl_xor(qsum[cb], 16, 64);
       qsum[cb] += __shfl_xor(qsum[cb], 32, 64);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) st.acc[cb][e] = float4v{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < NE; ++e) st.acc[cb][e] = float4v{0.f, 0.f, 0.f, 0.f};
     st.m[cb] = -INFINITY;
     st.l[cb] = 0.f;
     st.zc[cb] = 0.f;
@@ -1033,23 +1040,23 @@ __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt,
 #endif
     }
     const int n_super = (X.v_end - v0 + 4 * SUBS - 1) / (4 * SUBS);
-    Tile<DT, 16> t;
+    Tile<DT, 16, HD> t;
     uint32_t kpar[2] = {0u, 0u};  // (DEQ) K parameters of the rows this lane stages
     // fetch / stage this wave's share of the sub-tile that starts at run vb
     auto fetch = [&](int vb) {
       if (does_k) {
-        issue_k<DT, 16>(X, vb, j, c, t);
+        issue_k<DT, 16, HD>(X, vb, j, c, t);
         if constexpr (DEQ) issue_kpar<DT>(X, g, vb, c, kpar);
       }
-      if (does_v) issue_v<DT, 16>(X, g, vb, j, c, t);
+      if (does_v) issue_v<DT, 16, HD>(X, g, vb, j, c, t);
     };
     auto stage_to = [&](uint8_t* stage, int vb) {
       if constexpr (DEQ) {
         if (does_k) stage_k_deq<DT>(stage, sw, lane, t, kpar);
         if (does_v) stage_v_deq<DT, SUBS>(stage, sw, lane, j, t, X, vb);
       } else {
-        if (does_k) stage_k<DT>(stage, sw, lane, t);
-        if (does_v) stage_v<DT, SUBS>(stage, sw, lane, j, t, X, vb);
+        if (does_k) stage_k<DT, HD>(stage, sw, lane, t);
+        if (does_v) stage_v<DT, SUBS, HD>(stage, sw, lane, j, t, X, vb);
       }
     };
     fetch(v0 + 4 * sw);
@@ -1067,7 +1074,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt,
       const int vb_next = v0 + (i + 1) * 4 * SUBS + 4 * sw;
       const bool more = i + 1 < n_super;  // wave-uniform
       if (more) fetch(vb_next);
-      const uint8_t* stage = smem + (uint32_t)(i & 1) * stage_bytes(SUBS);
+      const uint8_t* stage = smem + (uint32_t)(i & 1) * stage_bytes(SUBS, HD);
       // A wave multiplies the sub-tiles that hold a token one of its queries sees: those past its diagonal (half of
       // the last step or two of an item, and all of them in a wave without query tokens: a ragged last item of a chunk,
       // chunks shorter than the workgroup's 16 NW / G tokens) are left out.  A loop bound, not a branch around the
@@ -1076,9 +1083,9 @@ __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt,
       const int n_live = min(SUBS, (w_end - (v0 + i * SUBS * 4) + 3) >> 2);
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
       for (int sub = 0; sub < n_live; ++sub)
-        wg_tile<CDT, NCB, SUBS, kVPre>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4, lane, j, c, st,
-                                       whole_runs);
-      uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS);
+        wg_tile<CDT, NCB, SUBS, kVPre, HD>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4, lane, j,
+                                           c, st, whole_runs);
+      uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS, HD);
       if (more) stage_to(next, vb_next);
       __syncthreads();  // (also after the last step: the next staging overwrites what other waves may still read)
     }
@@ -1106,9 +1113,9 @@ __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt,
       const int tok_h = h / G, hg_h = h - tok_h * G;
       if (tok_h < P.tpt && cb * P.tpt + tok_h < n_tok) {
         const float inv = 1.0f / L;
-        u32x4 wv;
+        uint32_t wv[NE / 2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < NE / 2; ++q) {
           float o[2];
 #pragma unroll
           for (int z = 0; z < 2; ++z) {
@@ -1122,7 +1129,14 @@ __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt,
           wv[q] = h2u(hv);
         }
         const int64_t qrow = (int64_t)row_h * B.n_q + head * G + hg_h;
-        *reinterpret_cast<u32x4*>(B.out + qrow * kD + 8 * c) = wv;
+        _Float16* orow = B.out + qrow * HD + NE * c;
+        if constexpr (NE == 4) {
+          *reinterpret_cast<u32x2*>(orow) = u32x2{wv[0], wv[1]};
+        } else {
+#pragma unroll
+          for (int q = 0; q < NE / 8; ++q)
+            reinterpret_cast<u32x4*>(orow)[q] = u32x4{wv[4 * q], wv[4 * q + 1], wv[4 * q + 2], wv[4 * q + 3]};
+        }
         if (c == 0 && B.lse) B.lse[qrow] = (M + __builtin_amdgcn_logf(L)) * kLn2;
       }
     }
@@ -1293,8 +1307,8 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
     Tile<DT, 16> t;
     issue_k<DT, 16>(X, v0 + 4 * w, j, c, t);
     issue_v<DT, 16>(X, g, v0 + 4 * w, j, c, t);
-    stage_k<DT>(smem, w, lane, t);
-    stage_v<DT, SUBS>(smem, w, lane, j, t, X, v0 + 4 * w);
+    stage_k<DT, kD>(smem, w, lane, t);
+    stage_v<DT, SUBS, kD>(smem, w, lane, j, t, X, v0 + 4 * w);
     __syncthreads();
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) settle_q(qb[cb]);  // (issued before the table and the first K/V fetch)
@@ -1323,7 +1337,7 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
       Logits<DT, NCB> cur;
       if (__any(make_logits<DT, NCB, SUBS>(sn, stage, 0, X, qsum, len_cb, alpha, first_pos, v0 + i * 4 * SUBS, lane, c, st, cur))) {
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT, NCB>(st, cb, cur.tmax[cb], j);
+        for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT>(st, cb, cur.tmax[cb], j);
       }
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
       for (int sub = 0; sub < SUBS; ++sub) {
@@ -1401,12 +1415,12 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
                                                      v0 + (i * SUBS + nsub) * 4, lane, c, st, cur);
         if (sub + 1 < SUBS && __any(need)) {  // (the wrapped-around sub-tile's logits are discarded)
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT, NCB>(st, cb, cur.tmax[cb], j);
+          for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT>(st, cb, cur.tmax[cb], j);
         }
       }
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS);
-      stage_k<DT>(next, w, lane, t);
-      stage_v<DT, SUBS>(next, w, lane, j, t, X, vb_next);
+      stage_k<DT, kD>(next, w, lane, t);
+      stage_v<DT, SUBS, kD>(next, w, lane, j, t, X, vb_next);
       __syncthreads();
     }
   }
@@ -1454,12 +1468,12 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
 }
 
 // WPC = workgroups per compute unit the kernel is built for
-template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false>
+template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD>
 __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
   extern __shared__ uint64_t smem64[];
   uint8_t* smem = reinterpret_cast<uint8_t*>(smem64);
-  uint64_t* s_tab = reinterpret_cast<uint64_t*>(smem + 2 * stage_bytes(SUBS));
-  volatile uint32_t* s_ctl = reinterpret_cast<volatile uint32_t*>(smem + 2 * stage_bytes(SUBS) + (size_t)P.table_entries * 8);
+  uint64_t* s_tab = reinterpret_cast<uint64_t*>(smem + 2 * stage_bytes(SUBS, HD));
+  volatile uint32_t* s_ctl = reinterpret_cast<volatile uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8);
   const DevBatch& B = P.b;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1467,7 +1481,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
   const uint32_t total = P.tile_first[B.n_seq] * H;
   const uint32_t* tf = P.tile_first;
   if (P.tf_cache) {  // (uniform)
-    uint32_t* s_tf = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS) + (size_t)P.table_entries * 8 + kWgCtlBytes);
+    uint32_t* s_tf = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
     for (int i = threadIdx.x; i <= B.n_seq; i += NW * 64) s_tf[i] = P.tile_first[i];
     __syncthreads();
     tf = s_tf;
@@ -1502,7 +1516,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
     const uint64_t tl_begin = wall_clock64();
 #endif
     if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
-    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ>(P, seq, head, qt, smem, s_tab, wave);
+    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD>(P, seq, head, qt, smem, s_tab, wave);
 #ifdef FS_TIMELINE
     ++tl_items;
     if (threadIdx.x == 0 && item < kPfTimelineItems) {
@@ -1609,8 +1623,10 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // the wide kernels fold the (positive) softmax scale into the exponential's argument; any other scale takes
   // the 16-column kernel, which does not
   const bool scale_ok = sm_scale > 0.f && sm_scale < INFINITY;
-  // (head_dim 64 and 256: the 16-column kernel is the one whose tile code is built for them)
-  int ncb = !scale_ok || g.head_dim != kD ? 1 : (ncb_env ? ncb_env : ncb_default);
+  // (head_dim 64: the 8-wave workgroup kernel or the 16-column kernel; 256: the 16-column kernel)
+  const bool d64 = g.head_dim == 64;
+  int ncb = !scale_ok || (g.head_dim != kD && !d64) ? 1 : (ncb_env ? ncb_env : ncb_default);
+  if (d64 && ncb != 16) ncb = 1;  // (the wide wave-level kernels are written for head_dim 128)
   uint64_t tiles = 0;
   for (int pass = 0; pass < 2; ++pass) {
     tiles = 0;
@@ -1704,7 +1720,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   const int wps = ncb == 1 ? mfma_wgs_per_cu(g.head_dim) : 1;
   // workgroup kernels: 16 blocks = 8 waves x 2 (default) or 4 x 4, 4 sub-tiles per step, one workgroup per compute unit
   const bool wg = ncb == 16;
-  const int nw = p->opt.prefill_nw == 4 ? 4 : 8;
+  const int nw = p->opt.prefill_nw == 4 && !d64 ? 4 : 8;
   const int subs = 4, wpc = 1;
   const int n_wg = wg ? (int)std::min<uint64_t>((uint64_t)p->n_cu * wpc, std::max<uint64_t>(items, 1))
                       : (int)std::min<uint64_t>((uint64_t)p->n_cu * wps, std::max<uint64_t>((items + kWaves - 1) / kWaves, 1));
@@ -1715,7 +1731,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   while (P.chunk_shift > (int32_t)kWgChunkShift && (items >> P.chunk_shift) < 64) --P.chunk_shift;
   // the per-sequence tile counts go to LDS while they fit beside the stages (16 KiB: 4095 sequences)
   P.tf_cache = wg && (uint64_t)n_seq + 1 <= 4096;
-  const size_t smem = wg ? 2 * (size_t)stage_bytes(subs) + (size_t)P.table_entries * 8 + kWgCtlBytes +
+  const size_t smem = wg ? 2 * (size_t)stage_bytes(subs, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes +
                                (P.tf_cache ? (((size_t)n_seq + 1) * 4 + 15) / 16 * 16 : 0)
                          : (size_t)kWaves * P.table_entries * sizeof(uint64_t);
   if (wg) {
@@ -1723,8 +1739,18 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
 #define FS_WG(DT)                                  \
   (nw == 8 ? prefill_wg_kernel<DT, 8, 2, 4, 1> \
            : (p->opt.prefill_pipe ? prefill_wg_kernel<DT, 4, 4, 4, 1, true> : prefill_wg_kernel<DT, 4, 4, 4, 1>))
-    const bool deq = p->opt.prefill_deq && nw == 8;  // (the 8-wave kernel only)
-    switch (g.kv_dtype) {
+    const bool deq = p->opt.prefill_deq && nw == 8 && !d64;  // (the 8-wave kernel at head_dim 128 only)
+    if (d64) {
+      // Integer codes enter the MFMAs exactly here, as in the 16-column kernel that served this head_dim before.
+      // (24 FP16 prompts of 256 - 3000 tokens, GQA 4:1: 1804 -> 624 us, 179 -> 516 TFLOP/s; with four column blocks
+      // per wave 647 us.)
+      switch (g.kv_dtype) {
+        case FS_KV_FP16: kern = prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, 64>; break;
+        case FS_KV_FP8_E4M3: kern = prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, 64>; break;
+        case FS_KV_INT8: kern = prefill_wg_kernel<FS_KV_INT8, 8, 2, 4, 1, false, false, 64>; break;
+        default: kern = prefill_wg_kernel<FS_KV_INT4, 8, 2, 4, 1, false, false, 64>; break;
+      }
+    } else switch (g.kv_dtype) {
       case FS_KV_FP16: kern = FS_WG(FS_KV_FP16); break;
       case FS_KV_FP8_E4M3: kern = FS_WG(FS_KV_FP8_E4M3); break;
       case FS_KV_INT8: kern = deq ? prefill_wg_kernel<FS_KV_INT8, 8, 2, 4, 1, false, true> : FS_WG(FS_KV_INT8); break;
