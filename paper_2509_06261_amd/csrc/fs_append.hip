@@ -12,9 +12,12 @@ namespace {
 using namespace append;
 constexpr int kWaves = 4;  // waves per workgroup
 
-template <bool kSrcF32>
+// The wave's number is made provably uniform, so that a unit's place is found with scalar arithmetic.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+template <bool kSrcF32, int DT, int HP>
 __global__ __launch_bounds__(kWaves * 64) void kv_append_kernel(AppendArgs A) {
-  append_rows<kSrcF32>(A, (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6), (int64_t)gridDim.x * kWaves);
+  append_rows<kSrcF32, DT, HP>(A, (int64_t)blockIdx.x * kWaves + wave_id(), (int64_t)gridDim.x * kWaves);
 }
 
 __global__ __launch_bounds__(kWaves * 64) void kv_append_multi_kernel(MultiAppendArgs P) { append_block(P, blockIdx.x, kWaves); }
@@ -52,7 +55,6 @@ int make_append_args(fs_pool* p, const fs_append_t& a, append::AppendArgs& A) {
   A.k_scale = M.d_k_scale ? M.d_k_scale + (size_t)a.layer * M.g.n_kv_heads : nullptr;
   A.v_scale = M.d_v_scale ? M.d_v_scale + (size_t)a.layer * M.g.n_kv_heads : nullptr;
   A.n_tokens = a.n_tokens;
-  A.n_rows = (a.n_tokens + 3) / 4 * 4 * M.g.n_kv_heads * 2;
   A.n_blocks = (int64_t)(p->pool_bytes / M.g.block_budget);
   A.layer = a.layer;
   A.max_blocks = a.max_blocks;
@@ -63,13 +65,18 @@ int make_append_args(fs_pool* p, const fs_append_t& a, append::AppendArgs& A) {
   return FS_OK;
 }
 
+// Units of `hp` rows of an append (see append_rows).
+static int64_t append_units(const append::AppendArgs& A, int hp) {
+  const int64_t tpw = 64 >> A.lpr_shift;
+  return (A.n_tokens + tpw - 1) / tpw * ((2 * (int64_t)A.g.H + hp - 1) / hp);
+}
+
 uint32_t plan_append_blocks(const fs_pool* p, append::MultiAppendArgs& P, int waves) {
   const int64_t cap = std::max<int64_t>((int64_t)p->n_cu * 64 * 4 / waves, 1);  // per append: as the single-append launch
   uint32_t next = 0;
   for (int i = 0; i < P.n; ++i) {
-    const int64_t rows_per_wg = (int64_t)waves * (64 >> P.a[i].lpr_shift);
     P.first_block[i] = next;
-    next += (uint32_t)std::min<int64_t>((P.a[i].n_rows + rows_per_wg - 1) / rows_per_wg, cap);
+    next += (uint32_t)std::min<int64_t>((append_units(P.a[i], 1) + waves - 1) / waves, cap);
   }
   for (int i = P.n; i <= append::kMaxAppends; ++i) P.first_block[i] = next;
   return next;
@@ -101,16 +108,22 @@ extern "C" int fs_kv_append(fs_pool* p, fs_model_t model, int layer, const void*
     set_error("fs_kv_append: pool has no HIP device");
     return FS_ERR_DEVICE;
   }
-  const int64_t rows_per_wg = (int64_t)kWaves * (64 >> A.lpr_shift);
-  int64_t blocks = (A.n_rows + rows_per_wg - 1) / rows_per_wg;
-  const int64_t cap = (int64_t)p->n_cu * 64;
-  if (blocks > cap) blocks = cap;
+  const bool wide = append_units(A, kWideUnit) >= (int64_t)p->n_cu * 32;  // (32 wave slots of a compute unit)
+  const int64_t blocks = std::min<int64_t>((append_units(A, wide ? kWideUnit : 1) + kWaves - 1) / kWaves, (int64_t)p->n_cu * 64);
   hipStream_t s = (hipStream_t)stream;
   (void)hipGetLastError();  // drop any stale error of an earlier, unrelated runtime call
-  if (A.src_f32)
-    hipLaunchKernelGGL(kv_append_kernel<true>, dim3((unsigned)blocks), dim3(kWaves * 64), 0, s, A);
-  else
-    hipLaunchKernelGGL(kv_append_kernel<false>, dim3((unsigned)blocks), dim3(kWaves * 64), 0, s, A);
+  void (*kern)(AppendArgs) = nullptr;
+#define FS_APPEND(DT)                                                                                   \
+  (A.src_f32 ? (wide ? kv_append_kernel<true, DT, kWideUnit> : kv_append_kernel<true, DT, 1>)           \
+             : (wide ? kv_append_kernel<false, DT, kWideUnit> : kv_append_kernel<false, DT, 1>))
+  switch (A.g.dtype) {
+    case FS_KV_FP16: kern = FS_APPEND(FS_KV_FP16); break;
+    case FS_KV_FP8_E4M3: kern = FS_APPEND(FS_KV_FP8_E4M3); break;
+    case FS_KV_INT8: kern = FS_APPEND(FS_KV_INT8); break;
+    default: kern = FS_APPEND(FS_KV_INT4); break;
+  }
+#undef FS_APPEND
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kWaves * 64), 0, s, A);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return device_error(e, "fs_kv_append launch");
   return FS_OK;
