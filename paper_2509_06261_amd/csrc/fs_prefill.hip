@@ -12,8 +12,8 @@
 // causality is a per-column sequence length, so only the tiles on the diagonal pay for masking.  Three kernels:
 // prefill_kernel keeps one block of 16 columns per wave (two waves per SIMD); prefill_wide_kernel 2 or 4
 // blocks (one wave per SIMD): a tile's K and V rows are then loaded, unpacked and transposed once for 32 or 64
-// columns; prefill_wg_kernel (the default for launches with at least one item per compute unit) lets the waves
-// of a workgroup share every unpacked K/V fragment through LDS.  Items of one (sequence, head) are neighbours in the queue, longest
+// columns; prefill_wg_kernel (the default at head_dim 64 and 128) lets the waves of a workgroup share every unpacked
+// K/V fragment through LDS.  Items of one (sequence, head) are neighbours in the queue, longest
 // first, so that the waves streaming the same keys and values run side by side and share them through the
 // L2.  Waves draw items from the same pooled ticket counters as the decode kernel.  A long context is
 // streamed in segments, the wave's block-address table being refilled per segment.
@@ -42,6 +42,7 @@ struct PrefillArgs {
   int32_t tf_cache;          // workgroup kernels: 1 = tile_first is copied into LDS at kernel start
   int32_t whole_runs;        // 1 = tokens per block is a multiple of 8: run r starts at token 8 r, no run is shifted
   int32_t chunk_shift;       // workgroup kernels: log2 of the consecutive work items that go to one XCD
+  int32_t direct;            // workgroup kernels: 1 = no preparation ran and no tickets are drawn (see "Direct launches")
 #ifdef FS_TIMELINE
   uint64_t* timeline;        // (timeline build) clock readings of the workgroup kernels, at the end of the workspace
 #endif
@@ -59,6 +60,20 @@ constexpr uint64_t kPfTimelineBytes = 64 * (kPfTimelineGroups + kPfTimelineItems
 
 constexpr int kPrepThreads = 1024;
 
+// Query tiles of sequence i; raises bit 0 of `flags` for a length or chunk out of range.
+__device__ __forceinline__ uint32_t seq_tiles(const PrefillArgs& P, int i, uint32_t& flags) {
+  const DevBatch& B = P.b;
+  const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
+  int len = B.seq_lens[i];
+  int n_new = P.q_offsets[i + 1] - P.q_offsets[i];
+  if (len < 1 || len > max_len || n_new < 0 || n_new > len) {
+    flags |= 1u;
+    len = len < 1 ? 1 : min(len, max_len);
+    n_new = n_new < 0 ? 0 : min(n_new, len);
+  }
+  return (uint32_t)((n_new + P.tpt * P.ncb - 1) / (P.tpt * P.ncb));
+}
+
 // Query tiles per sequence -> tile_first (exclusive scan), validation flags, counter reset.  One workgroup.
 __global__ __launch_bounds__(kPrepThreads) void prefill_prep_kernel(PrefillArgs P) {
   __shared__ uint32_t s_wave[kPrepThreads / 64];
@@ -71,19 +86,13 @@ __global__ __launch_bounds__(kPrepThreads) void prefill_prep_kernel(PrefillArgs 
   }
   if (tid < kPools) P.header[kHdrPools + tid * kPoolStride] = 0;
   __syncthreads();
-  const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
   for (int base = 0; base < B.n_seq; base += kPrepThreads) {
     const int i = base + tid;
     uint32_t v = 0;
     if (i < B.n_seq) {
-      int len = B.seq_lens[i];
-      int n_new = P.q_offsets[i + 1] - P.q_offsets[i];
-      if (len < 1 || len > max_len || n_new < 0 || n_new > len) {
-        atomicOr(P.header + kHdrStatus, 1u);
-        len = len < 1 ? 1 : min(len, max_len);
-        n_new = n_new < 0 ? 0 : min(n_new, len);
-      }
-      v = (uint32_t)((n_new + P.tpt * P.ncb - 1) / (P.tpt * P.ncb));
+      uint32_t flags = 0;
+      v = seq_tiles(P, i, flags);
+      if (flags) atomicOr(P.header + kHdrStatus, flags);
     }
     uint32_t incl = v;
 #pragma unroll
@@ -955,8 +964,10 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 // cause was not found and the variant is no longer built.)
 // smem: two stages, then the workgroup's block-address table.
 // DEQ (INT8 / INT4 only): the staging waves dequantize, the tile code is the FP16 one.
+// header: where a block-table entry outside the pool is reported.
 template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD>
-__device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt, uint8_t* smem, uint64_t* s_tab, int w) {
+__device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq, int head, int qt, uint8_t* smem, uint64_t* s_tab,
+                                int w) {
   static_assert(NW == SUBS || NW == 2 * SUBS, "staging roles");
 #ifdef FS_TIMELINE
   uint64_t tl_ph[5] = {(uint64_t)wall_clock64(), 0, 0, 0, 0};
@@ -1033,7 +1044,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, int seq, int head, int qt,
       // the previous segment's (or item's) last barrier lies behind every use of the old table
       const int nb = div_runs(X.v_end - 1, B.R, B.r_magic) - X.k0 + 1;
       for (int i = threadIdx.x; i < nb; i += NW * 64)
-        s_tab[i] = reinterpret_cast<uint64_t>(head_base + (uint64_t)checked_block(table[X.k0 + i], B.n_blocks, P.header) * g.block_budget);
+        s_tab[i] = reinterpret_cast<uint64_t>(head_base + (uint64_t)checked_block(table[X.k0 + i], B.n_blocks, header) * g.block_budget);
       __syncthreads();
 #ifdef FS_TIMELINE
       if (v0 == 0) tl_ph[1] = wall_clock64();
@@ -1467,6 +1478,57 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
   }
 }
 
+// ---- Direct launches ----------------------------------------------------------------------------------------------
+// A launch with no more work items than compute units needs no queue: workgroup b takes one item, found from the
+// sequences' tile counts, which every workgroup scans itself (as many sequences as it has threads, at most).  That
+// saves the preparation kernel and the gap behind it.  What the preparation also does, the reset of the status word,
+// cannot be ordered before other workgroups' reports without it, so the items report nothing (to a word nobody reads)
+// and the workgroup of the last item -- the first tile of a head, its shortest -- judges the call as a whole when it is
+// done: every length and chunk, and every block-table entry that the sequences with new tokens reach.
+constexpr int kSmallBlocks = 8;  // column blocks of the workgroup kernel's smaller item
+constexpr int kHdrIgnored = 4;  // header word the items of a direct launch report to
+static_assert(kHdrIgnored > kHdrTotalItems && kHdrIgnored < kHdrBatchFirst, "a free word of the header");
+
+__device__ __forceinline__ uint32_t direct_scan(const PrefillArgs& P, uint32_t* s_tf, uint32_t* s_wave) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t flags = 0;
+  const uint32_t v = tid < P.b.n_seq ? seq_tiles(P, tid, flags) : 0u;
+  uint32_t incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t u = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += u;
+  }
+  if (lane == 63) s_wave[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave; ++w) before += s_wave[w];
+  if (tid < P.b.n_seq) s_tf[tid + 1] = before + incl;
+  if (tid == 0) s_tf[0] = 0;
+  __syncthreads();
+  return s_tf[P.b.n_seq];
+}
+
+template <int NT>
+__device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_flags) {
+  const DevBatch& B = P.b;
+  if (threadIdx.x == 0) *s_flags = 0;
+  __syncthreads();
+  uint32_t flags = 0;
+  const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
+  for (int seq = threadIdx.x >> 6; seq < B.n_seq; seq += NT / 64) {
+    if (seq_tiles(P, seq, flags) == 0) continue;
+    int len = B.seq_lens[seq];
+    len = len < 1 ? 1 : min(len, max_len);
+    const int nb = (len + B.g.T - 1) / B.g.T;
+    const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
+    for (int i = threadIdx.x & 63; i < nb; i += 64) flags |= (uint32_t)table[i] < B.n_blocks ? 0u : 4u;
+  }
+  if (flags) atomicOr(s_flags, flags);
+  __syncthreads();
+  if (threadIdx.x == 0) P.header[kHdrStatus] = *s_flags;
+}
+
 // WPC = workgroups per compute unit the kernel is built for
 template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD>
 __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
@@ -1478,33 +1540,51 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t H = (uint32_t)B.g.H;
-  const uint32_t total = P.tile_first[B.n_seq] * H;
+  uint32_t* s_tf = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
+  const bool direct = !PIPE && P.direct;  // (uniform)
+  uint32_t* const header = direct ? P.header + kHdrIgnored - kHdrStatus : P.header;
   const uint32_t* tf = P.tile_first;
-  if (P.tf_cache) {  // (uniform)
-    uint32_t* s_tf = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
-    for (int i = threadIdx.x; i <= B.n_seq; i += NW * 64) s_tf[i] = P.tile_first[i];
-    __syncthreads();
+  uint32_t total;
+  if (direct) {
+    total = __builtin_amdgcn_readfirstlane(direct_scan(P, s_tf, reinterpret_cast<uint32_t*>(smem))) * H;
     tf = s_tf;
+  } else {
+    total = P.tile_first[B.n_seq] * H;
+    if (P.tf_cache) {  // (uniform)
+      for (int i = threadIdx.x; i <= B.n_seq; i += NW * 64) s_tf[i] = P.tile_first[i];
+      __syncthreads();
+      tf = s_tf;
+    }
   }
+  // direct: consecutive items, which stream the same keys and values, on one XCD (workgroups are dealt to the XCDs in
+  // turn); workgroup b takes items (b % 8) per + b / 8, + slots, ... of its XCD's share
+  const uint32_t per = (total + 7) / 8, slots = gridDim.x >> 3;  // (the host launches a multiple of eight)
+  uint32_t u = blockIdx.x >> 3;
 #ifdef FS_TIMELINE
   const uint64_t tl_start = wall_clock64();
   uint64_t tl_items = 0;
 #endif
   ItemDraw d{0u, 0u};
-  if (wave == 0) d = first_draw(P.header, blockIdx.x >> 3, lane);
+  if (wave == 0 && !direct) d = first_draw(P.header, blockIdx.x >> 3, lane);
   for (;;) {
 #ifdef FS_TIMELINE
     const uint64_t tl_top = wall_clock64();
 #endif
-    if (wave == 0) {  // one wave draws for the workgroup
-      uint32_t item;
-      const bool ok = next_item(d, P.header, total, (uint32_t)P.chunk_shift, lane, item);
-      if (lane == 0) s_ctl[0] = ok ? item : 0xffffffffu;
+    uint32_t item;
+    if (direct) {
+      item = (blockIdx.x & 7) * per + u;
+      if (u >= per || item >= total) break;
+      u += slots;
+    } else {
+      if (wave == 0) {  // one wave draws for the workgroup
+        const bool ok = next_item(d, P.header, total, (uint32_t)P.chunk_shift, lane, item);
+        if (lane == 0) s_ctl[0] = ok ? item : 0xffffffffu;
+      }
+      __syncthreads();
+      item = __builtin_amdgcn_readfirstlane(s_ctl[0]);  // (an LDS load is not uniform to the compiler)
+      __syncthreads();  // everyone holds the item before the next draw may overwrite it
+      if (item == 0xffffffffu) break;
     }
-    __syncthreads();
-    const uint32_t item = __builtin_amdgcn_readfirstlane(s_ctl[0]);  // (an LDS load is not uniform to the compiler)
-    __syncthreads();  // everyone holds the item before the next draw may overwrite it
-    if (item == 0xffffffffu) break;
     int seq, head, qt;
     if (!decode_item(P, tf, item, H, seq, head, qt)) continue;
     // (the same in every lane; said so, the item's addresses and bounds live in scalar registers: FP16 needs no
@@ -1516,7 +1596,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
     const uint64_t tl_begin = wall_clock64();
 #endif
     if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
-    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD>(P, seq, head, qt, smem, s_tab, wave);
+    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD>(P, header, seq, head, qt, smem, s_tab, wave);
 #ifdef FS_TIMELINE
     ++tl_items;
     if (threadIdx.x == 0 && item < kPfTimelineItems) {
@@ -1527,6 +1607,10 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
       row[3] = (uint64_t)blockIdx.x | ((tl_begin - tl_top) << 32);
     }
 #endif
+  }
+  if (direct) {
+    const uint32_t last = total ? total - 1 : 0u, n = total ? per : 1u;
+    if (blockIdx.x == (last % n % slots) * 8 + last / n) direct_status<NW * 64>(P, reinterpret_cast<uint32_t*>(smem));
   }
 #ifdef FS_TIMELINE
   if (threadIdx.x == 0 && blockIdx.x < kPfTimelineGroups) {
@@ -1617,30 +1701,38 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   }
   const int tpt = 16 / G;
   const int ncb_env = p->opt.prefill_ncb;  // FS_OPT_PREFILL_COLUMN_BLOCKS
-  // Default: the workgroup kernel (measured fastest for every format once a launch has a work item per
-  // compute unit); the 16-column wave-level kernel, whose items are sixteen times finer, for smaller launches.
-  const int ncb_default = 16;
   // the wide kernels fold the (positive) softmax scale into the exponential's argument; any other scale takes
   // the 16-column kernel, which does not
   const bool scale_ok = sm_scale > 0.f && sm_scale < INFINITY;
-  // (head_dim 64: the 8-wave workgroup kernel or the 16-column kernel; 256: the 16-column kernel)
+  // (head_dim 64: the 8-wave workgroup kernels or the 16-column kernel; 256: the 16-column kernel)
   const bool d64 = g.head_dim == 64;
-  int ncb = !scale_ok || (g.head_dim != kD && !d64) ? 1 : (ncb_env ? ncb_env : ncb_default);
+  int ncb = !scale_ok || (g.head_dim != kD && !d64) ? 1 : (ncb_env ? ncb_env : 16);
   if (d64 && ncb != 16) ncb = 1;  // (the wide wave-level kernels are written for head_dim 128)
   uint64_t tiles = 0;
-  for (int pass = 0; pass < 2; ++pass) {
+  auto count_tiles = [&](int blocks) {
     tiles = 0;
     for (int b = 0; b < n_seq; ++b) {
       const int64_t n_new = (int64_t)q_offsets_host[b + 1] - q_offsets_host[b];
-      if (n_new < 0) {
-        set_error("prefill attention: q_offsets must not decrease");
-        return FS_ERR_INVALID;
-      }
-      tiles += (uint64_t)((n_new + tpt * ncb - 1) / (tpt * ncb));
+      if (n_new < 0) return false;
+      tiles += (uint64_t)((n_new + tpt * blocks - 1) / (tpt * blocks));
     }
-    // a launch with fewer workgroup-level items than compute units: the finest items instead
-    if (pass == 0 && ncb == 16 && !ncb_env && tiles * (uint64_t)g.n_kv_heads < (uint64_t)p->n_cu) ncb = 1;
-    else break;
+    return true;
+  };
+  if (!count_tiles(ncb)) {
+    set_error("prefill attention: q_offsets must not decrease");
+    return FS_ERR_INVALID;
+  }
+  // By default the workgroup kernel with 16 blocks per item; with 8 blocks (eight waves of one block each) where even
+  // those items all find a compute unit of their own: twice the units work, and a step takes little more than half the
+  // time.  A prompt of 777 tokens, 8 KV heads x 4 of 128: 66 us in the 16-column kernel that served launches with fewer
+  // items than compute units before, 27.5 us with 8 blocks (200 items); one of 1500 tokens: 137 us, 75 with 8 blocks
+  // (376 items: some units take two), 60 with 16 (188 items).
+  if (ncb == 16 && !ncb_env && tiles * (uint64_t)g.n_kv_heads < (uint64_t)p->n_cu) {
+    (void)count_tiles(kSmallBlocks);
+    // (head_dim 64: too few items to matter stay with the 16-column kernel; two prompts of 100 and 600 tokens with 4 KV
+    // heads: 29 us)
+    if (tiles * (uint64_t)g.n_kv_heads <= (uint64_t)p->n_cu) ncb = d64 && tiles * (uint64_t)g.n_kv_heads < 64 ? 1 : kSmallBlocks;
+    if (ncb != kSmallBlocks) (void)count_tiles(ncb);
   }
   const int64_t n_rows = q_offsets_host[n_seq];
   if (tiles * (uint64_t)g.n_kv_heads > 0xfffffff0ull || n_rows > 0x7fffffff) {
@@ -1700,9 +1792,17 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   if (n_rows == 0) return FS_OK;
   hipStream_t s = (hipStream_t)stream;
   (void)hipGetLastError();
-  hipLaunchKernelGGL(prefill_prep_kernel, dim3(1), dim3(kPrepThreads), 0, s, P);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return device_error(e, "prefill prep launch");
+  const uint64_t items = tiles * (uint64_t)g.n_kv_heads;
+  const bool wg = ncb == 16 || ncb == kSmallBlocks;
+  const int nw = p->opt.prefill_nw == 4 && ncb == 16 && !d64 ? 4 : 8;
+  // no more items than compute units: a direct launch (see "Direct launches")
+  P.direct = wg && !generic && nw == 8 && items <= (uint64_t)p->n_cu && n_seq <= nw * 64;
+  hipError_t e = hipSuccess;
+  if (!P.direct) {
+    hipLaunchKernelGGL(prefill_prep_kernel, dim3(1), dim3(kPrepThreads), 0, s, P);
+    e = hipGetLastError();
+    if (e != hipSuccess) return device_error(e, "prefill prep launch");
+  }
   if (generic) {
     // one workgroup per (query row, KV head) on the vector ALU: every shape the pool can hold
     MultiArgs A{};
@@ -1715,14 +1815,11 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     if (e != hipSuccess) return device_error(e, "prefill launch (generic kernel)");
     return FS_OK;
   }
-  const uint64_t items = tiles * (uint64_t)g.n_kv_heads;
   // waves per SIMD: the 16-column kernel runs two, the wider wave-level ones one
   const int wps = ncb == 1 ? mfma_wgs_per_cu(g.head_dim) : 1;
   // workgroup kernels: 16 blocks = 8 waves x 2 (default) or 4 x 4, 4 sub-tiles per step, one workgroup per compute unit
-  const bool wg = ncb == 16;
-  const int nw = p->opt.prefill_nw == 4 && !d64 ? 4 : 8;
   const int subs = 4, wpc = 1;
-  const int n_wg = wg ? (int)std::min<uint64_t>((uint64_t)p->n_cu * wpc, std::max<uint64_t>(items, 1))
+  const int n_wg = P.direct ? (int)((items + 7) / 8 * 8) : wg ? (int)std::min<uint64_t>((uint64_t)p->n_cu * wpc, std::max<uint64_t>(items, 1))
                       : (int)std::min<uint64_t>((uint64_t)p->n_cu * wps, std::max<uint64_t>((items + kWaves - 1) / kWaves, 1));
   // Consecutive items -- the query tiles of one (sequence, head), which stream the same K/V -- go to one XCD in
   // chunks of 128 (a head of 8192 tokens in one piece: measured + 1.4 % over chunks of 32 on long prompts), of
@@ -1739,8 +1836,20 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
 #define FS_WG(DT)                                  \
   (nw == 8 ? prefill_wg_kernel<DT, 8, 2, 4, 1> \
            : (p->opt.prefill_pipe ? prefill_wg_kernel<DT, 4, 4, 4, 1, true> : prefill_wg_kernel<DT, 4, 4, 4, 1>))
-    const bool deq = p->opt.prefill_deq && nw == 8 && !d64;  // (the 8-wave kernel at head_dim 128 only)
-    if (d64) {
+    // (that kernel at head_dim 128 only; a smaller launch by the library's own choice keeps the integer codes exact, as
+    // the 16-column kernel that served it before)
+    const bool deq = p->opt.prefill_deq && nw == 8 && ncb == 16 && !d64 && (ncb_env || items >= (uint64_t)p->n_cu);
+    if (ncb == kSmallBlocks) {
+      // (integer codes exact, as in the 16-column kernel that served these launches before)
+#define FS_WG1(DT) (d64 ? prefill_wg_kernel<DT, 8, 1, 4, 1, false, false, 64> : prefill_wg_kernel<DT, 8, 1, 4, 1>)
+      switch (g.kv_dtype) {
+        case FS_KV_FP16: kern = FS_WG1(FS_KV_FP16); break;
+        case FS_KV_FP8_E4M3: kern = FS_WG1(FS_KV_FP8_E4M3); break;
+        case FS_KV_INT8: kern = FS_WG1(FS_KV_INT8); break;
+        default: kern = FS_WG1(FS_KV_INT4); break;
+      }
+#undef FS_WG1
+    } else if (d64) {
       // Integer codes enter the MFMAs exactly here, as in the 16-column kernel that served this head_dim before.
       // (24 FP16 prompts of 256 - 3000 tokens, GQA 4:1: 1804 -> 624 us, 179 -> 516 TFLOP/s; with four column blocks
       // per wave 647 us.)
@@ -1761,7 +1870,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return device_error(e, "prefill LDS attribute");
     const bool deq_used = deq && (g.kv_dtype == FS_KV_INT8 || g.kv_dtype == FS_KV_INT4);
-    p->opt.last_prefill = 16 | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
+    p->opt.last_prefill = ncb | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
     hipLaunchKernelGGL(kern, dim3(n_wg), dim3(nw * 64), smem, s, P);
   } else if (ncb == 1) {
     p->opt.last_prefill = 1;

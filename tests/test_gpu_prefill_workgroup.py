@@ -31,3 +31,60 @@ def test_workgroup_kernel_edges(dtype, head_dim, group, monkeypatch):
         assert bool(ran >> 16 & 1) == (head_dim == 128 and dtype in (INT8, INT4))  # exact codes at head_dim 64
     finally:
         par.close()
+
+
+@pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
+@pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 6, 4), (128, 2, 4), (128, 3, 1)])
+def test_small_launches(dtype, head_dim, kv_heads, group):
+    """Launches with no more items than compute units: no preparation kernel, items of half the size, exact codes."""
+    import gpu_harness
+    import paper_2509_06261_amd as fs
+
+    wl = Workload("pfsm", 384 * KiB, 384 * 200 * KiB,
+                  [ModelSpec("m", dtype, kv_heads, head_dim, 2, kv_heads * group, EDGES, tag=43, src_f32=dtype == INT4)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[1]])
+        n_new = EDGES if head_dim == 128 else np.minimum(EDGES, 40)
+        print(par.prefill_and_check(0, 1, n_new), par.prefill_and_check(0, 1, np.minimum(EDGES, CHUNKS)))
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
+    finally:
+        par.close()
+
+
+def test_small_launch_reports_and_follows_no_bad_entry():
+    """The status word of a launch without preparation: 0 for a good call whatever the workspace held, bit 0 for a length
+    or chunk out of range, bit 2 for a block-table entry outside the pool -- inside a sequence with new tokens only."""
+    import torch
+
+    import paper_2509_06261_amd as fs
+
+    slab, n_slabs, lens = 64 * KiB, 64, [40, 200, 90]
+    mem = torch.zeros(slab * n_slabs, dtype=torch.uint8, device="cuda")
+    pool = fs.fs_pool_create(slab, mem.numel(), mem)
+    try:
+        _, model = fs.fs_model_register(pool, fs.FS_KV_FP16, 2, 128, 1)
+        T = fs.fs_model_geometry(pool, model).tokens_per_block
+        table = np.full((3, -(-max(lens) // T)), -1, np.int32)
+        for i, n in enumerate(lens):
+            table[i, : -(-n // T)] = fs.fs_blocks_alloc(pool, model, -(-n // T))[1]
+        table[2, 0] = -1  # sequence 2 brings no tokens: its entries are not read
+
+        def status(lens, table, offsets):
+            off = np.array(offsets, np.int32)
+            q = torch.ones((int(off[-1]), 8, 128), dtype=torch.float16, device="cuda")
+            ws = torch.full((fs.fs_prefill_workspace_bytes(3),), 0xff, dtype=torch.uint8, device="cuda")
+            fs.fs_prefill_attention(pool, model, 0, 8, 0.1, q, torch.from_numpy(table).cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda"),
+                                    torch.from_numpy(off).cuda(), off, torch.empty_like(q), None, ws)
+            torch.cuda.synchronize()
+            assert fs.fs_pool_get_option(pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
+            return fs.fs_decode_status(ws)
+
+        assert status(lens, table, [0, 40, 240, 240]) == 0
+        assert status([30, 200, 90], table, [0, 40, 240, 240]) == 1
+        bad = table.copy()
+        bad[1, 0] = 1 << 20
+        assert status(lens, bad, [0, 40, 41, 41]) == 4
+        assert status([0, 200, 90], bad, [0, 40, 41, 41]) == 5
+    finally:
+        fs.fs_pool_destroy(pool)
