@@ -317,6 +317,7 @@ enum fs_option {
    * sizes in four tiers: 3/8 of a wave's share of the launch's KV bytes (judged from seq_lens_host where given,
    * otherwise from max_blocks * tokens_per_block), between 64 and 768 KiB, for the sequences that hold the first
    * 70 % of a batch's bytes, then half, a quarter and an eighth of it.  Otherwise 4096 .. 2^30: every item that size.
+   * (Launches whose sequences need few splits or none take no such items at 0: a workgroup each instead.)
    * fs_decode_workspace_bytes answers for the pool's current setting. */
   FS_OPT_SPLIT_BYTES = 1,
   /* non-zero: every decode call brackets its attention kernel (not the work-list and combine kernels) with HIP

@@ -82,6 +82,12 @@ uint32_t plan_append_blocks(const fs_pool* p, append::MultiAppendArgs& P, int wa
   return next;
 }
 
+hipError_t launch_append_multi(const fs_pool* p, append::MultiAppendArgs& P, hipStream_t s) {
+  const uint32_t blocks = plan_append_blocks(p, P, kWaves);
+  hipLaunchKernelGGL(kv_append_multi_kernel, dim3(blocks), dim3(kWaves * 64), 0, s, P);
+  return hipGetLastError();
+}
+
 }  // namespace fs
 
 using namespace fs;
@@ -145,10 +151,8 @@ extern "C" int fs_kv_append_multi(fs_pool* p, const fs_append_t* appends, int n_
     set_error("fs_kv_append_multi: pool has no HIP device");
     return FS_ERR_DEVICE;
   }
-  const uint32_t blocks = plan_append_blocks(p, P, kWaves);
   (void)hipGetLastError();
-  hipLaunchKernelGGL(kv_append_multi_kernel, dim3(blocks), dim3(kWaves * 64), 0, (hipStream_t)stream, P);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = launch_append_multi(p, P, (hipStream_t)stream);
   if (e != hipSuccess) return device_error(e, "fs_kv_append_multi launch");
   return FS_OK;
 }

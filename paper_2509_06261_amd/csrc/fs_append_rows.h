@@ -354,5 +354,6 @@ __device__ __forceinline__ void append_block(const MultiAppendArgs& P, uint32_t 
 // workgroups of `waves` waves (first_block, n; returns the number of workgroups).
 int make_append_args(fs_pool* p, const fs_append_t& a, append::AppendArgs& out);
 uint32_t plan_append_blocks(const fs_pool* p, append::MultiAppendArgs& P, int waves);
+hipError_t launch_append_multi(const fs_pool* p, append::MultiAppendArgs& P, hipStream_t s);
 
 }  // namespace fs

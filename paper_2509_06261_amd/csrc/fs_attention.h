@@ -49,6 +49,7 @@ enum : int {
   kHdrStatus = 1,      // bit 0: a sequence length was out of range; bit 1: partial buffer too small;
                        // bit 2: a block-table entry inside a sequence's length was outside the pool
   kHdrTotalItems = 2,  // number of work items
+  kHdrIgnored = 4,     // what the items of a launch without preparation report to (nobody clears the status word then)
   kHdrBatchFirst = 8,  // [kMaxBatches] first work item of each batch (sequence-major numbering)
   kHdrPartOff = 32,    // [kMaxBatches] uint64: float offset of each batch's partials (word index of a uint64 array)
   kHdrPools = 64       // [kPools] ticket counters of the MFMA kernel's end-of-launch pools, kPoolStride words apart
@@ -240,9 +241,65 @@ __device__ __host__ inline ItemRange item_range(const DevBatch& B, int seq, int 
   return r;
 }
 
+// ---- Direct launches (MFMA kernel without a work list): one workgroup per (sequence, split, KV head) ----
+constexpr int kDirectEntries = 1024;  // block-table entries of an item, at most
+struct DirectArgs {
+  MultiArgs m;                     // chunk_runs of a batch: runs per split (a multiple of 16; unused with one split)
+  uint32_t splits[kMaxBatches];    // splits the grid holds per sequence of the batch; the last one takes all that is left
+  uint32_t items[kMaxBatches];     // sequences x splits x KV heads
+  uint64_t magic[kMaxBatches];     // ceil(2^32 items / items of this batch and the later ones)
+  uint64_t part_off[kMaxBatches];  // float offset of the batch's partial records
+  int32_t entries;                 // entries of the LDS table: blocks an item can touch
+  int32_t pad;
+};
+
+// Place `i` of the grid -> batch, and `i` the item's index within it (sequence, then split, heads innermost): the
+// batches' item lists merged proportionally, so that formats bound by the vector ALU and formats bound by memory share
+// every compute unit.  Batch by batch: of the first i places of what is left, floor(i n_b / n_left) are batch b's.
+__device__ __host__ inline int direct_batch(const DirectArgs& D, uint32_t& i) {
+  int b = 0;
+  for (; b + 1 < D.m.n_batches; ++b) {
+    const uint32_t before = (uint32_t)(((uint64_t)i * D.magic[b]) >> 32);
+    if ((uint32_t)((((uint64_t)i + 1) * D.magic[b]) >> 32) > before) {
+      i = before;
+      break;
+    }
+    i -= before;
+  }
+  return b;
+}
+
+// Runs [v0, v1) of split `split` of a sequence of `runs` runs.  The last split takes all that is left, as far as the
+// address table reaches; cut: something does not fit.
+struct DirectRange {
+  int v0, v1;
+  bool cut;
+};
+__device__ __host__ inline DirectRange direct_range(const DirectArgs& D, int b, int split, int runs) {
+  const DevBatch& B = D.m.b[b];
+  DirectRange r;
+  r.v0 = split * B.chunk_runs;
+  const int64_t table_end = ((int64_t)div_runs(r.v0, B.R, B.r_magic) + D.entries) * B.R;
+  const int64_t end = split + 1 == (int)D.splits[b] ? runs : (runs < r.v0 + B.chunk_runs ? runs : r.v0 + B.chunk_runs);
+  r.cut = end > table_end;
+  r.v1 = (int)(r.cut ? table_end : end);
+  return r;
+}
+
+// Splits that sequence really has.
+__device__ __host__ inline int direct_splits_of(const DirectArgs& D, int b, int runs) {
+  const int S = (int)D.splits[b];
+  if (S == 1) return 1;
+  const int n = (runs + D.m.b[b].chunk_runs - 1) / D.m.b[b].chunk_runs;
+  return n < S ? n : S;
+}
+
 // The device-side records of a decode call as the launch would build them (no workspace pointers, nothing
 // enqueued): for checks that replay the kernels' index arithmetic on the host.  use_mfma: which kernel would run.
 int debug_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, MultiArgs* out, bool* use_mfma);
+
+// The records of a direct launch, or false if the call would not be one.
+bool debug_plan_direct(fs_pool* p, const fs_batch_t* batches, int n_batches, DirectArgs* out);
 
 // Launchers implemented in the kernel translation units.
 hipError_t launch_prep(const MultiArgs& A, hipStream_t s);
@@ -251,5 +308,7 @@ hipError_t launch_generic_prefill(const MultiArgs& A, const int32_t* q_offsets, 
 hipError_t launch_combine(const MultiArgs& A, hipStream_t s);
 bool mfma_supports(const DevBatch& b);
 hipError_t launch_mfma(const MultiArgs& A, int n_workgroups, hipStream_t s);
+hipError_t launch_mfma_direct(const DirectArgs& D, hipStream_t s);
+hipError_t launch_direct_combine(const DirectArgs& D, hipStream_t s);
 
 }  // namespace fs

@@ -314,7 +314,43 @@ __global__ __launch_bounds__(kCombineWaves * 64, MAXNK <= 2 ? 8 : 4) void combin
   else if (MAXNK >= 8) combine_row<8>(P, chunk_stride, n_chunks, D, lane, out, lse);
 }
 
+// The same for a direct launch, whose partial records are numbered by the grid.
+template <int MAXNK>
+__global__ __launch_bounds__(kCombineWaves * 64, MAXNK <= 2 ? 8 : 4) void direct_combine_kernel(DirectArgs D) {
+  const MultiArgs& A = D.m;
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * kCombineWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (row >= A.n_qrows_total) return;
+  int b = 0;
+  while (b + 1 < A.n_batches && row >= A.b[b + 1].qrow_first) ++b;
+  const DevBatch& B = A.b[b];
+  const int local = row - B.qrow_first;
+  const int seq = local / B.n_q, h = local % B.n_q;
+  const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
+  int len = B.seq_lens[seq];
+  len = len < 1 ? 1 : (len > max_len ? max_len : len);
+  const int n_chunks = direct_splits_of(D, b, n_runs(len, B.g.T, B.R));
+  if (n_chunks <= 1) return;
+  const int HD = B.g.D, H = B.g.H;
+  const uint64_t first = (uint64_t)seq * D.splits[b] * (uint32_t)H + (uint32_t)(h / B.G);
+  const float* P = A.partials + D.part_off[b] + first * (uint64_t)B.part_stride + (uint64_t)(h % B.G) * (HD + 2);
+  const uint64_t chunk_stride = (uint64_t)H * B.part_stride;
+  _Float16* out = B.out + ((int64_t)seq * B.n_q + h) * HD;
+  float* lse = B.lse ? B.lse + (int64_t)seq * B.n_q + h : nullptr;
+  combine_row<MAXNK>(P, chunk_stride, n_chunks, HD, lane, out, lse);
+}
+
 }  // namespace
+
+hipError_t launch_direct_combine(const DirectArgs& D, hipStream_t s) {
+  const dim3 grid((D.m.n_qrows_total + kCombineWaves - 1) / kCombineWaves), block(kCombineWaves * 64);
+  switch (D.m.b[0].g.D) {  // (the same in every batch)
+    case 64: hipLaunchKernelGGL(direct_combine_kernel<1>, grid, block, 0, s, D); break;
+    case 128: hipLaunchKernelGGL(direct_combine_kernel<2>, grid, block, 0, s, D); break;
+    default: hipLaunchKernelGGL(direct_combine_kernel<4>, grid, block, 0, s, D); break;
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_prep(const MultiArgs& A, hipStream_t s) {
   hipLaunchKernelGGL(prep_kernel, dim3(kPrepGroups), dim3(kPrepThreads), 0, s, A);
@@ -515,7 +551,112 @@ int make_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, void* worksp
   return FS_OK;
 }
 
+// Whether the launch runs without a work list (see mfma_direct_kernel), and its records.  What decides:
+//   - A workgroup streams at most about 33 KB per us (four waves of 16 KiB in flight; twice that at head_dim 256), the
+//     whole chip 6200.  Splits cost a partial record each and a combine launch (6 us).
+//   - With no more (sequence, KV head) pairs than workgroups fit the chip at once, the sequences are cut so that all items
+//     run in one round: a second round of a few items is worse than any split size (20 sequences of 1000 - 5000 tokens, 4
+//     KV heads of 256: 320 places 62 us, 480 places 90 us, work list 73 us).
+//   - With more pairs than that, or where one round leaves an item that alone streams most of the launch, items are cut
+//     to 0.7 MB or a tenth of the launch, if the wait for the last long one (about half its time) would cost more than
+//     the cut (64 FP16 sequences of 512 - 4096 tokens, 8 KV heads: whole 120 us, cut in three 105 - 115, work list 128 -
+//     139).
+//   - Long launches that would be cut stay with the work list, whose splits suit every sequence's own length and whose
+//     waves do not wait for each other (four models, lognormal lengths: 1860 us against 2190); long launches of sequences
+//     of about one length, which need no cut, do not (250 FP16 sequences of 7000 - 8000 tokens: 1229 -> 1178 us).
+constexpr double kDirectCutUs = 170;              // above this a launch that needs cuts takes the work list
+constexpr uint64_t kDirectItemBytes = 700 * 1000;  // the smallest item a cut for balance makes
+bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, const MultiArgs& A, DirectArgs& D) {
+  if (p->opt.split_bytes) return false;
+  uint64_t total = 0, pairs = 0, longest = 0;
+  for (int i = 0; i < n_batches; ++i) {
+    const fs_geometry_t& g = p->models[batches[i].model].g;
+    uint64_t sum = 0;
+    for (int s = 0; s < batches[i].n_seq; ++s) {
+      const uint64_t bytes = head_bytes(batches[i], g, s);
+      longest = std::max(longest, bytes);
+      sum += bytes;
+    }
+    total += sum * (uint64_t)g.n_kv_heads;
+    pairs += (uint64_t)batches[i].n_seq * (uint64_t)g.n_kv_heads;
+  }
+  const int per_cu = mfma_wgs_per_cu(A.b[0].g.D);
+  const uint64_t slots = (uint64_t)(p->n_cu ? p->n_cu : 256) * per_cu;  // (no device: replays of the plan on the host)
+  const double all_us = (double)total / 6.2e6, wg_rate = per_cu == 1 ? 66e3 : 33e3;  // bytes per us
+  D.m = A;
+  // Records for items of at most `want` bytes; false where a launch of that kind is not possible.  useful: items that are
+  // not past their sequence's end.
+  uint64_t items = 0, useful = 0;
+  auto cut = [&](uint64_t want) {
+    uint64_t floats = 0;
+    items = useful = 0;
+    D.entries = 0;
+    for (int i = 0; i < n_batches; ++i) {
+      const fs_batch_t& b = batches[i];
+      const fs_geometry_t& g = p->models[b.model].g;
+      DevBatch& B = D.m.b[i];
+      const uint64_t token_bytes = 2 * (g.row_bytes + (uint64_t)g.param_bytes);
+      uint64_t most = 0;
+      for (int s = 0; s < b.n_seq; ++s) most = std::max(most, head_bytes(b, g, s));
+      uint64_t splits = (most + want - 1) / want;
+      B.chunk_runs = 0;
+      if (splits > 1 || B.max_blocks > kDirectEntries) {
+        const int64_t runs = n_runs((int)(most / token_bytes), g.tokens_per_block, B.R);
+        const int64_t cap = (int64_t)(kDirectEntries / 2 - 4) * B.R / 16 * 16;  // runs whose blocks fit half the table
+        if (cap < 16) return false;
+        const int64_t cr = std::min<int64_t>((runs + (int64_t)splits * 16 - 1) / ((int64_t)splits * 16) * 16, cap);
+        B.chunk_runs = (int32_t)cr;
+        splits = (uint64_t)((runs + cr - 1) / cr);
+        for (int s = 0; s < b.n_seq; ++s) {
+          const int64_t r = n_runs((int)(head_bytes(b, g, s) / token_bytes), g.tokens_per_block, B.R);
+          useful += (uint64_t)((r + cr - 1) / cr * g.n_kv_heads);
+        }
+      } else {
+        useful += (uint64_t)B.n_seq * (uint64_t)g.n_kv_heads;
+      }
+      if (splits == 1 && B.max_blocks > kDirectEntries) return false;  // (a longer length on the device would not fit)
+      // (twice a split's blocks: the last split takes what a sequence holds beyond the length known here)
+      D.entries = std::max(D.entries, splits == 1 ? B.max_blocks : std::min(2 * (B.chunk_runs / B.R) + 4, kDirectEntries));
+      D.splits[i] = (uint32_t)splits;
+      const uint64_t n = (uint64_t)B.n_seq * splits * (uint64_t)g.n_kv_heads;
+      items += n;
+      if (items > 0x3fffffff) return false;
+      D.items[i] = (uint32_t)n;
+      D.part_off[i] = floats;
+      if (splits > 1) floats += n * (uint64_t)B.part_stride;
+    }
+    return floats <= A.part_capacity;
+  };
+  uint64_t want = ~0ull >> 1;
+  const uint64_t small = std::max<uint64_t>(kDirectItemBytes, total / 10 / (uint64_t)(6.2e6 / wg_rate));
+  if (pairs <= slots) {
+    want = std::max<uint64_t>(total / (slots - pairs / 2), 64 << 10);
+    bool ok = cut(want);
+    for (int k = 0; k < 16 && (!ok || useful > slots) && want < longest; ++k) ok = cut(want += want / 8);
+    if (!ok) return false;
+    if ((double)std::min(want, longest) / wg_rate > 0.6 * all_us && longest > small + small / 2) ok = cut(want = small);
+    if (!ok) return false;
+  } else {
+    if (0.55 * (double)longest / wg_rate > 6.0 + 0.1 * all_us) want = small;
+    if (!cut(want)) return false;
+  }
+  if (all_us > kDirectCutUs && items > pairs) return false;
+  if (items > 4 * slots && items > 2 * useful) return false;  // mostly places past their sequence's end
+  uint64_t left = items;
+  for (int i = 0; i < n_batches; ++i) {
+    D.magic[i] = (((uint64_t)D.items[i] << 32) + left - 1) / left;
+    left -= D.items[i];
+  }
+  return true;
+}
+
 }  // namespace
+
+bool debug_plan_direct(fs_pool* p, const fs_batch_t* batches, int n_batches, DirectArgs* out) {
+  Plan plan;
+  if (make_plan(p, batches, n_batches, nullptr, plan, false) != FS_OK || !plan.use_mfma) return false;
+  return plan_direct(p, batches, n_batches, plan.args, *out);
+}
 
 int debug_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, MultiArgs* out, bool* use_mfma) {
   Plan plan;
@@ -572,6 +713,24 @@ int decode_launch_one(fs_pool* p, const fs_batch_t* batches, int n_batches, void
   const uint64_t workers_per_wg = use_mfma ? 4 : 1;
   const int n_wg = (int)std::min<uint64_t>((uint64_t)p->n_cu * wgs_per_cu,
                                            std::max<uint64_t>((plan.ub_items + workers_per_wg - 1) / workers_per_wg, 1));
+#ifndef FS_TIMELINE  // (its clock readings are of the work-list kernel)
+  DirectArgs D;
+  if (use_mfma && plan_direct(p, batches, n_batches, plan.args, D)) {
+    hipError_t e = P.n ? launch_append_multi(p, P, s) : hipSuccess;
+    if (e != hipSuccess) return device_error(e, "append launch");
+    if (p->opt.timing && time_begin) (void)hipEventRecord(p->opt.ev0, s);
+    e = launch_mfma_direct(D, s);
+    if (p->opt.timing && time_end) (void)hipEventRecord(p->opt.ev1, s);
+    if (e != hipSuccess) return device_error(e, "attention launch");
+    for (int i = 0; i < n_batches; ++i) {
+      if (D.splits[i] == 1) continue;
+      e = launch_direct_combine(D, s);
+      if (e != hipSuccess) return device_error(e, "combine launch");
+      break;
+    }
+    return FS_OK;
+  }
+#endif
   plan.args.n_workers = use_mfma ? (uint32_t)n_wg * (uint32_t)workers_per_wg : 0u;
   hipError_t e = P.n ? launch_step_front(p, plan.args, P, s) : launch_prep(plan.args, s);
   if (e != hipSuccess) return device_error(e, "prep launch");

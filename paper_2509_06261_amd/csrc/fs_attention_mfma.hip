@@ -9,6 +9,8 @@
 //   the split's partial record) straight from its accumulators.  No wave waits for another.
 //   An item's record carries its sequence's length, so the only look-up between a queue ticket and the item's
 //   first K/V requests is the record, then the block-table entries.
+// Launches whose sequences need no fine splitting take mfma_direct_kernel instead: one workgroup per (sequence, split,
+// KV head), no queue (plan_direct decides).
 #include "fs_mfma_tiles.h"
 
 namespace fs {
@@ -113,6 +115,38 @@ __device__ __forceinline__ void stream_item(const MultiArgs& A, const ItemPlan& 
   stream_tiles<DT, GP, HD, true>(X, g, P.v0, qb, qsum, alpha, st, j, c);
 }
 
+// Per-head sums over the lanes of the head.
+template <int DT, int GP, int HD>
+__device__ __forceinline__ void reduce_sums(StateT<HD>& st) {
+  if constexpr (GP == 4) {
+    st.l += __shfl_xor(st.l, 4, 64);
+    st.l += __shfl_xor(st.l, 8, 64);
+  }
+  st.l += __shfl_xor(st.l, 16, 64);
+  st.l += __shfl_xor(st.l, 32, 64);
+  if constexpr (Fmt<DT, HD>::kParBytes != 0) {
+    if constexpr (GP == 4) {
+      st.zc += __shfl_xor(st.zc, 4, 64);
+      st.zc += __shfl_xor(st.zc, 8, 64);
+    }
+    st.zc += __shfl_xor(st.zc, 16, 64);
+    st.zc += __shfl_xor(st.zc, 32, 64);
+  }
+}
+
+// Accumulator row r of this lane, dequantized (not divided by the sum).
+template <int DT, int HD>
+__device__ __forceinline__ void output_row(const StateT<HD>& st, int r, float Z, float v_static, float (&o)[HD / 16]) {
+#pragma unroll
+  for (int e = 0; e < HD / 16; ++e) {
+    // integer formats: undo the 2^-24 of the subnormal encoding (and the 16 of INT4's odd code positions)
+    const float f = DT == FS_KV_INT8 ? kTwo24 : (DT == FS_KV_INT4 ? ((e & 1) ? kTwo20 : kTwo24) : 1.0f);
+    o[e] = st.acc[e][r] * f;
+    if constexpr (Fmt<DT, HD>::kParBytes != 0) o[e] += Z;
+    o[e] *= v_static;
+  }
+}
+
 // part_off: the batches' offsets into the partial buffer (the workspace header's words, copied to LDS once per
 // workgroup: read from memory here they would be one more round trip in front of every item's stores).
 template <int DT, int GP, int HD>
@@ -132,21 +166,8 @@ __device__ __forceinline__ void finish_item(const MultiArgs& A, const ItemPlan& 
     return;
   }
 
-  // ---- output: per-head sums over the lanes of the head, then rows h < G straight from the accumulators ----
-  if constexpr (GP == 4) {
-    st.l += __shfl_xor(st.l, 4, 64);
-    st.l += __shfl_xor(st.l, 8, 64);
-  }
-  st.l += __shfl_xor(st.l, 16, 64);
-  st.l += __shfl_xor(st.l, 32, 64);
-  if constexpr (Fmt<DT, HD>::kParBytes != 0) {
-    if constexpr (GP == 4) {
-      st.zc += __shfl_xor(st.zc, 4, 64);
-      st.zc += __shfl_xor(st.zc, 8, 64);
-    }
-    st.zc += __shfl_xor(st.zc, 16, 64);
-    st.zc += __shfl_xor(st.zc, 32, 64);
-  }
+  // ---- output: rows h < G straight from the accumulators ----
+  reduce_sums<DT, GP, HD>(st);
   const float v_static = DT == FS_KV_FP8_E4M3 ? B.v_scale[head] : 1.0f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -154,14 +175,7 @@ __device__ __forceinline__ void finish_item(const MultiArgs& A, const ItemPlan& 
     const float L = __shfl(st.l, h, 64), M = __shfl(st.m, h, 64), Z = __shfl(st.zc, h, 64);
     if (h < G) {
       float o[NE];
-#pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        // integer formats: undo the 2^-24 of the subnormal encoding (and the 16 of INT4's odd code positions)
-        const float f = DT == FS_KV_INT8 ? kTwo24 : (DT == FS_KV_INT4 ? ((e & 1) ? kTwo20 : kTwo24) : 1.0f);
-        o[e] = st.acc[e][r] * f;
-        if constexpr (Fmt<DT, HD>::kParBytes != 0) o[e] += Z;
-        o[e] *= v_static;
-      }
+      output_row<DT, HD>(st, r, Z, v_static, o);
       const int qh = head * G + h;
       if (n_chunks == 1) {
         const float inv = 1.0f / L;
@@ -194,14 +208,45 @@ __device__ __forceinline__ void finish_item(const MultiArgs& A, const ItemPlan& 
   }
 }
 
-// step 0: stream_item, step 1: finish_item
+// The state of a wave as the partial records of its G heads, rec[h (HD + 2)] in LDS: unnormalized output row,
+// reference (natural-log units), sum.
+template <int DT, int GP, int HD>
+__device__ __forceinline__ void leave_records(const MultiArgs& A, const ItemPlan& P, StateT<HD>& st, float* rec) {
+  constexpr int NE = HD / 16;
+  const DevBatch& B = A.b[P.b];
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  const int j = lane >> 4, c = lane & 15;
+  reduce_sums<DT, GP, HD>(st);
+  const float v_static = DT == FS_KV_FP8_E4M3 ? B.v_scale[P.head] : 1.0f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int h = 4 * j + r;
+    const float L = __shfl(st.l, h, 64), M = __shfl(st.m, h, 64), Z = __shfl(st.zc, h, 64);
+    if (h < B.G) {
+      float* pr = rec + h * (HD + 2);
+      float o[NE];
+      output_row<DT, HD>(st, r, Z, v_static, o);
+#pragma unroll
+      for (int e = 0; e < NE; e += 2) *reinterpret_cast<float2*>(pr + NE * c + e) = float2{o[e], o[e + 1]};
+      if (c == 0) *reinterpret_cast<float2*>(pr + HD) = float2{M * kLn2, L};
+    }
+  }
+}
+
+// step 0: stream_item, step 1: finish_item, step 2: stream_item and leave_records
 template <int STEP, int GP, int HD>
 __device__ __forceinline__ void dispatch_dtype(const MultiArgs& A, const ItemPlan& P, uint64_t* s_ptr, StateT<HD>& st,
-                                               const uint64_t* part_off) {
+                                               const uint64_t* part_off, float* rec) {
   switch (A.b[P.b].g.dtype) {
-#define FS_STEP(DT)                                                  \
-  if constexpr (STEP == 0) stream_item<DT, GP, HD>(A, P, s_ptr, st); \
-  else finish_item<DT, GP, HD>(A, P, st, part_off);                  \
+#define FS_STEP(DT)                                                       \
+  if constexpr (STEP == 0) stream_item<DT, GP, HD>(A, P, s_ptr, st);      \
+  else if constexpr (STEP == 1) finish_item<DT, GP, HD>(A, P, st, part_off); \
+  else {                                                                  \
+    StateT<HD> own;                                                       \
+    stream_item<DT, GP, HD>(A, P, s_ptr, own);                            \
+    leave_records<DT, GP, HD>(A, P, own, rec);                            \
+  }                                                                       \
   break
     case FS_KV_FP16: FS_STEP(FS_KV_FP16);
     case FS_KV_FP8_E4M3: FS_STEP(FS_KV_FP8_E4M3);
@@ -213,9 +258,9 @@ __device__ __forceinline__ void dispatch_dtype(const MultiArgs& A, const ItemPla
 
 template <int STEP, int HD>
 __device__ __forceinline__ void dispatch_item(const MultiArgs& A, const ItemPlan& P, uint64_t* s_ptr, StateT<HD>& st,
-                                              const uint64_t* part_off) {
-  if (A.b[P.b].G <= 4) dispatch_dtype<STEP, 4, HD>(A, P, s_ptr, st, part_off);
-  else dispatch_dtype<STEP, 16, HD>(A, P, s_ptr, st, part_off);
+                                              const uint64_t* part_off, float* rec = nullptr) {
+  if (A.b[P.b].G <= 4) dispatch_dtype<STEP, 4, HD>(A, P, s_ptr, st, part_off, rec);
+  else dispatch_dtype<STEP, 16, HD>(A, P, s_ptr, st, part_off, rec);
 }
 
 // One kernel per head_dim (every batch of a launch has the same one).
@@ -332,6 +377,139 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_attention_
 #endif
 }
 
+// ---- Direct launches: one workgroup per (sequence, split, KV head), no work list ------------------------------------
+// The grid itself is the queue: the hardware hands workgroups out in order as compute units fall free.  A workgroup finds
+// its item from its index, requests the sequence's length and the item's block-table entries together, its four waves
+// stream a quarter of the item's tiles each and leave their records in LDS, where the workgroup merges them: into the
+// output if the sequence has one split, into a partial record for direct_combine_kernel otherwise.
+// What it saves over the work list: the preparation launch, tickets, item records, most partial records, and the combine
+// wherever a sequence has one split.  Eight sequences of up to 256 tokens, 4 KV heads of 64: 19.3 -> 8.3 us; 64 FP16
+// sequences of 512 - 4096 tokens, 8 KV heads of 128: 128 - 139 -> 105 - 115 us (5.3 - 5.8 TB/s); 128 FP8 sequences of
+// 3000 - 4000 tokens: 184 - 202 -> 147 - 153 us; five FP8 sequences of 9000 - 32768: 56 -> 42 us.
+// The status word has nobody to clear it before the launch: the items report to a word that nobody reads, and workgroup
+// 0 does nothing but judge the whole call and write the word.
+constexpr int kEntriesPerThread = kDirectEntries / kThreads;
+
+// Status of the call: bit 0 for a length out of range, bit 1 for one that the launch's splits cannot hold, bit 2 for a
+// block-table entry outside the pool inside a length.
+__device__ __forceinline__ void direct_status(const DirectArgs& D, uint32_t* status) {
+  const MultiArgs& A = D.m;
+  __shared__ uint32_t s_flags;
+  if (threadIdx.x == 0) s_flags = 0;
+  __syncthreads();
+  // as many neighbouring threads per sequence as there are for all of them
+  int per = kThreads;
+  while (per > 1 && per * A.n_seq_total > kThreads) per >>= 1;
+  uint32_t flags = 0;
+  for (int i = threadIdx.x / per; i < A.n_seq_total; i += kThreads / per) {
+    int b = 0;
+    while (b + 1 < A.n_batches && i >= A.b[b + 1].seq_first) ++b;
+    const DevBatch& B = A.b[b];
+    const int seq = i - B.seq_first;
+    const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
+    int len = B.seq_lens[seq];
+    if (len < 1 || len > max_len) flags |= 1u;
+    len = len < 1 ? 1 : min(len, max_len);
+    if (direct_range(D, b, (int)D.splits[b] - 1, n_runs(len, B.g.T, B.R)).cut) flags |= 2u;
+    const int nb = (len + B.g.T - 1) / B.g.T;
+    const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
+#pragma unroll 8
+    for (int k = threadIdx.x % per; k < nb; k += per) flags |= (uint32_t)table[k] < B.n_blocks ? 0u : 4u;
+  }
+  if (flags) atomicOr(&s_flags, flags);
+  __syncthreads();
+  if (threadIdx.x == 0) *status = s_flags;
+}
+
+template <int HD>
+__global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_kernel(DirectArgs D, uint32_t* status) {
+  extern __shared__ uint64_t s_tab[];
+  if (blockIdx.x == 0) {
+    direct_status(D, status);
+    return;
+  }
+  const MultiArgs& A = D.m;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* s_rec = reinterpret_cast<float*>(s_tab + D.entries);
+  ItemPlan P;
+  uint32_t local = blockIdx.x - 1;
+  P.b = direct_batch(D, local);
+  const DevBatch& B = A.b[P.b];
+  const uint32_t H = (uint32_t)B.g.H;
+  P.head = (int)(local % H);
+  P.chunk = (int)(local / H % D.splits[P.b]);
+  P.seq = (int)(local / H / D.splits[P.b]);
+  P.local = local;
+  // the block-table entries do not wait for the length: the item's first run, and so its first block, is known
+  P.k0 = div_runs(P.chunk * B.chunk_runs, B.R, B.r_magic);
+  const int32_t* table = B.tables + (int64_t)P.seq * B.max_blocks;
+  int32_t tab[kEntriesPerThread];
+#pragma unroll
+  for (int q = 0; q < kEntriesPerThread; ++q) {
+    const int i = (int)threadIdx.x + kThreads * q;
+    tab[q] = i < D.entries && P.k0 + i < B.max_blocks ? table[P.k0 + i] : 0;
+  }
+  const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
+  int len = __builtin_amdgcn_readfirstlane(B.seq_lens[P.seq]);
+  len = len < 1 ? 1 : min(len, max_len);
+  P.len = len;
+  const int runs = n_runs(len, B.g.T, B.R);
+  const DirectRange r = direct_range(D, P.b, P.chunk, runs);
+  if (r.v0 >= r.v1) return;  // (uniform: a split past the sequence's end)
+  P.nb = div_runs(r.v1 - 1, B.R, B.r_magic) - P.k0 + 1;
+  const int share = ((r.v1 - r.v0 + 3) / 4 + kWaves - 1) / kWaves * 4;  // runs per wave: whole tiles
+  P.v0 = r.v0 + wave * share;
+  P.v1 = min(r.v1, P.v0 + share);
+  const uint8_t* head_base = B.layer_base + (uint64_t)P.head * B.g.head_chunk;
+#pragma unroll
+  for (int q = 0; q < kEntriesPerThread; ++q) {
+    const int i = (int)threadIdx.x + kThreads * q;
+    if (i < P.nb) s_tab[i] = reinterpret_cast<uint64_t>(head_base + (uint64_t)checked_block(tab[q], B.n_blocks, A.header) * B.g.block_budget);
+  }
+  __syncthreads();
+  const int G = B.G;
+  float* rec = s_rec + wave * G * (HD + 2);
+  if (P.v0 < P.v1) {  // wave-uniform
+    StateT<HD> unused;
+    dispatch_item<2, HD>(A, P, s_tab, unused, nullptr, rec);
+  } else if (lane < G) {
+    *reinterpret_cast<float2*>(rec + lane * (HD + 2) + HD) = float2{-INFINITY, 0.f};
+  }
+  __syncthreads();
+  const bool whole = direct_splits_of(D, P.b, runs) == 1;
+  float* part = A.partials + D.part_off[P.b] + (uint64_t)local * (uint64_t)B.part_stride;
+  for (int i = threadIdx.x; i < G * (HD / 2); i += kThreads) {
+    const int h = i / (HD / 2), d = 2 * (i % (HD / 2));
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_rec[(w * G + h) * (HD + 2) + HD]);
+    float L = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float* pr = s_rec + (w * G + h) * (HD + 2);
+      const float2 ml = *reinterpret_cast<const float2*>(pr + HD);
+      if (ml.y > 0.f) {  // (a wave without tokens left no row)
+        const float x = expf(ml.x - M);
+        const float2 v = *reinterpret_cast<const float2*>(pr + d);
+        L += ml.y * x;
+        o0 += v.x * x;
+        o1 += v.y * x;
+      }
+    }
+    if (whole) {
+      const float inv = 1.0f / L;
+      const int64_t row = (int64_t)P.seq * B.n_q + P.head * G + h;
+      const half2v hv = {(_Float16)(o0 * inv), (_Float16)(o1 * inv)};
+      *reinterpret_cast<uint32_t*>(B.out + row * HD + d) = h2u(hv);
+      if (d == 0 && B.lse) B.lse[row] = M + logf(L);
+    } else {
+      *reinterpret_cast<float2*>(part + h * (HD + 2) + d) = float2{o0, o1};
+      if (d == 0) *reinterpret_cast<float2*>(part + h * (HD + 2) + HD) = float2{M, L};
+    }
+  }
+}
+
 }  // namespace
 
 // Shapes this kernel covers: head_dim 64, 128 or 256, at least 8 tokens per block (a run of 8 slots fits a block),
@@ -352,6 +530,26 @@ hipError_t launch_mfma(const MultiArgs& A, int n_workgroups, hipStream_t s) {
     case 64: hipLaunchKernelGGL(mfma_attention_kernel<64>, dim3(n_workgroups), dim3(kThreads), smem, s, A, entries); break;
     case 128: hipLaunchKernelGGL(mfma_attention_kernel<128>, dim3(n_workgroups), dim3(kThreads), smem, s, A, entries); break;
     default: hipLaunchKernelGGL(mfma_attention_kernel<256>, dim3(n_workgroups), dim3(kThreads), smem, s, A, entries); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_mfma_direct(const DirectArgs& args, hipStream_t s) {
+  DirectArgs D = args;
+  int heads = 0;
+  uint32_t items = 0;
+  for (int i = 0; i < D.m.n_batches; ++i) {
+    heads = std::max(heads, (int)D.m.b[i].G);
+    items += D.items[i];
+  }
+  const int hd = D.m.b[0].g.D;
+  const size_t smem = (size_t)D.entries * sizeof(uint64_t) + (size_t)kWaves * heads * (hd + 2) * sizeof(float);
+  uint32_t* status = D.m.header + kHdrStatus;
+  D.m.header += kHdrIgnored - kHdrStatus;
+  switch (hd) {
+    case 64: hipLaunchKernelGGL(mfma_direct_kernel<64>, dim3(items + 1), dim3(kThreads), smem, s, D, status); break;
+    case 128: hipLaunchKernelGGL(mfma_direct_kernel<128>, dim3(items + 1), dim3(kThreads), smem, s, D, status); break;
+    default: hipLaunchKernelGGL(mfma_direct_kernel<256>, dim3(items + 1), dim3(kThreads), smem, s, D, status); break;
   }
   return hipGetLastError();
 }

@@ -1482,13 +1482,10 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
 // A launch with no more work items than compute units needs no queue: workgroup b takes one item, found from the
 // sequences' tile counts, which every workgroup scans itself (as many sequences as it has threads, at most).  That
 // saves the preparation kernel and the gap behind it.  What the preparation also does, the reset of the status word,
-// cannot be ordered before other workgroups' reports without it, so the items report nothing (to a word nobody reads)
+// cannot be ordered before other workgroups' reports without it, so the items report to a word that nobody reads (kHdrIgnored)
 // and the workgroup of the last item -- the first tile of a head, its shortest -- judges the call as a whole when it is
 // done: every length and chunk, and every block-table entry that the sequences with new tokens reach.
 constexpr int kSmallBlocks = 8;  // column blocks of the workgroup kernel's smaller item
-constexpr int kHdrIgnored = 4;  // header word the items of a direct launch report to
-static_assert(kHdrIgnored > kHdrTotalItems && kHdrIgnored < kHdrBatchFirst, "a free word of the header");
-
 __device__ __forceinline__ uint32_t direct_scan(const PrefillArgs& P, uint32_t* s_tf, uint32_t* s_wave) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t flags = 0;

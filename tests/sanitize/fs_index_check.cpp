@@ -17,6 +17,9 @@
 // have; and a table segment of a context never touches more blocks than the wave's address table holds.
 // The decode work queue's closed-form placement (queue_place: the batches' item lists merged proportionally) is
 // checked to be one-to-one onto the queue and order-preserving within a batch.
+// Launches without a work list (fs::debug_plan_direct) are replayed workgroup by workgroup, also where the device's
+// lengths are not the host's: every place of the grid is one item, the items' waves cover every token exactly once unless
+// the status says otherwise, table entries and partial records stay inside their buffers.
 // The vector-ALU kernel's launch is replayed where the device's lengths are not the ones the host sized the workspace
 // for: what is queued, every queued item's tokens and table entries, the partial records and the combine's rows stay
 // inside the plan's capacities or are the ones the kernels skip and report.
@@ -404,10 +407,147 @@ void token_split_overflow(int rounds) {
   }
 }
 
+// Launches without a work list.
+void direct_launches(int rounds) {
+  const int dtypes[4] = {FS_KV_FP16, FS_KV_FP8_E4M3, FS_KV_INT8, FS_KV_INT4};
+  const int dims[3] = {64, 128, 256};
+  int planned = 0, cut_in_splits = 0;
+  for (int round = 0; round < rounds; ++round) {
+    const uint64_t slab = (uint64_t)(16 << rnd_int(5)) << 10;
+    fs_pool* p = nullptr;
+    CHECK(fs_pool_create(slab, 2048 * slab, kFakeBase, &p) == FS_OK);
+    if (!p) continue;
+    const int nb = 1 + rnd_int(4), D = dims[rnd_int(3)];
+    fs_batch_t b[4] = {};
+    std::vector<int32_t> host[4], dev[4];
+    bool ok = true;
+    for (int k = 0; k < nb && ok; ++k) {
+      const int H = 1 + rnd_int(6);
+      fs_model_t m;
+      const int T = fs_model_register(p, dtypes[rnd_int(4)], H, D, 1 + rnd_int(2), &m);
+      ok = T >= 8;
+      if (!ok) break;
+      const int n_seq = 1 + rnd_int(rnd_int(3) ? 6 : 60), top = rnd_int(2) ? 300 : (rnd_int(3) ? 6000 : 40000);
+      int max_len = 1;
+      for (int i = 0; i < n_seq; ++i) {
+        host[k].push_back(1 + rnd_int(top));
+        max_len = std::max(max_len, (int)host[k].back());
+      }
+      dev[k] = host[k];
+      b[k].max_blocks = (max_len + T - 1) / T + rnd_int(3) * rnd_int(200);
+      if (round % 3 == 0)  // the device disagrees on some sequences
+        for (int i = 0; i < n_seq; ++i)
+          if (rnd_int(2)) dev[k][i] = rnd_int(4) == 0 ? 1000000 : (rnd_int(4) == 0 ? -rnd_int(2) : 1 + rnd_int(2 * max_len));
+      const int G[5] = {1, 2, 4, 8, 16};
+      b[k].model = m;
+      b[k].n_q_heads = H * G[rnd_int(5)];
+      b[k].sm_scale = 0.1f;
+      b[k].q = (const void*)0x20000000;
+      b[k].block_tables = (const int32_t*)0x30000000;
+      b[k].seq_lens = (const int32_t*)0x40000000;
+      b[k].seq_lens_host = rnd_int(4) ? host[k].data() : nullptr;
+      b[k].n_seq = n_seq;
+      b[k].out = (void*)0x50000000;
+    }
+    fs::DirectArgs A;
+    if (ok && fs::debug_plan_direct(p, b, nb, &A)) {
+      ++planned;
+      CHECK(A.entries >= 1 && A.entries <= fs::kDirectEntries);
+      uint32_t total = 0;
+      uint64_t part_end = 0;
+      std::vector<std::vector<std::vector<uint8_t>>> seen(nb);
+      std::vector<std::vector<uint8_t>> hit(nb);
+      std::vector<uint32_t> next(nb, 0);
+      std::vector<std::vector<int>> clen(nb);
+      for (int k = 0; k < nb; ++k) {
+        const fs::DevBatch& B = A.m.b[k];
+        CHECK(A.items[k] == (uint32_t)B.n_seq * A.splits[k] * (uint32_t)B.g.H);
+        CHECK(A.part_off[k] == part_end);
+        if (A.splits[k] > 1) {
+          ++cut_in_splits;
+          part_end += (uint64_t)A.items[k] * (uint64_t)B.part_stride;
+          CHECK(B.chunk_runs >= 16 && B.chunk_runs % 16 == 0);
+        }
+        total += A.items[k];
+        hit[k].assign(A.items[k], 0);
+        seen[k].resize(B.n_seq);
+        for (int i = 0; i < B.n_seq; ++i) {
+          const int max_len = (int)std::min<int64_t>((int64_t)B.max_blocks * B.g.T, 0x7fffffff);
+          clen[k].push_back(dev[k][i] < 1 ? 1 : std::min((int)dev[k][i], max_len));
+          seen[k][i].assign((size_t)clen[k][i] * B.g.H, 0);
+        }
+      }
+      CHECK(part_end <= A.m.part_capacity);
+      for (uint32_t place = 0; place < total; ++place) {
+        uint32_t local = place;
+        const int k = fs::direct_batch(A, local);
+        CHECK(k >= 0 && k < nb && local < A.items[k] && hit[k][local] == 0);
+        if (k < 0 || k >= nb || local >= A.items[k]) continue;
+        CHECK(local == next[k]);  // in order within the batch
+        next[k] = local + 1;
+        hit[k][local] = 1;
+        ++g_items;
+        const fs::DevBatch& B = A.m.b[k];
+        const uint32_t H = (uint32_t)B.g.H;
+        const int head = (int)(local % H), split = (int)(local / H % A.splits[k]), seq = (int)(local / H / A.splits[k]);
+        CHECK(seq < B.n_seq);
+        const int len = clen[k][seq], runs = fs::n_runs(len, B.g.T, B.R);
+        const int k0 = fs::div_runs(split * B.chunk_runs, B.R, B.r_magic);
+        const fs::DirectRange r = fs::direct_range(A, k, split, runs);
+        if (r.v0 >= r.v1) {
+          CHECK(split > 0);
+          continue;
+        }
+        CHECK(split < fs::direct_splits_of(A, k, runs));
+        const int nblk = fs::div_runs(r.v1 - 1, B.R, B.r_magic) - k0 + 1;
+        CHECK(nblk >= 1 && nblk <= A.entries && k0 + nblk <= B.max_blocks);
+        const int share = ((r.v1 - r.v0 + 3) / 4 + 3) / 4 * 4;
+        int covered = r.v0;
+        for (int wave = 0; wave < 4; ++wave) {
+          const int v0 = r.v0 + wave * share, v1 = std::min(r.v1, v0 + share);
+          if (v0 >= v1) continue;
+          CHECK(v0 == covered);
+          covered = v1;
+          fs::ItemCtx X;
+          X.chunk_ptr = nullptr;
+          X.T = B.g.T;
+          X.R = B.R;
+          X.r_magic = B.r_magic;
+          X.len = X.len_u = len;
+          X.v_end = v1;
+          X.k0 = k0;
+          for (int v = v0; v < v1 + 4; ++v) {
+            const fs::RunGeom L = fs::run_geom(X, v);
+            CHECK(L.k_rel >= 0 && L.k_rel < nblk && L.start >= 0 && L.start + 8 <= B.g.T);
+            for (int i = std::max(L.lo, 0); i < L.hi; ++i) {
+              const int tok = L.tok0 + i;
+              CHECK(tok >= 0 && tok < len);
+              if (tok >= 0 && tok < len) ++seen[k][seq][(size_t)tok * H + head];
+            }
+          }
+        }
+        CHECK(covered == r.v1);
+      }
+      for (int k = 0; k < nb; ++k) {
+        const fs::DevBatch& B = A.m.b[k];
+        CHECK(next[k] == A.items[k]);
+        for (int i = 0; i < B.n_seq; ++i) {
+          const bool cut = fs::direct_range(A, k, (int)A.splits[k] - 1, fs::n_runs(clen[k][i], B.g.T, B.R)).cut;
+          if (dev[k] == host[k] || !b[k].seq_lens_host || A.splits[k] == 1) CHECK(!cut);
+          for (size_t t = 0; t < seen[k][i].size(); ++t) CHECK(seen[k][i][t] == 1 || (cut && seen[k][i][t] == 0));
+        }
+      }
+    }
+    fs_pool_destroy(p);
+  }
+  CHECK(planned > rounds / 4 && cut_in_splits > rounds / 16);
+}
+
 }  // namespace
 
 int main() {
   run(600);
+  direct_launches(300);
   prefill_queues(60);
   decode_queue_places(200);
   token_split_overflow(400);
