@@ -801,7 +801,9 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
 
 // One staged 32-token sub-tile for the wave's column blocks: wide_tile with the operands read from LDS.
 // VPRE: V fragments requested in front of the softmax (registers permitting)
-template <int DT, int NCB, int SUBS, int VPRE, int HD>
+// SUM32: the running sum of an FP16 / FP8 column takes the weights before they are rounded to fp16 (twice the
+// instructions of the dot product with ones), as the 16-column kernel does: for launches that kernel served before
+template <int DT, int NCB, int SUBS, int VPRE, int HD, bool SUM32>
 __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const ItemCtx& X, const u32x4 (&qb)[NCB][HD / 32],
                                         const float (&qsum)[NCB], const int (&len_cb)[NCB], float alpha, int first_pos,
                                         int vb, int lane, int j, int c, WideState<NCB, HD>& st, bool whole_runs = false) {
@@ -938,7 +940,8 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
         const float e1 = __builtin_amdgcn_exp2f(fmaf(x[cb][2 * q + 1], alpha, -m));
         const half2v h = {(_Float16)e0, (_Float16)e1};
         pk[cb][q] = h2u(h);
-        l = __builtin_amdgcn_fdot2(h, one, l, false);
+        if constexpr (SUM32) l += e0 + e1;
+        else l = __builtin_amdgcn_fdot2(h, one, l, false);
       }
       st.l[cb] = l;
     }
@@ -965,7 +968,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 // smem: two stages, then the workgroup's block-address table.
 // DEQ (INT8 / INT4 only): the staging waves dequantize, the tile code is the FP16 one.
 // header: where a block-table entry outside the pool is reported.
-template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD>
+template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD, bool SUM32>
 __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq, int head, int qt, uint8_t* smem, uint64_t* s_tab,
                                 int w) {
   static_assert(NW == SUBS || NW == 2 * SUBS, "staging roles");
@@ -1094,7 +1097,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       const int n_live = min(SUBS, (w_end - (v0 + i * SUBS * 4) + 3) >> 2);
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
       for (int sub = 0; sub < n_live; ++sub)
-        wg_tile<CDT, NCB, SUBS, kVPre, HD>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4, lane, j,
+        wg_tile<CDT, NCB, SUBS, kVPre, HD, SUM32>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4, lane, j,
                                            c, st, whole_runs);
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS, HD);
       if (more) stage_to(next, vb_next);
@@ -1527,7 +1530,7 @@ __device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_
 }
 
 // WPC = workgroups per compute unit the kernel is built for
-template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD>
+template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false>
 __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
   extern __shared__ uint64_t smem64[];
   uint8_t* smem = reinterpret_cast<uint8_t*>(smem64);
@@ -1593,7 +1596,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
     const uint64_t tl_begin = wall_clock64();
 #endif
     if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
-    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD>(P, header, seq, head, qt, smem, s_tab, wave);
+    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32>(P, header, seq, head, qt, smem, s_tab, wave);
 #ifdef FS_TIMELINE
     ++tl_items;
     if (threadIdx.x == 0 && item < kPfTimelineItems) {
@@ -1833,12 +1836,14 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
 #define FS_WG(DT)                                  \
   (nw == 8 ? prefill_wg_kernel<DT, 8, 2, 4, 1> \
            : (p->opt.prefill_pipe ? prefill_wg_kernel<DT, 4, 4, 4, 1, true> : prefill_wg_kernel<DT, 4, 4, 4, 1>))
-    // (that kernel at head_dim 128 only; a smaller launch by the library's own choice keeps the integer codes exact, as
-    // the 16-column kernel that served it before)
-    const bool deq = p->opt.prefill_deq && nw == 8 && ncb == 16 && !d64 && (ncb_env || items >= (uint64_t)p->n_cu);
+    // (that kernel at head_dim 128 only; a smaller launch by the library's own choice keeps the integer codes exact and
+    // its sums over the unrounded weights, as the 16-column kernel that served it before)
+    const bool large = ncb_env || items >= (uint64_t)p->n_cu;
+    const bool deq = p->opt.prefill_deq && nw == 8 && ncb == 16 && !d64 && large;
     if (ncb == kSmallBlocks) {
       // (integer codes exact, as in the 16-column kernel that served these launches before)
-#define FS_WG1(DT) (d64 ? prefill_wg_kernel<DT, 8, 1, 4, 1, false, false, 64> : prefill_wg_kernel<DT, 8, 1, 4, 1>)
+#define FS_WG1(DT) \
+  (d64 ? prefill_wg_kernel<DT, 8, 1, 4, 1, false, false, 64, true> : prefill_wg_kernel<DT, 8, 1, 4, 1, false, false, kD, true>)
       switch (g.kv_dtype) {
         case FS_KV_FP16: kern = FS_WG1(FS_KV_FP16); break;
         case FS_KV_FP8_E4M3: kern = FS_WG1(FS_KV_FP8_E4M3); break;
@@ -1848,17 +1853,17 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
 #undef FS_WG1
     } else if (d64) {
       // Integer codes enter the MFMAs exactly here, as in the 16-column kernel that served this head_dim before.
-      // (24 FP16 prompts of 256 - 3000 tokens, GQA 4:1: 1804 -> 624 us, 179 -> 516 TFLOP/s; with four column blocks
+      // (24 FP16 prompts of 256 - 3000 tokens, GQA 4:1: 1804 -> 646 us, 179 -> 498 TFLOP/s; with four column blocks
       // per wave 647 us.)
       switch (g.kv_dtype) {
-        case FS_KV_FP16: kern = prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, 64>; break;
-        case FS_KV_FP8_E4M3: kern = prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, 64>; break;
-        case FS_KV_INT8: kern = prefill_wg_kernel<FS_KV_INT8, 8, 2, 4, 1, false, false, 64>; break;
-        default: kern = prefill_wg_kernel<FS_KV_INT4, 8, 2, 4, 1, false, false, 64>; break;
+        case FS_KV_FP16: kern = prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, 64, true>; break;
+        case FS_KV_FP8_E4M3: kern = prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, 64, true>; break;
+        case FS_KV_INT8: kern = prefill_wg_kernel<FS_KV_INT8, 8, 2, 4, 1, false, false, 64, true>; break;
+        default: kern = prefill_wg_kernel<FS_KV_INT4, 8, 2, 4, 1, false, false, 64, true>; break;
       }
     } else switch (g.kv_dtype) {
-      case FS_KV_FP16: kern = FS_WG(FS_KV_FP16); break;
-      case FS_KV_FP8_E4M3: kern = FS_WG(FS_KV_FP8_E4M3); break;
+      case FS_KV_FP16: kern = large || nw == 4 ? FS_WG(FS_KV_FP16) : prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, kD, true>; break;
+      case FS_KV_FP8_E4M3: kern = large || nw == 4 ? FS_WG(FS_KV_FP8_E4M3) : prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, kD, true>; break;
       case FS_KV_INT8: kern = deq ? prefill_wg_kernel<FS_KV_INT8, 8, 2, 4, 1, false, true> : FS_WG(FS_KV_INT8); break;
       default: kern = deq ? prefill_wg_kernel<FS_KV_INT4, 8, 2, 4, 1, false, true> : FS_WG(FS_KV_INT4); break;
     }
