@@ -194,6 +194,7 @@ struct ItemCtx {
   int len_u;                  // tokens the sequence holds for any column (wave-uniform); decode: == len
   int T, R;
   uint32_t r_magic;           // ceil(2^32 / R)
+  uint64_t base_off = 0;      // added to every address of the table
 };
 
 // run / R  (r_magic = ceil(2^32 / R) does not fit 32 bits for R = 1; exact while run * R < 2^32)

@@ -157,7 +157,7 @@ __device__ __forceinline__ RunLoc locate(const ItemCtx& X, int vr) {
   L.tok0 = r.tok0;
   L.hi = r.hi;
   L.hi_u = r.hi_u;
-  L.base = (gptr)X.chunk_ptr[r.k_rel];
+  L.base = (gptr)(X.chunk_ptr[r.k_rel] + X.base_off);
   return L;
 }
 

@@ -39,7 +39,8 @@ struct PrefillArgs {
   int32_t seg_runs;          // runs of 8 token slots streamed per refill of the block-address table (multiple of 4)
   int32_t table_entries;     // LDS table entries per wave
   int32_t n_rows;            // query rows in q / out (host value: every row index is clamped into it)
-  int32_t tf_cache;          // workgroup kernels: 1 = tile_first is copied into LDS at kernel start
+  int32_t tf_cache;          // workgroup kernels: 1 = tile_first is copied into LDS at kernel start, 2 = every workgroup
+                             // scans (and sorts) the sequences itself (see scan_sequences)
   int32_t whole_runs;        // 1 = tokens per block is a multiple of 8: run r starts at token 8 r, no run is shifted
   int32_t chunk_shift;       // workgroup kernels: log2 of the consecutive work items that go to one XCD
   int32_t direct;            // workgroup kernels: 1 = no preparation ran and no tickets are drawn (see "Direct launches")
@@ -60,18 +61,27 @@ constexpr uint64_t kPfTimelineBytes = 64 * (kPfTimelineGroups + kPfTimelineItems
 
 constexpr int kPrepThreads = 1024;
 
-// Query tiles of sequence i; raises bit 0 of `flags` for a length or chunk out of range.
-__device__ __forceinline__ uint32_t seq_tiles(const PrefillArgs& P, int i, uint32_t& flags) {
+// Sequence i's clamped length, the query tokens it brings and their first row; raises bit 0 of `flags` for a length or
+// chunk out of range.
+struct SeqShape {
+  int len, n_new, q0;
+};
+__device__ __forceinline__ SeqShape seq_shape(const PrefillArgs& P, int i, uint32_t& flags) {
   const DevBatch& B = P.b;
   const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
-  int len = B.seq_lens[i];
-  int n_new = P.q_offsets[i + 1] - P.q_offsets[i];
-  if (len < 1 || len > max_len || n_new < 0 || n_new > len) {
+  SeqShape s;
+  s.len = B.seq_lens[i];
+  s.q0 = P.q_offsets[i];
+  s.n_new = P.q_offsets[i + 1] - s.q0;
+  if (s.len < 1 || s.len > max_len || s.n_new < 0 || s.n_new > s.len) {
     flags |= 1u;
-    len = len < 1 ? 1 : min(len, max_len);
-    n_new = n_new < 0 ? 0 : min(n_new, len);
+    s.len = s.len < 1 ? 1 : min(s.len, max_len);
+    s.n_new = s.n_new < 0 ? 0 : min(s.n_new, s.len);
   }
-  return (uint32_t)((n_new + P.tpt * P.ncb - 1) / (P.tpt * P.ncb));
+  return s;
+}
+__device__ __forceinline__ uint32_t shape_tiles(const PrefillArgs& P, const SeqShape& s) {
+  return (uint32_t)((s.n_new + P.tpt * P.ncb - 1) / (P.tpt * P.ncb));
 }
 
 // Query tiles per sequence -> tile_first (exclusive scan), validation flags, counter reset.  One workgroup.
@@ -91,9 +101,10 @@ __global__ __launch_bounds__(kPrepThreads) void prefill_prep_kernel(PrefillArgs 
     uint32_t v = 0;
     if (i < B.n_seq) {
       uint32_t flags = 0;
-      v = seq_tiles(P, i, flags);
+      v = shape_tiles(P, seq_shape(P, i, flags));
       if (flags) atomicOr(P.header + kHdrStatus, flags);
     }
+    if (P.tf_cache == 2) break;  // (one round: every workgroup of the attention kernel scans for itself)
     uint32_t incl = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -968,9 +979,16 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 // smem: two stages, then the workgroup's block-address table.
 // DEQ (INT8 / INT4 only): the staging waves dequantize, the tile code is the FP16 one.
 // header: where a block-table entry outside the pool is reported.
+// S: what the workgroup holds of the sequence it last worked on.  A sequence that fits one table segment has all its
+// blocks' addresses in LDS (without the head, which is added at the use), so that an item of the same sequence as the one
+// before starts with its first K/V fetch.
+struct SeqHeld {
+  int seq = -1;
+  bool table = false;  // the address table holds all blocks of the sequence
+};
 template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD, bool SUM32>
-__device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq, int head, int qt, uint8_t* smem, uint64_t* s_tab,
-                                int w) {
+__device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq, const SeqShape& shape, int head, int qt,
+                                uint8_t* smem, uint64_t* s_tab, int w, SeqHeld& S) {
   static_assert(NW == SUBS || NW == 2 * SUBS, "staging roles");
 #ifdef FS_TIMELINE
   uint64_t tl_ph[5] = {(uint64_t)wall_clock64(), 0, 0, 0, 0};
@@ -990,11 +1008,9 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   asm volatile("" : "+v"(lane));
   const int j = lane >> 4, c = lane & 15;
   const int G = B.G;
-  const int max_len = (int)min((int64_t)B.max_blocks * g.T, (int64_t)0x7fffffff);
-  int len = B.seq_lens[seq];
-  len = len < 1 ? 1 : min(len, max_len);
-  int n_new = P.q_offsets[seq + 1] - P.q_offsets[seq];
-  n_new = n_new < 0 ? 0 : min(n_new, len);
+  if (seq != S.seq) S.table = false;  // (uniform)
+  S.seq = seq;
+  const int len = shape.len, n_new = shape.n_new;
   const int qw = P.tpt * NCB;                 // query tokens per wave
   const int r0_wg = qt * qw * NW;             // first query token of the item within the chunk
   if (r0_wg >= n_new) return;                 // (cannot happen with consistent inputs; uniform over the workgroup)
@@ -1011,6 +1027,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   X.len_u = len - n_new + r0_wg + n_tok_wg;
   X.len = X.len_u;
   X.chunk_ptr = s_tab;
+  X.base_off = (uint64_t)head * g.head_chunk;
 
   u32x4 qb[NCB][HD / 32];
   float qsum[NCB];
@@ -1023,7 +1040,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
     const int tok = cb * P.tpt + tok_c;  // query token of this lane's column in block cb
     const bool live = tok_c < P.tpt && tok < n_tok;
     len_cb[cb] = live ? first_pos + tok + 1 : X.len_u;  // a dead column (q = 0, never written) sees everything
-    row_cb[cb] = min(max(P.q_offsets[seq] + r0 + tok, 0), P.n_rows - 1);
+    row_cb[cb] = min(max(shape.q0 + r0 + tok, 0), P.n_rows - 1);
     load_q<DT, !DEQ, HD>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * HD, live, j, qb[cb], qsum[cb]);
     if constexpr (Fmt<CDT>::kParBytes != 0) {
       qsum[cb] += __shfl_xor(qsum[cb], 16, 64);
@@ -1037,22 +1054,23 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   }
 
   const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
-  const uint8_t* head_base = B.layer_base + (uint64_t)head * g.head_chunk;
   const int w_end = n_tok > 0 ? n_runs(first_pos + n_tok, g.T, B.R) : 0;  // runs this wave's last query sees
   const int n_run = n_runs(X.len_u, g.T, B.R);
   for (int v0 = 0; v0 < n_run; v0 += P.seg_runs) {
     X.v_end = min(n_run, v0 + P.seg_runs);
     X.k0 = div_runs(v0, B.R, B.r_magic);
-    {
+    if (!S.table) {  // (uniform)
       // the previous segment's (or item's) last barrier lies behind every use of the old table
-      const int nb = div_runs(X.v_end - 1, B.R, B.r_magic) - X.k0 + 1;
+      const int all = n_runs(len, g.T, B.R);
+      S.table = all <= P.seg_runs;  // one segment (v0 = 0): all of the sequence's blocks, for its next items
+      const int nb = div_runs((S.table ? all : X.v_end) - 1, B.R, B.r_magic) - X.k0 + 1;
       for (int i = threadIdx.x; i < nb; i += NW * 64)
-        s_tab[i] = reinterpret_cast<uint64_t>(head_base + (uint64_t)checked_block(table[X.k0 + i], B.n_blocks, header) * g.block_budget);
+        s_tab[i] = reinterpret_cast<uint64_t>(B.layer_base + (uint64_t)checked_block(table[X.k0 + i], B.n_blocks, header) * g.block_budget);
       __syncthreads();
-#ifdef FS_TIMELINE
-      if (v0 == 0) tl_ph[1] = wall_clock64();
-#endif
     }
+#ifdef FS_TIMELINE
+    if (v0 == 0) tl_ph[1] = wall_clock64();
+#endif
     const int n_super = (X.v_end - v0 + 4 * SUBS - 1) / (4 * SUBS);
     Tile<DT, 16, HD> t;
     uint32_t kpar[2] = {0u, 0u};  // (DEQ) K parameters of the rows this lane stages
@@ -1489,11 +1507,69 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
 // and the workgroup of the last item -- the first tile of a head, its shortest -- judges the call as a whole when it is
 // done: every length and chunk, and every block-table entry that the sequences with new tokens reach.
 constexpr int kSmallBlocks = 8;  // column blocks of the workgroup kernel's smaller item
-__device__ __forceinline__ uint32_t direct_scan(const PrefillArgs& P, uint32_t* s_tf, uint32_t* s_wave) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t flags = 0;
-  const uint32_t v = tid < P.b.n_seq ? seq_tiles(P, tid, flags) : 0u;
-  uint32_t incl = v;
+// The launch's sequences in LDS, where every item's look-ups find them: longest context first, so that the queue ends
+// with the shortest items (in the order of the call, 12 INT4 multi-head prompts of 300 - 3000 tokens left the workgroups
+// idle for 107 of 885 us at the launch's end on the timeline build, 64 FP16 prompts of 512 - 4096 tokens for 172 of 4800;
+// now 48 and 49).  The calls: 796 -> 754 us and 4075 - 4194 -> 3882 - 4110 us, 24 FP16 prompts of 256 - 3000 tokens at
+// head_dim 64 646 -> 605 us.
+struct SeqList {
+  uint32_t* tf;     // [n_seq + 1] first query tile of the k-th longest sequence
+  int32_t* seq;     // [n_seq] which sequence that is
+  SeqShape* shape;  // [n_seq] by sequence
+};
+__device__ __forceinline__ SeqList seq_list(void* lds, int n_seq) {
+  uint32_t* w = reinterpret_cast<uint32_t*>(lds);
+  return SeqList{w, reinterpret_cast<int32_t*>(w + n_seq + 1), reinterpret_cast<SeqShape*>(w + 2 * n_seq + 1)};
+}
+constexpr uint32_t seq_list_bytes(int n_seq) { return (5u * (uint32_t)n_seq + 1) * 4; }
+
+// Fills the list (n_seq <= threads of the workgroup); returns the number of query tiles.  s_tmp: n_seq + 16 words.
+__device__ __forceinline__ uint32_t scan_sequences(const PrefillArgs& P, const SeqList& L, uint32_t* s_tmp) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = P.b.n_seq;
+  uint32_t* s_wave = s_tmp + n;
+  SeqShape s{0, 0, 0};
+  if (n <= 64) {  // (uniform) one wave's work: no barrier but the last
+    if (wave == 0) {
+      uint32_t flags = 0;
+      if (lane < n) s = seq_shape(P, lane, flags);
+      int rank = 0;
+      for (int i = 0; i < n; ++i) {
+        const int l = __builtin_amdgcn_readlane(s.len, i);
+        rank += l > s.len || (l == s.len && i < lane);
+      }
+      const uint32_t v = lane < n ? shape_tiles(P, s) : 0u;
+      uint32_t first = 0;  // tiles of the longer sequences
+      for (int i = 0; i < n; ++i) {
+        const uint32_t r = __builtin_amdgcn_readlane(rank, i), u = __builtin_amdgcn_readlane(v, i);
+        first += (int)r < rank ? u : 0u;
+      }
+      if (lane < n) {
+        L.shape[lane] = s;
+        L.seq[rank] = lane;
+        L.tf[rank] = first;
+        if (rank == n - 1) L.tf[n] = first + v;
+      }
+    }
+    __syncthreads();
+    return L.tf[n];
+  }
+  if (tid < n) {
+    uint32_t flags = 0;
+    s = seq_shape(P, tid, flags);
+    L.shape[tid] = s;
+  }
+  __syncthreads();
+  if (tid < n) {
+    int rank = 0;
+    for (int i = 0; i < n; ++i) {
+      const int l = L.shape[i].len;
+      rank += l > s.len || (l == s.len && i < tid);
+    }
+    L.seq[rank] = tid;
+    s_tmp[rank] = shape_tiles(P, s);
+  }
+  __syncthreads();
+  uint32_t incl = tid < n ? s_tmp[tid] : 0u;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const uint32_t u = __shfl_up(incl, off, 64);
@@ -1503,10 +1579,10 @@ __device__ __forceinline__ uint32_t direct_scan(const PrefillArgs& P, uint32_t* 
   __syncthreads();
   uint32_t before = 0;
   for (int w = 0; w < wave; ++w) before += s_wave[w];
-  if (tid < P.b.n_seq) s_tf[tid + 1] = before + incl;
-  if (tid == 0) s_tf[0] = 0;
+  if (tid < n) L.tf[tid + 1] = before + incl;
+  if (tid == 0) L.tf[0] = 0;
   __syncthreads();
-  return s_tf[P.b.n_seq];
+  return L.tf[n];
 }
 
 template <int NT>
@@ -1515,12 +1591,10 @@ __device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_
   if (threadIdx.x == 0) *s_flags = 0;
   __syncthreads();
   uint32_t flags = 0;
-  const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
   for (int seq = threadIdx.x >> 6; seq < B.n_seq; seq += NT / 64) {
-    if (seq_tiles(P, seq, flags) == 0) continue;
-    int len = B.seq_lens[seq];
-    len = len < 1 ? 1 : min(len, max_len);
-    const int nb = (len + B.g.T - 1) / B.g.T;
+    const SeqShape s = seq_shape(P, seq, flags);
+    if (s.n_new == 0) continue;
+    const int nb = (s.len + B.g.T - 1) / B.g.T;
     const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
     for (int i = threadIdx.x & 63; i < nb; i += 64) flags |= (uint32_t)table[i] < B.n_blocks ? 0u : 4u;
   }
@@ -1535,7 +1609,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
   extern __shared__ uint64_t smem64[];
   uint8_t* smem = reinterpret_cast<uint8_t*>(smem64);
   uint64_t* s_tab = reinterpret_cast<uint64_t*>(smem + 2 * stage_bytes(SUBS, HD));
-  volatile uint32_t* s_ctl = reinterpret_cast<volatile uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8);
+  uint32_t* s_ctl = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8);
   const DevBatch& B = P.b;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1545,9 +1619,11 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
   uint32_t* const header = direct ? P.header + kHdrIgnored - kHdrStatus : P.header;
   const uint32_t* tf = P.tile_first;
   uint32_t total;
-  if (direct) {
-    total = __builtin_amdgcn_readfirstlane(direct_scan(P, s_tf, reinterpret_cast<uint32_t*>(smem))) * H;
-    tf = s_tf;
+  const SeqList list = seq_list(s_tf, B.n_seq);
+  const bool listed = !PIPE && P.tf_cache == 2;  // (uniform; always so in a direct launch)
+  if (listed) {
+    total = __builtin_amdgcn_readfirstlane(scan_sequences(P, list, reinterpret_cast<uint32_t*>(smem))) * H;
+    tf = list.tf;
   } else {
     total = P.tile_first[B.n_seq] * H;
     if (P.tf_cache) {  // (uniform)
@@ -1565,6 +1641,8 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
   uint64_t tl_items = 0;
 #endif
   ItemDraw d{0u, 0u};
+  SeqHeld held;
+  uint32_t turn = 0;
   if (wave == 0 && !direct) d = first_draw(P.header, blockIdx.x >> 3, lane);
   for (;;) {
 #ifdef FS_TIMELINE
@@ -1578,25 +1656,33 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
     } else {
       if (wave == 0) {  // one wave draws for the workgroup
         const bool ok = next_item(d, P.header, total, (uint32_t)P.chunk_shift, lane, item);
-        if (lane == 0) s_ctl[0] = ok ? item : 0xffffffffu;
+        if (lane == 0) s_ctl[turn] = ok ? item : 0xffffffffu;
       }
       __syncthreads();
-      item = __builtin_amdgcn_readfirstlane(s_ctl[0]);  // (an LDS load is not uniform to the compiler)
-      __syncthreads();  // everyone holds the item before the next draw may overwrite it
+      // (an LDS load is not uniform to the compiler; the next draw writes the other word, the one after it lies behind
+      // a barrier that every wave passes with this item in hand)
+      item = __builtin_amdgcn_readfirstlane(s_ctl[turn]);
+      turn ^= 1;
       if (item == 0xffffffffu) break;
     }
     int seq, head, qt;
-    if (!decode_item(P, tf, item, H, seq, head, qt)) continue;
+    const int found = decode_item(P, tf, item, H, seq, head, qt);
+    if (!__builtin_amdgcn_readfirstlane(found)) continue;  // (uniform, so that what lives across items stays scalar)
+    uint32_t unused = 0;
+    seq = __builtin_amdgcn_readfirstlane(listed ? list.seq[seq] : seq);
+    SeqShape shape = listed ? list.shape[seq] : seq_shape(P, seq, unused);
+    shape.len = __builtin_amdgcn_readfirstlane(shape.len);
+    shape.n_new = __builtin_amdgcn_readfirstlane(shape.n_new);
+    shape.q0 = __builtin_amdgcn_readfirstlane(shape.q0);
     // (the same in every lane; said so, the item's addresses and bounds live in scalar registers: FP16 needs no
     // scratch any more, and 64 prompts of 512 - 4096 tokens run 4232 -> 4126 us)
-    seq = __builtin_amdgcn_readfirstlane(seq);
     head = __builtin_amdgcn_readfirstlane(head);
     qt = __builtin_amdgcn_readfirstlane(qt);
 #ifdef FS_TIMELINE
     const uint64_t tl_begin = wall_clock64();
 #endif
     if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
-    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32>(P, header, seq, head, qt, smem, s_tab, wave);
+    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32>(P, header, seq, shape, head, qt, smem, s_tab, wave, held);
 #ifdef FS_TIMELINE
     ++tl_items;
     if (threadIdx.x == 0 && item < kPfTimelineItems) {
@@ -1795,8 +1881,11 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   const uint64_t items = tiles * (uint64_t)g.n_kv_heads;
   const bool wg = ncb == 16 || ncb == kSmallBlocks;
   const int nw = p->opt.prefill_nw == 4 && ncb == 16 && !d64 ? 4 : 8;
+  // the workgroups list the sequences themselves while they have a thread for each; the per-sequence tile counts of more
+  // go to LDS while they fit beside the stages (16 KiB: 4095 sequences)
+  P.tf_cache = !wg || generic ? 0 : nw == 8 && n_seq <= nw * 64 ? 2 : (uint64_t)n_seq + 1 <= 4096;
   // no more items than compute units: a direct launch (see "Direct launches")
-  P.direct = wg && !generic && nw == 8 && items <= (uint64_t)p->n_cu && n_seq <= nw * 64;
+  P.direct = P.tf_cache == 2 && items <= (uint64_t)p->n_cu;
   hipError_t e = hipSuccess;
   if (!P.direct) {
     hipLaunchKernelGGL(prefill_prep_kernel, dim3(1), dim3(kPrepThreads), 0, s, P);
@@ -1826,10 +1915,8 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // fewer while that leaves an XCD less than eight chunks to balance with.
   P.chunk_shift = 7;
   while (P.chunk_shift > (int32_t)kWgChunkShift && (items >> P.chunk_shift) < 64) --P.chunk_shift;
-  // the per-sequence tile counts go to LDS while they fit beside the stages (16 KiB: 4095 sequences)
-  P.tf_cache = wg && (uint64_t)n_seq + 1 <= 4096;
   const size_t smem = wg ? 2 * (size_t)stage_bytes(subs, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes +
-                               (P.tf_cache ? (((size_t)n_seq + 1) * 4 + 15) / 16 * 16 : 0)
+                               (P.tf_cache == 2 ? seq_list_bytes(n_seq) : P.tf_cache ? (((size_t)n_seq + 1) * 4 + 15) / 16 * 16 : 0)
                          : (size_t)kWaves * P.table_entries * sizeof(uint64_t);
   if (wg) {
     void (*kern)(PrefillArgs) = nullptr;
