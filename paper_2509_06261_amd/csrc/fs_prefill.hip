@@ -1507,6 +1507,7 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
 // cannot be ordered before other workgroups' reports without it, so the items report to a word that nobody reads (kHdrIgnored)
 // and the workgroup of the last item -- the first tile of a head, its shortest -- judges the call as a whole when it is
 // done: every length and chunk, and every block-table entry that the sequences with new tokens reach.
+constexpr int kBlocks256 = 4;    // ... and of its item at head_dim 256
 constexpr int kSmallBlocks = 8;  // column blocks of the workgroup kernel's smaller item
 // The launch's sequences in LDS, where every item's look-ups find them: longest context first, so that the queue ends
 // with the shortest items (in the order of the call, 12 INT4 multi-head prompts of 300 - 3000 tokens left the workgroups
@@ -1791,10 +1792,12 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // the wide kernels fold the (positive) softmax scale into the exponential's argument; any other scale takes
   // the 16-column kernel, which does not
   const bool scale_ok = sm_scale > 0.f && sm_scale < INFINITY;
-  // (head_dim 64: the 8-wave workgroup kernels or the 16-column kernel; 256: the 16-column kernel)
-  const bool d64 = g.head_dim == 64;
-  int ncb = !scale_ok || (g.head_dim != kD && !d64) ? 1 : (ncb_env ? ncb_env : 16);
-  if (d64 && ncb != 16) ncb = 1;  // (the wide wave-level kernels are written for head_dim 128)
+  // (head_dim 64: the 8-wave workgroup kernels or the 16-column kernel; 256: the 4-wave workgroup kernel of one block per
+  // wave or the 16-column kernel)
+  const bool d64 = g.head_dim == 64, d256 = g.head_dim == 256;
+  int ncb = !scale_ok || (g.head_dim != kD && !d64 && !d256) ? 1 : (ncb_env ? ncb_env : 16);
+  if ((d64 || d256) && ncb != 16) ncb = 1;  // (the wide wave-level kernels are written for head_dim 128)
+  if (d256 && ncb == 16) ncb = kBlocks256;
   uint64_t tiles = 0;
   auto count_tiles = [&](int blocks) {
     tiles = 0;
@@ -1820,6 +1823,16 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     // heads: 29 us)
     if (tiles * (uint64_t)g.n_kv_heads <= (uint64_t)p->n_cu) ncb = d64 && tiles * (uint64_t)g.n_kv_heads < 64 ? 1 : kSmallBlocks;
     if (ncb != kSmallBlocks) (void)count_tiles(ncb);
+  }
+  // head_dim 256: the workgroup kernel, one wave per SIMD, for FP16 and for launches of no more items than compute units
+  // (and at least half as many); the other formats' larger launches have enough waves in the 16-column kernel, which
+  // reads half the bytes per row.  12 prompts of 300 - 3000 tokens, 4 KV heads x 4: FP16 1541 -> 1176 us, but FP8 861 ->
+  // 1089; one FP16 prompt of 900 tokens 95 -> 52.5 us.
+  if (ncb == kBlocks256 && d256 && !ncb_env &&
+      (tiles * (uint64_t)g.n_kv_heads < (uint64_t)p->n_cu / 2 ||
+       (g.kv_dtype != FS_KV_FP16 && tiles * (uint64_t)g.n_kv_heads > (uint64_t)p->n_cu))) {
+    ncb = 1;
+    (void)count_tiles(ncb);
   }
   const int64_t n_rows = q_offsets_host[n_seq];
   if (tiles * (uint64_t)g.n_kv_heads > 0xfffffff0ull || n_rows > 0x7fffffff) {
@@ -1880,11 +1893,11 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   hipStream_t s = (hipStream_t)stream;
   (void)hipGetLastError();
   const uint64_t items = tiles * (uint64_t)g.n_kv_heads;
-  const bool wg = ncb == 16 || ncb == kSmallBlocks;
-  const int nw = p->opt.prefill_nw == 4 && ncb == 16 && !d64 ? 4 : 8;
+  const bool wg = ncb == 16 || ncb == kSmallBlocks || (d256 && ncb == kBlocks256);
+  const int nw = d256 || (p->opt.prefill_nw == 4 && ncb == 16 && !d64) ? 4 : 8;
   // the workgroups list the sequences themselves while they have a thread for each; the per-sequence tile counts of more
   // go to LDS while they fit beside the stages (16 KiB: 4095 sequences)
-  P.tf_cache = !wg || generic ? 0 : nw == 8 && n_seq <= nw * 64 ? 2 : (uint64_t)n_seq + 1 <= 4096;
+  P.tf_cache = !wg || generic ? 0 : (nw == 8 || d256) && n_seq <= nw * 64 ? 2 : (uint64_t)n_seq + 1 <= 4096;
   // no more items than compute units: a direct launch (see "Direct launches")
   P.direct = P.tf_cache == 2 && items <= (uint64_t)p->n_cu;
   hipError_t e = hipSuccess;
@@ -1908,7 +1921,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // waves per SIMD: the 16-column kernel runs two, the wider wave-level ones one
   const int wps = ncb == 1 ? mfma_wgs_per_cu(g.head_dim) : 1;
   // workgroup kernels: 16 blocks = 8 waves x 2 (default) or 4 x 4, 4 sub-tiles per step, one workgroup per compute unit
-  const int subs = 4, wpc = 1;
+  const int subs = d256 ? 2 : 4, wpc = 1;
   const int n_wg = P.direct ? (int)((items + 7) / 8 * 8) : wg ? (int)std::min<uint64_t>((uint64_t)p->n_cu * wpc, std::max<uint64_t>(items, 1))
                       : (int)std::min<uint64_t>((uint64_t)p->n_cu * wps, std::max<uint64_t>((items + kWaves - 1) / kWaves, 1));
   // Consecutive items -- the query tiles of one (sequence, head), which stream the same K/V -- go to one XCD in
@@ -1928,7 +1941,16 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     // its sums over the unrounded weights, as the 16-column kernel that served it before)
     const bool large = ncb_env || items >= (uint64_t)p->n_cu;
     const bool deq = p->opt.prefill_deq && nw == 8 && ncb == 16 && !d64 && large;
-    if (ncb == kSmallBlocks) {
+    if (d256) {
+      // Four waves of one block each (a wave's share of a sub-tile's K or V, 64 registers in FP16, and its accumulators
+      // leave room for no second one), one wave per SIMD, 64 tokens per step
+      switch (g.kv_dtype) {
+        case FS_KV_FP16: kern = prefill_wg_kernel<FS_KV_FP16, 4, 1, 2, 1, false, false, 256, true>; break;
+        case FS_KV_FP8_E4M3: kern = prefill_wg_kernel<FS_KV_FP8_E4M3, 4, 1, 2, 1, false, false, 256, true>; break;
+        case FS_KV_INT8: kern = prefill_wg_kernel<FS_KV_INT8, 4, 1, 2, 1, false, false, 256, true>; break;
+        default: kern = prefill_wg_kernel<FS_KV_INT4, 4, 1, 2, 1, false, false, 256, true>; break;
+      }
+    } else if (ncb == kSmallBlocks) {
       // (integer codes exact, as in the 16-column kernel that served these launches before)
 #define FS_WG1(DT) \
   (d64 ? prefill_wg_kernel<DT, 8, 1, 4, 1, false, false, 64, true> : prefill_wg_kernel<DT, 8, 1, 4, 1, false, false, kD, true>)

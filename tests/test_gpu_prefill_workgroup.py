@@ -13,7 +13,7 @@ CHUNKS = np.array([1, 0, 32, 1, 17, 64, 16, 128, 33, 200, 1, 300, 65], np.int32)
 
 
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
-@pytest.mark.parametrize("head_dim,group", [(64, 4), (64, 1), (64, 3), (128, 4), (128, 1)])
+@pytest.mark.parametrize("head_dim,group", [(64, 4), (64, 1), (64, 3), (128, 4), (128, 1), (256, 4), (256, 3)])
 def test_workgroup_kernel_edges(dtype, head_dim, group, monkeypatch):
     import gpu_harness
     import gpu_workload
@@ -27,7 +27,7 @@ def test_workgroup_kernel_edges(dtype, head_dim, group, monkeypatch):
         par.gw.populate([[1]])
         print("T", par.gw.T, par.prefill_and_check(0, 1, EDGES), par.prefill_and_check(0, 1, CHUNKS))
         ran = fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)
-        assert ran & 0xffff == (16 | 8 << 8), ran
+        assert ran & 0xffff == (4 | 4 << 8 if head_dim == 256 else 16 | 8 << 8), ran
         assert bool(ran >> 16 & 1) == (head_dim == 128 and dtype in (INT8, INT4))  # exact codes at head_dim 64
     finally:
         par.close()
