@@ -973,7 +973,8 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 // and stages K and V of sub-tile w; with NW == 2 SUBS waves 0..SUBS-1 stage the K fragments of sub-tile w and the
 // others the V fragments and parameters of sub-tile w - SUBS.  Built variants: 8 waves x 2 blocks, 4 sub-tiles per
 // step, one workgroup per compute unit (two waves per SIMD, so that one's softmax runs under the other's MFMAs);
-// 4 x 4, 4 sub-tiles (one wave per SIMD).  (A third one -- 4 x 2 with 2 sub-tiles per step, two workgroups per
+// 4 x 4, 4 sub-tiles (one wave per SIMD); 8 x 1 for small launches; 4 x 1 with 2 sub-tiles per step at head_dim 256.
+// (Another one -- 4 x 2 with 2 sub-tiles per step, two workgroups per
 // compute unit -- passed its small cases but ended a full-size two-model run with the GPU faulted or hung; the
 // cause was not found and the variant is no longer built.)
 // smem: two stages, then the workgroup's block-address table.
@@ -1711,7 +1712,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
 #endif
 }
 
-// The 16-column kernel; the only MFMA prefill kernel for head_dim 64 and 256 (HD: its tile code takes any of the three).
+// The 16-column kernel (HD: its tile code takes any of the three head_dims).
 template <int HD>
 __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void prefill_kernel(PrefillArgs P) {
   extern __shared__ uint64_t smem64[];
