@@ -108,7 +108,7 @@ __device__ __forceinline__ void stream_item(const MultiArgs& A, const ItemPlan& 
 
 #pragma unroll
   for (int e = 0; e < HD / 16; ++e) st.acc[e] = float4v{0.f, 0.f, 0.f, 0.f};
-  st.m = -INFINITY;
+  st.m = kNoReference;
   st.l = 0.f;
   st.zc = 0.f;
 
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_ker
     for (int w = 0; w < kWaves; ++w) {
       const float* pr = s_rec + (w * G + h) * (HD + 2);
       const float2 ml = *reinterpret_cast<const float2*>(pr + HD);
-      if (ml.y > 0.f) {  // (a wave without tokens left no row)
+      if (ml.x != -INFINITY) {  // (a wave without tokens left no row; one with a NaN logit has a NaN sum, which goes on)
         const float x = expf(ml.x - M);
         const float2 v = *reinterpret_cast<const float2*>(pr + d);
         L += ml.y * x;

@@ -130,6 +130,10 @@ __device__ __forceinline__ void int4x8(uint32_t w, uint32_t (&r)[4]) {
 constexpr float kTwo24 = 16777216.0f;
 constexpr float kTwo20 = 1048576.0f;
 constexpr float kTau = 3.0f;  // log2 of the largest softmax weight tolerated before the reference is moved
+// The decode kernel's reference before the first logit: the lowest finite number, below which only a logit of -inf lies.
+// Tokens of such a logit then weigh e^(-inf) = 0 wherever they stand.  (With -inf as the start they are -inf - -inf = NaN
+// for a wave that sees no other token yet, although the sequence as a whole has a finite result.)
+constexpr float kNoReference = -3.402823466e38f;
 
 // GP = padded group size: 4 when the KV head serves at most 4 query heads, else 16.  The MFMAs always work on 16
 // head columns; GP decides how the softmax between them is spread over the lanes (see softmax_pv).
@@ -395,8 +399,8 @@ __device__ __forceinline__ uint32_t from_shl(uint32_t src) {
 }
 
 // Moves the reference of the lazy online softmax: called when some logit of the tile exceeds its head's
-// reference by more than kTau (always on the first tile, where m = -inf).  tmax = largest logit among this
-// lane's tokens; the lanes of a head are those with equal c % GP.
+// reference by more than kTau (on the first tile always, unless all its logits are -inf).  tmax = largest logit among
+// this lane's tokens; the lanes of a head are those with equal c % GP.
 template <int DT, int GP, int HD>
 __device__ __forceinline__ void move_reference(StateT<HD>& st, float tmax, int j) {
   if constexpr (GP == 4) {
@@ -405,7 +409,7 @@ __device__ __forceinline__ void move_reference(StateT<HD>& st, float tmax, int j
   }
   tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
   tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-  const float m_new = fmaxf(st.m, tmax);  // finite: the tile's first run holds a token of the item
+  const float m_new = fmaxf(st.m, tmax);
   const float corr = __builtin_amdgcn_exp2f(st.m - m_new);
   st.l *= corr;
   if constexpr (Fmt<DT>::kParBytes != 0) st.zc *= corr;
