@@ -317,7 +317,7 @@ enum fs_option {
    * sizes in four tiers: 3/8 of a wave's share of the launch's KV bytes (judged from seq_lens_host where given,
    * otherwise from max_blocks * tokens_per_block), between 64 and 768 KiB, for the sequences that hold the first
    * 70 % of a batch's bytes, then half, a quarter and an eighth of it.  Otherwise 4096 .. 2^30: every item that size.
-   * (Launches whose sequences need few splits or none take no such items at 0: a workgroup each instead.)
+   * (At 0 this is about launches from a work list, see FS_OPT_DECODE_WORK_LIST; a forced size always takes one.)
    * fs_decode_workspace_bytes answers for the pool's current setting. */
   FS_OPT_SPLIT_BYTES = 1,
   /* non-zero: every decode call brackets its attention kernel (not the work-list and combine kernels) with HIP
@@ -341,7 +341,13 @@ enum fs_option {
   /* read-only: the kernel the pool's latest fs_prefill_attention call launched:
    * column blocks | waves << 8 | staged dequantization << 16 | pipelined << 17 (0: none yet; column blocks 0 with
    * bit 18 set: the vector-ALU kernel) */
-  FS_OPT_LAST_PREFILL_KERNEL = 7
+  FS_OPT_LAST_PREFILL_KERNEL = 7,
+  /* non-zero: the MFMA decode kernel always takes its work from a list that a preparation kernel writes; 0 (default): a
+   * launch whose sequences need few splits or none runs without one, a workgroup per (sequence, split, KV head) */
+  FS_OPT_DECODE_WORK_LIST = 8,
+  /* read-only: the kernels the pool's latest decode call launched, a bit mask: 1 = the generic kernel, 2 = the MFMA kernel
+   * with a work list, 4 = the MFMA kernel without one (0: none yet) */
+  FS_OPT_LAST_DECODE_KERNEL = 9
 };
 int fs_pool_set_option(fs_pool* pool, int option, int64_t value);
 int fs_pool_get_option(fs_pool* pool, int option, int64_t* value);

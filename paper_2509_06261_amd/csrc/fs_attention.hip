@@ -567,7 +567,7 @@ int make_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, void* worksp
 constexpr double kDirectCutUs = 170;              // above this a launch that needs cuts takes the work list
 constexpr uint64_t kDirectItemBytes = 700 * 1000;  // the smallest item a cut for balance makes
 bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, const MultiArgs& A, DirectArgs& D) {
-  if (p->opt.split_bytes) return false;
+  if (p->opt.split_bytes || p->opt.decode_list) return false;
   uint64_t total = 0, pairs = 0, longest = 0;
   for (int i = 0; i < n_batches; ++i) {
     const fs_geometry_t& g = p->models[batches[i].model].g;
@@ -713,9 +713,11 @@ int decode_launch_one(fs_pool* p, const fs_batch_t* batches, int n_batches, void
   const uint64_t workers_per_wg = use_mfma ? 4 : 1;
   const int n_wg = (int)std::min<uint64_t>((uint64_t)p->n_cu * wgs_per_cu,
                                            std::max<uint64_t>((plan.ub_items + workers_per_wg - 1) / workers_per_wg, 1));
+  if (time_begin) p->opt.last_decode = 0;  // (the call's first launch sequence)
 #ifndef FS_TIMELINE  // (its clock readings are of the work-list kernel)
   DirectArgs D;
   if (use_mfma && plan_direct(p, batches, n_batches, plan.args, D)) {
+    p->opt.last_decode |= 4;
     hipError_t e = P.n ? launch_append_multi(p, P, s) : hipSuccess;
     if (e != hipSuccess) return device_error(e, "append launch");
     if (p->opt.timing && time_begin) (void)hipEventRecord(p->opt.ev0, s);
@@ -731,6 +733,7 @@ int decode_launch_one(fs_pool* p, const fs_batch_t* batches, int n_batches, void
     return FS_OK;
   }
 #endif
+  p->opt.last_decode |= use_mfma ? 2 : 1;
   plan.args.n_workers = use_mfma ? (uint32_t)n_wg * (uint32_t)workers_per_wg : 0u;
   hipError_t e = P.n ? launch_step_front(p, plan.args, P, s) : launch_prep(plan.args, s);
   if (e != hipSuccess) return device_error(e, "prep launch");
@@ -868,6 +871,9 @@ int fs_pool_set_option(fs_pool* p, int option, int64_t value) {
     case FS_OPT_PREFILL_STAGED_DEQUANT:
       o.prefill_deq = value != 0;
       return FS_OK;
+    case FS_OPT_DECODE_WORK_LIST:
+      o.decode_list = value != 0;
+      return FS_OK;
     default:
       break;
   }
@@ -887,6 +893,8 @@ int fs_pool_get_option(fs_pool* p, int option, int64_t* value) {
     case FS_OPT_PREFILL_PIPELINED: *value = o.prefill_pipe; return FS_OK;
     case FS_OPT_PREFILL_STAGED_DEQUANT: *value = o.prefill_deq; return FS_OK;
     case FS_OPT_LAST_PREFILL_KERNEL: *value = o.last_prefill; return FS_OK;
+    case FS_OPT_DECODE_WORK_LIST: *value = o.decode_list; return FS_OK;
+    case FS_OPT_LAST_DECODE_KERNEL: *value = o.last_decode; return FS_OK;
     default: break;
   }
   set_error("fs_pool_get_option: unknown option");

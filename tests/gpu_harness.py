@@ -78,6 +78,10 @@ class Parity:
         """Whether the pool's latest prefill launch dequantized INT8 / INT4 operands while staging them."""
         return bool(self.fs.fs_pool_get_option(self.gw.pool, self.fs.FS_OPT_LAST_PREFILL_KERNEL) >> 16 & 1)
 
+    def last_decode(self):
+        """Bit mask of the kernels the pool's latest decode call launched (FS_OPT_LAST_DECODE_KERNEL)."""
+        return self.fs.fs_pool_get_option(self.gw.pool, self.fs.FS_OPT_LAST_DECODE_KERNEL)
+
     def check_allocator_state(self):
         ost, ok, ou, ofs = self.opool.dump()
         st, key, used, fstack = self.fs.fs_pool_dump(self.gw.pool)

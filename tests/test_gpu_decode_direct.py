@@ -16,6 +16,7 @@ def _check(wl, layers):
     par = gpu_harness.Parity(wl, zero_pool=True)
     try:
         print(par.gw.T, par.run_and_check(layers))
+        assert par.last_decode() == 4  # (the kernel this file is about)
     finally:
         par.close()
 
@@ -68,6 +69,7 @@ def test_status_without_preparation(n):
             ws = torch.full((fs.fs_decode_workspace_bytes(pool, b),), 0xff, dtype=torch.uint8, device="cuda")
             fs.fs_decode_attention_multi(pool, b, ws)
             torch.cuda.synchronize()
+            assert fs.fs_pool_get_option(pool, fs.FS_OPT_LAST_DECODE_KERNEL) == 4
             assert bool((out == 0).all())  # zero values in the pool, whatever block stands in for a bad entry
             return fs.fs_decode_status(ws)
 

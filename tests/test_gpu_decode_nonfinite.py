@@ -17,7 +17,7 @@ class _Case:
         import gpu_workload
         import paper_2509_06261_amd as fs
 
-        self.fs, self.dtype = fs, dtype
+        self.fs, self.dtype, self.split_bytes = fs, dtype, split_bytes
         self.gw = gpu_workload.GpuWorkload(
             Workload("nf", 64 * KiB, 64 * 800 * KiB, [ModelSpec("m", dtype, 2, 128, 1, 8, np.array(lens, np.int32), tag=61, src_f32=dtype == INT4)],
                      "shuffle"), zero_pool=True, options={fs.FS_OPT_SPLIT_BYTES: split_bytes})
@@ -37,6 +37,7 @@ class _Case:
         ws = self.gw.decode(batches)
         torch.cuda.synchronize()
         assert self.fs.fs_decode_status(ws) == 0
+        assert self.fs.fs_pool_get_option(self.gw.pool, self.fs.FS_OPT_LAST_DECODE_KERNEL) == (2 if self.split_bytes else 4)
         return keep["out"][0].cpu().numpy(), keep["lse"][0].cpu().numpy()
 
     def key_bytes(self, seq, token, head, new=None):

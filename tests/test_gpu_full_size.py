@@ -83,18 +83,22 @@ def test_every_sequence_mfma_against_generic_kernel(stood_up):
     import gpu_harness
 
     outs = {}
-    for mode in (0, 1):
+    for mode, work_list in ((0, 0), (1, 0), (0, 1)):
         par.gw.set_option(par.fs.FS_OPT_DECODE_KERNEL, mode)
+        par.gw.set_option(par.fs.FS_OPT_DECODE_WORK_LIST, work_list)
         try:
-            outs[mode] = _decode_all(par, layers)
+            outs[mode, work_list] = _decode_all(par, layers)
+            assert par.last_decode() == (1 if mode else 2) or (mode, work_list) == (0, 0)
         finally:
             par.gw.set_option(par.fs.FS_OPT_DECODE_KERNEL, 0)
+            par.gw.set_option(par.fs.FS_OPT_DECODE_WORK_LIST, 0)
     for k, s in enumerate(wl.models):
         tol = 2 * (gpu_harness.TOL_FP16 if s.kv_dtype == workloads.FP16 else gpu_harness.TOL_QUANT)
-        d = float(np.max(np.abs(outs[0][k] - outs[1][k])))
-        assert np.all(np.isfinite(outs[0][k])) and d <= tol, f"model {k}: kernels differ by {d:.3e}"
+        for key in ((0, 0), (0, 1)):
+            d = float(np.max(np.abs(outs[key][k] - outs[1, 0][k])))
+            assert np.all(np.isfinite(outs[key][k])) and d <= tol, f"model {k}: kernels differ by {d:.3e}"
         # and the launch the oracle tests looked at is this same deterministic launch
-        assert np.array_equal(outs[0][k], stood_up["keep"]["out"][k].float().cpu().numpy())
+        assert np.array_equal(outs[0, 0][k], stood_up["keep"]["out"][k].float().cpu().numpy())
 
 
 def test_many_small_items(stood_up):

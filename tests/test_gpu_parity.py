@@ -232,8 +232,12 @@ def test_mfma_kernel_head_dim_64_and_256(dtype, src_f32, head_dim, group):
     try:
         par.gw.set_option(par.fs.FS_OPT_SPLIT_BYTES, 16 * KiB)
         print(par.run_and_check([0], kernel_mode=2))
-        par.gw.set_option(par.fs.FS_OPT_SPLIT_BYTES, 0)  # size tiers, whole ring turns
-        print(par.run_and_check([0], kernel_mode=2))
+        assert par.last_decode() == 2
+        par.gw.set_option(par.fs.FS_OPT_SPLIT_BYTES, 0)
+        for work_list in (1, 0):  # the list's size tiers and whole ring turns; a workgroup per sequence and KV head
+            par.gw.set_option(par.fs.FS_OPT_DECODE_WORK_LIST, work_list)
+            print(par.run_and_check([0], kernel_mode=2))
+            assert par.last_decode() == (2 if work_list else 4)
     finally:
         par.gw.set_option(par.fs.FS_OPT_SPLIT_BYTES, 0)
         par.close()
@@ -277,7 +281,10 @@ def test_mfma_kernel_on_seeded_random_shapes(dtype, head_dim, group, n_kv, n_lay
         if par.gw.T[par.gw.model_ids[0]] < 8:
             pytest.skip("fewer than 8 tokens per block: the generic kernel's shape")
         par.gw.set_option(par.fs.FS_OPT_SPLIT_BYTES, split)
-        print(par.gw.T, par.run_and_check([n_layers - 1], kernel_mode=2))
+        for work_list in (0, 1) if split == 0 else (0,):
+            par.gw.set_option(par.fs.FS_OPT_DECODE_WORK_LIST, work_list)
+            print(par.gw.T, par.run_and_check([n_layers - 1], kernel_mode=2))
+            assert par.last_decode() == (2 if split or work_list else 4)
     finally:
         par.gw.set_option(par.fs.FS_OPT_SPLIT_BYTES, 0)
         par.close()
@@ -626,8 +633,9 @@ def test_weights_sum_to_one_on_gpu():
         si, po = torch.from_numpy(si).cuda(), torch.from_numpy(po).cuda()
         k = torch.randn((len(po), 2, 128), dtype=torch.float16, device="cuda:0")
         fs.fs_kv_append(gw.pool, gw.model_ids[0], 0, k, torch.ones_like(k), si, po, gw.tables[0])
-        for mode in KERNEL_MODES:
+        for mode, work_list in ((1, 0), (0, 0), (0, 1)):
             gw.set_option(fs.FS_OPT_DECODE_KERNEL, mode)
+            gw.set_option(fs.FS_OPT_DECODE_WORK_LIST, work_list)
             batches, keep = gw.make_batches([0])
             keep["q"][0].zero_()
             gw.decode(batches)
@@ -686,9 +694,9 @@ def test_argument_errors_and_status_flags():
         gw.close()
 
 
-@pytest.mark.parametrize("mode", KERNEL_MODES)
+@pytest.mark.parametrize("mode,work_list", [(1, 0), (0, 0), (0, 1)])
 @pytest.mark.parametrize("bad_entry", [-1, 1 << 30])
-def test_block_table_entry_outside_the_pool_is_reported_not_followed(mode, bad_entry):
+def test_block_table_entry_outside_the_pool_is_reported_not_followed(mode, work_list, bad_entry):
     """A stale or -1 block-table entry inside a sequence's length: decode and prefill read block 0 of the pool in its
     place (nothing outside the pool), raise bit 2 of the status word, and leave the other sequences' results as they
     are without the bad entry.  The pool is zero-filled, so the affected rows come out finite as well."""
@@ -703,6 +711,7 @@ def test_block_table_entry_outside_the_pool_is_reported_not_followed(mode, bad_e
         gw.place()
         gw.populate()
         gw.set_option(fs.FS_OPT_DECODE_KERNEL, mode)
+        gw.set_option(fs.FS_OPT_DECODE_WORK_LIST, work_list)
         batches, keep = gw.make_batches([0])
         ws = gw.decode(batches)
         assert fs.fs_decode_status(ws) == 0
