@@ -270,21 +270,24 @@ __device__ __host__ inline int direct_batch(const DirectArgs& D, uint32_t& i) {
   return b;
 }
 
-// Runs [v0, v1) of split `split` of a sequence of `runs` runs.  The last split takes all that is left, as far as the
-// address table reaches; cut: something does not fit.
+// Runs [v0, v1) of split `split` of a sequence of `runs` runs.  The last split takes all that is left: a sequence may be
+// longer on the device than the host knew when it sized the grid.
 struct DirectRange {
   int v0, v1;
-  bool cut;
 };
 __device__ __host__ inline DirectRange direct_range(const DirectArgs& D, int b, int split, int runs) {
   const DevBatch& B = D.m.b[b];
   DirectRange r;
   r.v0 = split * B.chunk_runs;
-  const int64_t table_end = ((int64_t)div_runs(r.v0, B.R, B.r_magic) + D.entries) * B.R;
-  const int64_t end = split + 1 == (int)D.splits[b] ? runs : (runs < r.v0 + B.chunk_runs ? runs : r.v0 + B.chunk_runs);
-  r.cut = end > table_end;
-  r.v1 = (int)(r.cut ? table_end : end);
+  r.v1 = split + 1 == (int)D.splits[b] ? runs : (runs < r.v0 + B.chunk_runs ? runs : r.v0 + B.chunk_runs);
   return r;
+}
+// An item is streamed in segments of what the address table reaches; one for all items but the last splits of sequences
+// that the host knew shorter.  v1 or the end of the segment that starts at run v.
+__device__ __host__ inline int direct_segment_end(const DirectArgs& D, int b, int v, int v1) {
+  const DevBatch& B = D.m.b[b];
+  const int64_t table_end = ((int64_t)div_runs(v, B.R, B.r_magic) + D.entries) * B.R;
+  return table_end < v1 ? (int)table_end : v1;
 }
 
 // Splits that sequence really has.

@@ -615,7 +615,8 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
         useful += (uint64_t)B.n_seq * (uint64_t)g.n_kv_heads;
       }
       if (splits == 1 && B.max_blocks > kDirectEntries) return false;  // (a longer length on the device would not fit)
-      // (twice a split's blocks: the last split takes what a sequence holds beyond the length known here)
+      // (twice a split's blocks: the last split takes what a sequence holds beyond the length known here, and streams it
+      // in segments of what the table reaches)
       D.entries = std::max(D.entries, splits == 1 ? B.max_blocks : std::min(2 * (B.chunk_runs / B.R) + 4, kDirectEntries));
       D.splits[i] = (uint32_t)splits;
       const uint64_t n = (uint64_t)B.n_seq * splits * (uint64_t)g.n_kv_heads;

@@ -390,8 +390,7 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_attention_
 // 0 does nothing but judge the whole call and write the word.
 constexpr int kEntriesPerThread = kDirectEntries / kThreads;
 
-// Status of the call: bit 0 for a length out of range, bit 1 for one that the launch's splits cannot hold, bit 2 for a
-// block-table entry outside the pool inside a length.
+// Status of the call: bit 0 for a length out of range, bit 2 for a block-table entry outside the pool inside a length.
 __device__ __forceinline__ void direct_status(const DirectArgs& D, uint32_t* status) {
   const MultiArgs& A = D.m;
   __shared__ uint32_t s_flags;
@@ -410,7 +409,6 @@ __device__ __forceinline__ void direct_status(const DirectArgs& D, uint32_t* sta
     int len = B.seq_lens[seq];
     if (len < 1 || len > max_len) flags |= 1u;
     len = len < 1 ? 1 : min(len, max_len);
-    if (direct_range(D, b, (int)D.splits[b] - 1, n_runs(len, B.g.T, B.R)).cut) flags |= 2u;
     const int nb = (len + B.g.T - 1) / B.g.T;
     const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
 #pragma unroll 8
@@ -424,6 +422,7 @@ __device__ __forceinline__ void direct_status(const DirectArgs& D, uint32_t* sta
 template <int HD>
 __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_kernel(DirectArgs D, uint32_t* status) {
   extern __shared__ uint64_t s_tab[];
+  __shared__ float2 s_before[2][16];
   if (blockIdx.x == 0) {
     direct_status(D, status);
     return;
@@ -441,72 +440,98 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_ker
   P.chunk = (int)(local / H % D.splits[P.b]);
   P.seq = (int)(local / H / D.splits[P.b]);
   P.local = local;
-  // the block-table entries do not wait for the length: the item's first run, and so its first block, is known
-  P.k0 = div_runs(P.chunk * B.chunk_runs, B.R, B.r_magic);
-  const int32_t* table = B.tables + (int64_t)P.seq * B.max_blocks;
-  int32_t tab[kEntriesPerThread];
-#pragma unroll
-  for (int q = 0; q < kEntriesPerThread; ++q) {
-    const int i = (int)threadIdx.x + kThreads * q;
-    tab[q] = i < D.entries && P.k0 + i < B.max_blocks ? table[P.k0 + i] : 0;
-  }
   const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
-  int len = __builtin_amdgcn_readfirstlane(B.seq_lens[P.seq]);
-  len = len < 1 ? 1 : min(len, max_len);
-  P.len = len;
-  const int runs = n_runs(len, B.g.T, B.R);
-  const DirectRange r = direct_range(D, P.b, P.chunk, runs);
-  if (r.v0 >= r.v1) return;  // (uniform: a split past the sequence's end)
-  P.nb = div_runs(r.v1 - 1, B.R, B.r_magic) - P.k0 + 1;
-  const int share = ((r.v1 - r.v0 + 3) / 4 + kWaves - 1) / kWaves * 4;  // runs per wave: whole tiles
-  P.v0 = r.v0 + wave * share;
-  P.v1 = min(r.v1, P.v0 + share);
+  const int32_t* table = B.tables + (int64_t)P.seq * B.max_blocks;
   const uint8_t* head_base = B.layer_base + (uint64_t)P.head * B.g.head_chunk;
-#pragma unroll
-  for (int q = 0; q < kEntriesPerThread; ++q) {
-    const int i = (int)threadIdx.x + kThreads * q;
-    if (i < P.nb) s_tab[i] = reinterpret_cast<uint64_t>(head_base + (uint64_t)checked_block(tab[q], B.n_blocks, A.header) * B.g.block_budget);
-  }
-  __syncthreads();
   const int G = B.G;
   float* rec = s_rec + wave * G * (HD + 2);
-  if (P.v0 < P.v1) {  // wave-uniform
-    StateT<HD> unused;
-    dispatch_item<2, HD>(A, P, s_tab, unused, nullptr, rec);
-  } else if (lane < G) {
-    *reinterpret_cast<float2*>(rec + lane * (HD + 2) + HD) = float2{-INFINITY, 0.f};
-  }
-  __syncthreads();
-  const bool whole = direct_splits_of(D, P.b, runs) == 1;
   float* part = A.partials + D.part_off[P.b] + (uint64_t)local * (uint64_t)B.part_stride;
-  for (int i = threadIdx.x; i < G * (HD / 2); i += kThreads) {
-    const int h = i / (HD / 2), d = 2 * (i % (HD / 2));
-    float M = -INFINITY;
+  DirectRange r{P.chunk * B.chunk_runs, 0};
+  bool whole = false;
+  // one turn per segment of the item (see direct_segment_end): nearly always one
+  for (int turn = 0;; ++turn) {
+    // the block-table entries do not wait for the length: the segment's first run, and so its first block, is known
+    P.k0 = div_runs(r.v0, B.R, B.r_magic);
+    int32_t tab[kEntriesPerThread];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_rec[(w * G + h) * (HD + 2) + HD]);
-    float L = 0.f, o0 = 0.f, o1 = 0.f;
+    for (int q = 0; q < kEntriesPerThread; ++q) {
+      const int i = (int)threadIdx.x + kThreads * q;
+      tab[q] = i < D.entries && P.k0 + i < B.max_blocks ? table[P.k0 + i] : 0;
+    }
+    if (turn == 0) {
+      int len = __builtin_amdgcn_readfirstlane(B.seq_lens[P.seq]);
+      len = len < 1 ? 1 : min(len, max_len);
+      P.len = len;
+      const int runs = n_runs(len, B.g.T, B.R);
+      r = direct_range(D, P.b, P.chunk, runs);
+      if (r.v0 >= r.v1) return;  // (uniform: a split past the sequence's end)
+      whole = direct_splits_of(D, P.b, runs) == 1;
+    }
+    const int end = direct_segment_end(D, P.b, r.v0, r.v1);
+    P.nb = div_runs(end - 1, B.R, B.r_magic) - P.k0 + 1;
+    const int share = ((end - r.v0 + 3) / 4 + kWaves - 1) / kWaves * 4;  // runs per wave: whole tiles
+    P.v0 = r.v0 + wave * share;
+    P.v1 = min(end, P.v0 + share);
+    if (turn) __syncthreads();  // (every wave is through with the last segment's table and records)
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const float* pr = s_rec + (w * G + h) * (HD + 2);
-      const float2 ml = *reinterpret_cast<const float2*>(pr + HD);
-      if (ml.x != -INFINITY) {  // (a wave without tokens left no row; one with a NaN logit has a NaN sum, which goes on)
-        const float x = expf(ml.x - M);
-        const float2 v = *reinterpret_cast<const float2*>(pr + d);
-        L += ml.y * x;
-        o0 += v.x * x;
-        o1 += v.y * x;
+    for (int q = 0; q < kEntriesPerThread; ++q) {
+      const int i = (int)threadIdx.x + kThreads * q;
+      if (i < P.nb) s_tab[i] = reinterpret_cast<uint64_t>(head_base + (uint64_t)checked_block(tab[q], B.n_blocks, A.header) * B.g.block_budget);
+    }
+    __syncthreads();
+    if (P.v0 < P.v1) {  // wave-uniform
+      StateT<HD> unused;
+      dispatch_item<2, HD>(A, P, s_tab, unused, nullptr, rec);
+    } else if (lane < G) {
+      *reinterpret_cast<float2*>(rec + lane * (HD + 2) + HD) = float2{-INFINITY, 0.f};
+    }
+    __syncthreads();
+    const bool last = end == r.v1;
+    for (int i = threadIdx.x; i < G * (HD / 2); i += kThreads) {
+      const int h = i / (HD / 2), d = 2 * (i % (HD / 2));
+      float2 ml_before{-INFINITY, 0.f}, o_before{0.f, 0.f};  // of the segments before this one
+      if (turn) {  // (rows only this thread writes; references and sums in turn in one half of s_before or the other)
+        ml_before = s_before[turn & 1][h];
+        o_before = *reinterpret_cast<const float2*>(part + h * (HD + 2) + d);
+      }
+      float M = ml_before.x;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_rec[(w * G + h) * (HD + 2) + HD]);
+      float L = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float* pr = s_rec + (w * G + h) * (HD + 2);
+        const float2 ml = *reinterpret_cast<const float2*>(pr + HD);
+        if (ml.x != -INFINITY) {  // (a wave without tokens left no row; one with a NaN logit has a NaN sum, which goes on)
+          const float x = expf(ml.x - M);
+          const float2 v = *reinterpret_cast<const float2*>(pr + d);
+          L += ml.y * x;
+          o0 += v.x * x;
+          o1 += v.y * x;
+        }
+      }
+      if (turn) {
+        const float x = expf(ml_before.x - M);
+        L += ml_before.y * x;
+        o0 += o_before.x * x;
+        o1 += o_before.y * x;
+      }
+      if (whole) {  // (never in several segments)
+        const float inv = 1.0f / L;
+        const int64_t row = (int64_t)P.seq * B.n_q + P.head * G + h;
+        const half2v hv = {(_Float16)(o0 * inv), (_Float16)(o1 * inv)};
+        *reinterpret_cast<uint32_t*>(B.out + row * HD + d) = h2u(hv);
+        if (d == 0 && B.lse) B.lse[row] = M + logf(L);
+      } else {
+        *reinterpret_cast<float2*>(part + h * (HD + 2) + d) = float2{o0, o1};
+        if (d == 0) {
+          if (last) *reinterpret_cast<float2*>(part + h * (HD + 2) + HD) = float2{M, L};
+          else s_before[(turn + 1) & 1][h] = float2{M, L};
+        }
       }
     }
-    if (whole) {
-      const float inv = 1.0f / L;
-      const int64_t row = (int64_t)P.seq * B.n_q + P.head * G + h;
-      const half2v hv = {(_Float16)(o0 * inv), (_Float16)(o1 * inv)};
-      *reinterpret_cast<uint32_t*>(B.out + row * HD + d) = h2u(hv);
-      if (d == 0 && B.lse) B.lse[row] = M + logf(L);
-    } else {
-      *reinterpret_cast<float2*>(part + h * (HD + 2) + d) = float2{o0, o1};
-      if (d == 0) *reinterpret_cast<float2*>(part + h * (HD + 2) + HD) = float2{M, L};
-    }
+    if (last) return;
+    r.v0 = end;
   }
 }
 

@@ -18,8 +18,8 @@
 // The decode work queue's closed-form placement (queue_place: the batches' item lists merged proportionally) is
 // checked to be one-to-one onto the queue and order-preserving within a batch.
 // Launches without a work list (fs::debug_plan_direct) are replayed workgroup by workgroup, also where the device's
-// lengths are not the host's: every place of the grid is one item, the items' waves cover every token exactly once unless
-// the status says otherwise, table entries and partial records stay inside their buffers.
+// lengths are not the host's: every place of the grid is one item, the items' waves cover every token exactly once, table
+// entries and partial records stay inside their buffers.
 // The vector-ALU kernel's launch is replayed where the device's lengths are not the ones the host sized the workspace
 // for: what is queued, every queued item's tokens and table entries, the partial records and the combine's rows stay
 // inside the plan's capacities or are the ones the kernels skip and report.
@@ -411,7 +411,7 @@ void token_split_overflow(int rounds) {
 void direct_launches(int rounds) {
   const int dtypes[4] = {FS_KV_FP16, FS_KV_FP8_E4M3, FS_KV_INT8, FS_KV_INT4};
   const int dims[3] = {64, 128, 256};
-  int planned = 0, cut_in_splits = 0;
+  int planned = 0, cut_in_splits = 0, in_segments = 0;
   for (int round = 0; round < rounds; ++round) {
     const uint64_t slab = (uint64_t)(16 << rnd_int(5)) << 10;
     fs_pool* p = nullptr;
@@ -492,55 +492,63 @@ void direct_launches(int rounds) {
         const int head = (int)(local % H), split = (int)(local / H % A.splits[k]), seq = (int)(local / H / A.splits[k]);
         CHECK(seq < B.n_seq);
         const int len = clen[k][seq], runs = fs::n_runs(len, B.g.T, B.R);
-        const int k0 = fs::div_runs(split * B.chunk_runs, B.R, B.r_magic);
         const fs::DirectRange r = fs::direct_range(A, k, split, runs);
         if (r.v0 >= r.v1) {
           CHECK(split > 0);
           continue;
         }
         CHECK(split < fs::direct_splits_of(A, k, runs));
-        const int nblk = fs::div_runs(r.v1 - 1, B.R, B.r_magic) - k0 + 1;
-        CHECK(nblk >= 1 && nblk <= A.entries && k0 + nblk <= B.max_blocks);
-        const int share = ((r.v1 - r.v0 + 3) / 4 + 3) / 4 * 4;
-        int covered = r.v0;
-        for (int wave = 0; wave < 4; ++wave) {
-          const int v0 = r.v0 + wave * share, v1 = std::min(r.v1, v0 + share);
-          if (v0 >= v1) continue;
-          CHECK(v0 == covered);
-          covered = v1;
-          fs::ItemCtx X;
-          X.chunk_ptr = nullptr;
-          X.T = B.g.T;
-          X.R = B.R;
-          X.r_magic = B.r_magic;
-          X.len = X.len_u = len;
-          X.v_end = v1;
-          X.k0 = k0;
-          for (int v = v0; v < v1 + 4; ++v) {
-            const fs::RunGeom L = fs::run_geom(X, v);
-            CHECK(L.k_rel >= 0 && L.k_rel < nblk && L.start >= 0 && L.start + 8 <= B.g.T);
-            for (int i = std::max(L.lo, 0); i < L.hi; ++i) {
-              const int tok = L.tok0 + i;
-              CHECK(tok >= 0 && tok < len);
-              if (tok >= 0 && tok < len) ++seen[k][seq][(size_t)tok * H + head];
+        for (int from = r.v0, end = 0; from < r.v1; from = end) {
+          end = fs::direct_segment_end(A, k, from, r.v1);
+          CHECK(end > from);
+          if (end <= from) break;
+          if (end < r.v1) {
+            // only a last split that holds more than the host knew; its record is a partial one, and so is the sequence's
+            CHECK(split + 1 == (int)A.splits[k] && fs::direct_splits_of(A, k, runs) > 1);
+            CHECK(dev[k] != host[k] && b[k].seq_lens_host);
+            ++in_segments;
+          }
+          const int k0 = fs::div_runs(from, B.R, B.r_magic);
+          const int nblk = fs::div_runs(end - 1, B.R, B.r_magic) - k0 + 1;
+          CHECK(nblk >= 1 && nblk <= A.entries && k0 + nblk <= B.max_blocks);
+          const int share = ((end - from + 3) / 4 + 3) / 4 * 4;
+          int covered = from;
+          for (int wave = 0; wave < 4; ++wave) {
+            const int v0 = from + wave * share, v1 = std::min(end, v0 + share);
+            if (v0 >= v1) continue;
+            CHECK(v0 == covered);
+            covered = v1;
+            fs::ItemCtx X;
+            X.chunk_ptr = nullptr;
+            X.T = B.g.T;
+            X.R = B.R;
+            X.r_magic = B.r_magic;
+            X.len = X.len_u = len;
+            X.v_end = v1;
+            X.k0 = k0;
+            for (int v = v0; v < v1 + 4; ++v) {
+              const fs::RunGeom L = fs::run_geom(X, v);
+              CHECK(L.k_rel >= 0 && L.k_rel < nblk && L.start >= 0 && L.start + 8 <= B.g.T);
+              for (int i = std::max(L.lo, 0); i < L.hi; ++i) {
+                const int tok = L.tok0 + i;
+                CHECK(tok >= 0 && tok < len);
+                if (tok >= 0 && tok < len) ++seen[k][seq][(size_t)tok * H + head];
+              }
             }
           }
+          CHECK(covered == end);
         }
-        CHECK(covered == r.v1);
       }
       for (int k = 0; k < nb; ++k) {
         const fs::DevBatch& B = A.m.b[k];
         CHECK(next[k] == A.items[k]);
-        for (int i = 0; i < B.n_seq; ++i) {
-          const bool cut = fs::direct_range(A, k, (int)A.splits[k] - 1, fs::n_runs(clen[k][i], B.g.T, B.R)).cut;
-          if (dev[k] == host[k] || !b[k].seq_lens_host || A.splits[k] == 1) CHECK(!cut);
-          for (size_t t = 0; t < seen[k][i].size(); ++t) CHECK(seen[k][i][t] == 1 || (cut && seen[k][i][t] == 0));
-        }
+        for (int i = 0; i < B.n_seq; ++i)
+          for (size_t t = 0; t < seen[k][i].size(); ++t) CHECK(seen[k][i][t] == 1);
       }
     }
     fs_pool_destroy(p);
   }
-  CHECK(planned > rounds / 4 && cut_in_splits > rounds / 16);
+  CHECK(planned > rounds / 4 && cut_in_splits > rounds / 16 && in_segments > rounds / 64);
 }
 
 }  // namespace

@@ -81,3 +81,28 @@ def test_status_without_preparation(n):
         assert status([n + 2 * T, 1, 3], bad) == 5  # (clamped to the table's last block)
     finally:
         fs.fs_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("dtype,head_dim,group", [(FP16, 128, 4), (INT4, 128, 1), (FP8, 64, 8), (INT8, 256, 4), (FP16, 256, 3)])
+def test_sequences_longer_on_the_device_than_on_the_host(dtype, head_dim, group):
+    """seq_lens_host only sizes the launch (a captured step replayed while its sequences grow): the last split of a
+    sequence takes whatever it holds beyond the host's length, here up to dozens of the address table's segments."""
+    import torch
+
+    import gpu_harness
+
+    lens = np.array([6000, 20, 9001, 700, 1], np.int32)
+    known = np.array([600, 20, 333, 700, 650], np.int32)
+    par = gpu_harness.Parity(Workload("dl", 96 * KiB, 96 * 700 * KiB,
+                                      [ModelSpec("m", dtype, 2, head_dim, 1, 2 * group, lens, tag=56, src_f32=dtype == INT4)],
+                                      "shuffle"), zero_pool=True)
+    try:
+        par.gw.populate([[0]])
+        batches, keep = par.gw.make_batches([0])
+        batches[0].seq_lens_host = known.ctypes.data
+        ws = par.gw.decode(batches)
+        torch.cuda.synchronize()
+        assert par.fs.fs_decode_status(ws) == 0 and par.last_decode() == 4
+        print(par.check_model(0, [0], keep))
+    finally:
+        par.close()
