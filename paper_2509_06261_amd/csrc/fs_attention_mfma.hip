@@ -419,6 +419,64 @@ __device__ __forceinline__ void direct_status(const DirectArgs& D, uint32_t* sta
   if (threadIdx.x == 0) *status = s_flags;
 }
 
+// Merges the four waves' records into the output (whole) or into the item's partial record.  SEGMENTS: the item has several
+// segments; `before` holds the references and sums of those already merged into the partial record (null: none), `after`
+// takes the new ones (null: the last segment, they go to the record).  Elements of the record are written and read again by
+// the same thread.
+template <int HD, bool SEGMENTS>
+__device__ __forceinline__ void merge_records(const MultiArgs& A, const ItemPlan& P, const float* s_rec, bool whole, float* part,
+                                              const float2* before, float2* after) {
+  const DevBatch& B = A.b[P.b];
+  const int G = B.G;
+  for (int i = threadIdx.x; i < G * (HD / 2); i += kThreads) {
+    const int h = i / (HD / 2), d = 2 * (i % (HD / 2));
+    float2 ml0{-INFINITY, 0.f}, v0{0.f, 0.f};
+    if constexpr (SEGMENTS) {
+      if (before) {
+        ml0 = before[h];
+        v0 = *reinterpret_cast<const float2*>(part + h * (HD + 2) + d);
+      }
+    }
+    float M = ml0.x;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_rec[(w * G + h) * (HD + 2) + HD]);
+    float L = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float* pr = s_rec + (w * G + h) * (HD + 2);
+      const float2 ml = *reinterpret_cast<const float2*>(pr + HD);
+      if (ml.x != -INFINITY) {  // (a wave without tokens left no row; one with a NaN logit has a NaN sum, which goes on)
+        const float x = expf(ml.x - M);
+        const float2 v = *reinterpret_cast<const float2*>(pr + d);
+        L += ml.y * x;
+        o0 += v.x * x;
+        o1 += v.y * x;
+      }
+    }
+    if constexpr (SEGMENTS) {
+      if (before) {
+        const float x = expf(ml0.x - M);
+        L += ml0.y * x;
+        o0 += v0.x * x;
+        o1 += v0.y * x;
+      }
+    }
+    if (whole) {
+      const float inv = 1.0f / L;
+      const int64_t row = (int64_t)P.seq * B.n_q + P.head * G + h;
+      const half2v hv = {(_Float16)(o0 * inv), (_Float16)(o1 * inv)};
+      *reinterpret_cast<uint32_t*>(B.out + row * HD + d) = h2u(hv);
+      if (d == 0 && B.lse) B.lse[row] = M + logf(L);
+    } else {
+      *reinterpret_cast<float2*>(part + h * (HD + 2) + d) = float2{o0, o1};
+      if (d == 0) {
+        if (SEGMENTS && after) after[h] = float2{M, L};
+        else *reinterpret_cast<float2*>(part + h * (HD + 2) + HD) = float2{M, L};
+      }
+    }
+  }
+}
+
 template <int HD>
 __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_kernel(DirectArgs D, uint32_t* status) {
   extern __shared__ uint64_t s_tab[];
@@ -435,17 +493,17 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_ker
   uint32_t local = blockIdx.x - 1;
   P.b = direct_batch(D, local);
   const DevBatch& B = A.b[P.b];
-  const uint32_t H = (uint32_t)B.g.H;
-  P.head = (int)(local % H);
-  P.chunk = (int)(local / H % D.splits[P.b]);
-  P.seq = (int)(local / H / D.splits[P.b]);
+  const DirectItem item = direct_item(D, P.b, local);
+  P.head = item.head;
+  P.chunk = item.split;
+  P.seq = item.seq;
   P.local = local;
   const int max_len = (int)min((int64_t)B.max_blocks * B.g.T, (int64_t)0x7fffffff);
   const int32_t* table = B.tables + (int64_t)P.seq * B.max_blocks;
   const uint8_t* head_base = B.layer_base + (uint64_t)P.head * B.g.head_chunk;
   const int G = B.G;
   float* rec = s_rec + wave * G * (HD + 2);
-  float* part = A.partials + D.part_off[P.b] + (uint64_t)local * (uint64_t)B.part_stride;
+  float* part = A.partials + D.part_off[P.b] + (uint64_t)item.rec * (uint64_t)B.part_stride;
   DirectRange r{P.chunk * B.chunk_runs, 0};
   bool whole = false;
   // one turn per segment of the item (see direct_segment_end): nearly always one
@@ -487,49 +545,8 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_ker
     }
     __syncthreads();
     const bool last = end == r.v1;
-    for (int i = threadIdx.x; i < G * (HD / 2); i += kThreads) {
-      const int h = i / (HD / 2), d = 2 * (i % (HD / 2));
-      float2 ml_before{-INFINITY, 0.f}, o_before{0.f, 0.f};  // of the segments before this one
-      if (turn) {  // (rows only this thread writes; references and sums in turn in one half of s_before or the other)
-        ml_before = s_before[turn & 1][h];
-        o_before = *reinterpret_cast<const float2*>(part + h * (HD + 2) + d);
-      }
-      float M = ml_before.x;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_rec[(w * G + h) * (HD + 2) + HD]);
-      float L = 0.f, o0 = 0.f, o1 = 0.f;
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const float* pr = s_rec + (w * G + h) * (HD + 2);
-        const float2 ml = *reinterpret_cast<const float2*>(pr + HD);
-        if (ml.x != -INFINITY) {  // (a wave without tokens left no row; one with a NaN logit has a NaN sum, which goes on)
-          const float x = expf(ml.x - M);
-          const float2 v = *reinterpret_cast<const float2*>(pr + d);
-          L += ml.y * x;
-          o0 += v.x * x;
-          o1 += v.y * x;
-        }
-      }
-      if (turn) {
-        const float x = expf(ml_before.x - M);
-        L += ml_before.y * x;
-        o0 += o_before.x * x;
-        o1 += o_before.y * x;
-      }
-      if (whole) {  // (never in several segments)
-        const float inv = 1.0f / L;
-        const int64_t row = (int64_t)P.seq * B.n_q + P.head * G + h;
-        const half2v hv = {(_Float16)(o0 * inv), (_Float16)(o1 * inv)};
-        *reinterpret_cast<uint32_t*>(B.out + row * HD + d) = h2u(hv);
-        if (d == 0 && B.lse) B.lse[row] = M + logf(L);
-      } else {
-        *reinterpret_cast<float2*>(part + h * (HD + 2) + d) = float2{o0, o1};
-        if (d == 0) {
-          if (last) *reinterpret_cast<float2*>(part + h * (HD + 2) + HD) = float2{M, L};
-          else s_before[(turn + 1) & 1][h] = float2{M, L};
-        }
-      }
-    }
+    if (turn == 0 && last) merge_records<HD, false>(A, P, s_rec, whole, part, nullptr, nullptr);
+    else merge_records<HD, true>(A, P, s_rec, false, part, turn ? s_before[turn & 1] : nullptr, last ? nullptr : s_before[(turn + 1) & 1]);
     if (last) return;
     r.v0 = end;
   }

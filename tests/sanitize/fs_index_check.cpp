@@ -489,8 +489,11 @@ void direct_launches(int rounds) {
         ++g_items;
         const fs::DevBatch& B = A.m.b[k];
         const uint32_t H = (uint32_t)B.g.H;
-        const int head = (int)(local % H), split = (int)(local / H % A.splits[k]), seq = (int)(local / H / A.splits[k]);
-        CHECK(seq < B.n_seq);
+        const fs::DirectItem item = fs::direct_item(A, k, local);
+        const int head = item.head, split = item.split, seq = item.seq;
+        CHECK(head >= 0 && head < (int)H && seq >= 0 && seq < B.n_seq && split >= 0 && split < (int)A.splits[k]);
+        // where the combine looks for this item's record
+        CHECK(item.rec < A.items[k] && item.rec == ((uint32_t)seq * A.splits[k] + (uint32_t)split) * H + (uint32_t)head);
         const int len = clen[k][seq], runs = fs::n_runs(len, B.g.T, B.R);
         const fs::DirectRange r = fs::direct_range(A, k, split, runs);
         if (r.v0 >= r.v1) {
@@ -551,10 +554,35 @@ void direct_launches(int rounds) {
   CHECK(planned > rounds / 4 && cut_in_splits > rounds / 16 && in_segments > rounds / 64);
 }
 
+// Places past their sequence's end fall on all bins of the chip (see direct_item) alike, whatever the number of splits and
+// sequences: where half of the sequences have one split only, no bin has much more than its share.
+void direct_order() {
+  for (uint32_t H : {1u, 2u, 4u, 5u, 8u, 40u})
+    for (uint32_t S : {2u, 3u, 4u, 6u, 8u})
+      for (uint32_t n : {5u, 16u, 20u, 31u, 40u, 64u}) {
+        fs::DirectArgs A{};
+        A.m.n_batches = 1;
+        A.m.b[0].g.H = (int)H;
+        A.m.b[0].n_seq = (int)n;
+        A.splits[0] = S;
+        uint32_t bins[fs::kDirectBins] = {}, useful = 0;
+        for (uint32_t place = 0; place < n * S * H; ++place) {
+          const fs::DirectItem it = fs::direct_item(A, 0, place);
+          const uint32_t own = (uint32_t)it.seq * 7 % 16 < 8 ? S : 1;
+          if ((uint32_t)it.split >= own) continue;
+          ++bins[(1 + place) % fs::kDirectBins];
+          ++useful;
+        }
+        const uint32_t most = *std::max_element(bins, bins + fs::kDirectBins);
+        CHECK(most <= useful * 5 / 4 / fs::kDirectBins + 7);
+      }
+}
+
 }  // namespace
 
 int main() {
   run(600);
+  direct_order();
   direct_launches(300);
   prefill_queues(60);
   decode_queue_places(200);
