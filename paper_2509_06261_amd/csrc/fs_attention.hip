@@ -8,7 +8,9 @@
 // flattened into one queue of work items (sequence, split, KV head) that a persistent grid
 // drains, in place of the paper's separate per-engine launches.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
+#include <vector>
 
 #include "fs_append_rows.h"
 #include "fs_attention.h"
@@ -551,69 +553,143 @@ int make_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, void* worksp
   return FS_OK;
 }
 
-// Whether the launch runs without a work list (see mfma_direct_kernel), and its records.  What decides:
-//   - A workgroup streams at most about 33 KB per us (four waves of 16 KiB in flight; twice that at head_dim 256), the
-//     whole chip 6200.  Splits cost a partial record each and a combine launch (6 us).
+// What a launch without a work list streams per us, in KB: one workgroup that has its compute unit to itself, and the whole
+// chip.  Measured (uncut sequences on 64 - 80 units; launches of 250 - 5000 MB): narrow rows leave fewer bytes in flight, the
+// integer formats and INT4 above all are bound by the vector ALU.
+struct DirectRate {
+  double wg, chip;
+};
+DirectRate direct_rate(const fs_geometry_t& g) {
+  switch (g.kv_dtype) {
+    case FS_KV_FP16: return g.head_dim == 256 ? DirectRate{33, 6200} : DirectRate{49, 6500};
+    case FS_KV_FP8_E4M3: return g.head_dim == 64 ? DirectRate{33, 5600} : DirectRate{44, 6500};
+    case FS_KV_INT8: return g.head_dim == 64 ? DirectRate{29, 5400} : DirectRate{38, 6500};
+    default: return g.head_dim == 64 ? DirectRate{15, 3600} : g.head_dim == 256 ? DirectRate{22, 4200} : DirectRate{20, 5500};
+  }
+}
+
+// Whether the items of a grid that are not past their sequence's end (n_of: splits each sequence has) all find a place at
+// once, bin by bin (see direct_item).
+bool fits(const DirectArgs& D, const uint16_t* n_of, uint64_t slots) {
+  struct {
+    uint32_t head, at, split, shift;  // shift: what the split's sequences begin with
+  } next[kMaxBatches] = {};           // of each batch
+  uint32_t bins[kDirectBins] = {}, items = 0;
+  for (int i = 0; i < D.m.n_batches; ++i) items += D.items[i];
+  for (uint32_t place = 0; place < items; ++place) {
+    uint32_t local = place;
+    const int i = direct_batch(D, local);
+    const DevBatch& B = D.m.b[i];
+    auto& c = next[i];
+    const uint32_t n = (uint32_t)B.n_seq, seq = c.at + c.shift < n ? c.at + c.shift : c.at + c.shift - n;
+    if (c.split < n_of[B.seq_first + seq]) ++bins[(1 + place) % kDirectBins];  // (place 0 of the grid is no item)
+    if (++c.head == (uint32_t)B.g.H) {
+      c.head = 0;
+      if (++c.at == n) {
+        c.at = 0;
+        ++c.split;
+        if (!(n & 1) && ++c.shift == n) c.shift = 0;
+      }
+    }
+  }
+  // (head_dim 256: one place of a bin left free; with all of them taken some items have been seen to wait for others -- 3 FP16
+  // sequences of 7896 - 28046 tokens, 4 KV heads: 72 us, 48 - 51 with larger items)
+  return *std::max_element(bins, bins + kDirectBins) + (D.m.b[0].g.D == 256) <= slots / kDirectBins;
+}
+
+// Whether the launch runs without a work list (see mfma_direct_kernel), and its records.  The choices, in estimated us (see
+// direct_rate; all: the whole launch at the chip's rate, longest and mean: a sequence's KV head in one workgroup; wait: what
+// the last long items take when the others are done):
 //   - With no more (sequence, KV head) pairs than workgroups fit the chip at once, the sequences are cut so that all items
-//     run in one round: a second round of a few items is worse than any split size (20 sequences of 1000 - 5000 tokens, 4
-//     KV heads of 256: 320 places 62 us, 480 places 90 us, work list 73 us).
-//   - With more pairs than that, or where one round leaves an item that alone streams most of the launch, items are cut
-//     to 0.7 MB or a tenth of the launch, if the wait for the last long one (about half its time) would cost more than
-//     the cut (64 FP16 sequences of 512 - 4096 tokens, 8 KV heads: whole 120 us, cut in three 105 - 115, work list 128 -
-//     139).
-//   - Long launches that would be cut stay with the work list, whose splits suit every sequence's own length and whose
-//     waves do not wait for each other (four models, lognormal lengths: 1860 us against 2190); long launches of sequences
-//     of about one length, which need no cut, do not (250 FP16 sequences of 7000 - 8000 tokens: 1229 -> 1178 us).
-constexpr double kDirectCutUs = 170;              // above this a launch that needs cuts takes the work list
+//     run in one round, judged bin by bin (see direct_item): a second round of a few items is worse than any split size (10
+//     FP16 sequences of 1000 - 5000 tokens, 4 KV heads of 256, in 10 splits that fill the chip to the last unit: 47 us, in
+//     7: 32).  If that shortens the longest item by less than the combine launch costs, they stay whole (20 FP16 sequences
+//     of 100 - 800 tokens, 8 KV heads of 64: 14 us cut, 10 whole).
+//   - With more pairs than that, or where one round is unbalanced, items are cut to 0.7 MB or a tenth of the launch where
+//     that is worth the combine launch (48 sequences of 200 - 6000 tokens of an FP16 and an INT4 model: whole 178 us, cut
+//     147; of an FP8 and an INT4 one: whole 94, cut 101); not at head_dim 256, whose single workgroup per unit leaves
+//     nothing to run while the next one starts.
+//   - Above kDirectCutUs a launch that would be cut takes the work list, whose splits suit every sequence's own length and
+//     whose waves do not wait for each other (four models: 1860 us, cut 2190), and so does any whole one that waits or, with
+//     many short items, starts workgroups for longer than what the list costs in front, behind and per item (256 INT4
+//     sequences of lognormal length, 40 KV heads: list 834 us, whole 862; 463 of 128 - 141 tokens: list 120, whole 246; 300
+//     FP16 sequences of 3500 - 4096 tokens, 8 KV heads: list 764, whole 704).
+constexpr double kDirectCutUs = 170;
+constexpr double kCombineUs = 6;
+constexpr double kStartUs = 6;                     // a workgroup from its start to its first tile, and its merge
 constexpr uint64_t kDirectItemBytes = 700 * 1000;  // the smallest item a cut for balance makes
 bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, const MultiArgs& A, DirectArgs& D) {
   if (p->opt.split_bytes || p->opt.decode_list) return false;
-  uint64_t total = 0, pairs = 0, longest = 0;
+  DirectRate rate[kMaxBatches];  // in bytes per us from here on
+  uint64_t most[kMaxBatches];    // bytes of the batch's longest sequence, one head
+  uint64_t pairs = 0;
+  double all_us = 0, longest_us = 0, sum_us = 0;
+  bool int4_only = true, memory_bound = false;
   for (int i = 0; i < n_batches; ++i) {
     const fs_geometry_t& g = p->models[batches[i].model].g;
+    rate[i] = direct_rate(g);
+    rate[i].wg *= 1e3;
+    rate[i].chip *= 1e3;
     uint64_t sum = 0;
+    most[i] = 0;
     for (int s = 0; s < batches[i].n_seq; ++s) {
       const uint64_t bytes = head_bytes(batches[i], g, s);
-      longest = std::max(longest, bytes);
+      most[i] = std::max(most[i], bytes);
       sum += bytes;
     }
-    total += sum * (uint64_t)g.n_kv_heads;
+    sum *= (uint64_t)g.n_kv_heads;
     pairs += (uint64_t)batches[i].n_seq * (uint64_t)g.n_kv_heads;
+    longest_us = std::max(longest_us, (double)most[i] / rate[i].wg);
+    sum_us += (double)sum / rate[i].wg;
+    all_us += (double)sum / rate[i].chip;
+    int4_only = int4_only && g.kv_dtype == FS_KV_INT4;
+    memory_bound = memory_bound || g.kv_dtype == FS_KV_FP16 || (g.kv_dtype == FS_KV_FP8_E4M3 && g.head_dim > 64);
   }
-  const int per_cu = mfma_wgs_per_cu(A.b[0].g.D);
+  const int hd = A.b[0].g.D, per_cu = mfma_wgs_per_cu(hd);
   const uint64_t slots = (uint64_t)(p->n_cu ? p->n_cu : 256) * per_cu;  // (no device: replays of the plan on the host)
-  const double all_us = (double)total / 6.2e6, wg_rate = per_cu == 1 ? 66e3 : 33e3;  // bytes per us
   D.m = A;
-  // Records for items of at most `want` bytes; false where a launch of that kind is not possible.  useful: items that are
-  // not past their sequence's end.
+  // Records for items of at most `want_us`, and of `least` bytes at least; false where a launch of that kind is not
+  // possible.  useful: items that are not past their sequence's end.  one_round: they all find a place at once.  item_us:
+  // the longest item.
   uint64_t items = 0, useful = 0;
-  auto cut = [&](uint64_t want) {
+  bool one_round = false;
+  int counts = 0;  // (a count costs a microsecond or two of the call, so there are five; then room for an uneven spread is asked for)
+  double item_us = 0;
+  std::vector<uint16_t> splits_of(pairs <= slots ? (size_t)A.n_seq_total : 0);
+  uint16_t* const n_of = splits_of.data();
+  auto cut = [&](double want_us, uint64_t least) {
     uint64_t floats = 0;
     items = useful = 0;
+    item_us = 0;
     D.entries = 0;
     for (int i = 0; i < n_batches; ++i) {
       const fs_batch_t& b = batches[i];
       const fs_geometry_t& g = p->models[b.model].g;
       DevBatch& B = D.m.b[i];
       const uint64_t token_bytes = 2 * (g.row_bytes + (uint64_t)g.param_bytes);
-      uint64_t most = 0;
-      for (int s = 0; s < b.n_seq; ++s) most = std::max(most, head_bytes(b, g, s));
-      uint64_t splits = (most + want - 1) / want;
+      const double want = std::max(want_us * rate[i].wg, (double)least);
+      uint64_t splits = want < (double)most[i] ? (uint64_t)std::ceil((double)most[i] / want) : 1;
+      uint64_t item = most[i];
       B.chunk_runs = 0;
       if (splits > 1 || B.max_blocks > kDirectEntries) {
-        const int64_t runs = n_runs((int)(most / token_bytes), g.tokens_per_block, B.R);
+        const int64_t runs = n_runs((int)(most[i] / token_bytes), g.tokens_per_block, B.R);
         const int64_t cap = (int64_t)(kDirectEntries / 2 - 4) * B.R / 16 * 16;  // runs whose blocks fit half the table
         if (cap < 16) return false;
         const int64_t cr = std::min<int64_t>((runs + (int64_t)splits * 16 - 1) / ((int64_t)splits * 16) * 16, cap);
         B.chunk_runs = (int32_t)cr;
         splits = (uint64_t)((runs + cr - 1) / cr);
+        item = std::min(item, (uint64_t)cr * 8 * token_bytes);
         for (int s = 0; s < b.n_seq; ++s) {
           const int64_t r = n_runs((int)(head_bytes(b, g, s) / token_bytes), g.tokens_per_block, B.R);
-          useful += (uint64_t)((r + cr - 1) / cr * g.n_kv_heads);
+          const int64_t n = (r + cr - 1) / cr;
+          useful += (uint64_t)(n * g.n_kv_heads);
+          if (pairs <= slots) n_of[B.seq_first + s] = (uint16_t)std::min<int64_t>(n, 0xffff);
         }
       } else {
         useful += (uint64_t)B.n_seq * (uint64_t)g.n_kv_heads;
+        if (pairs <= slots) std::fill_n(n_of + B.seq_first, b.n_seq, (uint16_t)1);
       }
+      item_us = std::max(item_us, (double)item / rate[i].wg);
       if (splits == 1 && B.max_blocks > kDirectEntries) return false;  // (a longer length on the device would not fit)
       // (twice a split's blocks: the last split takes what a sequence holds beyond the length known here, and streams it
       // in segments of what the table reaches)
@@ -626,28 +702,54 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
       D.part_off[i] = floats;
       if (splits > 1) floats += n * (uint64_t)B.part_stride;
     }
+    uint64_t left = items;
+    for (int i = 0; i < n_batches; ++i) {
+      D.magic[i] = (((uint64_t)D.items[i] << 32) + left - 1) / left;
+      left -= D.items[i];
+    }
+    one_round = useful <= slots;
+    if (one_round && items > pairs) one_round = counts++ < 5 ? fits(D, n_of, slots) : useful <= slots * 13 / 16;
     return floats <= A.part_capacity;
   };
-  uint64_t want = ~0ull >> 1;
-  const uint64_t small = std::max<uint64_t>(kDirectItemBytes, total / 10 / (uint64_t)(6.2e6 / wg_rate));
+  constexpr double kWhole = 1e18;
+  double small_us = 0;  // the longest item of a cut for balance
+  for (int i = 0; i < n_batches; ++i)
+    small_us = std::max(small_us, std::min(std::max(all_us / 10 * rate[i].wg, (double)kDirectItemBytes), (double)most[i]) / rate[i].wg);
+  const double mean_us = sum_us / (double)pairs;
+  // what the list costs: least where its waves are bound by the vector ALU (INT4 at head_dim 256)
+  const double list_us = hd == 256 && int4_only ? 18 : hd == 64 ? 15 + 0.05 * all_us : hd == 128 ? 30 + 0.06 * all_us : 30 + 0.1 * all_us;
   if (pairs <= slots) {
-    want = std::max<uint64_t>(total / (slots - pairs / 2), 64 << 10);
-    bool ok = cut(want);
-    for (int k = 0; k < 16 && (!ok || useful > slots) && want < longest; ++k) ok = cut(want += want / 8);
+    double want_us = std::max(sum_us / (double)(slots - pairs / 2), (64 << 10) / rate[0].wg);
+    bool ok = cut(longest_us - want_us < kCombineUs ? kWhole : want_us, 0);
+    for (int k = 0; k < 16 && (!ok || !one_round) && items > pairs && want_us < longest_us; ++k) ok = cut(want_us *= 1.125, 0);
+    if (ok && items > pairs && longest_us - item_us < kCombineUs) ok = cut(kWhole, 0);
     if (!ok) return false;
-    if ((double)std::min(want, longest) / wg_rate > 0.6 * all_us && longest > small + small / 2) ok = cut(want = small);
-    if (!ok) return false;
+    // one round or items cut for balance; some compute units with two whole sequences and some with one (two stream no
+    // faster together than one, where memory bounds them more slowly: 325 FP8 sequences' heads of 16442 - 21691 tokens 334
+    // us, by the list 300)
+    const double two_us = items == pairs && pairs > slots / per_cu ? (memory_bound ? 1.35 : 0.95) * (mean_us + longest_us) : 0;
+    const double last_us = std::max(item_us, two_us);
+    const double round_us = std::max((items > pairs ? 1.17 : 1.0) * all_us, last_us) + 0.15 * std::min(all_us, last_us);
+    const double balanced_us = all_us + kCombineUs + 0.65 * small_us + (per_cu > 1 ? 0 : 8);
+    const bool uneven = 0.5 * (longest_us - mean_us) > (per_cu > 1 ? 4 + 0.15 * small_us : 12 + 0.5 * small_us);
+    if (items > pairs ? balanced_us < round_us
+                      : all_us <= kDirectCutUs && longest_us > 1.5 * small_us && (uneven || (two_us > 0 && balanced_us < round_us))) {
+      if (!cut(all_us / 10, kDirectItemBytes)) return false;
+    }
+    const double behind = std::max(two_us - all_us, 0.0) + (all_us > kDirectCutUs ? 0.5 * (longest_us - mean_us) : 0.0);
+    if (items == pairs && behind > list_us) return false;
   } else {
-    if (0.55 * (double)longest / wg_rate > 6.0 + 0.1 * all_us) want = small;
-    if (!cut(want)) return false;
+    const double rounds = (double)pairs / (double)slots, part = rounds - std::floor(rounds);
+    const double wait = (per_cu > 1 ? 0.7 : 0.55) * (longest_us - 0.5 * mean_us);
+    const double odd = mean_us - part * all_us / rounds;  // a last round of few items, at their own pace
+    const double start = std::max(rounds * ((hd == 64 ? 0.75 : 1.0) * kStartUs + mean_us) - all_us, per_cu > 1 ? 0.0 : 0.95 * rounds * kStartUs);
+    const bool balance = all_us <= kDirectCutUs && (per_cu > 1 ? 0.65 * (longest_us - small_us) > kCombineUs && wait > kCombineUs + 0.05 * all_us
+                                                               : odd > wait && odd > 14 + 0.65 * small_us);
+    if (!cut(balance ? all_us / 10 : kWhole, balance ? kDirectItemBytes : 0)) return false;
+    if (items == pairs && std::max(wait, rounds < 2 ? odd : 0.0) + start > list_us) return false;
   }
   if (all_us > kDirectCutUs && items > pairs) return false;
   if (items > 4 * slots && items > 2 * useful) return false;  // mostly places past their sequence's end
-  uint64_t left = items;
-  for (int i = 0; i < n_batches; ++i) {
-    D.magic[i] = (((uint64_t)D.items[i] << 32) + left - 1) / left;
-    left -= D.items[i];
-  }
   return true;
 }
 

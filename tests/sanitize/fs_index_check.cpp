@@ -578,11 +578,64 @@ void direct_order() {
       }
 }
 
+// What the rule for launches without a work list decides where both sides were measured.
+void direct_rule() {
+  struct {
+    int dtype, heads, group, dim, n, lo, hi;
+    bool skewed, direct, whole;
+  } cases[] = {{FS_KV_INT4, 40, 1, 128, 256, 1, 32768, true, false, false},   // list 834 us, whole 862
+               {FS_KV_FP16, 8, 4, 128, 256, 1, 32768, true, false, false},    // list 610, whole 800
+               {FS_KV_FP16, 8, 4, 128, 300, 3500, 4096, false, true, true},   // list 764, whole 704
+               {FS_KV_INT4, 8, 4, 128, 256, 1024, 8192, false, true, true},   // list 285, whole 255
+               {FS_KV_INT4, 40, 1, 128, 463, 128, 141, false, false, false},  // list 120, whole 246
+               {FS_KV_INT4, 4, 4, 256, 100, 300, 6000, false, false, false},  // list 102, whole 121
+               {FS_KV_FP16, 4, 4, 256, 300, 300, 6000, false, false, false},  // list 698, whole 747
+               {FS_KV_FP8_E4M3, 4, 4, 256, 300, 300, 6000, false, true, true},  // list 355, whole 331
+               {FS_KV_FP16, 8, 4, 64, 20, 100, 800, false, true, true},       // cut 14, whole 10
+               {FS_KV_FP16, 8, 4, 128, 20, 500, 6000, false, true, false},    // cut 49, whole 67
+               {FS_KV_FP16, 8, 4, 128, 64, 512, 4096, false, true, false}};   // cut 103, whole 114
+  for (const auto& c : cases) {
+    fs_pool* p = nullptr;
+    CHECK(fs_pool_create(128 << 10, 4096ull * (128 << 10), kFakeBase, &p) == FS_OK);
+    if (!p) continue;
+    fs_model_t m;
+    const int T = fs_model_register(p, c.dtype, c.heads, c.dim, 1, &m);
+    CHECK(T >= 8);
+    std::vector<int32_t> lens;
+    int longest = 1;
+    for (int i = 0; i < c.n; ++i) {
+      const double u = ((i * 37) % c.n + 0.5) / c.n;
+      // skewed: a long tail, 1 % of the sequences over half the longest
+      lens.push_back(c.skewed ? (int)(c.lo + (c.hi - c.lo) * (0.08 * u + 0.92 * u * u * u * u * u * u * u * u * u * u * u * u * u * u * u * u)) : (int)(c.lo + u * (c.hi - c.lo)));
+      longest = std::max(longest, (int)lens.back());
+    }
+    fs_batch_t b{};
+    b.model = m;
+    b.n_q_heads = c.heads * c.group;
+    b.sm_scale = 0.1f;
+    b.q = (const void*)0x20000000;
+    b.block_tables = (const int32_t*)0x30000000;
+    b.seq_lens = (const int32_t*)0x40000000;
+    b.seq_lens_host = lens.data();
+    b.n_seq = c.n;
+    b.max_blocks = (longest + T - 1) / T;
+    b.out = (void*)0x50000000;
+    fs::DirectArgs A;
+    const bool direct = fs::debug_plan_direct(p, &b, 1, &A);
+    if (direct != c.direct || (direct && (A.splits[0] == 1) != c.whole))
+      std::printf("rule: dtype %d, %d KV heads x %d, %d sequences of %d - %d: direct %d splits %u\n", c.dtype, c.heads, c.dim, c.n, c.lo,
+                  c.hi, (int)direct, direct ? A.splits[0] : 0u);
+    CHECK(direct == c.direct && (!direct || (A.splits[0] == 1) == c.whole));
+    fs_pool_destroy(p);
+  }
+}
+
 }  // namespace
 
 int main() {
   run(600);
   direct_order();
+  direct_rule();
   direct_launches(300);
   prefill_queues(60);
   decode_queue_places(200);
