@@ -251,12 +251,30 @@ struct DirectArgs {
   uint64_t magic[kMaxBatches];     // ceil(2^32 items / items of this batch and the later ones)
   uint64_t part_off[kMaxBatches];  // float offset of the batch's partial records
   int32_t entries;                 // entries of the LDS table: blocks an item can touch
-  int32_t pad;
+  uint32_t total;                  // items of all batches
 };
 
-// Place `i` of the grid -> batch, and `i` the item's index within it (see direct_item): the batches' item lists merged
-// proportionally, so that formats bound by the vector ALU and formats bound by memory share every compute unit.  Batch by
-// batch: of the first i places of what is left, floor(i n_b / n_left) are batch b's.
+// Bins of the chip that the hardware deals the places of a grid to in turn: 8 XCDs x 4 shader engines each.
+constexpr uint32_t kDirectBins = 32;
+// Place of the grid -> index in the merged item lists (see direct_batch), and back.  Merged, two batches take every second
+// place each, that is every second XCD: 128 FP16 and 128 FP8 sequences of 1000 - 8100 tokens, 8 KV heads, ran 687 us like
+// that, the FP16 half of the chip long after the other.  So every round over the bins begins kRoundShift further on: with a
+// round's 32 places, 32 + 5 is prime to every number of batches up to eight (with 1, three batches keep to their bins).
+constexpr uint32_t kRoundShift = 5;
+__device__ __host__ inline uint32_t direct_index(const DirectArgs& D, uint32_t place) {
+  const uint32_t round = place / kDirectBins;
+  if (D.m.n_batches == 1 || (round + 1) * kDirectBins > D.total) return place;
+  return round * kDirectBins + (place + kRoundShift * round) % kDirectBins;
+}
+__device__ __host__ inline uint32_t direct_place(const DirectArgs& D, uint32_t index) {
+  const uint32_t round = index / kDirectBins;
+  if (D.m.n_batches == 1 || (round + 1) * kDirectBins > D.total) return index;
+  return round * kDirectBins + (index + kDirectBins - kRoundShift * round % kDirectBins) % kDirectBins;
+}
+
+// Index `i` -> batch, and `i` the item's index within it (see direct_item): the batches' item lists merged proportionally,
+// so that formats bound by the vector ALU and formats bound by memory share every compute unit.  Batch by batch: of the
+// first i items of what is left, floor(i n_b / n_left) are batch b's.
 __device__ __host__ inline int direct_batch(const DirectArgs& D, uint32_t& i) {
   int b = 0;
   for (; b + 1 < D.m.n_batches; ++b) {
@@ -286,7 +304,6 @@ __device__ __host__ inline DirectItem direct_item(const DirectArgs& D, int b, ui
   const uint32_t split = pair / n, seq = n & 1 ? pair % n : (pair + split) % n;
   return DirectItem{(int)seq, (int)split, (int)(local % H), (seq * S + split) * H + local % H};
 }
-constexpr uint32_t kDirectBins = 32;
 
 // Runs [v0, v1) of split `split` of a sequence of `runs` runs.  The last split takes all that is left: a sequence may be
 // longer on the device than the host knew when it sized the grid.

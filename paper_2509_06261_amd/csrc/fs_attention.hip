@@ -574,15 +574,14 @@ bool fits(const DirectArgs& D, const uint16_t* n_of, uint64_t slots) {
   struct {
     uint32_t head, at, split, shift;  // shift: what the split's sequences begin with
   } next[kMaxBatches] = {};           // of each batch
-  uint32_t bins[kDirectBins] = {}, items = 0;
-  for (int i = 0; i < D.m.n_batches; ++i) items += D.items[i];
-  for (uint32_t place = 0; place < items; ++place) {
-    uint32_t local = place;
+  uint32_t bins[kDirectBins] = {};
+  for (uint32_t index = 0; index < D.total; ++index) {
+    uint32_t local = index;
     const int i = direct_batch(D, local);
     const DevBatch& B = D.m.b[i];
     auto& c = next[i];
     const uint32_t n = (uint32_t)B.n_seq, seq = c.at + c.shift < n ? c.at + c.shift : c.at + c.shift - n;
-    if (c.split < n_of[B.seq_first + seq]) ++bins[(1 + place) % kDirectBins];  // (place 0 of the grid is no item)
+    if (c.split < n_of[B.seq_first + seq]) ++bins[(1 + direct_place(D, index)) % kDirectBins];  // (place 0 of the grid is no item)
     if (++c.head == (uint32_t)B.g.H) {
       c.head = 0;
       if (++c.at == n) {
@@ -702,6 +701,7 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
       D.part_off[i] = floats;
       if (splits > 1) floats += n * (uint64_t)B.part_stride;
     }
+    D.total = (uint32_t)items;
     uint64_t left = items;
     for (int i = 0; i < n_batches; ++i) {
       D.magic[i] = (((uint64_t)D.items[i] << 32) + left - 1) / left;

@@ -490,7 +490,7 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_ker
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* s_rec = reinterpret_cast<float*>(s_tab + D.entries);
   ItemPlan P;
-  uint32_t local = blockIdx.x - 1;
+  uint32_t local = direct_index(D, blockIdx.x - 1);
   P.b = direct_batch(D, local);
   const DevBatch& B = A.b[P.b];
   const DirectItem item = direct_item(D, P.b, local);

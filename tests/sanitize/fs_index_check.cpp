@@ -478,13 +478,17 @@ void direct_launches(int rounds) {
         }
       }
       CHECK(part_end <= A.m.part_capacity);
+      CHECK(total == A.total);
       for (uint32_t place = 0; place < total; ++place) {
+        const uint32_t index = fs::direct_index(A, place);
+        CHECK(index < total && fs::direct_place(A, index) == place);
         uint32_t local = place;
+        const int at = fs::direct_batch(A, local);  // the merged list itself is in order within a batch
+        CHECK(at >= 0 && at < nb && local == next[at]++);
+        local = index;
         const int k = fs::direct_batch(A, local);
         CHECK(k >= 0 && k < nb && local < A.items[k] && hit[k][local] == 0);
         if (k < 0 || k >= nb || local >= A.items[k]) continue;
-        CHECK(local == next[k]);  // in order within the batch
-        next[k] = local + 1;
         hit[k][local] = 1;
         ++g_items;
         const fs::DevBatch& B = A.m.b[k];
