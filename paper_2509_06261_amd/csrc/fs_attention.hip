@@ -716,8 +716,10 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
   for (int i = 0; i < n_batches; ++i)
     small_us = std::max(small_us, std::min(std::max(all_us / 10 * rate[i].wg, (double)kDirectItemBytes), (double)most[i]) / rate[i].wg);
   const double mean_us = sum_us / (double)pairs;
-  // what the list costs: least where its waves are bound by the vector ALU (INT4 at head_dim 256)
-  const double list_us = hd == 256 && int4_only ? 18 : hd == 64 ? 15 + 0.05 * all_us : hd == 128 ? 30 + 0.06 * all_us : 30 + 0.1 * all_us;
+  // what the list costs: least where its waves are bound by the vector ALU (INT4 at head_dim 256).  (For the calls on both
+  // sides of the line see tests/sanitize/fs_index_check.cpp; 128 FP16 and 128 FP8 sequences of 1000 - 8100 tokens over the
+  // slabs of two 32-layer models: list 615 us, whole 647.)
+  const double list_us = hd == 256 && int4_only ? 18 : hd == 64 ? 15 + 0.05 * all_us : hd == 128 ? 25 + 0.015 * all_us : 30 + 0.1 * all_us;
   if (pairs <= slots) {
     double want_us = std::max(sum_us / (double)(slots - pairs / 2), (64 << 10) / rate[0].wg);
     bool ok = cut(longest_us - want_us < kCombineUs ? kWhole : want_us, 0);
