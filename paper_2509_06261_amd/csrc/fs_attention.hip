@@ -621,7 +621,7 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
   if (p->opt.split_bytes || p->opt.decode_list) return false;
   DirectRate rate[kMaxBatches];  // in bytes per us from here on
   uint64_t most[kMaxBatches];    // bytes of the batch's longest sequence, one head
-  uint64_t pairs = 0;
+  uint64_t pairs = 0, entries = 0;  // entries: of all block tables, inside the lengths
   double all_us = 0, longest_us = 0, sum_us = 0;
   bool int4_only = true, memory_bound = false;
   for (int i = 0; i < n_batches; ++i) {
@@ -636,6 +636,7 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
       most[i] = std::max(most[i], bytes);
       sum += bytes;
     }
+    entries += sum / (2 * (g.row_bytes + (uint64_t)g.param_bytes)) / (uint64_t)g.tokens_per_block;
     sum *= (uint64_t)g.n_kv_heads;
     pairs += (uint64_t)batches[i].n_seq * (uint64_t)g.n_kv_heads;
     longest_us = std::max(longest_us, (double)most[i] / rate[i].wg);
@@ -644,6 +645,8 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
     int4_only = int4_only && g.kv_dtype == FS_KV_INT4;
     memory_bound = memory_bound || g.kv_dtype == FS_KV_FP16 || (g.kv_dtype == FS_KV_FP8_E4M3 && g.head_dim > 64);
   }
+  // one workgroup checks all entries, about 3500 per us
+  if ((double)entries / 3500 > 1.2 * all_us + 10) return false;
   const int hd = A.b[0].g.D, per_cu = mfma_wgs_per_cu(hd);
   const uint64_t slots = (uint64_t)(p->n_cu ? p->n_cu : 256) * per_cu;  // (no device: replays of the plan on the host)
   D.m = A;

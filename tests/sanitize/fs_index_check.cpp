@@ -587,6 +587,7 @@ void direct_rule() {
   struct {
     int dtype, heads, group, dim, n, lo, hi;
     bool skewed, direct, whole;
+    int slab;  // 0: 128 KiB
   } cases[] = {{FS_KV_INT4, 40, 1, 128, 256, 1, 32768, true, false, false},   // list 834 us, whole 862
                {FS_KV_FP16, 8, 4, 128, 256, 1, 32768, true, false, false},    // list 610, whole 800
                {FS_KV_FP16, 8, 4, 128, 300, 3500, 4096, false, true, true},   // list 764, whole 704
@@ -597,10 +598,14 @@ void direct_rule() {
                {FS_KV_FP8_E4M3, 4, 4, 256, 300, 300, 6000, false, true, true},  // list 355, whole 331
                {FS_KV_FP16, 8, 4, 64, 20, 100, 800, false, true, true},       // cut 14, whole 10
                {FS_KV_FP16, 8, 4, 128, 20, 500, 6000, false, true, false},    // cut 49, whole 67
-               {FS_KV_FP16, 8, 4, 128, 64, 512, 4096, false, true, false}};   // cut 103, whole 114
+               {FS_KV_FP16, 8, 4, 128, 64, 512, 4096, false, true, false},   // cut 103, whole 114
+               // 640 and 80 table entries each: one workgroup checks them all, 94 us for 65 us of keys and values
+               {FS_KV_INT4, 1, 4, 64, 512, 6390, 6400, false, false, false, 768},
+               {FS_KV_INT4, 1, 4, 64, 512, 790, 800, false, true, true, 768}};
   for (const auto& c : cases) {
     fs_pool* p = nullptr;
-    CHECK(fs_pool_create(128 << 10, 4096ull * (128 << 10), kFakeBase, &p) == FS_OK);
+    const uint64_t slab = c.slab ? c.slab : 128 << 10;
+    CHECK(fs_pool_create(slab, 4096 * slab, kFakeBase, &p) == FS_OK);
     if (!p) continue;
     fs_model_t m;
     const int T = fs_model_register(p, c.dtype, c.heads, c.dim, 1, &m);
