@@ -244,6 +244,7 @@ __device__ __host__ inline ItemRange item_range(const DevBatch& B, int seq, int 
 
 // ---- Direct launches (MFMA kernel without a work list): one workgroup per (sequence, split, KV head) ----
 constexpr int kDirectEntries = 1024;  // block-table entries of an item, at most
+constexpr uint32_t kDirectMaxItems = (1u << 24) - 2;  // a grid of 256-thread workgroups stays below 2^32 threads
 struct DirectArgs {
   MultiArgs m;                     // chunk_runs of a batch: runs per split (a multiple of 16; unused with one split)
   uint32_t splits[kMaxBatches];    // splits the grid holds per sequence of the batch; the last one takes all that is left

@@ -699,7 +699,7 @@ bool plan_direct(const fs_pool* p, const fs_batch_t* batches, int n_batches, con
       D.splits[i] = (uint32_t)splits;
       const uint64_t n = (uint64_t)B.n_seq * splits * (uint64_t)g.n_kv_heads;
       items += n;
-      if (items > 0x3fffffff) return false;
+      if (items > kDirectMaxItems) return false;
       D.items[i] = (uint32_t)n;
       D.part_off[i] = floats;
       if (splits > 1) floats += n * (uint64_t)B.part_stride;

@@ -598,11 +598,13 @@ hipError_t launch_mfma_direct(const DirectArgs& args, hipStream_t s) {
   const size_t smem = (size_t)D.entries * sizeof(uint64_t) + (size_t)kWaves * heads * (hd + 2) * sizeof(float);
   uint32_t* status = D.m.header + kHdrStatus;
   D.m.header += kHdrIgnored - kHdrStatus;
-  switch (hd) {
-    case 64: hipLaunchKernelGGL(mfma_direct_kernel<64>, dim3(items + 1), dim3(kThreads), smem, s, D, status); break;
-    case 128: hipLaunchKernelGGL(mfma_direct_kernel<128>, dim3(items + 1), dim3(kThreads), smem, s, D, status); break;
-    default: hipLaunchKernelGGL(mfma_direct_kernel<256>, dim3(items + 1), dim3(kThreads), smem, s, D, status); break;
+  static_assert(kThreads * ((uint64_t)kDirectMaxItems + 1) < 1ull << 32, "threads of the grid");
+  void (*const kern)(DirectArgs, uint32_t*) = hd == 64 ? mfma_direct_kernel<64> : hd == 128 ? mfma_direct_kernel<128> : mfma_direct_kernel<256>;
+  if (smem > 64 * 1024) {  // (head_dim 256 with 15 or 16 query heads per KV head: has to be granted per kernel)
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
   }
+  hipLaunchKernelGGL(kern, dim3(items + 1), dim3(kThreads), smem, s, D, status);
   return hipGetLastError();
 }
 

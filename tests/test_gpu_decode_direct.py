@@ -22,7 +22,7 @@ def _check(wl, layers):
 
 
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
-@pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 4, 1), (64, 2, 8), (128, 2, 4), (128, 3, 16), (256, 2, 3)])
+@pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 4, 1), (64, 2, 8), (128, 2, 4), (128, 3, 16), (256, 2, 3), (256, 2, 16)])
 def test_short_sequences(dtype, head_dim, kv_heads, group):
     lens = np.array([1, 7, 8, 9, 31, 32, 33, 127, 128, 129, 257, 400], np.int32)
     _check(Workload("dd", 160 * KiB, 160 * 400 * KiB,
