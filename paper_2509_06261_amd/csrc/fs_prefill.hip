@@ -1789,7 +1789,9 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     return FS_ERR_INVALID;
   }
   const int tpt = 16 / G;
-  const int ncb_env = p->opt.prefill_ncb;  // FS_OPT_PREFILL_COLUMN_BLOCKS
+  // (FS_OPT_PREFILL_COLUMN_BLOCKS chooses among variants that are built for head_dim 128: one setting for a pool must not
+  // take its models of head_dim 64 and 256 off the kernel that suits their launches)
+  const int ncb_env = g.head_dim == kD ? p->opt.prefill_ncb : 0;
   // the wide kernels fold the (positive) softmax scale into the exponential's argument; any other scale takes
   // the 16-column kernel, which does not
   const bool scale_ok = sm_scale > 0.f && sm_scale < INFINITY;
@@ -1797,7 +1799,6 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // wave or the 16-column kernel)
   const bool d64 = g.head_dim == 64, d256 = g.head_dim == 256;
   int ncb = !scale_ok || (g.head_dim != kD && !d64 && !d256) ? 1 : (ncb_env ? ncb_env : 16);
-  if ((d64 || d256) && ncb != 16) ncb = 1;  // (the wide wave-level kernels are written for head_dim 128)
   if (d256 && ncb == 16) ncb = kBlocks256;
   uint64_t tiles = 0;
   auto count_tiles = [&](int blocks) {

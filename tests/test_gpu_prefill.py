@@ -133,8 +133,8 @@ def test_group_sizes(group):
     (FP16, 512, 2, 2, 64, False),    # the largest: a whole wave per row
 ])
 def test_shapes_beside_head_dim_128(dtype, head_dim, kv_heads, q_heads, slab_kib, src_f32):
-    """Head_dim 64 and 256 with at least 8 tokens per block run the 16-column MFMA kernel (whatever kernel the options
-    ask for); every other shape the pool accepts (other head_dims, blocks of fewer than 8 tokens) the vector-ALU
+    """Launches of so few items run the 16-column MFMA kernel at head_dim 64 and 256 with at least 8 tokens per block
+    (whatever kernel the options ask for: they concern head_dim 128); every other shape the pool accepts (other head_dims, blocks of fewer than 8 tokens) the vector-ALU
     kernel.  The pool's record of the launched kernel says which one ran."""
     lens = np.array([1, 2, 7, 33, 100, 257], np.int32)
     wl = Workload("pfgen", slab_kib * KiB, slab_kib * KiB * (32 * MiB // (slab_kib * KiB)),

@@ -10,25 +10,48 @@ pytestmark = pytest.mark.gpu
 
 EDGES = np.array([1, 31, 32, 33, 64, 65, 127, 128, 129, 255, 257, 300, 511], np.int32)
 CHUNKS = np.array([1, 0, 32, 1, 17, 64, 16, 128, 33, 200, 1, 300, 65], np.int32)
+CHUNKS_256 = np.array([1, 0, 32, 1, 32, 64, 63, 128, 64, 200, 1, 300, 255], np.int32)  # half to one item per compute unit
 
 
+# (head_dim 64 and 256 take the kernel by the size of the launch alone: as many KV heads as that needs)
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
-@pytest.mark.parametrize("head_dim,group", [(64, 4), (64, 1), (64, 3), (128, 4), (128, 1), (256, 4), (256, 3)])
-def test_workgroup_kernel_edges(dtype, head_dim, group, monkeypatch):
+@pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 13, 4), (64, 20, 1), (64, 15, 3), (128, 2, 4), (128, 2, 1), (256, 2, 4), (256, 2, 3)])
+def test_workgroup_kernel_edges(dtype, head_dim, kv_heads, group, monkeypatch):
     import gpu_harness
     import gpu_workload
     import paper_2509_06261_amd as fs
 
     monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 16})
     wl = Workload("pfwg", 96 * KiB, 96 * 400 * KiB,
-                  [ModelSpec("m", dtype, 2, head_dim, 2, 2 * group, EDGES, tag=41, src_f32=dtype == INT4)], "shuffle")
+                  [ModelSpec("m", dtype, kv_heads, head_dim, 2, kv_heads * group, EDGES, tag=41, src_f32=dtype == INT4)], "shuffle")
     par = gpu_harness.Parity(wl, zero_pool=True)
     try:
         par.gw.populate([[1]])
-        print("T", par.gw.T, par.prefill_and_check(0, 1, EDGES), par.prefill_and_check(0, 1, CHUNKS))
-        ran = fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)
-        assert ran & 0xffff == (4 | 4 << 8 if head_dim == 256 else 16 | 8 << 8), ran
-        assert bool(ran >> 16 & 1) == (head_dim == 128 and dtype in (INT8, INT4))  # exact codes at head_dim 64
+        for n_new in (EDGES, CHUNKS_256 if head_dim == 256 else CHUNKS):
+            print("T", par.gw.T, par.prefill_and_check(0, 1, n_new))
+            ran = fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)
+            assert ran & 0xffff == (4 | 4 << 8 if head_dim == 256 else 16 | 8 << 8), ran
+            assert bool(ran >> 16 & 1) == (head_dim == 128 and dtype in (INT8, INT4))  # exact codes at head_dim 64
+    finally:
+        par.close()
+
+
+@pytest.mark.parametrize("head_dim,dtype,kernel", [(64, FP16, 1), (256, FP8, 1), (128, FP16, 16 | 8 << 8)])
+def test_column_blocks_option_concerns_head_dim_128(head_dim, dtype, kernel, monkeypatch):
+    """A pool-wide FS_OPT_PREFILL_COLUMN_BLOCKS of 16 leaves the models of other head_dims on the kernel that the size of
+    their launch asks for: here a few items, and at head_dim 256 FP8 prompts of more items than compute units."""
+    import gpu_harness
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 16})
+    lens = EDGES if head_dim == 256 else np.array([3, 40], np.int32)
+    wl = Workload("pfcb", 256 * KiB, 256 * 200 * KiB, [ModelSpec("m", dtype, 4, head_dim, 2, 16, lens, tag=44)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[1]])
+        par.prefill_and_check(0, 1, lens)
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == kernel
     finally:
         par.close()
 
