@@ -1896,7 +1896,11 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   (void)hipGetLastError();
   const uint64_t items = tiles * (uint64_t)g.n_kv_heads;
   const bool wg = ncb == 16 || ncb == kSmallBlocks || (d256 && ncb == kBlocks256);
-  const int nw = d256 || (p->opt.prefill_nw == 4 && ncb == 16 && !d64) ? 4 : 8;
+  // (FS_OPT_PREFILL_WAVES is about the launches that have a 16-block item per compute unit; a smaller launch by the
+  // library's own choice keeps the integer codes exact and its sums over the unrounded weights, as the 16-column kernel that
+  // served it before, and the 4-wave kernels are not built like that)
+  const bool large = ncb_env || items >= (uint64_t)p->n_cu;
+  const int nw = d256 || (p->opt.prefill_nw == 4 && ncb == 16 && !d64 && large) ? 4 : 8;
   // the workgroups list the sequences themselves while they have a thread for each; the per-sequence tile counts of more
   // go to LDS while they fit beside the stages (16 KiB: 4095 sequences)
   P.tf_cache = !wg || generic ? 0 : (nw == 8 || d256) && n_seq <= nw * 64 ? 2 : (uint64_t)n_seq + 1 <= 4096;
@@ -1939,9 +1943,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
 #define FS_WG(DT)                                  \
   (nw == 8 ? prefill_wg_kernel<DT, 8, 2, 4, 1> \
            : (p->opt.prefill_pipe ? prefill_wg_kernel<DT, 4, 4, 4, 1, true> : prefill_wg_kernel<DT, 4, 4, 4, 1>))
-    // (that kernel at head_dim 128 only; a smaller launch by the library's own choice keeps the integer codes exact and
-    // its sums over the unrounded weights, as the 16-column kernel that served it before)
-    const bool large = ncb_env || items >= (uint64_t)p->n_cu;
+    // (that kernel at head_dim 128 only)
     const bool deq = p->opt.prefill_deq && nw == 8 && ncb == 16 && !d64 && large;
     if (d256) {
       // Four waves of one block each (a wave's share of a sub-tile's K or V, 64 registers in FP16, and its accumulators
@@ -1974,8 +1976,8 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
         default: kern = prefill_wg_kernel<FS_KV_INT4, 8, 2, 4, 1, false, false, 64, true>; break;
       }
     } else switch (g.kv_dtype) {
-      case FS_KV_FP16: kern = large || nw == 4 ? FS_WG(FS_KV_FP16) : prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, kD, true>; break;
-      case FS_KV_FP8_E4M3: kern = large || nw == 4 ? FS_WG(FS_KV_FP8_E4M3) : prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, kD, true>; break;
+      case FS_KV_FP16: kern = large ? FS_WG(FS_KV_FP16) : prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, kD, true>; break;
+      case FS_KV_FP8_E4M3: kern = large ? FS_WG(FS_KV_FP8_E4M3) : prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, kD, true>; break;
       case FS_KV_INT8: kern = deq ? prefill_wg_kernel<FS_KV_INT8, 8, 2, 4, 1, false, true> : FS_WG(FS_KV_INT8); break;
       default: kern = deq ? prefill_wg_kernel<FS_KV_INT4, 8, 2, 4, 1, false, true> : FS_WG(FS_KV_INT4); break;
     }

@@ -56,6 +56,25 @@ def test_column_blocks_option_concerns_head_dim_128(head_dim, dtype, kernel, mon
         par.close()
 
 
+@pytest.mark.parametrize("dtype", [FP16, FP8, INT8])
+def test_four_wave_option_leaves_launches_below_an_item_per_unit_alone(dtype, monkeypatch):
+    """Between the direct launches and those with a 16-block item per compute unit: sums over the unrounded weights and
+    exact codes, which the 4-wave kernels of FS_OPT_PREFILL_WAVES = 4 do not have."""
+    import gpu_harness
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_WAVES: 4})
+    wl = Workload("pfnw", 384 * KiB, 384 * 200 * KiB, [ModelSpec("m", dtype, 5, 128, 2, 20, EDGES, tag=45)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[1]])
+        par.prefill_and_check(0, 1, EDGES)
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (16 | 8 << 8)
+    finally:
+        par.close()
+
+
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
 @pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 6, 4), (128, 2, 4), (128, 3, 1)])
 def test_small_launches(dtype, head_dim, kv_heads, group):
