@@ -814,10 +814,14 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
 // VPRE: V fragments requested in front of the softmax (registers permitting)
 // SUM32: the running sum of an FP16 / FP8 column takes the weights before they are rounded to fp16 (twice the
 // instructions of the dot product with ones), as the 16-column kernel does: for launches that kernel served before
-template <int DT, int NCB, int SUBS, int VPRE, int HD, bool SUM32>
+// CUT: values of tokens that no column of a block sees do not reach the block's MFMAs: an Inf or NaN among them (an fp32
+// value above 65504 is one in FP16) would turn weight 0 into NaN, in rows up to a sub-tile ahead of its token.  A tile code of
+// its own for the sub-tiles on the diagonal: as a branch in the common one it cost a prompt of 777 tokens 27.4 -> 31.4 us.
+template <int DT, int NCB, int SUBS, int VPRE, int HD, bool SUM32, bool CUT = false>
 __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const ItemCtx& X, const u32x4 (&qb)[NCB][HD / 32],
                                         const float (&qsum)[NCB], const int (&len_cb)[NCB], float alpha, int first_pos,
-                                        int vb, int lane, int j, int c, WideState<NCB, HD>& st, bool whole_runs = false) {
+                                        int vb, int lane, int j, int c, WideState<NCB, HD>& st, bool whole_runs = false,
+                                        int tpt = 0, int n_tok = 0) {
   using F = Fmt<DT, HD>;
   constexpr int KS = HD / 32;
   float4v s[NCB][2];
@@ -850,7 +854,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
   // location is needed on the mask path only.
   RunLoc L;
   bool interior;
-  if (F::kParBytes == 0 && whole_runs) {
+  if (!CUT && F::kParBytes == 0 && whole_runs) {
     interior = vb + 4 <= X.v_end && 8 * (vb + 4) <= first_pos + 1;
     if (!interior) L = locate(X, vb + j);
   } else {
@@ -964,7 +968,16 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
     if (e < VPRE) b = vpre[e];
     else b = *reinterpret_cast<const u32x4*>(stage + stage_v(SUBS, HD) + (uint32_t)((sub * F::kNE + e) * kFrag) + lane * 16);
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) st.acc[cb][e] = mfma(pk[cb], b, st.acc[cb][e]);
+    for (int cb = 0; cb < NCB; ++cb) {
+      u32x4 seen = b;
+      if constexpr (CUT) {
+        int n = first_pos + min((cb + 1) * tpt, n_tok) - L.tok0;  // slots of this lane's run that the block sees
+        if constexpr (NCB * HD > 128) asm volatile("" : "+v"(n));  // (masks made anew for each fragment: no registers to keep them in)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) seen[q] &= (2 * q < n ? 0xFFFFu : 0u) | (2 * q + 1 < n ? 0xFFFF0000u : 0u);
+      }
+      st.acc[cb][e] = mfma(pk[cb], seen, st.acc[cb][e]);
+    }
   }
 }
 
@@ -1057,6 +1070,8 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
 
   const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
   const int w_end = n_tok > 0 ? n_runs(first_pos + n_tok, g.T, B.R) : 0;  // runs this wave's last query sees
+  constexpr bool kCut = SUM32 && DT == FS_KV_FP16;  // (see wg_tile)
+  const int w_seen = kCut ? n_runs(first_pos + 1, g.T, B.R) - 1 : 0;
   const int n_run = n_runs(X.len_u, g.T, B.R);
   for (int v0 = 0; v0 < n_run; v0 += P.seg_runs) {
     X.v_end = min(n_run, v0 + P.seg_runs);
@@ -1115,10 +1130,18 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       // tile: it costs the accumulators' registers nothing.  (64 FP16 prompts of 512 - 4096 tokens, GQA 4:1: 4126 ->
       // 3977 us; 12 INT4 multi-head prompts of 300 - 3000 tokens, whose items span two steps of diagonal: 840 -> 800 us.)
       const int n_live = min(SUBS, (w_end - (v0 + i * SUBS * 4) + 3) >> 2);
+      // (runs in front of the one that holds the first query's own token are seen by all of the wave's columns)
+      const int n_seen = kCut ? min(n_live, max(w_seen - (v0 + i * SUBS * 4), 0) >> 2) : n_live;
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
-      for (int sub = 0; sub < n_live; ++sub)
+      for (int sub = 0; sub < n_seen; ++sub)
         wg_tile<CDT, NCB, SUBS, kVPre, HD, SUM32>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4, lane, j,
-                                           c, st, whole_runs);
+                                                  c, st, whole_runs);
+      if constexpr (kCut) {
+#pragma unroll 1
+        for (int sub = n_seen; sub < n_live; ++sub)
+          wg_tile<CDT, NCB, SUBS, 0, HD, SUM32, true>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4,
+                                                          lane, j, c, st, whole_runs, P.tpt, n_tok);
+      }
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS, HD);
       if (more) stage_to(next, vb_next);
       __syncthreads();  // (also after the last step: the next staging overwrites what other waves may still read)

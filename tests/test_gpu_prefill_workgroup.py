@@ -75,6 +75,50 @@ def test_four_wave_option_leaves_launches_below_an_item_per_unit_alone(dtype, mo
         par.close()
 
 
+@pytest.mark.parametrize("head_dim,kv_heads,group,kernel", [(64, 16, 4, 16 | 8 << 8), (64, 6, 4, 8 | 8 << 8), (128, 3, 4, 8 | 8 << 8),
+                                                            (128, 5, 1, 8 | 8 << 8), (128, 12, 4, 16 | 8 << 8), (256, 4, 4, 4 | 4 << 8)])
+def test_infinite_value_reaches_no_row_before_its_block(head_dim, kv_heads, group, kernel):
+    """An Inf among the values (an fp32 value above 65504 in an FP16 model) at token t: the rows of earlier blocks of 16
+    columns are what they are without it, and the rows from t on are not finite."""
+    import torch
+
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    lens = np.array([700, 300], np.int32)
+    gw = gpu_workload.GpuWorkload(Workload("pfinf", 512 * KiB, 512 * 200 * KiB,
+                                           [ModelSpec("m", FP16, kv_heads, head_dim, 1, kv_heads * group, lens, tag=46)], "shuffle"), zero_pool=True)
+    try:
+        gw.place()
+        gw.populate([[0]])
+        m, g = gw.model_ids[0], gw.geom[gw.model_ids[0]]
+        off = np.array([0, 700, 1000], np.int32)
+        q = torch.randn((1000, kv_heads * group, head_dim), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda", dtype=torch.float16)
+        ws = torch.empty(fs.fs_prefill_workspace_bytes(2), dtype=torch.uint8, device="cuda")
+
+        def run():
+            out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
+            fs.fs_prefill_attention(gw.pool, m, 0, kv_heads * group, 0.1, q, gw.tables[0], gw.seq_lens[0], torch.from_numpy(off).cuda(), off, out, lse, ws)
+            assert fs.fs_decode_status(ws) == 0 and fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == kernel
+            return out, lse
+
+        out0, lse0 = run()
+        T, per_block = g.tokens_per_block, 16 // group
+        for t in (5, 61, 133, 690):
+            at = int(gw.tables_host[0][0, t // T]) * g.block_budget + g.kv_tile + (t % T) * g.row_bytes  # KV head 0, element 0
+            part = gw.pool_mem[at: at + 2]
+            old = part.clone()
+            part.copy_(torch.tensor([0x00, 0x7C], dtype=torch.uint8))
+            out, lse = run()
+            part.copy_(old)
+            first = t // per_block * per_block
+            assert not torch.isfinite(out[t:700, :group, 0]).any(), t
+            out[first:700, :group, 0] = out0[first:700, :group, 0]
+            assert torch.equal(out, out0) and torch.equal(lse, lse0), t
+    finally:
+        gw.close()
+
+
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
 @pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 6, 4), (128, 2, 4), (128, 3, 1)])
 def test_small_launches(dtype, head_dim, kv_heads, group):
