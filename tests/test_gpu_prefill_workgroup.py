@@ -119,6 +119,29 @@ def test_infinite_value_reaches_no_row_before_its_block(head_dim, kv_heads, grou
         gw.close()
 
 
+@pytest.mark.parametrize("head_dim,n_seq,with_tokens,kernel", [(128, 600, 600, 16 | 8 << 8), (256, 300, 300, 4 | 4 << 8), (64, 700, 700, 16 | 8 << 8),
+                                                               (128, 100, 100, 8 | 8 << 8), (128, 500, 90, 8 | 8 << 8), (256, 200, 150, 4 | 4 << 8)])
+def test_many_sequences(head_dim, n_seq, with_tokens, kernel):
+    """More sequences than a workgroup has threads (their tile counts come from the preparation kernel), and direct launches
+    whose sequences several waves list, most of them without new tokens."""
+    import gpu_harness
+    import paper_2509_06261_amd as fs
+
+    rng = np.random.default_rng([head_dim, n_seq])
+    lens = rng.integers(1, 40, n_seq).astype(np.int32)
+    lens[[0, n_seq // 2, n_seq - 1]] = [150, 97, 33]
+    wl = Workload("pfmany", 64 * KiB, 64 * 1500 * KiB, [ModelSpec("m", FP16, 2 if head_dim != 256 else 1, head_dim, 1, 4, lens, tag=47)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[0]])
+        n_new = np.minimum(lens, rng.integers(1, 17, n_seq)).astype(np.int32) if with_tokens < 200 else lens.copy()
+        n_new[rng.permutation(n_seq)[: n_seq - with_tokens]] = 0
+        print(par.prefill_and_check(0, 0, n_new))
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == kernel
+    finally:
+        par.close()
+
+
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
 @pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 6, 4), (128, 2, 4), (128, 3, 1)])
 def test_small_launches(dtype, head_dim, kv_heads, group):
