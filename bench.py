@@ -2,8 +2,8 @@
 """Benchmark of the KV-slab decode hot path on one MI355X.
 
 A *step* is one decode step of one layer over the whole batch, one ``fs_decode_step_multi`` call: the
-append of every sequence's newest token (quantize + scatter into its slab block; all models in the
-launch that also prepares the work list), split-K paged attention over all co-located models, split
+append of every sequence's newest token (quantize + scatter into its slab block; all models in one
+launch, which also prepares the work list where there is one), split-K paged attention over all co-located models, split
 combine.  Slab allocation is host bookkeeping done while the workload
 is set up (its rate is reported under ``extra``).  KV, block tables, queries and lengths are
 resident in HBM before the timed region starts; the layer index rotates between steps so that no

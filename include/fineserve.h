@@ -181,7 +181,7 @@ int fs_kv_append_multi(fs_pool* pool, const fs_append_t* appends, int n_appends,
  *   q, out       : device fp16 [n_seq][n_q_heads][head_dim]
  *   block_tables : device int32 [n_seq][max_blocks]
  *   seq_lens     : device int32 [n_seq], 1 <= n_b <= max_blocks * tokens_per_block
- *   seq_lens_host: optional host copy of seq_lens, used only to size the workspace tightly
+ *   seq_lens_host: optional host copy of seq_lens, used only to size the workspace tightly and to choose the launch
  *   lse          : optional device fp32 [n_seq][n_q_heads], receives max_t s_t + ln sum_t e^(s_t - max)
  * n_q_heads must be a multiple of n_kv_heads with ratio <= 16; q and out must be 16-byte aligned. */
 typedef struct {
@@ -216,9 +216,10 @@ int fs_decode_attention_multi(fs_pool* pool, const fs_batch_t* batches, int n_ba
 
 /* One decode step of one layer for all co-located models (Sec. 2.1: append the newest token's K/V, then attend over
  * the whole cache): fs_kv_append_multi(appends) followed by fs_decode_attention_multi(batches), in three launches
- * instead of n_appends + 3 -- the appends and the decode launch's work-list preparation do not depend on each other
- * and run in one kernel.  n_appends may be 0 (then `appends` may be NULL).  Arguments, workspace and status as for
- * the two calls it stands for. */
+ * instead of n_appends + 3: with a work list (see FS_OPT_DECODE_WORK_LIST) the appends and the list's preparation, which
+ * do not depend on each other, in one kernel, then attention and combine; without one the appends, the attention and,
+ * where a sequence is split, the combine.  n_appends may be 0 (then `appends` may be NULL).  Arguments, workspace and
+ * status as for the two calls it stands for. */
 int fs_decode_step_multi(fs_pool* pool, const fs_append_t* appends, int n_appends, const fs_batch_t* batches,
                          int n_batches, void* workspace, uint64_t workspace_bytes, void* stream);
 
@@ -236,8 +237,9 @@ int fs_decode_attention_multi_static(fs_pool* pool, const fs_batch_t* batches, i
                                      void* stream);
 
 /* After the stream has passed a decode call: 0 if every sequence length and block-table entry was in
- * range and the workspace sufficed, else a bit mask (1: length out of range, clamped; 2: workspace too
- * small, affected sequences left unwritten; 4: a block-table entry inside a sequence's length named no
+ * range and the workspace sufficed, else a bit mask (1: length out of range, clamped; 2: a launch with a work
+ * list whose workspace, sized for seq_lens_host, is too small for the lengths on the device, affected sequences
+ * left unwritten; 4: a block-table entry inside a sequence's length named no
  * block of the pool -- it was read as block 0, so no byte outside the pool is touched, and the outputs
  * of the affected sequences are meaningless).  Synchronizes the stream. */
 int fs_decode_status(const void* workspace, void* stream);
@@ -257,11 +259,14 @@ int fs_decode_status(const void* workspace, void* stream);
  *            in use until the stream has passed the call.  fs_decode_status(workspace, stream) afterwards: bit 0
  *            set if a length or a chunk size was out of range (clamped), bit 2 (value 4) if a block-table entry
  *            named no block of the pool (read as block 0; the affected rows are meaningless).
- * At most 16 query heads per KV head (FS_ERR_INVALID otherwise).  head_dim 128 with at least 8 tokens per block
- * runs on the MFMA kernels; head_dim 64 and 256 on the 16-column MFMA kernel (the other variants are built for 128;
- * FS_OPT_PREFILL_COLUMN_BLOCKS is not consulted); every other shape the pool accepts on a vector-ALU kernel (one
- * workgroup per query row and KV head: correct, far slower).  A softmax scale that is not positive and finite is
- * served by the 16-column kernel as well.
+ * At most 16 query heads per KV head (FS_ERR_INVALID otherwise).  head_dim 64, 128 and 256 with at least 8 tokens per
+ * block run on the MFMA kernels: the workgroup kernel, which shares unpacked K/V between the waves of a workgroup, or,
+ * for head_dim 64 launches of very few items and most head_dim 256 launches of FP8 and integer formats, the 16-column
+ * kernel (at those head_dims the size of the launch decides and FS_OPT_PREFILL_COLUMN_BLOCKS is not consulted); every
+ * other shape the pool accepts on a vector-ALU kernel (one workgroup per query row and KV head: correct, far slower).
+ * A softmax scale that is not positive and finite is served by the 16-column kernel as well.
+ * An Inf or NaN among the cached values of a token reaches every row that attends to it; beside those, rows of the same
+ * chunk whose columns share an MFMA with one of them (up to 31 tokens ahead) may come out as NaN too.
  * Asynchronous on `stream`; no allocation, no host synchronisation. */
 uint64_t fs_prefill_workspace_bytes(int n_seq);
 int fs_prefill_attention(fs_pool* pool, fs_model_t model, int layer, int n_q_heads, float sm_scale, const void* q,
@@ -324,11 +329,12 @@ enum fs_option {
    * events on the call's stream; fs_pool_last_attention_kernel_ms waits for the latest pair.  (A call served by
    * several launch sequences, one per head_dim: from the first attention kernel's start to the last one's end.) */
   FS_OPT_KERNEL_TIMING = 2,
-  /* prefill kernel: 0 = automatic (default: the workgroup kernel, or the 16-column kernel for launches with fewer
-   * work items than compute units), 1 / 2 / 4 = the wave-level kernels with 16 / 32 / 64 logit columns per wave,
-   * 16 = the workgroup kernel */
+  /* prefill kernel of the models with a head_dim of 128: 0 = automatic (default: the workgroup kernel, with items of 16
+   * column blocks, or of 8 where even those all find a compute unit of their own), 1 / 2 / 4 = the wave-level kernels
+   * with 16 / 32 / 64 logit columns per wave, 16 = the workgroup kernel with items of 16 blocks */
   FS_OPT_PREFILL_COLUMN_BLOCKS = 3,
-  /* waves of the workgroup kernel: 0 or 8 = 8 x 32 columns (default), 4 = 4 x 64 columns */
+  /* waves of the workgroup kernel at head_dim 128, launches with at least one item of 16 blocks per compute unit (or
+   * FS_OPT_PREFILL_COLUMN_BLOCKS = 16): 0 or 8 = 8 x 32 columns (default), 4 = 4 x 64 columns */
   FS_OPT_PREFILL_WAVES = 4,
   /* non-zero: the 4-wave workgroup kernel in its software-pipelined form (one wave interleaves the MFMAs of the next
    * sub-tile's S^T with the current sub-tile's exponentials); default 0 */
@@ -340,7 +346,8 @@ enum fs_option {
   FS_OPT_PREFILL_STAGED_DEQUANT = 6,
   /* read-only: the kernel the pool's latest fs_prefill_attention call launched:
    * column blocks | waves << 8 | staged dequantization << 16 | pipelined << 17 (0: none yet; column blocks 0 with
-   * bit 18 set: the vector-ALU kernel) */
+   * bit 18 set: the vector-ALU kernel).  Workgroup kernels: 16 blocks with 8 or 4 waves, 8 with 8 (smaller launches),
+   * 4 with 4 (head_dim 256); wave-level kernels: 1, 2 or 4 blocks, waves 0 */
   FS_OPT_LAST_PREFILL_KERNEL = 7,
   /* non-zero: the MFMA decode kernel always takes its work from a list that a preparation kernel writes; 0 (default): a
    * launch whose sequences need few splits or none runs without one, a workgroup per (sequence, split, KV head) */

@@ -989,7 +989,10 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 // 4 x 4, 4 sub-tiles (one wave per SIMD); 8 x 1 for small launches; 4 x 1 with 2 sub-tiles per step at head_dim 256.
 // (Another one -- 4 x 2 with 2 sub-tiles per step, two workgroups per
 // compute unit -- passed its small cases but ended a full-size two-model run with the GPU faulted or hung; the
-// cause was not found and the variant is no longer built.)
+// cause was not found and the variant is no longer built.  What was particular to it is absent from the 4 x 1 kernel of
+// head_dim 256: that one has a compute unit to itself (its two stages alone are 129 KiB of the 160), a wave has one column
+// block, and its staging roles, fragment offsets and barriers are those of the 8-wave kernels, NW == 2 SUBS, with half the
+// counts: fragment indices end at SUBS * HD / 16 on both sides, which is where stage_v and stage_par begin.)
 // smem: two stages, then the workgroup's block-address table.
 // DEQ (INT8 / INT4 only): the staging waves dequantize, the tile code is the FP16 one.
 // header: where a block-table entry outside the pool is reported.
@@ -1012,7 +1015,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   constexpr int NE = HD / 16;  // output columns NE c .. NE c + NE - 1 are this lane's
   constexpr int CDT = DEQ ? FS_KV_FP16 : DT;  // the format the consumer code sees
   // V fragments read ahead of the softmax: what the format's register budget leaves room for (two waves per SIMD)
-  // (eight instead of four: a 4 x 512-token FP8 chunk step 447 -> 440 us, INT8 prompts 848 -> 841 us; FP16 would spill)
+  // (eight instead of four: a 4 x 512-token FP8 chunk step 429.5 -> 423 us, INT8 prompts 817 -> 811 us; FP16 would spill)
   constexpr int kVPre = NW != 8 ? 0 : (HD == kD && (DEQ || DT == FS_KV_FP8_E4M3) ? 8 : 4);
   const bool whole_runs = P.whole_runs != 0;  // (uniform)
   const bool does_k = NW == SUBS || w < SUBS, does_v = NW == SUBS || w >= SUBS;  // wave-uniform staging roles

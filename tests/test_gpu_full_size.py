@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 # config -> (layer per model, oracle sample per model (None = every sequence), prefill sample per model)
 # "2-d64" / "2-d256": config 2 with head_dim 64 / 256, the launches bench.py times on the MFMA decode kernel's other two
-# instantiations (whole-prompt prefill there runs the 16-column MFMA kernel)
+# instantiations (whole-prompt prefill there runs the workgroup kernel's)
 CONFIGS = {"2": ([17], None, 3), "3": ([3, 29], 32, 1), "4": ([11], 32, 1), "5": ([7, 0, 3, 9], 32, 1),
            "2-d64": ([17], None, 1), "2-d256": ([17], None, 1)}
 
