@@ -564,7 +564,14 @@ DirectRate direct_rate(const fs_geometry_t& g) {
     case FS_KV_FP16: return g.head_dim == 256 ? DirectRate{33, 6200} : DirectRate{49, 6500};
     case FS_KV_FP8_E4M3: return g.head_dim == 64 ? DirectRate{33, 5600} : DirectRate{44, 6500};
     case FS_KV_INT8: return g.head_dim == 64 ? DirectRate{29, 5400} : DirectRate{38, 6500};
-    default: return g.head_dim == 64 ? DirectRate{15, 3600} : g.head_dim == 256 ? DirectRate{22, 4200} : DirectRate{20, 5500};
+    default: {
+      if (g.head_dim != 128) return g.head_dim == 64 ? DirectRate{15, 3600} : DirectRate{22, 4200};
+      // bound by the vector ALU, which works through whole runs of 8 slots: a block's last run costs the same when it is
+      // partly empty (256 sequences of 1024 - 8192 tokens, 8 KV heads, blocks of 120 tokens: whole 257 us, list 284; of 60,
+      // seven runs and a half: 296 and 301, as a step of a 32-layer pool 310 and 298)
+      const double full = g.tokens_per_block / (8.0 * ((g.tokens_per_block + 7) / 8));
+      return {20 * full, 5500 * full};
+    }
   }
 }
 

@@ -592,6 +592,7 @@ void direct_rule() {
                {FS_KV_FP16, 8, 4, 128, 256, 1, 32768, true, false, false},    // list 610, whole 800
                {FS_KV_FP16, 8, 4, 128, 300, 3500, 4096, false, true, true},   // list 764, whole 704
                {FS_KV_INT4, 8, 4, 128, 256, 1024, 8192, false, true, true},   // list 285, whole 255
+               {FS_KV_INT4, 8, 4, 128, 256, 1024, 8192, false, false, false, 64 << 10},  // (blocks of 60 tokens) list 298, whole 310
                {FS_KV_INT4, 40, 1, 128, 463, 128, 141, false, false, false},  // list 120, whole 246
                {FS_KV_INT4, 4, 4, 256, 100, 300, 6000, false, false, false},  // list 102, whole 121
                {FS_KV_FP16, 4, 4, 256, 300, 300, 6000, false, false, false},  // list 698, whole 747
