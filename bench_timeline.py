@@ -8,6 +8,8 @@ are ordered against memory operations only: arithmetic of the last tiles may lan
 config's decode attention (one layer) is read back and summarised: how the launch's wave time divides into look-ups,
 streaming, output, pauses between items and idling at the end, how long items of each size tier take, and when the
 tiers start.  The product library is never touched; the readings cost the kernel about 1 %.
+The twin always runs the work list: a launch that the product serves without one (config 2) is shown as it runs with
+FS_OPT_DECODE_WORK_LIST.
 
     python bench_timeline.py [config ...]        (default: 5 2 4)
     python bench_timeline.py --prefill [config ...]   the prefill workgroup kernel instead (default: 2 4): per workgroup

@@ -321,8 +321,8 @@ __device__ __forceinline__ void append_rows(const AppendArgs& A, int64_t worker,
 
 // Rows of a unit: four while that leaves every wave slot of the chip work (the look-ups are shared and four source rows
 // are in flight per wave), one otherwise: a decode step's few tokens spread over as many waves as there are rows.
-// Measured, 65 600 tokens x 8 heads of 128, units of 1 / 2 / 4 / 8 rows: FP16 -> FP8 102 / 84 / 84 / 105 us, FP16 -> FP16
-// 103 / 97 / 97 / 99 us, fp32 -> INT4 133 / 129 / 130 / 129 us.
+// Measured, 65 600 tokens x 8 heads of 128, units of 1 / 2 / 4 / 8 rows: FP16 -> FP16 89 / 80 / 79 / 82 us, FP16 -> FP8
+// 84 / 79 / 73 / 82 us, FP16 -> INT8 103 / 87 / 82 / 89 us, fp32 -> INT4 124 / 120 / 122 / 123 us.
 constexpr int kWideUnit = 4;
 
 template <bool kSrcF32, int HP>
