@@ -810,6 +810,39 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
   }
 }
 
+// Column c's value combined over the four lanes j that hold its tokens (every lane of the column gets the result).
+template <typename Op>
+__device__ __forceinline__ float over_column(float x, Op op) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const u2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const u2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// The workgroup kernel keeps its accumulators transposed (rows = output elements, columns = logit columns): the V fragment is
+// the A operand, the weights are the B operand.  A lane then holds elements of its own column only, the one whose logits it
+// exponentiates, and moving the reference is a maximum over four lanes (row swaps on the vector ALU) and plain
+// multiplications.  With the weights as the A operand a lane held four other columns, and the maximum and the factors came
+// through LDS, three dependent round trips while the other waves waited at the step's barrier; and in most of an item's first
+// sub-tiles some column of a wave moves its reference.  Each block of 16 columns moves on its own.  (us: 64 FP16 prompts of
+// 512 - 4096 tokens, GQA 4:1, 3920 -> 3801; 32 such INT4 prompts 2369 -> 2271; 24 FP16 prompts of 256 - 3000 tokens at
+// head_dim 64 625 -> 576; one of 777 tokens 27.7 -> 26.2.  A wider window than 2^kTau saves another 1 - 3 %, but the largest
+// weights of a row are then no longer near 1, where fp16 holds them exactly, and the results are 6 - 14 % further from
+// the definition.  Weights first and a check on their sum in the place of the maxima: slower wherever references move.)
+template <int DT, int NCB, int HD>
+__device__ __forceinline__ void wg_move_reference(WideState<NCB, HD>& st, int cb, float tmax) {
+  const float m_new = fmaxf(st.m[cb], over_column(tmax, [](float a, float b) { return fmaxf(a, b); }));
+  const float corr = __builtin_amdgcn_exp2f(st.m[cb] - m_new);
+  st.l[cb] *= corr;
+  if constexpr (Fmt<DT>::kParBytes != 0) st.zc[cb] *= corr;
+#pragma unroll
+  for (int e = 0; e < HD / 16; ++e)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) st.acc[cb][e][r] *= corr;
+  st.m[cb] = m_new;
+}
+
 // One staged 32-token sub-tile for the wave's column blocks: wide_tile with the operands read from LDS.
 // VPRE: V fragments requested in front of the softmax (registers permitting)
 // SUM32: the running sum of an FP16 / FP8 column takes the weights before they are rounded to fp16 (twice the
@@ -911,8 +944,6 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
       }
     }
   }
-  float tmax[NCB];
-  bool need = false;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
     float mx = fmaxf(fmaxf(x[cb][0], x[cb][1]), x[cb][2]);
@@ -920,12 +951,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
     mx = fmaxf(fmaxf(mx, x[cb][5]), x[cb][6]);
     mx = fmaxf(mx, x[cb][7]);
     if constexpr (F::kParBytes == 0) mx *= alpha;
-    tmax[cb] = mx;
-    need |= mx - st.m[cb] > kTau;
-  }
-  if (__any(need)) {
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) wide_move_reference<DT>(st, cb, tmax[cb], j);
+    if (__any(mx - st.m[cb] > kTau)) wg_move_reference<DT>(st, cb, mx);
   }
   u32x4 pk[NCB];
 #pragma unroll
@@ -976,7 +1002,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 #pragma unroll
         for (int q = 0; q < 4; ++q) seen[q] &= (2 * q < n ? 0xFFFFu : 0u) | (2 * q + 1 < n ? 0xFFFF0000u : 0u);
       }
-      st.acc[cb][e] = mfma(pk[cb], seen, st.acc[cb][e]);
+      st.acc[cb][e] = mfma(seen, pk[cb], st.acc[cb][e]);
     }
   }
 }
@@ -1066,7 +1092,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
     }
 #pragma unroll
     for (int e = 0; e < NE; ++e) st.acc[cb][e] = float4v{0.f, 0.f, 0.f, 0.f};
-    st.m[cb] = -INFINITY;
+    st.m[cb] = kNoReference;  // (a masked logit then weighs 0 from the start; with -inf it would be NaN)
     st.l[cb] = 0.f;
     st.zc[cb] = 0.f;
   }
@@ -1158,48 +1184,39 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   const float v_static = DT == FS_KV_FP8_E4M3 ? B.v_scale[head] : 1.0f;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
-    float l = st.l[cb], zc = st.zc[cb];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
-    if constexpr (Fmt<CDT>::kParBytes != 0) {
-      zc += __shfl_xor(zc, 16, 64);
-      zc += __shfl_xor(zc, 32, 64);
-    }
+    auto sum = [](float a, float b) { return a + b; };
+    const float l = over_column(st.l[cb], sum);
+    const float zc = Fmt<CDT>::kParBytes != 0 ? over_column(st.zc[cb], sum) : 0.f;
+    if (tok_c >= P.tpt || cb * P.tpt + tok_c >= n_tok) continue;
+    const float inv = 1.0f / l;
+    const int64_t qrow = (int64_t)row_cb[cb] * B.n_q + head * G + hg_c;
+    _Float16* const orow = B.out + qrow * HD + 4 * NE * j;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int h = 4 * j + r;  // accumulator row r of this lane is logit column h of block cb
-      const float L = __shfl(l, h, 64), M = __shfl(st.m[cb], h, 64), Z = __shfl(zc, h, 64);
-      const int row_h = __shfl(row_cb[cb], h, 64);
-      const int tok_h = h / G, hg_h = h - tok_h * G;
-      if (tok_h < P.tpt && cb * P.tpt + tok_h < n_tok) {
-        const float inv = 1.0f / L;
-        uint32_t wv[NE / 2];
+    for (int r = 0; r < 4; ++r) {  // row 4 j + r of the transposed accumulators e: element NE (4 j + r) + e of the column
+      uint32_t wv[NE / 2];
 #pragma unroll
-        for (int q = 0; q < NE / 2; ++q) {
-          float o[2];
+      for (int q = 0; q < NE / 2; ++q) {
+        float o[2];
 #pragma unroll
-          for (int z = 0; z < 2; ++z) {
-            const int e = 2 * q + z;
-            const float f = CDT == FS_KV_INT8 ? kTwo24 : (CDT == FS_KV_INT4 ? ((e & 1) ? kTwo20 : kTwo24) : 1.0f);
-            o[z] = st.acc[cb][e][r] * f;
-            if constexpr (Fmt<CDT>::kParBytes != 0) o[z] += Z;
-            o[z] *= v_static * inv;
-          }
-          const half2v hv = {(_Float16)o[0], (_Float16)o[1]};
-          wv[q] = h2u(hv);
+        for (int z = 0; z < 2; ++z) {
+          const int e = 2 * q + z;
+          const float f = CDT == FS_KV_INT8 ? kTwo24 : (CDT == FS_KV_INT4 ? ((e & 1) ? kTwo20 : kTwo24) : 1.0f);
+          o[z] = st.acc[cb][e][r] * f;
+          if constexpr (Fmt<CDT>::kParBytes != 0) o[z] += zc;
+          o[z] *= v_static * inv;
         }
-        const int64_t qrow = (int64_t)row_h * B.n_q + head * G + hg_h;
-        _Float16* orow = B.out + qrow * HD + NE * c;
-        if constexpr (NE == 4) {
-          *reinterpret_cast<u32x2*>(orow) = u32x2{wv[0], wv[1]};
-        } else {
+        const half2v hv = {(_Float16)o[0], (_Float16)o[1]};
+        wv[q] = h2u(hv);
+      }
+      if constexpr (NE == 4) {
+        reinterpret_cast<u32x2*>(orow)[r] = u32x2{wv[0], wv[1]};
+      } else {
 #pragma unroll
-          for (int q = 0; q < NE / 8; ++q)
-            reinterpret_cast<u32x4*>(orow)[q] = u32x4{wv[4 * q], wv[4 * q + 1], wv[4 * q + 2], wv[4 * q + 3]};
-        }
-        if (c == 0 && B.lse) B.lse[qrow] = (M + __builtin_amdgcn_logf(L)) * kLn2;
+        for (int q = 0; q < NE / 8; ++q)
+          reinterpret_cast<u32x4*>(orow)[NE / 8 * r + q] = u32x4{wv[4 * q], wv[4 * q + 1], wv[4 * q + 2], wv[4 * q + 3]};
       }
     }
+    if (j == 0 && B.lse) B.lse[qrow] = (st.m[cb] + __builtin_amdgcn_logf(l)) * kLn2;
   }
 #ifdef FS_TIMELINE
   if (threadIdx.x == 0 && blockIdx.x < kPfTimelineGroups) {
