@@ -41,7 +41,9 @@ struct PrefillArgs {
   int32_t n_rows;            // query rows in q / out (host value: every row index is clamped into it)
   int32_t tf_cache;          // workgroup kernels: 1 = tile_first is copied into LDS at kernel start, 2 = every workgroup
                              // scans (and sorts) the sequences itself (see scan_sequences)
-  int32_t whole_runs;        // 1 = tokens per block is a multiple of 8: run r starts at token 8 r, no run is shifted
+  int32_t whole_runs;        // 1 = tokens per block is a multiple of 8: no eight tokens from a multiple of 8 on cross a block
+  int32_t seg_tokens;        // workgroup kernels: tokens streamed per refill of the block-address table (multiple of 128)
+  uint32_t t_magic;          // workgroup kernels: for the division by the tokens per block (block_of, fs_prefill_index.h)
   int32_t chunk_shift;       // workgroup kernels: log2 of the consecutive work items that go to one XCD
   int32_t direct;            // workgroup kernels: 1 = no preparation ran and no tickets are drawn (see "Direct launches")
 #ifdef FS_TIMELINE
@@ -658,16 +660,15 @@ __device__ __forceinline__ void stage_k(uint8_t* stage, int sub, int lane, Tile<
   }
 }
 template <int DT, int SUBS, int HD>
-__device__ __forceinline__ void stage_v(uint8_t* stage, int sub, int lane, int j, Tile<DT, 16, HD>& t, const ItemCtx& X, int vb) {
+__device__ __forceinline__ void stage_v(uint8_t* stage, int sub, int lane, int live, Tile<DT, 16, HD>& t) {
   using F = Fmt<DT, HD>;
   if constexpr (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3) {
     // slots past the sequence's end may hold NaN/Inf bit patterns; 0 * NaN would poison the MFMA
-    const RunLoc L = locate(X, vb + j);
-    if (!__all(L.hi_u >= 8)) {
+    if (!__all(live >= 8)) {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int q = 0; q < F::kVWords; ++q) t.v[i][q] = i < L.hi_u ? t.v[i][q] : 0u;
+        for (int q = 0; q < F::kVWords; ++q) t.v[i][q] = i < live ? t.v[i][q] : 0u;
     }
   }
   uint32_t vx[8][F::kVRegs];
@@ -743,16 +744,93 @@ __device__ __forceinline__ void dequant8(const uint32_t* w, const Deq<DT>& q, ui
   }
 }
 
-// K parameters of the rows this lane stages: row c of half-tile u is slot 4u + (c & 3) of run c >> 2 (as issue_k)
-template <int DT>
-__device__ __forceinline__ void issue_kpar(const ItemCtx& X, const DevGeom& g, int vb, int c, uint32_t (&kpar)[2]) {
-  using F = Fmt<DT>;
-  const RunLoc L = locate(X, vb + (c >> 2));
-  const gptr p = L.base + 2u * g.kv_tile + (uint32_t)((L.start + (c & 3)) * F::kParBytes);
+// ---- Token-addressed fetch of the workgroup kernels --------------------------------------------------------------------
+// A sub-tile is 32 consecutive tokens of the sequence, wherever its blocks end: blocks of 60 or 31 tokens cost no repeated
+// slots, no masks for them and no look-up of a run's place in every wave that multiplies the sub-tile (the wave-level kernels
+// walk runs of eight slots that never cross a block).  The fetching lane pays: a row of K has its own block, and the eight
+// rows of V may come from two.  Rows past the segment's last token are that token's again where blocks are no multiple of
+// eight tokens; otherwise eight slots are always inside a block, and those past the end are cleared when they are staged.
+// (us: 32 INT4 prompts of 512 - 4096 tokens in blocks of 60, GQA 4:1, 2273 -> 1946; 12 multi-head ones of 300 - 3000 in blocks
+// of 46 720 -> 599; FP8 ones in blocks of 25 804 -> 542; 8 INT8 prompts of 2000 - 6000, GQA 8:1, blocks of 31, 2933 -> 2577;
+// blocks of 16 or 32 tokens the same within 1 %.)
+struct TokenCtx {
+  const uint64_t* ptr;  // LDS: addresses of the blocks' layers from the segment's first block on
+  uint64_t base_off;    // of the KV head
+  int rel0;             // the segment's first token within its first block
+  int last;             // the segment's last token, counted from its first one
+  int T;
+  uint32_t magic;
+};
+struct TokenPlace {
+  gptr base;  // the head's chunk in the token's block
+  int k, slot;
+};
+__device__ __forceinline__ TokenPlace place_token(const TokenCtx& X, int t) {
+  TokenPlace p;
+  const int rel = X.rel0 + t;
+  p.k = block_of(rel, X.T, X.magic);
+  p.slot = rel - p.k * X.T;
+  p.base = (gptr)(X.ptr[p.k] + X.base_off);
+  return p;
+}
+
+// K rows of the sub-tile from token tb of the segment on: row c of half-tile u is token 8 (c / 4) + 4 u + c % 4.
+// kpar (DEQ): their parameters
+template <int DT, int HD, bool DEQ>
+__device__ __forceinline__ void fetch_k(const TokenCtx& X, const DevGeom& g, bool whole, int tb, int j, int c, Tile<DT, 16, HD>& t,
+                                        uint32_t (&kpar)[2]) {
+  using F = Fmt<DT, HD>;
+  typedef typename KVec<F::kKLane>::type kvec;
+  auto row = [&](const TokenPlace& p, int u) {
+    const gptr at = p.base + (uint32_t)(p.slot * F::kRowBytes) + F::kKLane * j;
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    if constexpr (F::kParBytes == 2) kpar[u] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(p + u * 4 * F::kParBytes);
-    else kpar[u] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(p + u * 4 * F::kParBytes);
+    for (int s = 0; s < F::kKLoads; ++s) t.k[u][s] = *reinterpret_cast<const FS_GLOBAL kvec*>(at + 4 * F::kKLane * s);
+    if constexpr (DEQ) {
+      const gptr pp = p.base + 2u * g.kv_tile + (uint32_t)(p.slot * F::kParBytes);
+      if constexpr (F::kParBytes == 2) kpar[u] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(pp);
+      else kpar[u] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(pp);
+    }
+  };
+  const int run = tb + 8 * (c >> 2);
+  if (whole) {  // (uniform)
+    TokenPlace p = place_token(X, min(run, X.last & ~7));
+    p.slot += c & 3;
+    row(p, 0);
+    p.slot += 4;
+    row(p, 1);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) row(place_token(X, min(run + 4 * u + (c & 3), X.last)), u);
+  }
+}
+
+// V rows of the sub-tile: lane j takes tokens 8 j .. 8 j + 7; and its parameters: lane c those of token c % 8, K for c < 8
+// (DEQ: not used), V for the others.
+template <int DT, int HD>
+__device__ __forceinline__ void fetch_v(const TokenCtx& X, const DevGeom& g, bool whole, int tb, int j, int c, Tile<DT, 16, HD>& t) {
+  using F = Fmt<DT, HD>;
+  const int run = tb + 8 * j;
+  const RunRows R = run_rows(X.rel0, X.last, X.T, X.magic, run, whole);
+  const TokenPlace p{(gptr)(X.ptr[R.k] + X.base_off), R.k, R.slot};
+  if constexpr (F::kParBytes != 0) {  // parameters first: they are needed before the rows
+    TokenPlace o = p;
+    if (whole) o.slot += c & 7;
+    else o = place_token(X, min(run + (c & 7), X.last));
+    const gptr pp = o.base + 2u * g.kv_tile + ((c >> 3) ? g.par_tile : 0u) + (uint32_t)(o.slot * F::kParBytes);
+    if constexpr (F::kParBytes == 2) t.par[0] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(pp);
+    else t.par[0] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(pp);
+  }
+  const gptr p0 = p.base + g.kv_tile + (uint32_t)(p.slot * F::kRowBytes) + c * F::kVBytes;
+  if (whole || __all(R.left >= 8 && R.most >= 7)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) load_v_row<DT, HD>(p0 + i * F::kRowBytes, t.v[i]);
+  } else {
+    const gptr p1 = (gptr)(X.ptr[R.k1] + X.base_off) + g.kv_tile + c * F::kVBytes - (uint32_t)(R.left * F::kRowBytes);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = min(i, R.most);
+      load_v_row<DT, HD>((r < R.left ? p0 : p1) + (uint32_t)(r * F::kRowBytes), t.v[i]);
+    }
   }
 }
 
@@ -781,7 +859,7 @@ __device__ __forceinline__ void stage_k_deq(uint8_t* stage, int sub, int lane, T
 }
 
 template <int DT, int SUBS>
-__device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, int j, Tile<DT, 16>& t, const ItemCtx& X, int vb) {
+__device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, int live, Tile<DT, 16>& t) {
   uint32_t vx[8][4];
   static_for(std::make_integer_sequence<int, 8>{}, [&](auto I) {
     constexpr int i = decltype(I)::value;
@@ -792,12 +870,11 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
   });
   // slots past the sequence's end may hold any codes and parameters (NaN / Inf after the conversion); 0 * NaN
   // would poison the MFMA
-  const RunLoc L = locate(X, vb + j);
-  if (!__all(L.hi_u >= 8)) {
+  if (!__all(live >= 8)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) vx[i][q] = i < L.hi_u ? vx[i][q] : 0u;
+      for (int q = 0; q < 4; ++q) vx[i][q] = i < live ? vx[i][q] : 0u;
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -830,6 +907,9 @@ __device__ __forceinline__ float over_column(float x, Op op) {
 // head_dim 64 625 -> 576; one of 777 tokens 27.7 -> 26.2.  A wider window than 2^kTau saves another 1 - 3 %, but the largest
 // weights of a row are then no longer near 1, where fp16 holds them exactly, and the results are 6 - 14 % further from
 // the definition.  Weights first and a check on their sum in the place of the maxima: slower wherever references move.)
+// A little less than kTau: with it, blocks that move alone left results 0.5 % further from the definition than blocks that
+// moved together (1 % of the time).
+constexpr float kTauBlock = 2.5f;
 template <int DT, int NCB, int HD>
 __device__ __forceinline__ void wg_move_reference(WideState<NCB, HD>& st, int cb, float tmax) {
   const float m_new = fmaxf(st.m[cb], over_column(tmax, [](float a, float b) { return fmaxf(a, b); }));
@@ -851,10 +931,9 @@ __device__ __forceinline__ void wg_move_reference(WideState<NCB, HD>& st, int cb
 // value above 65504 is one in FP16) would turn weight 0 into NaN, in rows up to a sub-tile ahead of its token.  A tile code of
 // its own for the sub-tiles on the diagonal: as a branch in the common one it cost a prompt of 777 tokens 27.4 -> 31.4 us.
 template <int DT, int NCB, int SUBS, int VPRE, int HD, bool SUM32, bool CUT = false>
-__device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const ItemCtx& X, const u32x4 (&qb)[NCB][HD / 32],
+__device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, int len_u, const u32x4 (&qb)[NCB][HD / 32],
                                         const float (&qsum)[NCB], const int (&len_cb)[NCB], float alpha, int first_pos,
-                                        int vb, int lane, int j, int c, WideState<NCB, HD>& st, bool whole_runs = false,
-                                        int tpt = 0, int n_tok = 0) {
+                                        int lane, int j, int c, WideState<NCB, HD>& st, int tpt = 0, int n_tok = 0) {
   using F = Fmt<DT, HD>;
   constexpr int KS = HD / 32;
   float4v s[NCB][2];
@@ -882,18 +961,9 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
 #pragma unroll
   for (int e = 0; e < VPRE; ++e)
     vpre[e] = *reinterpret_cast<const u32x4*>(stage + stage_v(SUBS, HD) + (uint32_t)((sub * F::kNE + e) * kFrag) + lane * 16);
-  // interior (wave-uniform): every token of the sub-tile lies at or before the wave's first query token and no run
-  // is a shifted one -- nothing to mask.  With whole runs per block the test is scalar arithmetic and the run's
-  // location is needed on the mask path only.
-  RunLoc L;
-  bool interior;
-  if (!CUT && F::kParBytes == 0 && whole_runs) {
-    interior = vb + 4 <= X.v_end && 8 * (vb + 4) <= first_pos + 1;
-    if (!interior) L = locate(X, vb + j);
-  } else {
-    L = locate(X, vb + j);
-    interior = __all(L.lo == 0 && L.tok0 + 8 <= first_pos + 1);
-  }
+  // interior (uniform): every token of the sub-tile lies at or before the wave's first query token: nothing to mask
+  const bool interior = tb + 32 <= first_pos + 1;
+  const int tok0 = tb + 8 * j;  // the lane's first token
   float ka[8], kb[8], va[8], vb2[8];
   if constexpr (F::kParBytes != 0) {
     const uint32_t par = *reinterpret_cast<const uint32_t*>(stage + stage_par(SUBS, HD) + sub * 256 + lane * 4);
@@ -904,7 +974,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
       pa = alpha * kTwo24 * sc;
       pb = -alpha * sc * zp;
     } else {      // V: p' = p * sc, zero-point term -p * sc * zp
-      const bool ok = (c & 7) >= L.lo && (c & 7) < L.hi_u;  // a slot past the sequence may hold any bit pattern
+      const bool ok = (c & 7) < len_u - tok0;  // a slot past the sequence may hold any bit pattern
       pa = ok ? sc : 0.f;
       pb = ok ? -sc * zp : 0.f;
     }
@@ -926,22 +996,11 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
       else x[cb][i] = v;
     }
   if (!interior) {
-    // Blocks whose token count is no multiple of 8 end in a shifted run, whose first slots repeat tokens of the run
-    // before: with 38 or 60 tokens per block most sub-tiles hold one.  Where every slot is a token that every
-    // column sees, those repeats are all there is to mask.
-    if (__all(L.tok0 + 8 <= first_pos + 1)) {
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb)
+    for (int cb = 0; cb < NCB; ++cb) {
+      const int hi = len_cb[cb] - tok0;  // causality: this lane's column sees tokens < len_cb
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[cb][i] = i >= L.lo ? x[cb][i] : -INFINITY;
-    } else {
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        const int hi = min(L.hi_u, len_cb[cb] - L.tok0);  // causality: this lane's column sees tokens < len_cb
-        const uint32_t n_ok = (uint32_t)max(hi - L.lo, 0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[cb][i] = (uint32_t)(i - L.lo) < n_ok ? x[cb][i] : -INFINITY;
-      }
+      for (int i = 0; i < 8; ++i) x[cb][i] = i < hi ? x[cb][i] : -INFINITY;
     }
   }
 #pragma unroll
@@ -951,7 +1010,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
     mx = fmaxf(fmaxf(mx, x[cb][5]), x[cb][6]);
     mx = fmaxf(mx, x[cb][7]);
     if constexpr (F::kParBytes == 0) mx *= alpha;
-    if (__any(mx - st.m[cb] > kTau)) wg_move_reference<DT>(st, cb, mx);
+    if (__any(mx - st.m[cb] > kTauBlock)) wg_move_reference<DT>(st, cb, mx);
   }
   u32x4 pk[NCB];
 #pragma unroll
@@ -997,7 +1056,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, const Ite
     for (int cb = 0; cb < NCB; ++cb) {
       u32x4 seen = b;
       if constexpr (CUT) {
-        int n = first_pos + min((cb + 1) * tpt, n_tok) - L.tok0;  // slots of this lane's run that the block sees
+        int n = first_pos + min((cb + 1) * tpt, n_tok) - tok0;  // slots of this lane's run that the block sees
         if constexpr (NCB * HD > 128) asm volatile("" : "+v"(n));  // (masks made anew for each fragment: no registers to keep them in)
 #pragma unroll
         for (int q = 0; q < 4; ++q) seen[q] &= (2 * q < n ? 0xFFFFu : 0u) | (2 * q + 1 < n ? 0xFFFF0000u : 0u);
@@ -1043,7 +1102,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   // V fragments read ahead of the softmax: what the format's register budget leaves room for (two waves per SIMD)
   // (eight instead of four: a 4 x 512-token FP8 chunk step 429.5 -> 423 us, INT8 prompts 817 -> 811 us; FP16 would spill)
   constexpr int kVPre = NW != 8 ? 0 : (HD == kD && (DEQ || DT == FS_KV_FP8_E4M3) ? 8 : 4);
-  const bool whole_runs = P.whole_runs != 0;  // (uniform)
+  const bool whole = P.whole_runs != 0;  // (uniform)
   const bool does_k = NW == SUBS || w < SUBS, does_v = NW == SUBS || w >= SUBS;  // wave-uniform staging roles
   const int sw = w % SUBS;                                                       // the sub-tile this wave stages
   const DevBatch& B = P.b;
@@ -1064,14 +1123,12 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   const int first_pos = len - n_new + r0;
   const int tok_c = c / G, hg_c = c - tok_c * G;
 
-  ItemCtx X;  // of the workgroup: everything its last query token sees
-  X.T = g.T;
-  X.R = B.R;
-  X.r_magic = B.r_magic;
-  X.len_u = len - n_new + r0_wg + n_tok_wg;
-  X.len = X.len_u;
-  X.chunk_ptr = s_tab;
+  const int len_u = len - n_new + r0_wg + n_tok_wg;  // tokens that the workgroup's last query sees
+  TokenCtx X;
+  X.ptr = s_tab;
   X.base_off = (uint64_t)head * g.head_chunk;
+  X.T = g.T;
+  X.magic = P.t_magic;
 
   u32x4 qb[NCB][HD / 32];
   float qsum[NCB];
@@ -1083,7 +1140,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   for (int cb = 0; cb < NCB; ++cb) {
     const int tok = cb * P.tpt + tok_c;  // query token of this lane's column in block cb
     const bool live = tok_c < P.tpt && tok < n_tok;
-    len_cb[cb] = live ? first_pos + tok + 1 : X.len_u;  // a dead column (q = 0, never written) sees everything
+    len_cb[cb] = live ? first_pos + tok + 1 : len_u;  // a dead column (q = 0, never written) sees everything
     row_cb[cb] = min(max(shape.q0 + r0 + tok, 0), P.n_rows - 1);
     load_q<DT, !DEQ, HD>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * HD, live, j, qb[cb], qsum[cb]);
     if constexpr (Fmt<CDT>::kParBytes != 0) {
@@ -1098,50 +1155,46 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   }
 
   const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
-  const int w_end = n_tok > 0 ? n_runs(first_pos + n_tok, g.T, B.R) : 0;  // runs this wave's last query sees
+  const int w_end = n_tok > 0 ? first_pos + n_tok : 0;  // tokens this wave's last query sees
   constexpr bool kCut = SUM32 && DT == FS_KV_FP16;  // (see wg_tile)
-  const int w_seen = kCut ? n_runs(first_pos + 1, g.T, B.R) - 1 : 0;
-  const int n_run = n_runs(X.len_u, g.T, B.R);
-  for (int v0 = 0; v0 < n_run; v0 += P.seg_runs) {
-    X.v_end = min(n_run, v0 + P.seg_runs);
-    X.k0 = div_runs(v0, B.R, B.r_magic);
+  for (int t0 = 0; t0 < len_u; t0 += P.seg_tokens) {  // (t0, and what is counted from it: multiples of 32)
+    const int n = min(len_u - t0, P.seg_tokens), k0 = t0 / g.T;
+    X.rel0 = t0 - k0 * g.T;
+    X.last = n - 1;
     if (!S.table) {  // (uniform)
       // the previous segment's (or item's) last barrier lies behind every use of the old table
-      const int all = n_runs(len, g.T, B.R);
-      S.table = all <= P.seg_runs;  // one segment (v0 = 0): all of the sequence's blocks, for its next items
-      const int nb = div_runs((S.table ? all : X.v_end) - 1, B.R, B.r_magic) - X.k0 + 1;
+      S.table = len <= P.seg_tokens;  // one segment (t0 = 0): all of the sequence's blocks, for its next items
+      const int nb = (X.rel0 + (S.table ? len : n) - 1) / g.T + 1;
       for (int i = threadIdx.x; i < nb; i += NW * 64)
-        s_tab[i] = reinterpret_cast<uint64_t>(B.layer_base + (uint64_t)checked_block(table[X.k0 + i], B.n_blocks, header) * g.block_budget);
+        s_tab[i] = reinterpret_cast<uint64_t>(B.layer_base + (uint64_t)checked_block(table[k0 + i], B.n_blocks, header) * g.block_budget);
       __syncthreads();
     }
 #ifdef FS_TIMELINE
-    if (v0 == 0) tl_ph[1] = wall_clock64();
+    if (t0 == 0) tl_ph[1] = wall_clock64();
 #endif
-    const int n_super = (X.v_end - v0 + 4 * SUBS - 1) / (4 * SUBS);
+    const int n_super = (n + 32 * SUBS - 1) / (32 * SUBS);
     Tile<DT, 16, HD> t;
     uint32_t kpar[2] = {0u, 0u};  // (DEQ) K parameters of the rows this lane stages
-    // fetch / stage this wave's share of the sub-tile that starts at run vb
-    auto fetch = [&](int vb) {
-      if (does_k) {
-        issue_k<DT, 16, HD>(X, vb, j, c, t);
-        if constexpr (DEQ) issue_kpar<DT>(X, g, vb, c, kpar);
-      }
-      if (does_v) issue_v<DT, 16, HD>(X, g, vb, j, c, t);
+    // fetch / stage this wave's share of the sub-tile that starts at token tb of the segment
+    auto fetch = [&](int tb) {
+      if (does_k) fetch_k<DT, HD, DEQ>(X, g, whole, tb, j, c, t, kpar);
+      if (does_v) fetch_v<DT, HD>(X, g, whole, tb, j, c, t);
     };
-    auto stage_to = [&](uint8_t* stage, int vb) {
+    auto stage_to = [&](uint8_t* stage, int tb) {
+      const int live = whole ? n - (tb + 8 * j) : 8;  // (the other rows past the end are live ones again)
       if constexpr (DEQ) {
         if (does_k) stage_k_deq<DT>(stage, sw, lane, t, kpar);
-        if (does_v) stage_v_deq<DT, SUBS>(stage, sw, lane, j, t, X, vb);
+        if (does_v) stage_v_deq<DT, SUBS>(stage, sw, lane, live, t);
       } else {
         if (does_k) stage_k<DT, HD>(stage, sw, lane, t);
-        if (does_v) stage_v<DT, SUBS, HD>(stage, sw, lane, j, t, X, vb);
+        if (does_v) stage_v<DT, SUBS, HD>(stage, sw, lane, live, t);
       }
     };
-    fetch(v0 + 4 * sw);
-    stage_to(smem, v0 + 4 * sw);
+    fetch(32 * sw);
+    stage_to(smem, 32 * sw);
     __syncthreads();
 #ifdef FS_TIMELINE
-    if (v0 == 0) tl_ph[2] = wall_clock64();
+    if (t0 == 0) tl_ph[2] = wall_clock64();
 #endif
     // the query operands' loads, issued before the table and the first K/V fetch, are collected here
 #pragma unroll
@@ -1149,30 +1202,30 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
     for (int i = 0; i < n_super; ++i) {
       // next step's sub-tile of this wave; the segment's last step fetches and stages nothing (the wait in stage_to
       // is for this step's fetch alone, so the condition costs the compiler's wait counts nothing)
-      const int vb_next = v0 + (i + 1) * 4 * SUBS + 4 * sw;
+      const int tb_next = 32 * ((i + 1) * SUBS + sw);
       const bool more = i + 1 < n_super;  // wave-uniform
-      if (more) fetch(vb_next);
+      if (more) fetch(tb_next);
       const uint8_t* stage = smem + (uint32_t)(i & 1) * stage_bytes(SUBS, HD);
       // A wave multiplies the sub-tiles that hold a token one of its queries sees: those past its diagonal (half of
       // the last step or two of an item, and all of them in a wave without query tokens: a ragged last item of a chunk,
       // chunks shorter than the workgroup's 16 NW / G tokens) are left out.  A loop bound, not a branch around the
       // tile: it costs the accumulators' registers nothing.  (64 FP16 prompts of 512 - 4096 tokens, GQA 4:1: 4126 ->
       // 3977 us; 12 INT4 multi-head prompts of 300 - 3000 tokens, whose items span two steps of diagonal: 840 -> 800 us.)
-      const int n_live = min(SUBS, (w_end - (v0 + i * SUBS * 4) + 3) >> 2);
-      // (runs in front of the one that holds the first query's own token are seen by all of the wave's columns)
-      const int n_seen = kCut ? min(n_live, max(w_seen - (v0 + i * SUBS * 4), 0) >> 2) : n_live;
+      const int ts = t0 + 32 * SUBS * i;  // the step's first token
+      const int n_live = min(SUBS, (w_end - ts + 31) >> 5);
+      // (sub-tiles that end at or before the first query's own token are seen by all of the wave's columns)
+      const int n_seen = kCut ? min(n_live, max(first_pos + 1 - ts, 0) >> 5) : n_live;
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
       for (int sub = 0; sub < n_seen; ++sub)
-        wg_tile<CDT, NCB, SUBS, kVPre, HD, SUM32>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4, lane, j,
-                                                  c, st, whole_runs);
+        wg_tile<CDT, NCB, SUBS, kVPre, HD, SUM32>(stage, sub, ts + 32 * sub, len_u, qb, qsum, len_cb, alpha, first_pos, lane, j, c, st);
       if constexpr (kCut) {
 #pragma unroll 1
         for (int sub = n_seen; sub < n_live; ++sub)
-          wg_tile<CDT, NCB, SUBS, 0, HD, SUM32, true>(stage, sub, X, qb, qsum, len_cb, alpha, first_pos, v0 + (i * SUBS + sub) * 4,
-                                                          lane, j, c, st, whole_runs, P.tpt, n_tok);
+          wg_tile<CDT, NCB, SUBS, 0, HD, SUM32, true>(stage, sub, ts + 32 * sub, len_u, qb, qsum, len_cb, alpha, first_pos, lane, j, c,
+                                                      st, P.tpt, n_tok);
       }
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS, HD);
-      if (more) stage_to(next, vb_next);
+      if (more) stage_to(next, tb_next);
       __syncthreads();  // (also after the last step: the next staging overwrites what other waves may still read)
     }
   }
@@ -1385,7 +1438,7 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
     issue_k<DT, 16>(X, v0 + 4 * w, j, c, t);
     issue_v<DT, 16>(X, g, v0 + 4 * w, j, c, t);
     stage_k<DT, kD>(smem, w, lane, t);
-    stage_v<DT, SUBS, kD>(smem, w, lane, j, t, X, v0 + 4 * w);
+    stage_v<DT, SUBS, kD>(smem, w, lane, locate(X, v0 + 4 * w + j).hi_u, t);
     __syncthreads();
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) settle_q(qb[cb]);  // (issued before the table and the first K/V fetch)
@@ -1497,7 +1550,7 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
       }
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS);
       stage_k<DT, kD>(next, w, lane, t);
-      stage_v<DT, SUBS, kD>(next, w, lane, j, t, X, vb_next);
+      stage_v<DT, SUBS, kD>(next, w, lane, locate(X, vb_next + j).hi_u, t);
       __syncthreads();
     }
   }
@@ -1931,7 +1984,9 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   P.tpt = tpt;
   P.ncb = ncb;
   P.seg_runs = prefill_seg_runs(B.R);
-  P.table_entries = prefill_table_entries(P.seg_runs, B.R);
+  P.seg_tokens = prefill_seg_tokens(g.tokens_per_block);
+  P.t_magic = token_magic(g.tokens_per_block);
+  P.table_entries = std::max(prefill_table_entries(P.seg_runs, B.R), P.seg_tokens / g.tokens_per_block + 3);
   P.n_rows = (int32_t)n_rows;
   P.whole_runs = (g.tokens_per_block & 7) == 0;
   if (n_rows == 0) return FS_OK;

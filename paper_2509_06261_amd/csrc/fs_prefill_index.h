@@ -43,4 +43,36 @@ __device__ __host__ inline int32_t prefill_seg_runs(int R) {
 }
 __device__ __host__ inline int32_t prefill_table_entries(int seg_runs, int R) { return seg_runs / R + 4; }
 
+// ---- Token-addressed walk of the workgroup kernels: 32 consecutive tokens per sub-tile, wherever the blocks end ----
+// Tokens streamed per refill of the address table: whole steps of 128, about 500 blocks, at most 8192.  A segment begins
+// somewhere in its first block and touches at most seg / T + 2 blocks.
+__device__ __host__ inline int32_t prefill_seg_tokens(int T) {
+  const int64_t want = (int64_t)500 * T / 128 * 128;
+  return (int32_t)(want < 128 ? 128 : (want > 8192 ? 8192 : want));
+}
+// rel / T for 0 <= rel < T + 8192, rel counted from a block's start.  Below 2^15 tokens a block, ceil(2^32 / T) is off by less
+// than T / 2^32, and rel T < 2^32; above, a segment spans two blocks at most.
+__device__ __host__ inline uint32_t token_magic(int T) { return T >= 2 && T < (1 << 15) ? (uint32_t)(((1ull << 32) + (uint64_t)T - 1) / (uint64_t)T) : 0u; }
+__device__ __host__ inline int block_of(int rel, int T, uint32_t magic) {
+  return magic ? (int)(((uint64_t)(uint32_t)rel * magic) >> 32) : (rel >= T ? 1 : 0);
+}
+// The eight tokens from `run` (a multiple of 8) on of a segment that begins `rel0` tokens into its first block and ends with
+// token `last`: the first one is slot `slot` of block k (counted from the segment's first); token i is row r = min(i, most),
+// slot + r of block k where r < left, else r - left of block k1.  whole (T and so rel0 multiples of 8): eight slots of block k,
+// those past `last` not tokens of the segment; a run past the end is the last one again.
+struct RunRows {
+  int k, slot, left, most, k1;
+};
+__device__ __host__ inline RunRows run_rows(int rel0, int last, int T, uint32_t magic, int run, bool whole) {
+  const int end = whole ? last & ~7 : last, rel = rel0 + (run < end ? run : end);
+  RunRows r;
+  r.k = block_of(rel, T, magic);
+  r.slot = rel - r.k * T;
+  r.left = T - r.slot;
+  r.most = last - run > 0 ? last - run : 0;
+  const int kl = block_of(rel0 + last, T, magic);
+  r.k1 = r.k + 1 < kl ? r.k + 1 : kl;
+  return r;
+}
+
 }  // namespace fs

@@ -640,9 +640,48 @@ void direct_rule() {
   }
 }
 
+// The workgroup prefill kernels' walk by tokens: every row of every sub-tile of a context is its token's place, the last
+// token's past a segment's end, and no look-up leaves the segment's table.
+void prefill_token_walk(int rounds) {
+  for (int r = 0; r < rounds; ++r) {
+    const int kind = r % 4;
+    const int T = kind == 0 ? 8 + (int)(rnd() % 60) : kind == 1 ? 8 * (1 + (int)(rnd() % 40)) : kind == 2 ? 8 + (int)(rnd() % 9000)
+                                                                                    : (1 << 15) - 4 + (int)(rnd() % 9) + (int)(rnd() % 2) * 100000;
+    const bool whole = T % 8 == 0;
+    const uint32_t magic = fs::token_magic(T);
+    const int seg = fs::prefill_seg_tokens(T), entries = seg / T + 3;
+    CHECK(seg % 128 == 0);
+    const int len = 1 + (int)(rnd() % (kind == 3 ? 3 * T : 20000));
+    for (int t0 = 0; t0 < len; t0 += seg) {
+      const int n = std::min(len - t0, seg), k0 = t0 / T, rel0 = t0 - k0 * T, last = n - 1;
+      const int nb = (rel0 + n - 1) / T + 1;
+      CHECK(nb <= entries && rel0 + last < T + 8192);
+      for (int run = 0; run < (n + 127) / 128 * 128; run += 8) {
+        const fs::RunRows R = fs::run_rows(rel0, last, T, magic, run, whole);
+        CHECK(R.k >= 0 && R.k < nb && R.k1 >= 0 && R.k1 < nb && R.slot >= 0 && R.slot < T && (!whole || R.slot + 8 <= T));
+        for (int i = 0; i < 8; ++i) {
+          const int want = std::min(run + i, last);  // token of the segment
+          int block = R.k, slot = R.slot + i;
+          if (!whole) {
+            const int row = std::min(i, R.most);
+            block = row < R.left ? R.k : R.k1;
+            slot = row < R.left ? R.slot + row : row - R.left;
+          } else if (run + i > last) {
+            continue;  // (a slot inside the block whose value is masked)
+          }
+          CHECK(block == (rel0 + want) / T && slot == (rel0 + want) % T && (k0 + block) * (long)T + slot == t0 + want);
+          CHECK(fs::block_of(rel0 + want, T, magic) == (rel0 + want) / T);
+          ++g_tiles;
+        }
+      }
+    }
+  }
+}
+
 }  // namespace
 
 int main() {
+  prefill_token_walk(240);
   run(600);
   direct_order();
   direct_rule();

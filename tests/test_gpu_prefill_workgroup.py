@@ -161,6 +161,29 @@ def test_small_launches(dtype, head_dim, kv_heads, group):
         par.close()
 
 
+@pytest.mark.parametrize("dtype,T,head_dim,heads,group,large", [(FP16, 13, 128, 2, 4, 1), (FP8, 9, 128, 2, 1, 1), (INT8, 31, 128, 2, 4, 1),
+                                                                (INT4, 11, 128, 2, 4, 1), (INT4, 61, 128, 2, 1, 0), (INT8, 8, 128, 3, 4, 0),
+                                                                (FP8, 250, 64, 16, 4, 1), (INT4, 15, 64, 16, 4, 1), (FP16, 9, 256, 4, 4, 1)])
+def test_blocks_of_any_token_count(dtype, T, head_dim, heads, group, large, monkeypatch):
+    """Sub-tiles of 32 tokens over blocks that end anywhere: rows of eight tokens from two blocks, the last block's end."""
+    import gpu_harness
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    if large and head_dim == 128:
+        monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 16})
+    bits, par = {FP16: (16, 0), FP8: (8, 0), INT8: (8, 2), INT4: (4, 4)}[dtype]
+    slab = -(-T * 2 * heads * (head_dim * bits // 8 + par) // 256) * 256 + 256 * heads
+    wl = Workload("pftok", slab, slab * 600, [ModelSpec("m", dtype, heads, head_dim, 1, heads * group, EDGES, tag=48, src_f32=dtype == INT4)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[0]])
+        print("T", par.gw.T, par.prefill_and_check(0, 0, EDGES), par.prefill_and_check(0, 0, np.minimum(EDGES, CHUNKS)))
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) >> 8 & 255 in (4, 8) or head_dim == 256
+    finally:
+        par.close()
+
+
 def test_small_launch_reports_and_follows_no_bad_entry():
     """The status word of a launch without preparation: 0 for a good call whatever the workspace held, bit 0 for a length
     or chunk out of range, bit 2 for a block-table entry outside the pool -- inside a sequence with new tokens only."""
