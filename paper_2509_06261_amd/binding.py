@@ -123,6 +123,11 @@ def _load():
 
 
 _L = _load()
+try:
+    from . import _fsfast
+except ImportError as e:
+    raise ImportError("paper_2509_06261_amd/_fsfast.so is missing: build it with __graft_entry__.build() "
+                      "(python paper_2509_06261_amd/build.py); there is no fallback path") from e
 
 
 class FsError(RuntimeError):
@@ -146,6 +151,41 @@ def _stream(stream):
         import torch
         return torch.cuda.current_stream().cuda_stream
     return getattr(stream, "cuda_stream", stream)
+
+
+# Native marshaling of the device calls (csrc/fs_fastcall.c): takes a call whose arguments are the usual ones on torch's
+# current stream, and answers None for any other, which then goes through ctypes as below.  Filled in by the first call
+# after torch's CUDA side is up (before that the current stream is not known); a forked child starts without it.
+class _NotYet:
+    @staticmethod
+    def _none(*args):
+        return None
+
+    kv_append = kv_append_multi = decode_attention = decode_attention_multi = decode_step_multi = _none
+
+
+_fast = _NotYet
+
+
+def _slow():
+    """What a call that the native marshaling did not take begins with: tries to bring it up for the next ones."""
+    global _fast
+    if _fast is _NotYet:
+        import torch
+        if torch.cuda.is_initialized():
+            at = [ctypes.cast(getattr(_L, f), ctypes.c_void_p).value for f in
+                  ("fs_kv_append", "fs_kv_append_multi", "fs_decode_attention", "fs_decode_attention_multi", "fs_decode_step_multi")]
+            _fsfast.init(torch.Tensor, torch.float16, torch.float32, torch.int32, ctypes.c_void_p, fs_batch_t, fs_append_t,
+                         torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, *at)
+            _fast = _fsfast
+
+
+def _after_fork():
+    global _fast
+    _fast = _NotYet
+
+
+os.register_at_fork(after_in_child=_after_fork)
 
 
 def fs_last_error() -> str:
@@ -280,13 +320,16 @@ def fs_model_dump_live(pool, model) -> np.ndarray:
 def fs_kv_append(pool, model, layer, k_new, v_new, seq_idx, pos, block_tables, stream=None):
     """k_new/v_new: CUDA fp16 or fp32 [n_tokens][H][D]; seq_idx/pos: CUDA int32 [n_tokens];
     block_tables: CUDA int32 [n_seq][max_blocks]."""
-    import torch
-    assert k_new.dtype == v_new.dtype and k_new.dtype in (torch.float16, torch.float32)
-    assert k_new.is_contiguous() and v_new.is_contiguous() and block_tables.is_contiguous()
-    assert seq_idx.dtype == torch.int32 and pos.dtype == torch.int32 and block_tables.dtype == torch.int32
-    rc = _L.fs_kv_append(pool, model, layer, _dp(k_new), _dp(v_new),
-                         FS_SRC_FP32 if k_new.dtype == torch.float32 else FS_SRC_FP16, _dp(seq_idx), _dp(pos),
-                         _dp(block_tables), block_tables.shape[1], seq_idx.numel(), _stream(stream))
+    rc = _fast.kv_append(pool, model, layer, k_new, v_new, seq_idx, pos, block_tables, stream)
+    if rc is None:
+        import torch
+        _slow()
+        assert k_new.dtype == v_new.dtype and k_new.dtype in (torch.float16, torch.float32)
+        assert k_new.is_contiguous() and v_new.is_contiguous() and block_tables.is_contiguous()
+        assert seq_idx.dtype == torch.int32 and pos.dtype == torch.int32 and block_tables.dtype == torch.int32
+        rc = _L.fs_kv_append(pool, model, layer, _dp(k_new), _dp(v_new),
+                             FS_SRC_FP32 if k_new.dtype == torch.float32 else FS_SRC_FP16, _dp(seq_idx), _dp(pos),
+                             _dp(block_tables), block_tables.shape[1], seq_idx.numel(), _stream(stream))
     if rc != FS_OK:
         raise FsError(rc, "fs_kv_append")
 
@@ -307,17 +350,23 @@ def make_append(model, layer, k_new, v_new, seq_idx, pos, block_tables) -> fs_ap
 
 
 def fs_kv_append_multi(pool, appends, stream=None):
-    arr = (fs_append_t * len(appends))(*appends)
-    rc = _L.fs_kv_append_multi(pool, arr, len(appends), _stream(stream))
+    rc = _fast.kv_append_multi(pool, appends, stream)
+    if rc is None:
+        _slow()
+        arr = (fs_append_t * len(appends))(*appends)
+        rc = _L.fs_kv_append_multi(pool, arr, len(appends), _stream(stream))
     if rc != FS_OK:
         raise FsError(rc, "fs_kv_append_multi")
 
 
 def fs_decode_step_multi(pool, appends, batches, workspace, stream=None):
-    aarr = (fs_append_t * max(len(appends), 1))(*appends)
-    barr = (fs_batch_t * len(batches))(*batches)
-    rc = _L.fs_decode_step_multi(pool, aarr, len(appends), barr, len(batches), _dp(workspace),
-                                 workspace.numel() * workspace.element_size(), _stream(stream))
+    rc = _fast.decode_step_multi(pool, appends, batches, workspace, stream)
+    if rc is None:
+        _slow()
+        aarr = (fs_append_t * max(len(appends), 1))(*appends)
+        barr = (fs_batch_t * len(batches))(*batches)
+        rc = _L.fs_decode_step_multi(pool, aarr, len(appends), barr, len(batches), _dp(workspace),
+                                     workspace.numel() * workspace.element_size(), _stream(stream))
     if rc != FS_OK:
         raise FsError(rc, "fs_decode_step_multi")
 
@@ -346,17 +395,23 @@ def fs_decode_workspace_bytes(pool, batches) -> int:
 
 def fs_decode_attention(pool, model, layer, n_q_heads, sm_scale, q, block_tables, seq_lens, out, lse, workspace,
                         stream=None):
-    rc = _L.fs_decode_attention(pool, model, layer, n_q_heads, sm_scale, _dp(q), _dp(block_tables), _dp(seq_lens),
-                                seq_lens.numel(), block_tables.shape[1], _dp(out), _dp(lse), _dp(workspace),
-                                workspace.numel() * workspace.element_size(), _stream(stream))
+    rc = _fast.decode_attention(pool, model, layer, n_q_heads, sm_scale, q, block_tables, seq_lens, out, lse, workspace, stream)
+    if rc is None:
+        _slow()
+        rc = _L.fs_decode_attention(pool, model, layer, n_q_heads, sm_scale, _dp(q), _dp(block_tables), _dp(seq_lens),
+                                    seq_lens.numel(), block_tables.shape[1], _dp(out), _dp(lse), _dp(workspace),
+                                    workspace.numel() * workspace.element_size(), _stream(stream))
     if rc != FS_OK:
         raise FsError(rc, "fs_decode_attention")
 
 
 def fs_decode_attention_multi(pool, batches, workspace, stream=None):
-    arr = (fs_batch_t * len(batches))(*batches)
-    rc = _L.fs_decode_attention_multi(pool, arr, len(batches), _dp(workspace),
-                                      workspace.numel() * workspace.element_size(), _stream(stream))
+    rc = _fast.decode_attention_multi(pool, batches, workspace, stream)
+    if rc is None:
+        _slow()
+        arr = (fs_batch_t * len(batches))(*batches)
+        rc = _L.fs_decode_attention_multi(pool, arr, len(batches), _dp(workspace),
+                                          workspace.numel() * workspace.element_size(), _stream(stream))
     if rc != FS_OK:
         raise FsError(rc, "fs_decode_attention_multi")
 

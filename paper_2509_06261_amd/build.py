@@ -3,10 +3,12 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 _DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_DIR)
 LIB = os.path.join(_DIR, "libfineserve.so")
+FAST = os.path.join(_DIR, "_fsfast.so")
 SOURCES = ["fs_pool.hip", "fs_append.hip", "fs_attention.hip", "fs_attention_generic.hip", "fs_attention_mfma.hip",
            "fs_prefill.hip", "fs_sched.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -44,6 +46,12 @@ def build(verbose: bool = False, timeline: bool = False) -> str:
             raise RuntimeError(f"hipcc failed on {src}:\n{out}")
         if verbose and out.strip():
             print(out)
+    if not timeline:  # the binding's native marshaling: a CPython module, no device code
+        cc = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-Wextra", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+              "-I", os.path.join(ROOT, "include"), os.path.join(csrc, "fs_fastcall.c"), "-o", FAST]
+        if verbose:
+            print(" ".join(cc))
+        subprocess.run(cc, check=True)
     lib = TIMELINE_LIB if timeline else LIB
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-o", lib, *objs], check=True)
     return lib
