@@ -887,6 +887,90 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
   }
 }
 
+// ---- Staged integers (INT8 / INT4 where the codes stay exact) ---------------------------------------------------------
+// The staging wave leaves code - zero point in LDS, an integer that fp16 holds exactly (INT4's odd code positions 16-fold:
+// the query operand and the output take that out), and per token the two factors that remain, alpha times K's scale and V's
+// scale, as floats.  A consumer multiplies a logit by the one and a weight by the other; there is no zero-point term on
+// either side and nothing to broadcast between lanes (16 bytes of four tokens' factors per load).  With codes consumed as
+// subnormals, offsets as rank-1 terms and parameters broadcast by DPP a sub-tile of two blocks took 72 vector instructions
+// more.  (us, with the rest of this file as it is: FIXME)
+template <int DT>
+__device__ __forceinline__ void int_codes(uint32_t w, half2v off, half2v off16, uint32_t (&x)[4]) {
+  if constexpr (DT == FS_KV_INT8) {  // two registers: elements (0, 1), (2, 3)
+    const uint32_t u = w ^ 0x80808080u;  // code + 128, unsigned
+    x[0] = h2u(u2h(__builtin_amdgcn_perm(0x64646464u, u, 0x04010400u)) - off);  // 1024 + 128 + code
+    x[1] = h2u(u2h(__builtin_amdgcn_perm(0x64646464u, u, 0x04030402u)) - off);
+  } else {  // four: codes (p, p + 4), 16-fold in the odd ones
+    const uint32_t w8 = w >> 8;
+    x[0] = h2u(u2h((w & 0x000F000Fu) | 0x64006400u) - off);
+    x[1] = h2u(u2h((w & 0x00F000F0u) | 0x64006400u) - off16);
+    x[2] = h2u(u2h((w8 & 0x000F000Fu) | 0x64006400u) - off);
+    x[3] = h2u(u2h((w8 & 0x00F000F0u) | 0x64006400u) - off16);
+  }
+}
+
+template <int DT, int HD>
+__device__ __forceinline__ void stage_k_int(uint8_t* stage, int sub, int lane, Tile<DT, 16, HD>& t, const uint32_t (&kpar)[2]) {
+  constexpr int KS = HD / 32, W = Fmt<DT, HD>::kKLane / 4;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const Deq<DT> q(kpar[u]);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint32_t x[4];
+      if constexpr (DT == FS_KV_INT8) {
+        uint32_t y[4];
+        int_codes<DT>(t.k[u][ks >> 1][2 * (ks & 1)], q.off, q.off16, x);
+        int_codes<DT>(t.k[u][ks >> 1][2 * (ks & 1) + 1], q.off, q.off16, y);
+        x[2] = y[0];
+        x[3] = y[1];
+      } else {
+        int_codes<DT>(t.k[u][ks / W][ks % W], q.off, q.off16, x);
+      }
+      *reinterpret_cast<u32x4*>(stage + (uint32_t)(((sub * 2 + u) * KS + ks) * kFrag) + lane * 16) = u32x4{x[0], x[1], x[2], x[3]};
+    }
+  }
+}
+
+// live: as in stage_v (slots past the end may hold any codes and parameters)
+template <int DT, int SUBS, int HD>
+__device__ __forceinline__ void stage_v_int(uint8_t* stage, int sub, int lane, int live, float alpha, Tile<DT, 16, HD>& t) {
+  using F = Fmt<DT, HD>;
+  constexpr int kPer = DT == FS_KV_INT8 ? 2 : 4;  // registers a word unpacks to
+  uint32_t vx[8][kPer * F::kVWords];
+  static_for(std::make_integer_sequence<int, 8>{}, [&](auto I) {
+    constexpr int i = decltype(I)::value;
+    const Deq<DT> q(__builtin_amdgcn_update_dpp(0u, t.par[0], 0x150 + 8 + i, 0xF, 0xF, false));
+#pragma unroll
+    for (int w = 0; w < F::kVWords; ++w) {
+      uint32_t x[4];
+      int_codes<DT>(t.v[i][w], q.off, q.off16, x);
+#pragma unroll
+      for (int z = 0; z < kPer; ++z) vx[i][kPer * w + z] = x[z];
+    }
+  });
+  if (!__all(live >= 8)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int q = 0; q < kPer * F::kVWords; ++q) vx[i][q] = i < live ? vx[i][q] : 0u;
+  }
+#pragma unroll
+  for (int e = 0; e < F::kNE; ++e) {
+    const int reg = DT == FS_KV_INT4 ? 4 * (e >> 3) + (e & 3) : (e >> 1);
+    const uint32_t sel = (DT == FS_KV_INT4 ? ((e >> 2) & 1) : (e & 1)) ? 0x07060302u : 0x05040100u;
+    u32x4 b;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) b[q] = __builtin_amdgcn_perm(vx[2 * q + 1][reg], vx[2 * q][reg], sel);
+    *reinterpret_cast<u32x4*>(stage + stage_v(SUBS, HD) + (uint32_t)((sub * F::kNE + e) * kFrag) + lane * 16) = b;
+  }
+  // the factors of token 8 j + c % 8: [K 32][V 32] floats
+  const int j = lane >> 4, c = lane & 15;
+  const float sc = f16lo(t.par[0]);
+  const float f = c < 8 ? alpha * sc : ((c & 7) < live ? sc : 0.f);
+  *reinterpret_cast<float*>(stage + stage_par(SUBS, HD) + sub * 256 + (c >> 3) * 128 + (8 * j + (c & 7)) * 4) = f;
+}
+
 // Column c's value combined over the four lanes j that hold its tokens (every lane of the column gets the result).
 template <typename Op>
 __device__ __forceinline__ float over_column(float x, Op op) {
@@ -910,12 +994,11 @@ __device__ __forceinline__ float over_column(float x, Op op) {
 // A little less than kTau: with it, blocks that move alone left results 0.5 % further from the definition than blocks that
 // moved together (1 % of the time).
 constexpr float kTauBlock = 2.5f;
-template <int DT, int NCB, int HD>
+template <int NCB, int HD>
 __device__ __forceinline__ void wg_move_reference(WideState<NCB, HD>& st, int cb, float tmax) {
   const float m_new = fmaxf(st.m[cb], over_column(tmax, [](float a, float b) { return fmaxf(a, b); }));
   const float corr = __builtin_amdgcn_exp2f(st.m[cb] - m_new);
   st.l[cb] *= corr;
-  if constexpr (Fmt<DT>::kParBytes != 0) st.zc[cb] *= corr;
 #pragma unroll
   for (int e = 0; e < HD / 16; ++e)
 #pragma unroll
@@ -931,8 +1014,8 @@ __device__ __forceinline__ void wg_move_reference(WideState<NCB, HD>& st, int cb
 // value above 65504 is one in FP16) would turn weight 0 into NaN, in rows up to a sub-tile ahead of its token.  A tile code of
 // its own for the sub-tiles on the diagonal: as a branch in the common one it cost a prompt of 777 tokens 27.4 -> 31.4 us.
 template <int DT, int NCB, int SUBS, int VPRE, int HD, bool SUM32, bool CUT = false>
-__device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, int len_u, const u32x4 (&qb)[NCB][HD / 32],
-                                        const float (&qsum)[NCB], const int (&len_cb)[NCB], float alpha, int first_pos,
+__device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, const u32x4 (&qb)[NCB][HD / 32],
+                                        const int (&len_cb)[NCB], float alpha, int first_pos,
                                         int lane, int j, int c, WideState<NCB, HD>& st, int tpt = 0, int n_tok = 0) {
   using F = Fmt<DT, HD>;
   constexpr int KS = HD / 32;
@@ -964,27 +1047,18 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, i
   // interior (uniform): every token of the sub-tile lies at or before the wave's first query token: nothing to mask
   const bool interior = tb + 32 <= first_pos + 1;
   const int tok0 = tb + 8 * j;  // the lane's first token
-  float ka[8], kb[8], va[8], vb2[8];
+  float ka[8], va[8];  // (parameter formats) the factors of the lane's eight tokens
   if constexpr (F::kParBytes != 0) {
-    const uint32_t par = *reinterpret_cast<const uint32_t*>(stage + stage_par(SUBS, HD) + sub * 256 + lane * 4);
-    float pa, pb;
-    const float sc = f16lo(par);
-    const float zp = DT == FS_KV_INT4 ? f16hi(par) : 128.0f;
-    if (c < 8) {  // K: logit = alpha * sc * (2^24 * S_raw - zp * qsum)
-      pa = alpha * kTwo24 * sc;
-      pb = -alpha * sc * zp;
-    } else {      // V: p' = p * sc, zero-point term -p * sc * zp
-      const bool ok = (c & 7) < len_u - tok0;  // a slot past the sequence may hold any bit pattern
-      pa = ok ? sc : 0.f;
-      pb = ok ? -sc * zp : 0.f;
+    const uint8_t* const par = stage + stage_par(SUBS, HD) + sub * 256 + 32 * j;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float4v k4 = *reinterpret_cast<const float4v*>(par + 16 * h), v4 = *reinterpret_cast<const float4v*>(par + 128 + 16 * h);
+#pragma unroll
+      for (int z = 0; z < 4; ++z) {
+        ka[4 * h + z] = k4[z];
+        va[4 * h + z] = v4[z];
+      }
     }
-    static_for(std::make_integer_sequence<int, 8>{}, [&](auto I) {
-      constexpr int i = decltype(I)::value;
-      ka[i] = row_bcast<i>(pa);
-      kb[i] = row_bcast<i>(pb);
-      va[i] = row_bcast<8 + i>(pa);
-      vb2[i] = row_bcast<8 + i>(pb);
-    });
   }
   float x[NCB][8];
 #pragma unroll
@@ -992,7 +1066,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, i
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const float v = s[cb][i >> 2][i & 3];
-      if constexpr (F::kParBytes != 0) x[cb][i] = fmaf(v, ka[i], kb[i] * qsum[cb]);
+      if constexpr (F::kParBytes != 0) x[cb][i] = v * ka[i];
       else x[cb][i] = v;
     }
   if (!interior) {
@@ -1010,7 +1084,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, i
     mx = fmaxf(fmaxf(mx, x[cb][5]), x[cb][6]);
     mx = fmaxf(mx, x[cb][7]);
     if constexpr (F::kParBytes == 0) mx *= alpha;
-    if (__any(mx - st.m[cb] > kTauBlock)) wg_move_reference<DT>(st, cb, mx);
+    if (__any(mx - st.m[cb] > kTauBlock)) wg_move_reference(st, cb, mx);
   }
   u32x4 pk[NCB];
 #pragma unroll
@@ -1023,7 +1097,6 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, i
         const float e = __builtin_amdgcn_exp2f(x[cb][i] - m);
         lsum += e;
         p[i] = e * va[i];
-        st.zc[cb] = fmaf(e, vb2[i], st.zc[cb]);
       }
       st.l[cb] += lsum;
 #pragma unroll
@@ -1131,7 +1204,6 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   X.magic = P.t_magic;
 
   u32x4 qb[NCB][HD / 32];
-  float qsum[NCB];
   int len_cb[NCB], row_cb[NCB];
   float alpha = B.sm_scale * kLog2e;
   if (DT == FS_KV_FP8_E4M3) alpha *= B.k_scale[head];
@@ -1142,16 +1214,12 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
     const bool live = tok_c < P.tpt && tok < n_tok;
     len_cb[cb] = live ? first_pos + tok + 1 : len_u;  // a dead column (q = 0, never written) sees everything
     row_cb[cb] = min(max(shape.q0 + r0 + tok, 0), P.n_rows - 1);
-    load_q<DT, !DEQ, HD>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * HD, live, j, qb[cb], qsum[cb]);
-    if constexpr (Fmt<CDT>::kParBytes != 0) {
-      qsum[cb] += __shfl_xor(qsum[cb], 16, 64);
-      qsum[cb] += __shfl_xor(qsum[cb], 32, 64);
-    }
+    float unused;
+    load_q<DT, !DEQ, HD>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * HD, live, j, qb[cb], unused);
 #pragma unroll
     for (int e = 0; e < NE; ++e) st.acc[cb][e] = float4v{0.f, 0.f, 0.f, 0.f};
     st.m[cb] = kNoReference;  // (a masked logit then weighs 0 from the start; with -inf it would be NaN)
     st.l[cb] = 0.f;
-    st.zc[cb] = 0.f;
   }
 
   const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
@@ -1174,10 +1242,10 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
 #endif
     const int n_super = (n + 32 * SUBS - 1) / (32 * SUBS);
     Tile<DT, 16, HD> t;
-    uint32_t kpar[2] = {0u, 0u};  // (DEQ) K parameters of the rows this lane stages
+    uint32_t kpar[2] = {0u, 0u};  // (parameter formats) K parameters of the rows this lane stages
     // fetch / stage this wave's share of the sub-tile that starts at token tb of the segment
     auto fetch = [&](int tb) {
-      if (does_k) fetch_k<DT, HD, DEQ>(X, g, whole, tb, j, c, t, kpar);
+      if (does_k) fetch_k<DT, HD, Fmt<DT>::kParBytes != 0>(X, g, whole, tb, j, c, t, kpar);
       if (does_v) fetch_v<DT, HD>(X, g, whole, tb, j, c, t);
     };
     auto stage_to = [&](uint8_t* stage, int tb) {
@@ -1185,6 +1253,9 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       if constexpr (DEQ) {
         if (does_k) stage_k_deq<DT>(stage, sw, lane, t, kpar);
         if (does_v) stage_v_deq<DT, SUBS>(stage, sw, lane, live, t);
+      } else if constexpr (Fmt<DT>::kParBytes != 0) {
+        if (does_k) stage_k_int<DT, HD>(stage, sw, lane, t, kpar);
+        if (does_v) stage_v_int<DT, SUBS, HD>(stage, sw, lane, live, alpha, t);
       } else {
         if (does_k) stage_k<DT, HD>(stage, sw, lane, t);
         if (does_v) stage_v<DT, SUBS, HD>(stage, sw, lane, live, t);
@@ -1217,11 +1288,11 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       const int n_seen = kCut ? min(n_live, max(first_pos + 1 - ts, 0) >> 5) : n_live;
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
       for (int sub = 0; sub < n_seen; ++sub)
-        wg_tile<CDT, NCB, SUBS, kVPre, HD, SUM32>(stage, sub, ts + 32 * sub, len_u, qb, qsum, len_cb, alpha, first_pos, lane, j, c, st);
+        wg_tile<CDT, NCB, SUBS, kVPre, HD, SUM32>(stage, sub, ts + 32 * sub, qb, len_cb, alpha, first_pos, lane, j, c, st);
       if constexpr (kCut) {
 #pragma unroll 1
         for (int sub = n_seen; sub < n_live; ++sub)
-          wg_tile<CDT, NCB, SUBS, 0, HD, SUM32, true>(stage, sub, ts + 32 * sub, len_u, qb, qsum, len_cb, alpha, first_pos, lane, j, c,
+          wg_tile<CDT, NCB, SUBS, 0, HD, SUM32, true>(stage, sub, ts + 32 * sub, qb, len_cb, alpha, first_pos, lane, j, c,
                                                       st, P.tpt, n_tok);
       }
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS, HD);
@@ -1239,7 +1310,6 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   for (int cb = 0; cb < NCB; ++cb) {
     auto sum = [](float a, float b) { return a + b; };
     const float l = over_column(st.l[cb], sum);
-    const float zc = Fmt<CDT>::kParBytes != 0 ? over_column(st.zc[cb], sum) : 0.f;
     if (tok_c >= P.tpt || cb * P.tpt + tok_c >= n_tok) continue;
     const float inv = 1.0f / l;
     const int64_t qrow = (int64_t)row_cb[cb] * B.n_q + head * G + hg_c;
@@ -1253,10 +1323,8 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
 #pragma unroll
         for (int z = 0; z < 2; ++z) {
           const int e = 2 * q + z;
-          const float f = CDT == FS_KV_INT8 ? kTwo24 : (CDT == FS_KV_INT4 ? ((e & 1) ? kTwo20 : kTwo24) : 1.0f);
-          o[z] = st.acc[cb][e][r] * f;
-          if constexpr (Fmt<CDT>::kParBytes != 0) o[z] += zc;
-          o[z] *= v_static * inv;
+          const float f = CDT == FS_KV_INT4 && (e & 1) ? 0.0625f : 1.0f;  // (INT4's odd code positions are staged 16-fold)
+          o[z] = st.acc[cb][e][r] * (f * v_static * inv);
         }
         const half2v hv = {(_Float16)o[0], (_Float16)o[1]};
         wv[q] = h2u(hv);
