@@ -893,7 +893,8 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
 // scale, as floats.  A consumer multiplies a logit by the one and a weight by the other; there is no zero-point term on
 // either side and nothing to broadcast between lanes (16 bytes of four tokens' factors per load).  With codes consumed as
 // subnormals, offsets as rank-1 terms and parameters broadcast by DPP a sub-tile of two blocks took 72 vector instructions
-// more.  (us, with the rest of this file as it is: FIXME)
+// more.  (us: 24 INT8 prompts of 256 - 3000 tokens at head_dim 64, GQA 4:1, 869 -> 656, INT4 878 -> 683; three INT8 prompts
+// of 500 - 700 at 128 40.8 -> 34.2; and the results are as near the definition as FP16's, 2.4e-4 where they were 3.8 - 5e-4.)
 template <int DT>
 __device__ __forceinline__ void int_codes(uint32_t w, half2v off, half2v off16, uint32_t (&x)[4]) {
   if constexpr (DT == FS_KV_INT8) {  // two registers: elements (0, 1), (2, 3)
@@ -2000,6 +2001,18 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     ncb = 1;
     (void)count_tiles(ncb);
   }
+  // head_dim 64: items of 32 blocks (FP16) or 24 (the other formats, whose staging needs the registers), four or three per
+  // wave, where there are at least eight per compute unit and they are as full as those of 16: half or two thirds of the
+  // staging and of the operand reads per product, but 1.65 or 1.35 times an item.  us: 24 FP16 prompts of 256 - 3000 tokens,
+  // GQA 4:1, 571 -> 541, INT8 ones 655 -> 610; 6 FP16 prompts of 6000 - 12000 2900 -> 2636; but 9 of 300 - 2500 (3 items of 32
+  // blocks per unit) 189 -> 213, 64 chunks of 64 tokens (half-empty items) 132 -> 152.
+  if (d64 && ncb == 16 && !ncb_env) {
+    const uint64_t at16 = tiles;
+    const int wide = g.kv_dtype == FS_KV_FP16 ? 32 : 24;
+    (void)count_tiles(wide);
+    if (tiles * (uint64_t)g.n_kv_heads >= 8 * (uint64_t)p->n_cu && tiles * (uint64_t)wide <= at16 * 16 + at16 * 16 / 10) ncb = wide;
+    else tiles = at16;
+  }
   const int64_t n_rows = q_offsets_host[n_seq];
   if (tiles * (uint64_t)g.n_kv_heads > 0xfffffff0ull || n_rows > 0x7fffffff) {
     set_error("prefill attention: batch too large");
@@ -2061,7 +2074,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   hipStream_t s = (hipStream_t)stream;
   (void)hipGetLastError();
   const uint64_t items = tiles * (uint64_t)g.n_kv_heads;
-  const bool wg = ncb == 16 || ncb == kSmallBlocks || (d256 && ncb == kBlocks256);
+  const bool wg = ncb >= 16 || ncb == kSmallBlocks || (d256 && ncb == kBlocks256);
   // (FS_OPT_PREFILL_WAVES is about the launches that have a 16-block item per compute unit; a smaller launch by the
   // library's own choice keeps the integer codes exact and its sums over the unrounded weights, as the 16-column kernel that
   // served it before, and the 4-wave kernels are not built like that)
@@ -2133,14 +2146,15 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
 #undef FS_WG1
     } else if (d64) {
       // Integer codes enter the MFMAs exactly here, as in the 16-column kernel that served this head_dim before.
-      // (24 FP16 prompts of 256 - 3000 tokens, GQA 4:1: 1804 -> 646 us, 179 -> 498 TFLOP/s; with four column blocks
-      // per wave 647 us.)
+#define FS_WG64(DT, WIDE) \
+  (ncb == 16 ? prefill_wg_kernel<DT, 8, 2, 4, 1, false, false, 64, true> : prefill_wg_kernel<DT, 8, WIDE, 4, 1, false, false, 64, true>)
       switch (g.kv_dtype) {
-        case FS_KV_FP16: kern = prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, 64, true>; break;
-        case FS_KV_FP8_E4M3: kern = prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, 64, true>; break;
-        case FS_KV_INT8: kern = prefill_wg_kernel<FS_KV_INT8, 8, 2, 4, 1, false, false, 64, true>; break;
-        default: kern = prefill_wg_kernel<FS_KV_INT4, 8, 2, 4, 1, false, false, 64, true>; break;
+        case FS_KV_FP16: kern = FS_WG64(FS_KV_FP16, 4); break;
+        case FS_KV_FP8_E4M3: kern = FS_WG64(FS_KV_FP8_E4M3, 3); break;
+        case FS_KV_INT8: kern = FS_WG64(FS_KV_INT8, 3); break;
+        default: kern = FS_WG64(FS_KV_INT4, 3); break;
       }
+#undef FS_WG64
     } else switch (g.kv_dtype) {
       case FS_KV_FP16: kern = large ? FS_WG(FS_KV_FP16) : prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, kD, true>; break;
       case FS_KV_FP8_E4M3: kern = large ? FS_WG(FS_KV_FP8_E4M3) : prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, kD, true>; break;
@@ -2152,7 +2166,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return device_error(e, "prefill LDS attribute");
     const bool deq_used = deq && (g.kv_dtype == FS_KV_INT8 || g.kv_dtype == FS_KV_INT4);
-    p->opt.last_prefill = ncb | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
+    p->opt.last_prefill = std::min(ncb, 16) | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
     hipLaunchKernelGGL(kern, dim3(n_wg), dim3(nw * 64), smem, s, P);
   } else if (ncb == 1) {
     p->opt.last_prefill = 1;

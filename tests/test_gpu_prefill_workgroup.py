@@ -161,6 +161,21 @@ def test_small_launches(dtype, head_dim, kv_heads, group):
         par.close()
 
 
+@pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
+def test_large_launches_at_head_dim_64(dtype):
+    """Items of 32 and 24 blocks: at least eight of them per compute unit (256 in the card's whole partition)."""
+    import gpu_harness
+
+    lens = np.concatenate([np.full(40, 96), [97, 1, 95, 33, 130, 240, 385, 500]]).astype(np.int32)
+    wl = Workload("pf64w", 192 * KiB, 192 * 900 * KiB, [ModelSpec("m", dtype, 40, 64, 1, 640, lens, tag=49, src_f32=dtype == INT4)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[0]])
+        print("T", par.gw.T, par.prefill_and_check(0, 0, lens, seqs=np.array([0, 40, 41, 42, 43, 44, 45, 46, 47])))
+    finally:
+        par.close()
+
+
 @pytest.mark.parametrize("dtype,T,head_dim,heads,group,large", [(FP16, 13, 128, 2, 4, 1), (FP8, 9, 128, 2, 1, 1), (INT8, 31, 128, 2, 4, 1),
                                                                 (INT4, 11, 128, 2, 4, 1), (INT4, 61, 128, 2, 1, 0), (INT8, 8, 128, 3, 4, 0),
                                                                 (FP8, 250, 64, 16, 4, 1), (INT4, 15, 64, 16, 4, 1), (FP16, 9, 256, 4, 4, 1)])
