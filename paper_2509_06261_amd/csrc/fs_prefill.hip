@@ -45,6 +45,7 @@ struct PrefillArgs {
   int32_t seg_tokens;        // workgroup kernels: tokens streamed per refill of the block-address table (multiple of 128)
   uint32_t t_magic;          // workgroup kernels: for the division by the tokens per block (block_of, fs_prefill_index.h)
   int32_t chunk_shift;       // workgroup kernels: log2 of the consecutive work items that go to one XCD
+  int32_t kv_shift;          // workgroup kernels: log2 of the groups of waves that share an item's context (merge_groups)
   int32_t direct;            // workgroup kernels: 1 = no preparation ran and no tickets are drawn (see "Direct launches")
 #ifdef FS_TIMELINE
   uint64_t* timeline;        // (timeline build) clock readings of the workgroup kernels, at the end of the workspace
@@ -1152,6 +1153,86 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, c
 // head_dim 256: that one has a compute unit to itself (its two stages alone are 129 KiB of the 160), a wave has one column
 // block, and its staging roles, fragment offsets and barriers are those of the 8-wave kernels, NW == 2 SUBS, with half the
 // counts: fragment indices end at SUBS * HD / 16 on both sides, which is where stage_v and stage_par begin.)
+// An item whose context was dealt to 2^kv_shift groups of waves (sub-tile s to group s mod 2^kv_shift): the waves of a query
+// tile exchange their accumulators through LDS, where the stages were, and each finishes one part of them: with two groups a
+// column block, with four half of one's output elements.  Every wave of the workgroup takes part.
+template <int DT, int NW, int NCB, int HD>
+__device__ __forceinline__ void merge_groups(const PrefillArgs& P, WideState<NCB, HD>& st, uint8_t* smem, int w, int lane, int head,
+                                             int row0, int n_tok, float v_static) {
+  constexpr int NE = HD / 16, N = NCB * NE;  // accumulator tiles of a wave
+  static_assert(NW * (N * 1024 + NCB * 128) <= 2 * (int)stage_bytes(NW == 8 ? 4 : 2, HD), "the partial sums fit the stages");
+  const DevBatch& B = P.b;
+  const int j = lane >> 4, c = lane & 15;
+  const int n_kv = 1 << P.kv_shift, n_q = NW >> P.kv_shift, size = N >> P.kv_shift;
+  const int qg = w & (n_q - 1), kv = w / n_q;
+  float4v* const s_acc = reinterpret_cast<float4v*>(smem);                       // [wave][tile][lane]
+  float2* const s_ml = reinterpret_cast<float2*>(smem + NW * N * 1024);          // [wave][block][column]
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) {
+    st.l[cb] = over_column(st.l[cb], [](float a, float b) { return a + b; });
+    if (j == 0) s_ml[(w * NCB + cb) * 16 + c] = float2{st.m[cb], st.l[cb]};
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i / size != kv) s_acc[(w * N + i) * 64 + lane] = st.acc[i / NE][i % NE];
+  __syncthreads();
+  const int tok_c = c / B.G, hg_c = c - tok_c * B.G;
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) {
+    if ((cb * NE + NE - 1) / size < kv || cb * NE / size > kv) continue;  // (uniform) none of this block's tiles are this wave's
+    float M = st.m[cb];
+    for (int g = 0; g < n_kv; ++g) M = fmaxf(M, s_ml[((g * n_q + qg) * NCB + cb) * 16 + c].x);
+    float L = 0.f;
+    const float own = __builtin_amdgcn_exp2f(st.m[cb] - M);
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+      if ((cb * NE + e) / size == kv) st.acc[cb][e] *= own;
+    for (int g = 0; g < n_kv; ++g) {
+      const int wg = g * n_q + qg;
+      const float2 ml = s_ml[(wg * NCB + cb) * 16 + c];
+      const float f = __builtin_amdgcn_exp2f(ml.x - M);
+      L += f * ml.y;
+      if (g == kv) continue;
+#pragma unroll
+      for (int e = 0; e < NE; ++e)
+        if ((cb * NE + e) / size == kv) {
+          const float4v x = s_acc[(wg * N + cb * NE + e) * 64 + lane];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) st.acc[cb][e][r] += f * x[r];
+        }
+    }
+    if (tok_c >= P.tpt || cb * P.tpt + tok_c >= n_tok) continue;
+    const float inv = v_static / L;
+    const int row = min(max(row0 + cb * P.tpt + tok_c, 0), P.n_rows - 1);
+    const int64_t qrow = (int64_t)row * B.n_q + head * B.G + hg_c;
+    _Float16* const orow = B.out + qrow * HD + 4 * NE * j;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      uint32_t wv[NE / 2];
+#pragma unroll
+      for (int q = 0; q < NE / 2; ++q) {
+        const half2v hv = {(_Float16)(st.acc[cb][2 * q][r] * inv), (_Float16)(st.acc[cb][2 * q + 1][r] * (DT == FS_KV_INT4 ? 0.0625f * inv : inv))};
+        wv[q] = h2u(hv);
+      }
+      if (NE == 8 && size == N / 2) {  // (uniform) a whole block
+        *reinterpret_cast<u32x4*>(orow + NE * r) = u32x4{wv[0], wv[1], wv[NE / 2 - 2], wv[NE / 2 - 1]};
+      } else {
+#pragma unroll
+        for (int q = 0; q < NE / 2; q += 2) {  // four or (head_dim 64 with four groups) two elements
+          if (size >= 4) {
+            if ((cb * NE + 2 * q) / size == kv) *reinterpret_cast<u32x2*>(orow + NE * r + 2 * q) = u32x2{wv[q], wv[q + 1]};
+          } else {
+            if ((cb * NE + 2 * q) / size == kv) *reinterpret_cast<uint32_t*>(orow + NE * r + 2 * q) = wv[q];
+            if ((cb * NE + 2 * q + 2) / size == kv) *reinterpret_cast<uint32_t*>(orow + NE * r + 2 * q + 2) = wv[q + 1];
+          }
+        }
+      }
+    }
+    if (j == 0 && B.lse && cb * NE / size == kv) B.lse[qrow] = (M + __builtin_amdgcn_logf(L)) * kLn2;
+  }
+  __syncthreads();  // (the next item's first stage goes where the partial sums are)
+}
+
 // smem: two stages, then the workgroup's block-address table.
 // DEQ (INT8 / INT4 only): the staging waves dequantize, the tile code is the FP16 one.
 // header: where a block-table entry outside the pool is reported.
@@ -1162,7 +1243,7 @@ struct SeqHeld {
   int seq = -1;
   bool table = false;  // the address table holds all blocks of the sequence
 };
-template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD, bool SUM32>
+template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD, bool SUM32, bool GROUPS>
 __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq, const SeqShape& shape, int head, int qt,
                                 uint8_t* smem, uint64_t* s_tab, int w, SeqHeld& S) {
   static_assert(NW == SUBS || NW == 2 * SUBS, "staging roles");
@@ -1188,12 +1269,16 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   if (seq != S.seq) S.table = false;  // (uniform)
   S.seq = seq;
   const int len = shape.len, n_new = shape.n_new;
+  // groups of waves that share the context; the wave's query tile and its group
+  const int kv_shift = GROUPS ? P.kv_shift : 0, n_kv = 1 << kv_shift;
+  const int qg = GROUPS ? w & ((NW >> kv_shift) - 1) : w, kv = GROUPS ? w / (NW >> kv_shift) : 0;
   const int qw = P.tpt * NCB;                 // query tokens per wave
-  const int r0_wg = qt * qw * NW;             // first query token of the item within the chunk
+  const int q_wg = qw * (NW >> kv_shift);     // query tokens per item
+  const int r0_wg = qt * q_wg;                // first query token of the item within the chunk
   if (r0_wg >= n_new) return;                 // (cannot happen with consistent inputs; uniform over the workgroup)
-  const int n_tok_wg = min(qw * NW, n_new - r0_wg);
-  const int r0 = r0_wg + w * qw;              // this wave's share
-  const int n_tok = max(0, min(qw, n_tok_wg - w * qw));
+  const int n_tok_wg = min(q_wg, n_new - r0_wg);
+  const int r0 = r0_wg + qg * qw;             // this wave's share
+  const int n_tok = max(0, min(qw, n_tok_wg - qg * qw));
   const int first_pos = len - n_new + r0;
   const int tok_c = c / G, hg_c = c - tok_c * G;
 
@@ -1288,11 +1373,11 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       // (sub-tiles that end at or before the first query's own token are seen by all of the wave's columns)
       const int n_seen = kCut ? min(n_live, max(first_pos + 1 - ts, 0) >> 5) : n_live;
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
-      for (int sub = 0; sub < n_seen; ++sub)
+      for (int sub = kv; sub < n_seen; sub += n_kv)
         wg_tile<CDT, NCB, SUBS, kVPre, HD, SUM32>(stage, sub, ts + 32 * sub, qb, len_cb, alpha, first_pos, lane, j, c, st);
       if constexpr (kCut) {
 #pragma unroll 1
-        for (int sub = n_seen; sub < n_live; ++sub)
+        for (int sub = n_seen + ((kv - n_seen) & (n_kv - 1)); sub < n_live; sub += n_kv)
           wg_tile<CDT, NCB, SUBS, 0, HD, SUM32, true>(stage, sub, ts + 32 * sub, qb, len_cb, alpha, first_pos, lane, j, c,
                                                       st, P.tpt, n_tok);
       }
@@ -1304,9 +1389,12 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
 #ifdef FS_TIMELINE
   tl_ph[3] = wall_clock64();
 #endif
-  if (n_tok == 0) return;
-
   const float v_static = DT == FS_KV_FP8_E4M3 ? B.v_scale[head] : 1.0f;
+  if constexpr (GROUPS) {
+    merge_groups<CDT, NW, NCB, HD>(P, st, smem, w, lane, head, shape.q0 + r0, n_tok, v_static);
+    return;
+  }
+  if (n_tok == 0) return;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
     auto sum = [](float a, float b) { return a + b; };
@@ -1674,6 +1762,13 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
 // and the workgroup of the last item -- the first tile of a head, its shortest -- judges the call as a whole when it is
 // done: every length and chunk, and every block-table entry that the sequences with new tokens reach.
 constexpr int kBlocks256 = 4;    // ... and of its item at head_dim 256
+// Small launches over tables of at least this many tokens deal the context to two groups of waves, or four where even items of
+// four blocks all find a compute unit (the host does not know the lengths; a short prompt behind a wide table pays the merge,
+// 2 - 2.7 us).  us, items of 8 blocks whose waves all walk the whole context -> groups: 3 x 100 new tokens behind 3000 - 7000,
+// FP8, 8 KV heads x 4 of 128, 137 -> 83; 4 x 33 behind 2049 - 7581, INT4, 40 heads, 129 -> 115; 2 x 200 behind 3000, INT8,
+// head_dim 64, 53 -> 40; 2 x 100 FP16 tokens behind 1024 30.6 -> 26.3, behind 800 26.2 -> 24.9; but whole prompts of 777, 400
+// and 300 25.0 -> 27.2, 15.9 -> 18.6, 14.5 -> 16.8.
+constexpr int64_t kGroupContext = 1024;
 constexpr int kSmallBlocks = 8;  // column blocks of the workgroup kernel's smaller item
 // The launch's sequences in LDS, where every item's look-ups find them: longest context first, so that the queue ends
 // with the shortest items (in the order of the call, 12 INT4 multi-head prompts of 300 - 3000 tokens left the workgroups
@@ -1772,7 +1867,7 @@ __device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_
 }
 
 // WPC = workgroups per compute unit the kernel is built for
-template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false>
+template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false, bool GROUPS = false>
 __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
   extern __shared__ uint64_t smem64[];
   uint8_t* smem = reinterpret_cast<uint8_t*>(smem64);
@@ -1850,7 +1945,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
     const uint64_t tl_begin = wall_clock64();
 #endif
     if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
-    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32>(P, header, seq, shape, head, qt, smem, s_tab, wave, held);
+    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32, GROUPS>(P, header, seq, shape, head, qt, smem, s_tab, wave, held);
 #ifdef FS_TIMELINE
     ++tl_items;
     if (threadIdx.x == 0 && item < kPfTimelineItems) {
@@ -1966,6 +2061,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   int ncb = !scale_ok || (g.head_dim != kD && !d64 && !d256) ? 1 : (ncb_env ? ncb_env : 16);
   if (d256 && ncb == 16) ncb = kBlocks256;
   uint64_t tiles = 0;
+  int kv_shift = 0;
   auto count_tiles = [&](int blocks) {
     tiles = 0;
     for (int b = 0; b < n_seq; ++b) {
@@ -1990,6 +2086,12 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     // heads: 29 us)
     if (tiles * (uint64_t)g.n_kv_heads <= (uint64_t)p->n_cu) ncb = d64 && tiles * (uint64_t)g.n_kv_heads < 64 ? 1 : kSmallBlocks;
     if (ncb != kSmallBlocks) (void)count_tiles(ncb);
+    else if ((int64_t)max_blocks * g.tokens_per_block >= kGroupContext) {
+      const uint64_t at8 = tiles;
+      (void)count_tiles(kSmallBlocks / 2);
+      if (tiles * (uint64_t)g.n_kv_heads <= (uint64_t)p->n_cu) kv_shift = 2, ncb = kSmallBlocks / 2;
+      else tiles = at8, kv_shift = 1;
+    }
   }
   // head_dim 256: the workgroup kernel, one wave per SIMD, for FP16 and for launches of no more items than compute units
   // (and at least half as many); the other formats' larger launches have enough waves in the 16-column kernel, which
@@ -2064,6 +2166,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
 #endif
   P.tpt = tpt;
   P.ncb = ncb;
+  P.kv_shift = kv_shift;
   P.seg_runs = prefill_seg_runs(B.R);
   P.seg_tokens = prefill_seg_tokens(g.tokens_per_block);
   P.t_magic = token_magic(g.tokens_per_block);
@@ -2074,7 +2177,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   hipStream_t s = (hipStream_t)stream;
   (void)hipGetLastError();
   const uint64_t items = tiles * (uint64_t)g.n_kv_heads;
-  const bool wg = ncb >= 16 || ncb == kSmallBlocks || (d256 && ncb == kBlocks256);
+  const bool wg = ncb >= 16 || kv_shift || ncb == kSmallBlocks || (d256 && ncb == kBlocks256);
   // (FS_OPT_PREFILL_WAVES is about the launches that have a 16-block item per compute unit; a smaller launch by the
   // library's own choice keeps the integer codes exact and its sums over the unrounded weights, as the 16-column kernel that
   // served it before, and the 4-wave kernels are not built like that)
@@ -2133,6 +2236,16 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
         case FS_KV_INT8: kern = prefill_wg_kernel<FS_KV_INT8, 4, 1, 2, 1, false, false, 256, true>; break;
         default: kern = prefill_wg_kernel<FS_KV_INT4, 4, 1, 2, 1, false, false, 256, true>; break;
       }
+    } else if (kv_shift) {
+#define FS_WGKV(DT) \
+  (d64 ? prefill_wg_kernel<DT, 8, 2, 4, 1, false, false, 64, true, true> : prefill_wg_kernel<DT, 8, 2, 4, 1, false, false, kD, true, true>)
+      switch (g.kv_dtype) {
+        case FS_KV_FP16: kern = FS_WGKV(FS_KV_FP16); break;
+        case FS_KV_FP8_E4M3: kern = FS_WGKV(FS_KV_FP8_E4M3); break;
+        case FS_KV_INT8: kern = FS_WGKV(FS_KV_INT8); break;
+        default: kern = FS_WGKV(FS_KV_INT4); break;
+      }
+#undef FS_WGKV
     } else if (ncb == kSmallBlocks) {
       // (integer codes exact, as in the 16-column kernel that served these launches before)
 #define FS_WG1(DT) \
@@ -2166,7 +2279,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return device_error(e, "prefill LDS attribute");
     const bool deq_used = deq && (g.kv_dtype == FS_KV_INT8 || g.kv_dtype == FS_KV_INT4);
-    p->opt.last_prefill = std::min(ncb, 16) | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
+    p->opt.last_prefill = (kv_shift ? kSmallBlocks : std::min(ncb, 16)) | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
     hipLaunchKernelGGL(kern, dim3(n_wg), dim3(nw * 64), smem, s, P);
   } else if (ncb == 1) {
     p->opt.last_prefill = 1;

@@ -162,6 +162,68 @@ def test_small_launches(dtype, head_dim, kv_heads, group):
 
 
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
+@pytest.mark.parametrize("head_dim,kv_heads,group,n_new", [(128, 8, 4, [100, 16, 0, 70]), (128, 8, 1, [33, 200, 40, 5]), (128, 6, 4, [300, 40, 40, 1]),
+                                                           (64, 16, 4, [64, 17, 40, 3]), (64, 12, 8, [90, 30, 40, 33])])
+def test_context_groups(dtype, head_dim, kv_heads, group, n_new):
+    """Small launches behind long contexts: two and four groups of waves per context (items of 8 and 4 blocks), sequences
+    of less than a step, a group without tokens, ragged items."""
+    import gpu_harness
+    import paper_2509_06261_amd as fs
+
+    lens = np.array([1500, 1111, 40, 260], np.int32)
+    wl = Workload("pfgrp", 160 * KiB, 160 * 600 * KiB, [ModelSpec("m", dtype, kv_heads, head_dim, 1, kv_heads * group, lens, tag=50, src_f32=dtype == INT4)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[0]])
+        print(par.prefill_and_check(0, 0, np.array(n_new, np.int32)))
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
+    finally:
+        par.close()
+
+
+@pytest.mark.parametrize("head_dim,kv_heads", [(128, 8), (64, 24)])
+def test_infinite_value_with_context_groups(head_dim, kv_heads):
+    """The rows of blocks in front of the token that holds an Inf are what they are without it, with groups of waves too."""
+    import torch
+
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    lens, n_new, group = np.array([1400], np.int32), 90, 4
+    gw = gpu_workload.GpuWorkload(Workload("pfgi", 512 * KiB, 512 * 200 * KiB,
+                                           [ModelSpec("m", FP16, kv_heads, head_dim, 1, kv_heads * group, lens, tag=51)], "shuffle"), zero_pool=True)
+    try:
+        gw.place()
+        gw.populate([[0]])
+        m, g = gw.model_ids[0], gw.geom[gw.model_ids[0]]
+        off = np.array([0, n_new], np.int32)
+        q = torch.randn((n_new, kv_heads * group, head_dim), generator=torch.Generator(device="cuda").manual_seed(6), device="cuda", dtype=torch.float16)
+        ws = torch.empty(fs.fs_prefill_workspace_bytes(1), dtype=torch.uint8, device="cuda")
+
+        def run():
+            out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
+            fs.fs_prefill_attention(gw.pool, m, 0, kv_heads * group, 0.1, q, gw.tables[0], gw.seq_lens[0], torch.from_numpy(off).cuda(), off, out, lse, ws)
+            assert fs.fs_decode_status(ws) == 0 and fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
+            return out, lse
+
+        out0, lse0 = run()
+        T = g.tokens_per_block
+        for t in (1311, 1337, 1398):
+            at = int(gw.tables_host[0][0, t // T]) * g.block_budget + g.kv_tile + (t % T) * g.row_bytes  # KV head 0, element 0
+            part = gw.pool_mem[at: at + 2]
+            old = part.clone()
+            part.copy_(torch.tensor([0x00, 0x7C], dtype=torch.uint8))
+            out, lse = run()
+            part.copy_(old)
+            row = t - (1400 - n_new)
+            assert not torch.isfinite(out[row:, :group, 0]).any(), t
+            out[row // 4 * 4:, :group, 0] = out0[row // 4 * 4:, :group, 0]
+            assert torch.equal(out, out0) and torch.equal(lse, lse0), t
+    finally:
+        gw.close()
+
+
+@pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
 def test_large_launches_at_head_dim_64(dtype):
     """Items of 32 and 24 blocks: at least eight of them per compute unit (256 in the card's whole partition)."""
     import gpu_harness
