@@ -330,7 +330,8 @@ enum fs_option {
    * several launch sequences, one per head_dim: from the first attention kernel's start to the last one's end.) */
   FS_OPT_KERNEL_TIMING = 2,
   /* prefill kernel of the models with a head_dim of 128: 0 = automatic (default: the workgroup kernel, with items of 16
-   * column blocks, or of 8 where even those all find a compute unit of their own), 1 / 2 / 4 = the wave-level kernels
+   * column blocks, or of 8 -- 8 or 4 behind long contexts -- where even those all find a compute unit of their own),
+   * 1 / 2 / 4 = the wave-level kernels
    * with 16 / 32 / 64 logit columns per wave, 16 = the workgroup kernel with items of 16 blocks */
   FS_OPT_PREFILL_COLUMN_BLOCKS = 3,
   /* waves of the workgroup kernel at head_dim 128, launches with at least one item of 16 blocks per compute unit (or
@@ -341,13 +342,13 @@ enum fs_option {
   FS_OPT_PREFILL_PIPELINED = 5,
   /* INT8 / INT4 models on the 8-wave workgroup kernel: non-zero (default) = the waves that stage K and V in LDS leave
    * dequantized fp16 operands there, (code - zero point) * scale rounded to fp16, and every wave runs the FP16 tile
-   * code: 15-26 % faster; 0 = the integer codes reach the MFMAs exactly and scales and zero points are applied in
-   * fp32 around them, as in decode.  Both stay inside the prefill tolerance. */
+   * code; 0 = the integer codes (less the zero point) reach the MFMAs exactly and the scales are applied in
+   * fp32 around them.  Both stay inside the prefill tolerance. */
   FS_OPT_PREFILL_STAGED_DEQUANT = 6,
   /* read-only: the kernel the pool's latest fs_prefill_attention call launched:
    * column blocks | waves << 8 | staged dequantization << 16 | pipelined << 17 (0: none yet; column blocks 0 with
-   * bit 18 set: the vector-ALU kernel).  Workgroup kernels: 16 blocks with 8 or 4 waves, 8 with 8 (smaller launches),
-   * 4 with 4 (head_dim 256); wave-level kernels: 1, 2 or 4 blocks, waves 0 */
+   * bit 18 set: the vector-ALU kernel).  Workgroup kernels: 16 with 8 or 4 waves (items of 16 blocks, of 24 or 32 in large
+   * launches at head_dim 64), 8 with 8 (smaller launches), 4 with 4 (head_dim 256); wave-level kernels: 1, 2 or 4 blocks, waves 0 */
   FS_OPT_LAST_PREFILL_KERNEL = 7,
   /* non-zero: the MFMA decode kernel always takes its work from a list that a preparation kernel writes; 0 (default): a
    * launch whose sequences need few splits or none runs without one, a workgroup per (sequence, split, KV head) */

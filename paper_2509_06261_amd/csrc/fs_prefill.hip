@@ -13,9 +13,9 @@
 // prefill_kernel keeps one block of 16 columns per wave (two waves per SIMD); prefill_wide_kernel 2 or 4
 // blocks (one wave per SIMD): a tile's K and V rows are then loaded, unpacked and transposed once for 32 or 64
 // columns; prefill_wg_kernel (the default at head_dim 64 and 128) lets the waves of a workgroup share every unpacked
-// K/V fragment through LDS.  Items of one (sequence, head) are neighbours in the queue, longest
-// first, so that the waves streaming the same keys and values run side by side and share them through the
-// L2.  Waves draw items from the same pooled ticket counters as the decode kernel.  A long context is
+// K/V fragment through LDS.  Items of one (sequence, head) are neighbours in the queue (or, in the workgroup kernels,
+// a number of heads apart that brings them to the same XCD), longest first, so that the waves streaming the same keys and
+// values run side by side and share them through the L2.  Waves draw items from the same pooled ticket counters as the decode kernel.  A long context is
 // streamed in segments, the wave's block-address table being refilled per segment.
 #include <cstdlib>
 
@@ -46,6 +46,7 @@ struct PrefillArgs {
   uint32_t t_magic;          // workgroup kernels: for the division by the tokens per block (block_of, fs_prefill_index.h)
   int32_t chunk_shift;       // workgroup kernels: log2 of the consecutive work items that go to one XCD
   int32_t kv_shift;          // workgroup kernels: log2 of the groups of waves that share an item's context (merge_groups)
+  int32_t by_tile;           // workgroup kernels: 1 = items in the order of decode_item_by_tile
   int32_t direct;            // workgroup kernels: 1 = no preparation ran and no tickets are drawn (see "Direct launches")
 #ifdef FS_TIMELINE
   uint64_t* timeline;        // (timeline build) clock readings of the workgroup kernels, at the end of the workspace
@@ -637,8 +638,8 @@ __global__ __launch_bounds__(kThreads, WPS) void prefill_wide_kernel(PrefillArgs
 // LDS.  Global loads, unpacking and transposes per wave drop to a quarter; the fragments are written and read
 // lane-contiguously (16 bytes per lane), free of bank conflicts.  Two stages alternate, so one barrier per
 // step suffices: a stage is rewritten only after the barrier that follows its last readers.
-// Stage layout: K fragments [sub-tile][u][k-step][lane] 16 B, V fragments [sub-tile][e][lane] 16 B, per-token
-// parameters [sub-tile][lane] 4 B.
+// Stage layout: K fragments [sub-tile][u][k-step][lane] 16 B, V fragments [sub-tile][e][lane] 16 B, per token of the
+// parameter formats two factors [sub-tile][K, V][32] 4 B (the pipelined kernel: parameters [sub-tile][lane] 4 B).
 constexpr uint32_t kFrag = 64 * 16;  // one operand fragment of a wave
 // K (and V) fragments of a sub-tile: two 16-token halves x HD / 32 k-steps (HD / 16 groups of 16 output columns)
 constexpr int frags(int hd) { return hd / 16; }
@@ -776,8 +777,8 @@ __device__ __forceinline__ TokenPlace place_token(const TokenCtx& X, int t) {
 }
 
 // K rows of the sub-tile from token tb of the segment on: row c of half-tile u is token 8 (c / 4) + 4 u + c % 4.
-// kpar (DEQ): their parameters
-template <int DT, int HD, bool DEQ>
+// kpar (PAR): their parameters
+template <int DT, int HD, bool PAR>
 __device__ __forceinline__ void fetch_k(const TokenCtx& X, const DevGeom& g, bool whole, int tb, int j, int c, Tile<DT, 16, HD>& t,
                                         uint32_t (&kpar)[2]) {
   using F = Fmt<DT, HD>;
@@ -786,7 +787,7 @@ __device__ __forceinline__ void fetch_k(const TokenCtx& X, const DevGeom& g, boo
     const gptr at = p.base + (uint32_t)(p.slot * F::kRowBytes) + F::kKLane * j;
 #pragma unroll
     for (int s = 0; s < F::kKLoads; ++s) t.k[u][s] = *reinterpret_cast<const FS_GLOBAL kvec*>(at + 4 * F::kKLane * s);
-    if constexpr (DEQ) {
+    if constexpr (PAR) {
       const gptr pp = p.base + 2u * g.kv_tile + (uint32_t)(p.slot * F::kParBytes);
       if constexpr (F::kParBytes == 2) kpar[u] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(pp);
       else kpar[u] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(pp);
@@ -806,7 +807,7 @@ __device__ __forceinline__ void fetch_k(const TokenCtx& X, const DevGeom& g, boo
 }
 
 // V rows of the sub-tile: lane j takes tokens 8 j .. 8 j + 7; and its parameters: lane c those of token c % 8, K for c < 8
-// (DEQ: not used), V for the others.
+// (dequantizing staging does not use them), V for the others.
 template <int DT, int HD>
 __device__ __forceinline__ void fetch_v(const TokenCtx& X, const DevGeom& g, bool whole, int tb, int j, int c, Tile<DT, 16, HD>& t) {
   using F = Fmt<DT, HD>;
@@ -1146,7 +1147,8 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, c
 // and stages K and V of sub-tile w; with NW == 2 SUBS waves 0..SUBS-1 stage the K fragments of sub-tile w and the
 // others the V fragments and parameters of sub-tile w - SUBS.  Built variants: 8 waves x 2 blocks, 4 sub-tiles per
 // step, one workgroup per compute unit (two waves per SIMD, so that one's softmax runs under the other's MFMAs);
-// 4 x 4, 4 sub-tiles (one wave per SIMD); 8 x 1 for small launches; 4 x 1 with 2 sub-tiles per step at head_dim 256.
+// 4 x 4, 4 sub-tiles (one wave per SIMD); 8 x 4 and 8 x 3 for large launches at head_dim 64; 8 x 1 for small launches, 8 x 2 in
+// groups (GROUPS) for those behind long contexts; 4 x 1 with 2 sub-tiles per step at head_dim 256.
 // (Another one -- 4 x 2 with 2 sub-tiles per step, two workgroups per
 // compute unit -- passed its small cases but ended a full-size two-model run with the GPU faulted or hung; the
 // cause was not found and the variant is no longer built.  What was particular to it is absent from the 4 x 1 kernel of
@@ -1913,7 +1915,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
 #endif
     uint32_t item;
     if (direct) {
-      item = (blockIdx.x & 7) * per + u;
+      item = P.by_tile ? 8 * u + (blockIdx.x & 7) : (blockIdx.x & 7) * per + u;
       if (u >= per || item >= total) break;
       u += slots;
     } else {
@@ -1929,7 +1931,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
       if (item == 0xffffffffu) break;
     }
     int seq, head, qt;
-    const int found = decode_item(P, tf, item, H, seq, head, qt);
+    const int found = P.by_tile ? fs::decode_item_by_tile(tf, B.n_seq, item, H, seq, head, qt) : decode_item(P, tf, item, H, seq, head, qt);
     if (!__builtin_amdgcn_readfirstlane(found)) continue;  // (uniform, so that what lives across items stays scalar)
     uint32_t unused = 0;
     seq = __builtin_amdgcn_readfirstlane(listed ? list.seq[seq] : seq);
@@ -1959,7 +1961,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
   }
   if (direct) {
     const uint32_t last = total ? total - 1 : 0u, n = total ? per : 1u;
-    if (blockIdx.x == (last % n % slots) * 8 + last / n) direct_status<NW * 64>(P, reinterpret_cast<uint32_t*>(smem));
+    if (blockIdx.x == (P.by_tile ? last % gridDim.x : (last % n % slots) * 8 + last / n)) direct_status<NW * 64>(P, reinterpret_cast<uint32_t*>(smem));
   }
 #ifdef FS_TIMELINE
   if (threadIdx.x == 0 && blockIdx.x < kPfTimelineGroups) {
@@ -2212,11 +2214,18 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   const int subs = d256 ? 2 : 4, wpc = 1;
   const int n_wg = P.direct ? (int)((items + 7) / 8 * 8) : wg ? (int)std::min<uint64_t>((uint64_t)p->n_cu * wpc, std::max<uint64_t>(items, 1))
                       : (int)std::min<uint64_t>((uint64_t)p->n_cu * wps, std::max<uint64_t>((items + kWaves - 1) / kWaves, 1));
-  // Consecutive items -- the query tiles of one (sequence, head), which stream the same K/V -- go to one XCD in
-  // chunks of 128 (a head of 8192 tokens in one piece: measured + 1.4 % over chunks of 32 on long prompts), of
+  // (The other kernels, and other numbers of heads:) consecutive items -- the query tiles of one (sequence, head), which stream
+  // the same K/V -- go to one XCD in chunks of 128 (a head of 8192 tokens in one piece: measured + 1.4 % over chunks of 32 on long prompts), of
   // fewer while that leaves an XCD less than eight chunks to balance with.
   P.chunk_shift = 7;
   while (P.chunk_shift > (int32_t)kWgChunkShift && (items >> P.chunk_shift) < 64) --P.chunk_shift;
+  // Where the heads allow it (see decode_item_by_tile) the workgroup kernels take a sequence's tiles longest first over all its
+  // heads, dealt to the XCDs in turn: head by head, a launch's last head began with its longest tile.  us: one FP16 prompt of
+  // 3000 tokens, GQA 4:1, 159 -> 142; four of 1200 at head_dim 64 82 -> 69; two of 800 and 1500 at 256 142 -> 118; 16 x 512 INT8
+  // tokens behind 2000 - 6000 632 -> 585; 4 x 512 FP8 tokens (one item per unit) 420 -> 394; 64 FP16 prompts 3915 -> 3885; two of
+  // 1107 and 2179 114 -> 119, four FP8 ones of 500 - 2000, GQA 8:1, 171 -> 175.
+  P.by_tile = wg && (g.n_kv_heads % 8 == 0 || 8 % g.n_kv_heads == 0);
+  if (P.by_tile) P.chunk_shift = 0;
   const size_t smem = wg ? 2 * (size_t)stage_bytes(subs, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes +
                                (P.tf_cache == 2 ? seq_list_bytes(n_seq) : P.tf_cache ? (((size_t)n_seq + 1) * 4 + 15) / 16 * 16 : 0)
                          : (size_t)kWaves * P.table_entries * sizeof(uint64_t);

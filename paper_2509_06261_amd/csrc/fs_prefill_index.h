@@ -35,6 +35,17 @@ __device__ __host__ inline bool decode_item(const uint32_t* tf, int n_seq, uint3
   return true;
 }
 
+// The same sequences, but the tiles of all heads together, longest first, heads innermost: with H a multiple or a divisor of 8
+// and items dealt to the XCDs in turn a head's tiles still meet on one XCD (two, four, eight for fewer heads).
+__device__ __host__ inline bool decode_item_by_tile(const uint32_t* tf, int n_seq, uint32_t item, uint32_t H, int& seq, int& head,
+                                                    int& qt) {
+  if (!decode_item(tf, n_seq, item, H, seq, head, qt)) return false;
+  const uint32_t nt = tf[seq + 1] - tf[seq], li = item - tf[seq] * H;
+  head = (int)(li % H);
+  qt = (int)(nt - 1 - li / H);
+  return true;
+}
+
 // Runs of 8 token slots streamed per refill of a wave's block-address table (a multiple of 4, about 500 blocks),
 // and the table's entries: the blocks such a segment can touch.
 __device__ __host__ inline int32_t prefill_seg_runs(int R) {

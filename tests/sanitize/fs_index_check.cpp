@@ -640,6 +640,33 @@ void direct_rule() {
   }
 }
 
+// The workgroup prefill kernels' order by tiles: every (sequence, head, tile) once, a sequence's tiles from the longest on,
+// and a head's items on 8 / gcd(heads, 8) XCDs when item i goes to XCD i % 8.
+void prefill_order_by_tile(int rounds) {
+  for (int round = 0; round < rounds; ++round) {
+    const int n_seq = 1 + rnd_int(round % 7 == 0 ? 600 : 40);
+    const uint32_t H = round % 3 ? 1u << rnd_int(4) : 8u * (1 + (uint32_t)rnd_int(6));
+    std::vector<uint32_t> tf(n_seq + 1, 0);
+    for (int i = 0; i < n_seq; ++i) tf[i + 1] = tf[i] + (rnd_int(5) ? 1 + (uint32_t)rnd_int(rnd_int(4) ? 6 : 60) : 0u);
+    const uint32_t total = tf[n_seq] * H;
+    std::vector<uint8_t> hit(total, 0), xcds((size_t)n_seq * H, 0);
+    int last_seq = -1, last_qt = 0;
+    for (uint32_t item = 0; item < total; ++item) {
+      int seq = -1, head = -1, qt = -1;
+      CHECK(fs::decode_item_by_tile(tf.data(), n_seq, item, H, seq, head, qt));
+      CHECK(seq >= 0 && seq < n_seq && head >= 0 && (uint32_t)head < H && qt >= 0 && (uint32_t)qt < tf[seq + 1] - tf[seq]);
+      CHECK(seq > last_seq || (seq == last_seq && qt <= last_qt));
+      last_seq = seq, last_qt = qt;
+      const size_t at = (size_t)tf[seq] * H + (size_t)head * (tf[seq + 1] - tf[seq]) + qt;
+      CHECK(!hit[at]);
+      hit[at] = 1;
+      xcds[(size_t)seq * H + head] |= (uint8_t)(1u << (item % 8));
+      ++g_items;
+    }
+    for (uint8_t x : xcds) CHECK((uint32_t)__builtin_popcount(x) <= (H >= 8 ? 1u : 8u / H));
+  }
+}
+
 // The workgroup prefill kernels' walk by tokens: every row of every sub-tile of a context is its token's place, the last
 // token's past a segment's end, and no look-up leaves the segment's table.
 void prefill_token_walk(int rounds) {
@@ -682,6 +709,7 @@ void prefill_token_walk(int rounds) {
 
 int main() {
   prefill_token_walk(240);
+  prefill_order_by_tile(60);
   run(600);
   direct_order();
   direct_rule();

@@ -233,7 +233,7 @@ def test_large_launches_at_head_dim_64(dtype):
     par = gpu_harness.Parity(wl, zero_pool=True)
     try:
         par.gw.populate([[0]])
-        print("T", par.gw.T, par.prefill_and_check(0, 0, lens, seqs=np.array([0, 40, 41, 42, 43, 44, 45, 46, 47])))
+        print("T", par.gw.T, par.prefill_and_check(0, 0, lens, seqs=np.array([0, 40, 41, 42, 43, 44])))
     finally:
         par.close()
 
