@@ -252,14 +252,18 @@ static PyObject* decode_step_multi(PyObject* self, PyObject* const* a, Py_ssize_
 }
 
 /* init(Tensor, float16, float32, int32, c_void_p, fs_batch_t, fs_append_t, get_device, get_stream, addresses of the five
- * entry points in the order of L) */
+ * entry points in the order of L); init() forgets them: every call is answered None until the next one */
 static PyObject* init(PyObject* self, PyObject* const* a, Py_ssize_t n) {
   PyObject** const objs[9] = {&L.tensor, &L.float16, &L.float32, &L.int32, &L.c_void_p, &L.batch, &L.append, &L.get_device, &L.get_stream};
   void* fn[5];
   int i;
   (void)self;
+  if (n == 0) {
+    for (i = 0; i < 9; ++i) Py_CLEAR(*objs[i]);
+    Py_RETURN_NONE;
+  }
   if (n != 14) {
-    PyErr_SetString(PyExc_TypeError, "init takes 14 arguments");
+    PyErr_SetString(PyExc_TypeError, "init takes 14 arguments or none");
     return NULL;
   }
   for (i = 0; i < 5; ++i) {

@@ -1,6 +1,9 @@
 """The binding's native marshaling (csrc/fs_fastcall.c) against ctypes' conversions, on the CPU: its entry points are
 callbacks that record what arrives, torch's current device and stream stand-ins; what it does not take, it answers None to."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -18,7 +21,10 @@ STREAM = 0x5EED0
 
 @pytest.fixture(scope="module")
 def got():
+    """The recorders take the place of the library's entry points in the whole process, so the binding's own calls keep to
+    ctypes meanwhile; afterwards the module forgets them and the binding starts anew."""
     seen = {}
+    slow, binding._slow, binding._fast = binding._slow, lambda: None, binding._NotYet
 
     def recorder(name, types):
         def f(*args):
@@ -34,7 +40,9 @@ def got():
     seen["keep"] = [recorder(*x) for x in SIGNATURES]
     _fsfast.init(torch.Tensor, torch.float16, torch.float32, torch.int32, ctypes.c_void_p, binding.fs_batch_t, binding.fs_append_t,
                  lambda: 3, lambda d: STREAM + d, *[ctypes.cast(f, vp).value for f in seen["keep"]])
-    return seen
+    yield seen
+    _fsfast.init()
+    binding._slow = slow
 
 
 def rows(dt=torch.float16):
@@ -88,3 +96,18 @@ def test_decode(got):
     assert _fsfast.decode_attention_multi(vp(5), a, ws, None) is None
     assert _fsfast.decode_attention(vp(5), 1, 2, 4, 1, q, t, n, out, lse, ws, None) is None
     assert _fsfast.decode_attention(vp(5), 1, 2, 4, 0.125, q, n, n, out, lse, ws, None) is None
+
+
+def test_nothing_is_left_behind():
+    """After this module's tests no call reaches their recorders (a child process runs them, then calls)."""
+    code = """
+import ctypes, sys, pytest
+assert pytest.main([sys.argv[1], "-q", "-p", "no:cacheprovider", "-k", "append or decode"]) == 0
+from paper_2509_06261_amd import _fsfast, binding
+import torch
+r = [torch.zeros((5, 2, 8), dtype=torch.float16)] * 2 + [torch.zeros(5, dtype=torch.int32)] * 2 + [torch.zeros((3, 4), dtype=torch.int32)]
+assert _fsfast.kv_append(ctypes.c_void_p(1), 1, 2, *r, None) is None
+assert binding._fast is binding._NotYet and binding._slow.__name__ == "_slow"
+"""
+    p = subprocess.run([sys.executable, "-c", code, __file__], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout[-2000:] + p.stderr[-2000:]
