@@ -751,7 +751,7 @@ __device__ __forceinline__ void dequant8(const uint32_t* w, const Deq<DT>& q, ui
 // slots, no masks for them and no look-up of a run's place in every wave that multiplies the sub-tile (the wave-level kernels
 // walk runs of eight slots that never cross a block).  The fetching lane pays: a row of K has its own block, and the eight
 // rows of V may come from two.  Rows past the segment's last token are that token's again where blocks are no multiple of
-// eight tokens; otherwise eight slots are always inside a block, and those past the end are cleared when they are staged.
+// eight tokens; otherwise eight slots are always inside a block.  Either way those of V are cleared when they are staged.
 // (us: 32 INT4 prompts of 512 - 4096 tokens in blocks of 60, GQA 4:1, 2273 -> 1946; 12 multi-head ones of 300 - 3000 in blocks
 // of 46 720 -> 599; FP8 ones in blocks of 25 804 -> 542; 8 INT8 prompts of 2000 - 6000, GQA 8:1, blocks of 31, 2933 -> 2577;
 // blocks of 16 or 32 tokens the same within 1 %.)
@@ -1337,7 +1337,9 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       if (does_v) fetch_v<DT, HD>(X, g, whole, tb, j, c, t);
     };
     auto stage_to = [&](uint8_t* stage, int tb) {
-      const int live = whole ? n - (tb + 8 * j) : 8;  // (the other rows past the end are live ones again)
+      // V slots past the segment's last token are cleared whatever they hold -- the last token's rows again where blocks are no
+      // multiple of eight tokens: weight 0 times its Inf made its own row NaN.
+      const int live = n - (tb + 8 * j);
       if constexpr (DEQ) {
         if (does_k) stage_k_deq<DT>(stage, sw, lane, t, kpar);
         if (does_v) stage_v_deq<DT, SUBS>(stage, sw, lane, live, t);

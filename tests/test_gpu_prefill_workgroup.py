@@ -119,6 +119,51 @@ def test_infinite_value_reaches_no_row_before_its_block(head_dim, kv_heads, grou
         gw.close()
 
 
+@pytest.mark.parametrize("dtype,T", [(FP16, 13), (FP16, 16), (INT8, 11), (INT4, 15)])
+def test_infinite_last_value_in_large_launches(dtype, T, monkeypatch):
+    """An Inf in the sequence's last token (integer formats: in its V scale): its own row is infinite, not NaN, though the
+    slots behind it are multiplied with weight 0, and the rows more than a sub-tile in front are what they are without it."""
+    import torch
+
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 16})
+    n, H, group = 700, 2, 4
+    bits, par = {FP16: (16, 0), INT8: (8, 2), INT4: (4, 4)}[dtype]
+    slab = -(-T * 2 * H * (128 * bits // 8 + par) // 256) * 256 + 256 * H
+    gw = gpu_workload.GpuWorkload(Workload("pfinfl", slab, slab * 200, [ModelSpec("m", dtype, H, 128, 1, H * group, np.array([n], np.int32), tag=52,
+                                                                                  src_f32=dtype == INT4)], "shuffle"), zero_pool=True)
+    try:
+        gw.place()
+        gw.populate([[0]])
+        m, g = gw.model_ids[0], gw.geom[gw.model_ids[0]]
+        off = np.array([0, n], np.int32)
+        q = torch.randn((n, H * group, 128), generator=torch.Generator(device="cuda").manual_seed(8), device="cuda", dtype=torch.float16)
+        ws = torch.empty(fs.fs_prefill_workspace_bytes(1), dtype=torch.uint8, device="cuda")
+
+        def run():
+            out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
+            fs.fs_prefill_attention(gw.pool, m, 0, H * group, 0.1, q, gw.tables[0], gw.seq_lens[0], torch.from_numpy(off).cuda(), off, out, lse, ws)
+            assert fs.fs_decode_status(ws) == 0 and fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) & 0xffff == (16 | 8 << 8)
+            return out, lse
+
+        out0, lse0 = run()
+        t, tpb = n - 1, g.tokens_per_block
+        print("T", tpb)
+        block = int(gw.tables_host[0][0, t // tpb]) * g.block_budget
+        at = block + (g.kv_tile + (t % tpb) * g.row_bytes if dtype == FP16 else 2 * g.kv_tile + g.par_tile + (t % tpb) * par)  # KV head 0
+        gw.pool_mem[at: at + 2] = torch.tensor([0x00, 0x7C], dtype=torch.uint8, device="cuda")
+        out, lse = run()
+        last = out[t, :group, :1 if dtype == FP16 else 128].float()
+        # (integers: a code at its zero point is 0 * Inf)
+        assert torch.isinf(last).all() if dtype == FP16 else torch.isinf(last).float().mean() > 0.5, last
+        out[t // 32 * 32:, :group] = out0[t // 32 * 32:, :group]
+        assert torch.equal(out, out0) and torch.equal(lse, lse0)
+    finally:
+        gw.close()
+
+
 @pytest.mark.parametrize("head_dim,n_seq,with_tokens,kernel", [(128, 600, 600, 16 | 8 << 8), (256, 300, 300, 4 | 4 << 8), (64, 700, 700, 16 | 8 << 8),
                                                                (128, 100, 100, 8 | 8 << 8), (128, 500, 90, 8 | 8 << 8), (256, 200, 150, 4 | 4 << 8)])
 def test_many_sequences(head_dim, n_seq, with_tokens, kernel):
