@@ -1048,7 +1048,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, c
   for (int e = 0; e < VPRE; ++e)
     vpre[e] = *reinterpret_cast<const u32x4*>(stage + stage_v(SUBS, HD) + (uint32_t)((sub * F::kNE + e) * kFrag) + lane * 16);
   // interior (uniform): every token of the sub-tile lies at or before the wave's first query token: nothing to mask
-  const bool interior = tb + 32 <= first_pos + 1;
+  const bool interior = sub_tile_interior(tb, first_pos);
   const int tok0 = tb + 8 * j;  // the lane's first token
   float ka[8], va[8];  // (parameter formats) the factors of the lane's eight tokens
   if constexpr (F::kParBytes != 0) {
@@ -1313,7 +1313,8 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
   const int w_end = n_tok > 0 ? first_pos + n_tok : 0;  // tokens this wave's last query sees
   constexpr bool kCut = SUM32 && DT == FS_KV_FP16;  // (see wg_tile)
-  for (int t0 = 0; t0 < len_u; t0 += P.seg_tokens) {  // (t0, and what is counted from it: multiples of 32)
+  int t0 = 0;  // (and what is counted from it: multiples of 32)
+  do {
     const int n = min(len_u - t0, P.seg_tokens), k0 = t0 / g.T;
     X.rel0 = t0 - k0 * g.T;
     X.last = n - 1;
@@ -1373,7 +1374,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       // tile: it costs the accumulators' registers nothing.  (64 FP16 prompts of 512 - 4096 tokens, GQA 4:1: 4126 ->
       // 3977 us; 12 INT4 multi-head prompts of 300 - 3000 tokens, whose items span two steps of diagonal: 840 -> 800 us.)
       const int ts = t0 + 32 * SUBS * i;  // the step's first token
-      const int n_live = min(SUBS, (w_end - ts + 31) >> 5);
+      const int n_live = live_sub_tiles(w_end, ts, SUBS);
       // (sub-tiles that end at or before the first query's own token are seen by all of the wave's columns)
       const int n_seen = kCut ? min(n_live, max(first_pos + 1 - ts, 0) >> 5) : n_live;
 #pragma unroll 1  // (unrolled by two: measured 0.5 % slower)
@@ -1389,7 +1390,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       if (more) stage_to(next, tb_next);
       __syncthreads();  // (also after the last step: the next staging overwrites what other waves may still read)
     }
-  }
+  } while (next_segment(t0, len_u, P.seg_tokens));
 #ifdef FS_TIMELINE
   tl_ph[3] = wall_clock64();
 #endif

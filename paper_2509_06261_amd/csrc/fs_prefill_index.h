@@ -61,6 +61,20 @@ __device__ __host__ inline int32_t prefill_seg_tokens(int T) {
   const int64_t want = (int64_t)500 * T / 128 * 128;
   return (int32_t)(want < 128 ? 128 : (want > 8192 ? 8192 : want));
 }
+// The next segment's first token; false behind the last one.  (The differences, not the sums, stay below 2^31 in contexts of
+// nearly 2^31 tokens, which a table whose entries name one block many times can hold: t0 + seg < len never ended there.)
+__device__ __host__ inline bool next_segment(int& t0, int len, int seg) {
+  if (len - t0 <= seg) return false;
+  t0 += seg;
+  return true;
+}
+// Of the `subs` sub-tiles of 32 tokens from token ts on, those that hold one of the first `end` tokens (none: <= 0), ...
+__device__ __host__ inline int live_sub_tiles(int end, int ts, int subs) {
+  const int left = end - ts;
+  return ((left < 32 * subs ? left : 32 * subs) + 31) >> 5;
+}
+// ... and whether all of the sub-tile from token tb on lies at or before token `first`.
+__device__ __host__ inline bool sub_tile_interior(int tb, int first) { return first - tb >= 31; }
 // rel / T for 0 <= rel < T + 8192, rel counted from a block's start.  Below 2^15 tokens a block, ceil(2^32 / T) is off by less
 // than T / 2^32, and rel T < 2^32; above, a segment spans two blocks at most.
 __device__ __host__ inline uint32_t token_magic(int T) { return T >= 2 && T < (1 << 15) ? (uint32_t)(((1ull << 32) + (uint64_t)T - 1) / (uint64_t)T) : 0u; }

@@ -679,7 +679,8 @@ void prefill_token_walk(int rounds) {
     const int seg = fs::prefill_seg_tokens(T), entries = seg / T + 3;
     CHECK(seg % 128 == 0);
     const int len = 1 + (int)(rnd() % (kind == 3 ? 3 * T : 20000));
-    for (int t0 = 0; t0 < len; t0 += seg) {
+    int t0 = 0;
+    do {
       const int n = std::min(len - t0, seg), k0 = t0 / T, rel0 = t0 - k0 * T, last = n - 1;
       const int nb = (rel0 + n - 1) / T + 1;
       CHECK(nb <= entries && rel0 + last < T + 8192);
@@ -701,13 +702,37 @@ void prefill_token_walk(int rounds) {
           ++g_tiles;
         }
       }
+    } while (fs::next_segment(t0, len, seg));
+  }
+}
+
+// Contexts of up to 2^31 - 1 tokens: the segments end, one after the other, and the sub-tiles of the last ones are counted
+// and told interior as 64-bit arithmetic has it.
+void prefill_longest_contexts() {
+  for (int k = 0; k < 400; ++k) {
+    const int len = 0x7fffffff - (k < 200 ? k : (int)(rnd() % 40000)), seg = fs::prefill_seg_tokens(8 + (int)(rnd() % 60000));
+    const int first = len - 1 - (int)(rnd() % 300), subs = k % 2 ? 2 : 4;
+    int t0 = (len / seg - 2) * seg, t = t0, n = 1;
+    while (n < 10 && fs::next_segment(t, len, seg)) {
+      ++n;
+      CHECK(t > t0 && t < len);
+      t0 = t;
     }
+    CHECK(n == (len - (len / seg - 2) * seg + seg - 1) / seg);
+    for (int i = 0; i * 32 * subs < len - t0; ++i) {
+      const int ts = t0 + 32 * subs * i, live = fs::live_sub_tiles(len, ts, subs);
+      CHECK(live == (int)std::min<int64_t>(subs, ((int64_t)len - ts + 31) / 32));
+      CHECK(fs::live_sub_tiles(0, ts, subs) <= 0);
+      for (int s = 0; s < live; ++s) CHECK(fs::sub_tile_interior(ts + 32 * s, first) == ((int64_t)ts + 32 * s + 32 <= (int64_t)first + 1));
+    }
+    CHECK(fs::live_sub_tiles(len, 0, subs) == subs && fs::sub_tile_interior(0, first));
   }
 }
 
 }  // namespace
 
 int main() {
+  prefill_longest_contexts();
   prefill_token_walk(240);
   prefill_order_by_tile(60);
   run(600);
