@@ -662,11 +662,11 @@ __device__ __forceinline__ void stage_k(uint8_t* stage, int sub, int lane, Tile<
   }
 }
 template <int DT, int SUBS, int HD>
-__device__ __forceinline__ void stage_v(uint8_t* stage, int sub, int lane, int live, Tile<DT, 16, HD>& t) {
+__device__ __forceinline__ void stage_v(uint8_t* stage, int sub, int lane, bool clear, int live, Tile<DT, 16, HD>& t) {
   using F = Fmt<DT, HD>;
   if constexpr (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3) {
     // slots past the sequence's end may hold NaN/Inf bit patterns; 0 * NaN would poison the MFMA
-    if (!__all(live >= 8)) {
+    if (clear) {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -861,7 +861,7 @@ __device__ __forceinline__ void stage_k_deq(uint8_t* stage, int sub, int lane, T
 }
 
 template <int DT, int SUBS>
-__device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, int live, Tile<DT, 16>& t) {
+__device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, bool clear, int live, Tile<DT, 16>& t) {
   uint32_t vx[8][4];
   static_for(std::make_integer_sequence<int, 8>{}, [&](auto I) {
     constexpr int i = decltype(I)::value;
@@ -872,7 +872,7 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, i
   });
   // slots past the sequence's end may hold any codes and parameters (NaN / Inf after the conversion); 0 * NaN
   // would poison the MFMA
-  if (!__all(live >= 8)) {
+  if (clear) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -937,7 +937,7 @@ __device__ __forceinline__ void stage_k_int(uint8_t* stage, int sub, int lane, T
 
 // live: as in stage_v (slots past the end may hold any codes and parameters)
 template <int DT, int SUBS, int HD>
-__device__ __forceinline__ void stage_v_int(uint8_t* stage, int sub, int lane, int live, float alpha, Tile<DT, 16, HD>& t) {
+__device__ __forceinline__ void stage_v_int(uint8_t* stage, int sub, int lane, bool clear, int live, float alpha, Tile<DT, 16, HD>& t) {
   using F = Fmt<DT, HD>;
   constexpr int kPer = DT == FS_KV_INT8 ? 2 : 4;  // registers a word unpacks to
   uint32_t vx[8][kPer * F::kVWords];
@@ -952,7 +952,7 @@ __device__ __forceinline__ void stage_v_int(uint8_t* stage, int sub, int lane, i
       for (int z = 0; z < kPer; ++z) vx[i][kPer * w + z] = x[z];
     }
   });
-  if (!__all(live >= 8)) {
+  if (clear) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -1340,16 +1340,17 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
     auto stage_to = [&](uint8_t* stage, int tb) {
       // V slots past the segment's last token are cleared whatever they hold -- the last token's rows again where blocks are no
       // multiple of eight tokens: weight 0 times its Inf made its own row NaN.
+      const bool clear = n - tb < 32;  // (uniform)
       const int live = n - (tb + 8 * j);
       if constexpr (DEQ) {
         if (does_k) stage_k_deq<DT>(stage, sw, lane, t, kpar);
-        if (does_v) stage_v_deq<DT, SUBS>(stage, sw, lane, live, t);
+        if (does_v) stage_v_deq<DT, SUBS>(stage, sw, lane, clear, live, t);
       } else if constexpr (Fmt<DT>::kParBytes != 0) {
         if (does_k) stage_k_int<DT, HD>(stage, sw, lane, t, kpar);
-        if (does_v) stage_v_int<DT, SUBS, HD>(stage, sw, lane, live, alpha, t);
+        if (does_v) stage_v_int<DT, SUBS, HD>(stage, sw, lane, clear, live, alpha, t);
       } else {
         if (does_k) stage_k<DT, HD>(stage, sw, lane, t);
-        if (does_v) stage_v<DT, SUBS, HD>(stage, sw, lane, live, t);
+        if (does_v) stage_v<DT, SUBS, HD>(stage, sw, lane, clear, live, t);
       }
     };
     fetch(32 * sw);
@@ -1600,7 +1601,10 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
     issue_k<DT, 16>(X, v0 + 4 * w, j, c, t);
     issue_v<DT, 16>(X, g, v0 + 4 * w, j, c, t);
     stage_k<DT, kD>(smem, w, lane, t);
-    stage_v<DT, SUBS, kD>(smem, w, lane, locate(X, v0 + 4 * w + j).hi_u, t);
+    {
+      const int live = locate(X, v0 + 4 * w + j).hi_u;
+      stage_v<DT, SUBS, kD>(smem, w, lane, !__all(live >= 8), live, t);
+    }
     __syncthreads();
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) settle_q(qb[cb]);  // (issued before the table and the first K/V fetch)
@@ -1712,7 +1716,10 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
       }
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS);
       stage_k<DT, kD>(next, w, lane, t);
-      stage_v<DT, SUBS, kD>(next, w, lane, locate(X, vb_next + j).hi_u, t);
+      {
+        const int live = locate(X, vb_next + j).hi_u;
+        stage_v<DT, SUBS, kD>(next, w, lane, !__all(live >= 8), live, t);
+      }
       __syncthreads();
     }
   }
