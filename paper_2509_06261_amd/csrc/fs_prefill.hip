@@ -45,7 +45,8 @@ struct PrefillArgs {
   int32_t seg_tokens;        // workgroup kernels: tokens streamed per refill of the block-address table (multiple of 128)
   uint32_t t_magic;          // workgroup kernels: for the division by the tokens per block (block_of, fs_prefill_index.h)
   int32_t chunk_shift;       // workgroup kernels: log2 of the consecutive work items that go to one XCD
-  int32_t kv_shift;          // workgroup kernels: log2 of the groups of waves that share an item's context (merge_groups)
+  int32_t kv_shift;          // workgroup kernels: log2 of the groups of waves that share an item's context (merge_groups) ...
+  int32_t group_len;         // ... in launches with a sequence of at least this many tokens (see scan_sequences)
   int32_t by_tile;           // workgroup kernels: 1 = items in the order of decode_item_by_tile
   int32_t direct;            // workgroup kernels: 1 = no preparation ran and no tickets are drawn (see "Direct launches")
 #ifdef FS_TIMELINE
@@ -84,8 +85,8 @@ __device__ __forceinline__ SeqShape seq_shape(const PrefillArgs& P, int i, uint3
   }
   return s;
 }
-__device__ __forceinline__ uint32_t shape_tiles(const PrefillArgs& P, const SeqShape& s) {
-  return (uint32_t)((s.n_new + P.tpt * P.ncb - 1) / (P.tpt * P.ncb));
+__device__ __forceinline__ uint32_t shape_tiles(const PrefillArgs& P, const SeqShape& s, int ncb) {
+  return (uint32_t)((s.n_new + P.tpt * ncb - 1) / (P.tpt * ncb));
 }
 
 // Query tiles per sequence -> tile_first (exclusive scan), validation flags, counter reset.  One workgroup.
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(kPrepThreads) void prefill_prep_kernel(PrefillArgs 
     uint32_t v = 0;
     if (i < B.n_seq) {
       uint32_t flags = 0;
-      v = shape_tiles(P, seq_shape(P, i, flags));
+      v = shape_tiles(P, seq_shape(P, i, flags), P.ncb);
       if (flags) atomicOr(P.header + kHdrStatus, flags);
     }
     if (P.tf_cache == 2) break;  // (one round: every workgroup of the attention kernel scans for itself)
@@ -1774,13 +1775,25 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
 // and the workgroup of the last item -- the first tile of a head, its shortest -- judges the call as a whole when it is
 // done: every length and chunk, and every block-table entry that the sequences with new tokens reach.
 constexpr int kBlocks256 = 4;    // ... and of its item at head_dim 256
-// Small launches over tables of at least this many tokens deal the context to two groups of waves, or four where even items of
-// four blocks all find a compute unit (the host does not know the lengths; a short prompt behind a wide table pays the merge,
-// 2 - 2.7 us).  us, items of 8 blocks whose waves all walk the whole context -> groups: 3 x 100 new tokens behind 3000 - 7000,
-// FP8, 8 KV heads x 4 of 128, 137 -> 83; 4 x 33 behind 2049 - 7581, INT4, 40 heads, 129 -> 115; 2 x 200 behind 3000, INT8,
-// head_dim 64, 53 -> 40; 2 x 100 FP16 tokens behind 1024 30.6 -> 26.3, behind 800 26.2 -> 24.9; but whole prompts of 777, 400
-// and 300 25.0 -> 27.2, 15.9 -> 18.6, 14.5 -> 16.8.
-constexpr int64_t kGroupContext = 1024;
+// Small launches with a long context deal it to two groups of waves, or four where even items of four blocks all find a
+// compute unit.  The host does not know the lengths: over tables that can hold contexts long enough it launches the kernel that
+// has both walks, and that kernel's scan of the sequences says which (scan_sequences).  The lines, for the longest sequence with
+// new tokens; us with every launch forced to either side, items of 8 blocks whose waves all walk the whole context -> groups,
+// FP16 / FP8 / INT8 / INT4, 8 KV heads x 4 of 128 unless said otherwise:
+//   four groups: 2 x 100 tokens behind 600 21.4 -> 21.4 (FP16), behind 700 23.7 -> 22.9 / 22.4 -> 20.0 / 26.7 -> 23.2 / 25.4 -> 22.9, behind
+//   1024 30.2 -> 26.1 / 28.5 -> 23.6 / 35.0 -> 28.1 / 32.9 -> 27.4; but a prompt of 400 15.9 -> 18.6 / 15.2 -> 16.8 / 17.1 -> 18.6 / 16.5 -> 18.7;
+//   four groups, at most four blocks of columns a sequence, which leave half the waves of the other walk idle: 6 x 16 tokens
+//   behind 700 20.0 -> 23.8 / 19.9 -> 20.8 / 21.9 -> 23.8 / 21.5 -> 23.6, 1024 25.0 -> 27.9 / 25.3 -> 24.1 / 29.4 -> 29.1 / 27.7 -> 28.0, 2048
+//   42.2 -> 43.1 / 45.4 -> 35.8 / 52.6 -> 47.4 / 48.7 -> 43.8, 3072 59.3 -> 58.1 / 64.8 -> 48.1 / ...; FP16 at head_dim 64 (16 heads) 1024
+//   21.0 -> 19.3;
+//   two groups: a prompt of 777 24.9 -> 27.0 (FP16), 2 x 300 behind 1024 30.7 -> 32.5 / 28.8 -> 29.5 / 35.3 -> 34.7 / 33.2 -> 33.3, 1536
+//   42.2 -> 42.7 / 39.3 -> 38.3 / 49.4 -> 46.9 / 46.2 -> 44.3, 2048 53.5 -> 52.7 / 49.8 -> 47.1 / 63.7 -> 58.8 / 59.1 -> 55.3.
+// (The walk without groups is up to 5 % slower in that kernel than in its own for FP8 and INT4 -- a prompt of 400 tokens 14.8 ->
+// 15.2, 15.8 -> 16.6 -- and the same for the others.)
+constexpr int group_context(int kv_shift, int dtype, bool d64, bool few_columns) {
+  if (kv_shift == 1) return dtype == FS_KV_FP16 ? 2048 : dtype == FS_KV_FP8_E4M3 ? 1536 : 1024;
+  return !few_columns ? 640 : dtype == FS_KV_FP16 && !d64 ? 3072 : 1024;
+}
 constexpr int kSmallBlocks = 8;  // column blocks of the workgroup kernel's smaller item
 // The launch's sequences in LDS, where every item's look-ups find them: longest context first, so that the queue ends
 // with the shortest items (in the order of the call, 12 INT4 multi-head prompts of 300 - 3000 tokens left the workgroups
@@ -1799,7 +1812,10 @@ __device__ __forceinline__ SeqList seq_list(void* lds, int n_seq) {
 constexpr uint32_t seq_list_bytes(int n_seq) { return (5u * (uint32_t)n_seq + 1) * 4; }
 
 // Fills the list (n_seq <= threads of the workgroup); returns the number of query tiles.  s_tmp: n_seq + 16 words.
-__device__ __forceinline__ uint32_t scan_sequences(const PrefillArgs& P, const SeqList& L, uint32_t* s_tmp) {
+// GROUPS: *s_long says whether some sequence with new tokens is long enough for groups of waves; if none is, the tiles are
+// those of items of kSmallBlocks (never more than the host counted).
+template <bool GROUPS>
+__device__ __forceinline__ uint32_t scan_sequences(const PrefillArgs& P, const SeqList& L, uint32_t* s_tmp, uint32_t* s_long) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = P.b.n_seq;
   uint32_t* s_wave = s_tmp + n;
   SeqShape s{0, 0, 0};
@@ -1807,12 +1823,18 @@ __device__ __forceinline__ uint32_t scan_sequences(const PrefillArgs& P, const S
     if (wave == 0) {
       uint32_t flags = 0;
       if (lane < n) s = seq_shape(P, lane, flags);
+      int ncb = P.ncb;
+      if constexpr (GROUPS) {
+        const bool grouped = __ballot(s.n_new > 0 && s.len >= P.group_len) != 0;
+        if (lane == 0) *s_long = grouped;
+        ncb = grouped ? ncb : kSmallBlocks;
+      }
       int rank = 0;
       for (int i = 0; i < n; ++i) {
         const int l = __builtin_amdgcn_readlane(s.len, i);
         rank += l > s.len || (l == s.len && i < lane);
       }
-      const uint32_t v = lane < n ? shape_tiles(P, s) : 0u;
+      const uint32_t v = lane < n ? shape_tiles(P, s, ncb) : 0u;
       uint32_t first = 0;  // tiles of the longer sequences
       for (int i = 0; i < n; ++i) {
         const uint32_t r = __builtin_amdgcn_readlane(rank, i), u = __builtin_amdgcn_readlane(v, i);
@@ -1835,13 +1857,19 @@ __device__ __forceinline__ uint32_t scan_sequences(const PrefillArgs& P, const S
   }
   __syncthreads();
   if (tid < n) {
-    int rank = 0;
+    int rank = 0, ncb = P.ncb;
+    bool grouped = false;
     for (int i = 0; i < n; ++i) {
       const int l = L.shape[i].len;
       rank += l > s.len || (l == s.len && i < tid);
+      if constexpr (GROUPS) grouped |= L.shape[i].n_new > 0 && l >= P.group_len;
+    }
+    if constexpr (GROUPS) {
+      if (tid == 0) *s_long = grouped;
+      ncb = grouped ? ncb : kSmallBlocks;
     }
     L.seq[rank] = tid;
-    s_tmp[rank] = shape_tiles(P, s);
+    s_tmp[rank] = shape_tiles(P, s, ncb);
   }
   __syncthreads();
   uint32_t incl = tid < n ? s_tmp[tid] : 0u;
@@ -1878,74 +1906,63 @@ __device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_
   if (threadIdx.x == 0) P.header[kHdrStatus] = *s_flags;
 }
 
-// WPC = workgroups per compute unit the kernel is built for
-template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false, bool GROUPS = false>
-__global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
-  extern __shared__ uint64_t smem64[];
-  uint8_t* smem = reinterpret_cast<uint8_t*>(smem64);
-  uint64_t* s_tab = reinterpret_cast<uint64_t*>(smem + 2 * stage_bytes(SUBS, HD));
-  uint32_t* s_ctl = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8);
+// What a workgroup knows of the launch, and where its shared memory is.
+struct WgLaunch {
+  uint8_t* smem;           // two stages
+  uint64_t* s_tab;         // block-address table
+  uint32_t* s_ctl;         // kWgCtlBytes
+  uint32_t* header;        // where a block-table entry outside the pool is reported
+  const uint32_t* tf;      // first query tile of the k-th sequence
+  SeqList list;            // (listed)
+  uint32_t total;          // work items
+  bool listed, direct;
+  int wave, lane;
+};
+
+// The workgroup's work items.
+template <int DT, int NW, int NCB, int SUBS, bool PIPE, bool DEQ, int HD, bool SUM32, bool GROUPS>
+__device__ __forceinline__ void run_items(const PrefillArgs& P, const WgLaunch& W
+#ifdef FS_TIMELINE
+                                          , uint64_t& tl_items
+#endif
+) {
   const DevBatch& B = P.b;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t H = (uint32_t)B.g.H;
-  uint32_t* s_tf = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
-  const bool direct = !PIPE && P.direct;  // (uniform)
-  uint32_t* const header = direct ? P.header + kHdrIgnored - kHdrStatus : P.header;
-  const uint32_t* tf = P.tile_first;
-  uint32_t total;
-  const SeqList list = seq_list(s_tf, B.n_seq);
-  const bool listed = !PIPE && P.tf_cache == 2;  // (uniform; always so in a direct launch)
-  if (listed) {
-    total = __builtin_amdgcn_readfirstlane(scan_sequences(P, list, reinterpret_cast<uint32_t*>(smem))) * H;
-    tf = list.tf;
-  } else {
-    total = P.tile_first[B.n_seq] * H;
-    if (P.tf_cache) {  // (uniform)
-      for (int i = threadIdx.x; i <= B.n_seq; i += NW * 64) s_tf[i] = P.tile_first[i];
-      __syncthreads();
-      tf = s_tf;
-    }
-  }
   // direct: consecutive items, which stream the same keys and values, on one XCD (workgroups are dealt to the XCDs in
   // turn); workgroup b takes items (b % 8) per + b / 8, + slots, ... of its XCD's share
-  const uint32_t per = (total + 7) / 8, slots = gridDim.x >> 3;  // (the host launches a multiple of eight)
+  const uint32_t per = (W.total + 7) / 8, slots = gridDim.x >> 3;  // (the host launches a multiple of eight)
   uint32_t u = blockIdx.x >> 3;
-#ifdef FS_TIMELINE
-  const uint64_t tl_start = wall_clock64();
-  uint64_t tl_items = 0;
-#endif
   ItemDraw d{0u, 0u};
   SeqHeld held;
   uint32_t turn = 0;
-  if (wave == 0 && !direct) d = first_draw(P.header, blockIdx.x >> 3, lane);
+  if (W.wave == 0 && !W.direct) d = first_draw(P.header, blockIdx.x >> 3, W.lane);
   for (;;) {
 #ifdef FS_TIMELINE
     const uint64_t tl_top = wall_clock64();
 #endif
     uint32_t item;
-    if (direct) {
+    if (W.direct) {
       item = P.by_tile ? 8 * u + (blockIdx.x & 7) : (blockIdx.x & 7) * per + u;
-      if (u >= per || item >= total) break;
+      if (u >= per || item >= W.total) break;
       u += slots;
     } else {
-      if (wave == 0) {  // one wave draws for the workgroup
-        const bool ok = next_item(d, P.header, total, (uint32_t)P.chunk_shift, lane, item);
-        if (lane == 0) s_ctl[turn] = ok ? item : 0xffffffffu;
+      if (W.wave == 0) {  // one wave draws for the workgroup
+        const bool ok = next_item(d, P.header, W.total, (uint32_t)P.chunk_shift, W.lane, item);
+        if (W.lane == 0) W.s_ctl[turn] = ok ? item : 0xffffffffu;
       }
       __syncthreads();
       // (an LDS load is not uniform to the compiler; the next draw writes the other word, the one after it lies behind
       // a barrier that every wave passes with this item in hand)
-      item = __builtin_amdgcn_readfirstlane(s_ctl[turn]);
+      item = __builtin_amdgcn_readfirstlane(W.s_ctl[turn]);
       turn ^= 1;
       if (item == 0xffffffffu) break;
     }
     int seq, head, qt;
-    const int found = P.by_tile ? fs::decode_item_by_tile(tf, B.n_seq, item, H, seq, head, qt) : decode_item(P, tf, item, H, seq, head, qt);
+    const int found = P.by_tile ? fs::decode_item_by_tile(W.tf, B.n_seq, item, H, seq, head, qt) : decode_item(P, W.tf, item, H, seq, head, qt);
     if (!__builtin_amdgcn_readfirstlane(found)) continue;  // (uniform, so that what lives across items stays scalar)
     uint32_t unused = 0;
-    seq = __builtin_amdgcn_readfirstlane(listed ? list.seq[seq] : seq);
-    SeqShape shape = listed ? list.shape[seq] : seq_shape(P, seq, unused);
+    seq = __builtin_amdgcn_readfirstlane(W.listed ? W.list.seq[seq] : seq);
+    SeqShape shape = W.listed ? W.list.shape[seq] : seq_shape(P, seq, unused);
     shape.len = __builtin_amdgcn_readfirstlane(shape.len);
     shape.n_new = __builtin_amdgcn_readfirstlane(shape.n_new);
     shape.q0 = __builtin_amdgcn_readfirstlane(shape.q0);
@@ -1956,8 +1973,8 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
 #ifdef FS_TIMELINE
     const uint64_t tl_begin = wall_clock64();
 #endif
-    if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
-    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32, GROUPS>(P, header, seq, shape, head, qt, smem, s_tab, wave, held);
+    if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, W.smem, W.s_tab, W.wave);
+    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32, GROUPS>(P, W.header, seq, shape, head, qt, W.smem, W.s_tab, W.wave, held);
 #ifdef FS_TIMELINE
     ++tl_items;
     if (threadIdx.x == 0 && item < kPfTimelineItems) {
@@ -1969,9 +1986,55 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
     }
 #endif
   }
-  if (direct) {
-    const uint32_t last = total ? total - 1 : 0u, n = total ? per : 1u;
-    if (blockIdx.x == (P.by_tile ? last % gridDim.x : (last % n % slots) * 8 + last / n)) direct_status<NW * 64>(P, reinterpret_cast<uint32_t*>(smem));
+}
+
+// WPC = workgroups per compute unit the kernel is built for.  GROUPS: the groups' items, or -- where the scan finds no context
+// long enough -- those of the small launches' kernel, one block per wave.
+template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false, bool GROUPS = false>
+__global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
+  extern __shared__ uint64_t smem64[];
+  const DevBatch& B = P.b;
+  WgLaunch W;
+  W.smem = reinterpret_cast<uint8_t*>(smem64);
+  W.s_tab = reinterpret_cast<uint64_t*>(W.smem + 2 * stage_bytes(SUBS, HD));
+  W.s_ctl = reinterpret_cast<uint32_t*>(W.smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8);
+  W.lane = threadIdx.x & 63;
+  W.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t H = (uint32_t)B.g.H;
+  uint32_t* s_tf = reinterpret_cast<uint32_t*>(W.smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
+  W.direct = GROUPS || (!PIPE && P.direct);  // (uniform)
+  W.header = W.direct ? P.header + kHdrIgnored - kHdrStatus : P.header;
+  W.tf = P.tile_first;
+  W.list = seq_list(s_tf, B.n_seq);
+  W.listed = GROUPS || (!PIPE && P.tf_cache == 2);  // (uniform; always so in a direct launch)
+  if (W.listed) {
+    W.total = __builtin_amdgcn_readfirstlane(scan_sequences<GROUPS>(P, W.list, reinterpret_cast<uint32_t*>(W.smem), W.s_ctl)) * H;
+    W.tf = W.list.tf;
+  } else {
+    W.total = P.tile_first[B.n_seq] * H;
+    if (P.tf_cache) {  // (uniform)
+      for (int i = threadIdx.x; i <= B.n_seq; i += NW * 64) s_tf[i] = P.tile_first[i];
+      __syncthreads();
+      W.tf = s_tf;
+    }
+  }
+#ifdef FS_TIMELINE
+  const uint64_t tl_start = wall_clock64();
+  uint64_t tl_items = 0;
+#define FS_TL_ITEMS , tl_items
+#else
+#define FS_TL_ITEMS
+#endif
+  if constexpr (GROUPS) {
+    if (__builtin_amdgcn_readfirstlane(W.s_ctl[0])) run_items<DT, NW, NCB, SUBS, PIPE, DEQ, HD, SUM32, true>(P, W FS_TL_ITEMS);
+    else run_items<DT, NW, 1, SUBS, PIPE, DEQ, HD, SUM32, false>(P, W FS_TL_ITEMS);
+  } else {
+    run_items<DT, NW, NCB, SUBS, PIPE, DEQ, HD, SUM32, false>(P, W FS_TL_ITEMS);
+  }
+#undef FS_TL_ITEMS
+  if (W.direct) {
+    const uint32_t last = W.total ? W.total - 1 : 0u, per = (W.total + 7) / 8, slots = gridDim.x >> 3, n = W.total ? per : 1u;
+    if (blockIdx.x == (P.by_tile ? last % gridDim.x : (last % n % slots) * 8 + last / n)) direct_status<NW * 64>(P, reinterpret_cast<uint32_t*>(W.smem));
   }
 #ifdef FS_TIMELINE
   if (threadIdx.x == 0 && blockIdx.x < kPfTimelineGroups) {
@@ -2073,7 +2136,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   int ncb = !scale_ok || (g.head_dim != kD && !d64 && !d256) ? 1 : (ncb_env ? ncb_env : 16);
   if (d256 && ncb == 16) ncb = kBlocks256;
   uint64_t tiles = 0;
-  int kv_shift = 0;
+  int kv_shift = 0, group_len = 0;
   auto count_tiles = [&](int blocks) {
     tiles = 0;
     for (int b = 0; b < n_seq; ++b) {
@@ -2098,11 +2161,16 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     // heads: 29 us)
     if (tiles * (uint64_t)g.n_kv_heads <= (uint64_t)p->n_cu) ncb = d64 && tiles * (uint64_t)g.n_kv_heads < 64 ? 1 : kSmallBlocks;
     if (ncb != kSmallBlocks) (void)count_tiles(ncb);
-    else if ((int64_t)max_blocks * g.tokens_per_block >= kGroupContext) {
+    else if (n_seq <= 8 * 64) {  // (the workgroups list the sequences)
       const uint64_t at8 = tiles;
       (void)count_tiles(kSmallBlocks / 2);
-      if (tiles * (uint64_t)g.n_kv_heads <= (uint64_t)p->n_cu) kv_shift = 2, ncb = kSmallBlocks / 2;
-      else tiles = at8, kv_shift = 1;
+      const int shift = tiles * (uint64_t)g.n_kv_heads <= (uint64_t)p->n_cu ? 2 : 1;
+      int most = 0;
+      for (int b = 0; b < n_seq; ++b) most = std::max(most, q_offsets_host[b + 1] - q_offsets_host[b]);
+      group_len = group_context(shift, g.kv_dtype, d64, most <= 4 * tpt);
+      if ((int64_t)max_blocks * g.tokens_per_block >= group_len) kv_shift = shift;
+      if (kv_shift == 2) ncb = kSmallBlocks / 2;
+      else tiles = at8;
     }
   }
   // head_dim 256: the workgroup kernel, one wave per SIMD, for FP16 and for launches of no more items than compute units
@@ -2179,6 +2247,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   P.tpt = tpt;
   P.ncb = ncb;
   P.kv_shift = kv_shift;
+  P.group_len = group_len;
   P.seg_runs = prefill_seg_runs(B.R);
   P.seg_tokens = prefill_seg_tokens(g.tokens_per_block);
   P.t_magic = token_magic(g.tokens_per_block);

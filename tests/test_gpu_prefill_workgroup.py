@@ -226,6 +226,44 @@ def test_context_groups(dtype, head_dim, kv_heads, group, n_new):
         par.close()
 
 
+@pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
+@pytest.mark.parametrize("head_dim,kv_heads,lens,n_new", [(128, 8, [777], [777]), (128, 8, [400, 63], [400, 63]), (64, 16, [500], [300]),
+                                                          (128, 4, [880, 40], [40, 7]), (128, 1, [150] + [30] * 99, [60] + [30] * 99)])
+def test_short_contexts_behind_a_wide_table(dtype, head_dim, kv_heads, lens, n_new):
+    """Short prompts and chunks take the walk without groups of waves however long a context the table could hold: the very
+    results of the same call over a table that just fits."""
+    import torch
+
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    lens, n_new, group = np.array(lens, np.int32), np.array(n_new, np.int32), 4
+    slab = kv_heads * head_dim * 2 * 70  # 35 to 140 tokens
+    gw = gpu_workload.GpuWorkload(Workload("pfwide", slab, slab * 400, [ModelSpec("m", dtype, kv_heads, head_dim, 1, kv_heads * group, lens, tag=53,
+                                                                                          src_f32=dtype == INT4)], "shuffle"), zero_pool=True)
+    try:
+        gw.place()
+        gw.populate([[0]])
+        m, T = gw.model_ids[0], gw.geom[gw.model_ids[0]].tokens_per_block
+        off = np.concatenate([[0], np.cumsum(n_new)]).astype(np.int32)
+        q = torch.randn((int(off[-1]), kv_heads * group, head_dim), generator=torch.Generator(device="cuda").manual_seed(9), device="cuda", dtype=torch.float16)
+        ws = torch.empty(fs.fs_prefill_workspace_bytes(len(lens)), dtype=torch.uint8, device="cuda")
+        narrow = gw.tables[0].contiguous()
+        wide = torch.zeros((len(lens), 32768 // T), dtype=torch.int32, device="cuda")
+        wide[:, : narrow.shape[1]] = narrow
+        assert narrow.shape[1] * T < 1024
+        got = []
+        for table in (narrow, wide):
+            out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
+            fs.fs_prefill_attention(gw.pool, m, 0, kv_heads * group, 0.1, q, table, gw.seq_lens[0], torch.from_numpy(off).cuda(), off, out, lse, ws)
+            assert fs.fs_decode_status(ws) == 0 and fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) & 0xffff == (8 | 8 << 8)
+            got.append((out, lse))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+        assert bool(got[0][0].ne(0).any(-1).all())
+    finally:
+        gw.close()
+
+
 @pytest.mark.parametrize("head_dim,kv_heads", [(128, 8), (64, 24)])
 def test_infinite_value_with_context_groups(head_dim, kv_heads):
     """The rows of blocks in front of the token that holds an Inf are what they are without it, with groups of waves too."""
