@@ -2367,7 +2367,8 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return device_error(e, "prefill LDS attribute");
     const bool deq_used = deq && (g.kv_dtype == FS_KV_INT8 || g.kv_dtype == FS_KV_INT4);
-    p->opt.last_prefill = (kv_shift ? kSmallBlocks : std::min(ncb, 16)) | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
+    p->opt.last_prefill = (kv_shift ? kSmallBlocks : std::min(ncb, 16)) | (nw << 8) | ((int64_t)deq_used << 16) |
+                          ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17) | ((int64_t)kv_shift << 19) | ((int64_t)(ncb == 24 ? 1 : ncb == 32 ? 2 : 0) << 21);
     hipLaunchKernelGGL(kern, dim3(n_wg), dim3(nw * 64), smem, s, P);
   } else if (ncb == 1) {
     p->opt.last_prefill = 1;

@@ -130,8 +130,8 @@ def test_infinite_last_value_in_large_launches(dtype, T, monkeypatch):
 
     monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 16})
     n, H, group = 700, 2, 4
-    bits, par = {FP16: (16, 0), INT8: (8, 2), INT4: (4, 4)}[dtype]
-    slab = -(-T * 2 * H * (128 * bits // 8 + par) // 256) * 256 + 256 * H
+    par = {FP16: 0, INT8: 2, INT4: 4}[dtype]
+    slab = -(-fs.fs_block_bytes(dtype, H, 128, 1, T) // 256) * 256
     gw = gpu_workload.GpuWorkload(Workload("pfinfl", slab, slab * 200, [ModelSpec("m", dtype, H, 128, 1, H * group, np.array([n], np.int32), tag=52,
                                                                                   src_f32=dtype == INT4)], "shuffle"), zero_pool=True)
     try:
@@ -150,7 +150,7 @@ def test_infinite_last_value_in_large_launches(dtype, T, monkeypatch):
 
         out0, lse0 = run()
         t, tpb = n - 1, g.tokens_per_block
-        print("T", tpb)
+        assert tpb == T
         block = int(gw.tables_host[0][0, t // tpb]) * g.block_budget
         at = block + (g.kv_tile + (t % tpb) * g.row_bytes if dtype == FP16 else 2 * g.kv_tile + g.par_tile + (t % tpb) * par)  # KV head 0
         gw.pool_mem[at: at + 2] = torch.tensor([0x00, 0x7C], dtype=torch.uint8, device="cuda")
@@ -206,24 +206,92 @@ def test_small_launches(dtype, head_dim, kv_heads, group):
         par.close()
 
 
+def _groups(kernel):
+    """log2 of the groups of waves that the launch may deal contexts to; the kernel is that of the small launches."""
+    assert kernel & ~(3 << 19) == (8 | 8 << 8), kernel
+    return kernel >> 19 & 3
+
+
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
-@pytest.mark.parametrize("head_dim,kv_heads,group,n_new", [(128, 8, 4, [100, 16, 0, 70]), (128, 8, 1, [33, 200, 40, 5]), (128, 6, 4, [300, 40, 40, 1]),
-                                                           (64, 16, 4, [64, 17, 40, 3]), (64, 12, 8, [90, 30, 40, 33])])
-def test_context_groups(dtype, head_dim, kv_heads, group, n_new):
+@pytest.mark.parametrize("head_dim,kv_heads,group,n_new,shift", [(128, 8, 4, [100, 16, 0, 70], 2), (128, 8, 1, [33, 200, 40, 5], 2), (128, 6, 4, [300, 40, 40, 1], 2),
+                                                                 (64, 16, 4, [64, 17, 40, 3], 2), (64, 12, 8, [90, 30, 40, 33], 1), (128, 12, 8, [90, 30, 40, 33], 1)])
+def test_context_groups(dtype, head_dim, kv_heads, group, n_new, shift):
     """Small launches behind long contexts: two and four groups of waves per context (items of 8 and 4 blocks), sequences
     of less than a step, a group without tokens, ragged items."""
     import gpu_harness
     import paper_2509_06261_amd as fs
 
-    lens = np.array([1500, 1111, 40, 260], np.int32)
+    lens = np.array([1500 if shift == 2 else 2060, 1111, 40, 260], np.int32)
     wl = Workload("pfgrp", 160 * KiB, 160 * 600 * KiB, [ModelSpec("m", dtype, kv_heads, head_dim, 1, kv_heads * group, lens, tag=50, src_f32=dtype == INT4)], "shuffle")
     par = gpu_harness.Parity(wl, zero_pool=True)
     try:
         par.gw.populate([[0]])
         print(par.prefill_and_check(0, 0, np.array(n_new, np.int32)))
-        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
+        assert _groups(fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)) == shift
     finally:
         par.close()
+
+
+@pytest.mark.parametrize("dtype,T,shift", [(FP16, 9, 2), (INT8, 13, 2), (INT4, 60, 2), (FP16, 13, 1), (FP8, 9, 1), (INT4, 11, 1), (FP16, 13, 0), (FP8, 9, 0),
+                                           (INT8, 11, 0), (INT4, 60, 0)])
+def test_several_table_segments_of_odd_blocks(dtype, T, shift, monkeypatch):
+    """Contexts of two and three table segments whose blocks are no multiple of eight tokens: segments that begin inside a
+    block, the refilled table, the last segment's end; in two and four groups of waves and in the 16-block kernel (0)."""
+    import gpu_harness
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    if shift == 0:
+        monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 16})
+    segment = min(500 * T // 128 * 128, 8192)
+    # (two groups: one new token more than four blocks hold in every sequence, tiles enough for every unit but in halves)
+    lens, n_new, heads, group = {0: ([2 * segment + 77, segment + 1], [70, 33], 2, 4), 1: ([2 * segment + 77, segment + 3] + [40] * 15, [5] * 17, 8, 9),
+                                 2: ([2 * segment + 77, segment + 1], [40, 18], 4, 4)}[shift]
+    lens = np.array(lens, np.int32)
+    slab = -(-fs.fs_block_bytes(dtype, heads, 128, 1, T) // 256) * 256
+    wl = Workload("pfseg", slab, slab * int((-(-lens // T)).sum() + 20),
+                  [ModelSpec("m", dtype, heads, 128, 1, heads * group, lens, tag=54, src_f32=dtype == INT4)], "shuffle")
+    p = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        assert p.gw.T[p.gw.model_ids[0]] == T
+        p.gw.populate([[0]])
+        print(p.prefill_and_check(0, 0, np.array(n_new, np.int32)))
+        ran = fs.fs_pool_get_option(p.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)
+        assert _groups(ran) == shift if shift else ran & 0xffff == (16 | 8 << 8)
+    finally:
+        p.close()
+
+
+def test_contexts_are_dealt_to_groups_by_their_lengths():
+    """A chunk behind 3000 tokens: its kernel has groups of waves and uses them (other roundings than the walk without, which
+    the same chunk takes among more sequences than a workgroup lists)."""
+    import torch
+
+    import gpu_workload
+    import paper_2509_06261_amd as fs
+
+    n_new, H, group = 40, 8, 4
+    gw = gpu_workload.GpuWorkload(Workload("pfdeal", 256 * KiB, 256 * 300 * KiB, [ModelSpec("m", FP16, H, 128, 1, H * group, np.array([3000], np.int32), tag=55)], "shuffle"),
+                                  zero_pool=True)
+    try:
+        gw.place()
+        gw.populate([[0]])
+        q = torch.randn((n_new, H * group, 128), generator=torch.Generator(device="cuda").manual_seed(10), device="cuda", dtype=torch.float16)
+        got = []
+        for n_seq, groups in ((1, 2), (600, 0)):
+            off = np.full(n_seq + 1, n_new, np.int32)
+            off[0] = 0
+            ws = torch.empty(fs.fs_prefill_workspace_bytes(n_seq), dtype=torch.uint8, device="cuda")
+            table, lens = gw.tables[0].repeat(n_seq, 1), gw.seq_lens[0].repeat(n_seq)
+            out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
+            fs.fs_prefill_attention(gw.pool, gw.model_ids[0], 0, H * group, 0.1, q, table, lens, torch.from_numpy(off).cuda(), off, out, lse, ws)
+            assert fs.fs_decode_status(ws) == 0 and _groups(fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)) == groups
+            got.append(out.float())
+        # (values of N(0, 1) averaged: below 4, so two results each within 2^-11 of a weight's rounding and the output's)
+        diff = (got[0] - got[1]).abs().max().item()
+        assert 0 < diff < 2 * 4 * 2.0 ** -10, diff
+    finally:
+        gw.close()
 
 
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
@@ -264,15 +332,15 @@ def test_short_contexts_behind_a_wide_table(dtype, head_dim, kv_heads, lens, n_n
         gw.close()
 
 
-@pytest.mark.parametrize("head_dim,kv_heads", [(128, 8), (64, 24)])
-def test_infinite_value_with_context_groups(head_dim, kv_heads):
+@pytest.mark.parametrize("head_dim,kv_heads,length,shift", [(128, 8, 1400, 2), (64, 24, 1400, 2), (128, 48, 2200, 1)])
+def test_infinite_value_with_context_groups(head_dim, kv_heads, length, shift):
     """The rows of blocks in front of the token that holds an Inf are what they are without it, with groups of waves too."""
     import torch
 
     import gpu_workload
     import paper_2509_06261_amd as fs
 
-    lens, n_new, group = np.array([1400], np.int32), 90, 4
+    lens, n_new, group = np.array([length], np.int32), 90, 4
     gw = gpu_workload.GpuWorkload(Workload("pfgi", 512 * KiB, 512 * 200 * KiB,
                                            [ModelSpec("m", FP16, kv_heads, head_dim, 1, kv_heads * group, lens, tag=51)], "shuffle"), zero_pool=True)
     try:
@@ -286,19 +354,19 @@ def test_infinite_value_with_context_groups(head_dim, kv_heads):
         def run():
             out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
             fs.fs_prefill_attention(gw.pool, m, 0, kv_heads * group, 0.1, q, gw.tables[0], gw.seq_lens[0], torch.from_numpy(off).cuda(), off, out, lse, ws)
-            assert fs.fs_decode_status(ws) == 0 and fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
+            assert fs.fs_decode_status(ws) == 0 and _groups(fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)) == shift
             return out, lse
 
         out0, lse0 = run()
         T = g.tokens_per_block
-        for t in (1311, 1337, 1398):
+        for t in (length - 89, length - 63, length - 2):
             at = int(gw.tables_host[0][0, t // T]) * g.block_budget + g.kv_tile + (t % T) * g.row_bytes  # KV head 0, element 0
             part = gw.pool_mem[at: at + 2]
             old = part.clone()
             part.copy_(torch.tensor([0x00, 0x7C], dtype=torch.uint8))
             out, lse = run()
             part.copy_(old)
-            row = t - (1400 - n_new)
+            row = t - (length - n_new)
             assert not torch.isfinite(out[row:, :group, 0]).any(), t
             out[row // 4 * 4:, :group, 0] = out0[row // 4 * 4:, :group, 0]
             assert torch.equal(out, out0) and torch.equal(lse, lse0), t
@@ -307,16 +375,20 @@ def test_infinite_value_with_context_groups(head_dim, kv_heads):
 
 
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
-def test_large_launches_at_head_dim_64(dtype):
-    """Items of 32 and 24 blocks: at least eight of them per compute unit (256 in the card's whole partition)."""
+@pytest.mark.parametrize("group,lens,seqs", [(16, [96] * 40 + [97, 1, 95, 33, 130, 240, 385, 500], [0, 40, 41, 42, 43, 44]), (4, [480] * 12 + [500, 97, 130, 1], [12, 13, 14, 15])])
+def test_large_launches_at_head_dim_64(dtype, group, lens, seqs):
+    """Items of 32 and 24 blocks: at least eight of them per compute unit (256 in the card's whole partition).  (With 16 query heads
+    per KV head the oracle would take most of a minute over the three longest sequences; with four it does the longest.)"""
     import gpu_harness
+    import paper_2509_06261_amd as fs
 
-    lens = np.concatenate([np.full(40, 96), [97, 1, 95, 33, 130, 240, 385, 500]]).astype(np.int32)
-    wl = Workload("pf64w", 192 * KiB, 192 * 900 * KiB, [ModelSpec("m", dtype, 40, 64, 1, 640, lens, tag=49, src_f32=dtype == INT4)], "shuffle")
+    lens = np.array(lens, np.int32)
+    wl = Workload("pf64w", 192 * KiB, 192 * 900 * KiB, [ModelSpec("m", dtype, 40, 64, 1, 40 * group, lens, tag=49, src_f32=dtype == INT4)], "shuffle")
     par = gpu_harness.Parity(wl, zero_pool=True)
     try:
         par.gw.populate([[0]])
-        print("T", par.gw.T, par.prefill_and_check(0, 0, lens, seqs=np.array([0, 40, 41, 42, 43, 44])))
+        print("T", par.gw.T, par.prefill_and_check(0, 0, lens, seqs=np.array(seqs)))
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (16 | 8 << 8 | (2 if dtype == FP16 else 1) << 21)
     finally:
         par.close()
 
@@ -332,11 +404,11 @@ def test_blocks_of_any_token_count(dtype, T, head_dim, heads, group, large, monk
 
     if large and head_dim == 128:
         monkeypatch.setattr(gpu_workload, "DEFAULT_OPTIONS", {fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 16})
-    bits, par = {FP16: (16, 0), FP8: (8, 0), INT8: (8, 2), INT4: (4, 4)}[dtype]
-    slab = -(-T * 2 * heads * (head_dim * bits // 8 + par) // 256) * 256 + 256 * heads
+    slab = -(-fs.fs_block_bytes(dtype, heads, head_dim, 1, T) // 256) * 256
     wl = Workload("pftok", slab, slab * 600, [ModelSpec("m", dtype, heads, head_dim, 1, heads * group, EDGES, tag=48, src_f32=dtype == INT4)], "shuffle")
     par = gpu_harness.Parity(wl, zero_pool=True)
     try:
+        assert par.gw.T[par.gw.model_ids[0]] == T
         par.gw.populate([[0]])
         print("T", par.gw.T, par.prefill_and_check(0, 0, EDGES), par.prefill_and_check(0, 0, np.minimum(EDGES, CHUNKS)))
         assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) >> 8 & 255 in (4, 8) or head_dim == 256
