@@ -125,9 +125,8 @@ def _load():
 _L = _load()
 try:
     from . import _fsfast
-except ImportError as e:
-    raise ImportError("paper_2509_06261_amd/_fsfast.so is missing: build it with __graft_entry__.build() "
-                      "(python paper_2509_06261_amd/build.py); there is no fallback path") from e
+except ImportError:  # (not built for this interpreter: every call goes through ctypes)
+    _fsfast = None
 
 
 class FsError(RuntimeError):
@@ -170,8 +169,7 @@ _fast = _NotYet
 def _slow():
     """What a call that the native marshaling did not take begins with: tries to bring it up for the next ones."""
     global _fast
-    if _fast is _NotYet:
-        import torch
+    if _fast is _NotYet and _fsfast is not None:
         if torch.cuda.is_initialized():
             at = [ctypes.cast(getattr(_L, f), ctypes.c_void_p).value for f in
                   ("fs_kv_append", "fs_kv_append_multi", "fs_decode_attention", "fs_decode_attention_multi", "fs_decode_step_multi")]

@@ -111,3 +111,24 @@ assert binding._fast is binding._NotYet and binding._slow.__name__ == "_slow"
 """
     p = subprocess.run([sys.executable, "-c", code, __file__], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), capture_output=True, text=True, timeout=300)
     assert p.returncode == 0, p.stdout[-2000:] + p.stderr[-2000:]
+
+
+def test_package_without_the_module():
+    """Not built for the interpreter, the module is done without: every call goes through ctypes."""
+    code = """
+import ctypes, sys
+if sys.argv[1] == "without":
+    sys.modules["paper_2509_06261_amd._fsfast"] = None
+import paper_2509_06261_amd as fs
+from paper_2509_06261_amd import binding
+assert (binding._fsfast is None) == (sys.argv[1] == "without")
+try:
+    fs.fs_kv_append_multi(None, [binding.fs_append_t()], stream=0)
+    raise SystemExit("a call without a pool was taken")
+except fs.FsError:
+    pass
+assert binding._fast is binding._NotYet
+"""
+    for which in ("with", "without"):
+        p = subprocess.run([sys.executable, "-c", code, which], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), capture_output=True, text=True, timeout=300)
+        assert p.returncode == 0, which + p.stdout[-2000:] + p.stderr[-2000:]
