@@ -2154,7 +2154,10 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // those items all find a compute unit of their own: twice the units work, and a step takes little more than half the
   // time.  A prompt of 777 tokens, 8 KV heads x 4 of 128: 66 us in the 16-column kernel that served launches with fewer
   // items than compute units before, 27.5 us with 8 blocks (200 items); one of 1500 tokens: 137 us, 75 with 8 blocks
-  // (376 items: some units take two), 60 with 16 (188 items).
+  // (376 items: some units take two), 60 with 16 (188 items).  (us, items of 16 -> of 8, FP16 / FP8 / INT4: one of 777 34.4 -> 24.4 / 31.7 ->
+  // 23.0 / 36.4 -> 25.5, of 1000 41.3 -> 30.0 / 38.0 -> 28.3 / 44.1 -> 31.5; past an item of 8 per unit: of 1040 42.7 -> 34.0 / 39.0 -> 32.7 / 45.3 ->
+  // 35.6, of 1200 47.7 -> 47.0 / 43.4 -> 44.2 / 51.6 -> 49.1, of 1750 65.3 -> 71.0 / 59.6 -> 67.4 / 71.5 -> 75.0, 4 of 400 24.7 -> 31.1 / 23.2 ->
+  // 29.2 / 25.2 -> 31.3, 24 chunks of 64 behind 2000 85 -> 120 / 73 -> 104 / 87 -> 116.)
   if (ncb == 16 && !ncb_env && tiles * (uint64_t)g.n_kv_heads < (uint64_t)p->n_cu) {
     (void)count_tiles(kSmallBlocks);
     // (head_dim 64: too few items to matter stay with the 16-column kernel; two prompts of 100 and 600 tokens with 4 KV
@@ -2185,9 +2188,10 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   }
   // head_dim 64: items of 32 blocks (FP16) or 24 (the other formats, whose staging needs the registers), four or three per
   // wave, where there are at least eight per compute unit and they are as full as those of 16: half or two thirds of the
-  // staging and of the operand reads per product, but 1.65 or 1.35 times an item.  us: 24 FP16 prompts of 256 - 3000 tokens,
-  // GQA 4:1, 571 -> 541, INT8 ones 655 -> 610; 6 FP16 prompts of 6000 - 12000 2900 -> 2636; but 9 of 300 - 2500 (3 items of 32
-  // blocks per unit) 189 -> 213, 64 chunks of 64 tokens (half-empty items) 132 -> 152.
+  // staging and of the operand reads per product, but 1.65 or 1.35 times an item.  us, 8 heads x 4, items of 16 -> wide ones, prompts of
+  // 256 - 3000 tokens, by wide items per unit: FP16 at 4 268 -> 261, 6 374 -> 369, 8 487 -> 471, 9 552 -> 506, 12 710 -> 647, 16 934 -> 856;
+  // INT8 at 4 251 -> 267, 5 281 -> 302, 6 328 -> 323, 8 429 -> 404, 12 632 -> 596; INT4 at 6 343 -> 334, 8 452 -> 419; FP8 at 6 278 -> 272, 8 358 ->
+  // 344; prompts of 5000 - 12000 at 8 FP16 1791 -> 1693, INT8 1628 -> 1550; 64 chunks of 64 tokens (half-empty items) 132 -> 152.
   if (d64 && ncb == 16 && !ncb_env) {
     const uint64_t at16 = tiles;
     const int wide = g.kv_dtype == FS_KV_FP16 ? 32 : 24;
@@ -2299,11 +2303,15 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   P.chunk_shift = 7;
   while (P.chunk_shift > (int32_t)kWgChunkShift && (items >> P.chunk_shift) < 64) --P.chunk_shift;
   // Where the heads allow it (see decode_item_by_tile) the workgroup kernels take a sequence's tiles longest first over all its
-  // heads, dealt to the XCDs in turn: head by head, a launch's last head began with its longest tile.  us: one FP16 prompt of
-  // 3000 tokens, GQA 4:1, 159 -> 142; four of 1200 at head_dim 64 82 -> 69; two of 800 and 1500 at 256 142 -> 118; 16 x 512 INT8
-  // tokens behind 2000 - 6000 632 -> 585; 4 x 512 FP8 tokens (one item per unit) 420 -> 394; 64 FP16 prompts 3915 -> 3885; two of
-  // 1107 and 2179 114 -> 119, four FP8 ones of 500 - 2000, GQA 8:1, 171 -> 175.
-  P.by_tile = wg && (g.n_kv_heads % 8 == 0 || 8 % g.n_kv_heads == 0);
+  // heads, dealt to the XCDs in turn: head by head, a launch's last head began with its longest tile.  us, head by head -> by
+  // tile: one FP16 prompt of 3000 tokens, GQA 4:1, 155 -> 139; two of 1107 and 2179 124 -> 114; four FP8 ones of 500 - 2000, GQA
+  // 8:1, 194 -> 174; two of 7000 and 8000, 8 / 16 / 40 heads, 1114 -> 968 / 1098 -> 971 / 1449 -> 1309; 12 of 500 - 3500 the same within
+  // 1.5 %; 4 heads: two of 7000 and 8000 594 -> 573, six FP8 ones of 11000 - 16000 4202 -> 4029, 48 of 500 - 3500 1129 -> 1136.
+  // One or two heads put a head's tiles on eight or four XCDs, each of which fetches the context.  That pays while the launch's
+  // end matters: 12 prompts (5 items per unit) 322 -> 314 / 324 -> 323, six FP8 ones of 11000 - 16000 (20) 4116 -> 3993 / 4151 -> 4001;
+  // two of 7000 and 8000 (4) 568 -> 575 / 562 -> 575; but 48 of 500 - 3500 (23) 1105 -> 1120 / 1112 -> 1124 and 24 of 14000 - 16000 (87)
+  // 21045 -> 21929 / 21370 -> 21957.
+  P.by_tile = wg && (g.n_kv_heads % 8 == 0 || g.n_kv_heads == 4 || (g.n_kv_heads <= 2 && items <= 20 * (uint64_t)p->n_cu));
   if (P.by_tile) P.chunk_shift = 0;
   const size_t smem = wg ? 2 * (size_t)stage_bytes(subs, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes +
                                (P.tf_cache == 2 ? seq_list_bytes(n_seq) : P.tf_cache ? (((size_t)n_seq + 1) * 4 + 15) / 16 * 16 : 0)

@@ -187,6 +187,23 @@ def test_many_sequences(head_dim, n_seq, with_tokens, kernel):
         par.close()
 
 
+@pytest.mark.parametrize("kv_heads,n_seq", [(1, 5200), (2, 2500)])
+def test_many_items_of_one_or_two_heads(kv_heads, n_seq):
+    """Either side of 20 items per compute unit (256 in the card's whole partition), where one or two heads' items are
+    ordered head by head and by tile."""
+    import gpu_harness
+
+    lens = np.random.default_rng(n_seq).integers(1, 4, n_seq).astype(np.int32)
+    lens[[7, n_seq - 3]] = [70, 33]
+    wl = Workload("pf1h", 8 * KiB, 8 * KiB * (n_seq + 100), [ModelSpec("m", FP16, kv_heads, 128, 1, 4, lens, tag=57)], "shuffle")
+    par = gpu_harness.Parity(wl, zero_pool=True)
+    try:
+        par.gw.populate([[0]])
+        print(par.prefill_and_check(0, 0, lens))
+    finally:
+        par.close()
+
+
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
 @pytest.mark.parametrize("head_dim,kv_heads,group", [(64, 6, 4), (128, 2, 4), (128, 3, 1)])
 def test_small_launches(dtype, head_dim, kv_heads, group):
