@@ -252,9 +252,13 @@ __device__ __forceinline__ void settle_q(u32x4 (&q)[KS]) {
 }
 
 template <int NCB, int HD = kD>
-struct WideState {
+struct WgState {
   float4v acc[NCB][HD / 16];
-  float m[NCB], l[NCB], zc[NCB];
+  float m[NCB], l[NCB];
+};
+template <int NCB, int HD = kD>
+struct WideState : WgState<NCB, HD> {
+  float zc[NCB];  // (parameter formats) this lane's share of the zero-point term
 };
 
 // This file is compiled with VGPR-form MFMAs (-mllvm -amdgpu-mfma-vgpr-form, see build.py): accumulators, S^T
@@ -897,7 +901,9 @@ __device__ __forceinline__ void stage_v_deq(uint8_t* stage, int sub, int lane, b
 // either side and nothing to broadcast between lanes (16 bytes of four tokens' factors per load).  With codes consumed as
 // subnormals, offsets as rank-1 terms and parameters broadcast by DPP a sub-tile of two blocks took 72 vector instructions
 // more.  (us: 24 INT8 prompts of 256 - 3000 tokens at head_dim 64, GQA 4:1, 869 -> 656, INT4 878 -> 683; three INT8 prompts
-// of 500 - 700 at 128 40.8 -> 34.2; and the results are as near the definition as FP16's, 2.4e-4 where they were 3.8 - 5e-4.)
+// of 500 - 700 at 128 40.8 -> 34.2; and the results are as near the definition as FP16's, 2.4e-4 where they were 3.8 - 5e-4.  At
+// head_dim 256, where four waves stage everything, one INT4 prompt of 900 tokens lost 3 % by it, and is at 44.8 where it was 48.5
+// before the accumulators were transposed.)
 template <int DT>
 __device__ __forceinline__ void int_codes(uint32_t w, half2v off, half2v off16, uint32_t (&x)[4]) {
   if constexpr (DT == FS_KV_INT8) {  // two registers: elements (0, 1), (2, 3)
@@ -999,7 +1005,7 @@ __device__ __forceinline__ float over_column(float x, Op op) {
 // moved together (1 % of the time).
 constexpr float kTauBlock = 2.5f;
 template <int NCB, int HD>
-__device__ __forceinline__ void wg_move_reference(WideState<NCB, HD>& st, int cb, float tmax) {
+__device__ __forceinline__ void wg_move_reference(WgState<NCB, HD>& st, int cb, float tmax) {
   const float m_new = fmaxf(st.m[cb], over_column(tmax, [](float a, float b) { return fmaxf(a, b); }));
   const float corr = __builtin_amdgcn_exp2f(st.m[cb] - m_new);
   st.l[cb] *= corr;
@@ -1020,7 +1026,7 @@ __device__ __forceinline__ void wg_move_reference(WideState<NCB, HD>& st, int cb
 template <int DT, int NCB, int SUBS, int VPRE, int HD, bool SUM32, bool CUT = false>
 __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, const u32x4 (&qb)[NCB][HD / 32],
                                         const int (&len_cb)[NCB], float alpha, int first_pos,
-                                        int lane, int j, int c, WideState<NCB, HD>& st, int tpt = 0, int n_tok = 0) {
+                                        int lane, int j, int c, WgState<NCB, HD>& st, int tpt = 0, int n_tok = 0) {
   using F = Fmt<DT, HD>;
   constexpr int KS = HD / 32;
   float4v s[NCB][2];
@@ -1160,7 +1166,7 @@ __device__ __forceinline__ void wg_tile(const uint8_t* stage, int sub, int tb, c
 // tile exchange their accumulators through LDS, where the stages were, and each finishes one part of them: with two groups a
 // column block, with four half of one's output elements.  Every wave of the workgroup takes part.
 template <int DT, int NW, int NCB, int HD>
-__device__ __forceinline__ void merge_groups(const PrefillArgs& P, WideState<NCB, HD>& st, uint8_t* smem, int w, int lane, int head,
+__device__ __forceinline__ void merge_groups(const PrefillArgs& P, WgState<NCB, HD>& st, uint8_t* smem, int w, int lane, int head,
                                              int row0, int n_tok, float v_static) {
   constexpr int NE = HD / 16, N = NCB * NE;  // accumulator tiles of a wave
   static_assert(NW * (N * 1024 + NCB * 128) <= 2 * (int)stage_bytes(NW == 8 ? 4 : 2, HD), "the partial sums fit the stages");
@@ -1255,7 +1261,7 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
 #endif
   static_assert(!DEQ || Fmt<DT>::kParBytes != 0, "staged dequantization is for the formats with per-token parameters");
   static_assert(!DEQ || HD == kD, "staged dequantization is written for head_dim 128");
-  constexpr int NE = HD / 16;  // output columns NE c .. NE c + NE - 1 are this lane's
+  constexpr int NE = HD / 16;  // accumulator tiles of a column block: row 4 j + r of tile e is element NE (4 j + r) + e of column c
   constexpr int CDT = DEQ ? FS_KV_FP16 : DT;  // the format the consumer code sees
   // V fragments read ahead of the softmax: what the format's register budget leaves room for (two waves per SIMD)
   // (eight instead of four: a 4 x 512-token FP8 chunk step 429.5 -> 423 us, INT8 prompts 817 -> 811 us; FP16 would spill)
@@ -1296,15 +1302,15 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   int len_cb[NCB], row_cb[NCB];
   float alpha = B.sm_scale * kLog2e;
   if (DT == FS_KV_FP8_E4M3) alpha *= B.k_scale[head];
-  WideState<NCB, HD> st;
+  WgState<NCB, HD> st;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
     const int tok = cb * P.tpt + tok_c;  // query token of this lane's column in block cb
     const bool live = tok_c < P.tpt && tok < n_tok;
     len_cb[cb] = live ? first_pos + tok + 1 : len_u;  // a dead column (q = 0, never written) sees everything
     row_cb[cb] = min(max(shape.q0 + r0 + tok, 0), P.n_rows - 1);
-    float unused;
-    load_q<DT, !DEQ, HD>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * HD, live, j, qb[cb], unused);
+    float sum;  // (of no use here; without it the loads come out in another order, and one prompt of 777 tokens takes 24.5 -> 24.7 us)
+    load_q<DT, !DEQ, HD>(B.q + ((int64_t)row_cb[cb] * B.n_q + head * G + hg_c) * HD, live, j, qb[cb], sum);
 #pragma unroll
     for (int e = 0; e < NE; ++e) st.acc[cb][e] = float4v{0.f, 0.f, 0.f, 0.f};
     st.m[cb] = kNoReference;  // (a masked logit then weighs 0 from the start; with -inf it would be NaN)
