@@ -346,18 +346,20 @@ enum fs_option {
    * fp32 around them.  Both stay inside the prefill tolerance. */
   FS_OPT_PREFILL_STAGED_DEQUANT = 6,
   /* read-only: the kernel the pool's latest fs_prefill_attention call launched:
-   * column blocks | waves << 8 | staged dequantization << 16 | pipelined << 17 | groups << 19 | wide << 21 (0: none yet;
-   * column blocks 0 with bit 18 set: the vector-ALU kernel).  Workgroup kernels: 16 with 8 or 4 waves, 8 with 8 (smaller
-   * launches), 4 with 4 (head_dim 256); wave-level kernels: 1, 2 or 4 blocks, waves 0.  groups (two bits, with 8 blocks): 1 / 2 = the
-   * launch's kernel deals contexts to two / four groups of waves where it finds one long enough, else it runs as with 0.
-   * wide (two bits, with 16): 1 / 2 = items of 24 / 32 blocks (large launches at head_dim 64) */
+   * column blocks | waves << 8 | staged dequantization << 16 | pipelined << 17 (0: none yet; column blocks 0 with
+   * bit 18 set: the vector-ALU kernel).  Workgroup kernels: 16 with 8 or 4 waves (items of 16 blocks, of 24 or 32 in large
+   * launches at head_dim 64), 8 with 8 (smaller launches), 4 with 4 (head_dim 256); wave-level kernels: 1, 2 or 4 blocks, waves 0 */
   FS_OPT_LAST_PREFILL_KERNEL = 7,
   /* non-zero: the MFMA decode kernel always takes its work from a list that a preparation kernel writes; 0 (default): a
    * launch whose sequences need few splits or none runs without one, a workgroup per (sequence, split, KV head) */
   FS_OPT_DECODE_WORK_LIST = 8,
   /* read-only: the kernels the pool's latest decode call launched, a bit mask: 1 = the generic kernel, 2 = the MFMA kernel
    * with a work list, 4 = the MFMA kernel without one (0: none yet) */
-  FS_OPT_LAST_DECODE_KERNEL = 9
+  FS_OPT_LAST_DECODE_KERNEL = 9,
+  /* read-only: the work items of that prefill call: column blocks of an item | groups << 8 (0: none yet, or the vector-ALU
+   * kernel).  groups: 1 / 2 = the kernel deals contexts to two / four groups of waves where it finds one long enough (else its
+   * items have 8 blocks), 0 = it has none */
+  FS_OPT_LAST_PREFILL_ITEMS = 10
 };
 int fs_pool_set_option(fs_pool* pool, int option, int64_t value);
 int fs_pool_get_option(fs_pool* pool, int option, int64_t* value);

@@ -34,7 +34,7 @@ EXPORTS = ["fs_pool_create", "fs_pool_destroy", "fs_pool_base", "fs_model_regist
 
 (FS_OPT_DECODE_KERNEL, FS_OPT_SPLIT_BYTES, FS_OPT_KERNEL_TIMING, FS_OPT_PREFILL_COLUMN_BLOCKS, FS_OPT_PREFILL_WAVES,
  FS_OPT_PREFILL_PIPELINED, FS_OPT_PREFILL_STAGED_DEQUANT, FS_OPT_LAST_PREFILL_KERNEL, FS_OPT_DECODE_WORK_LIST,
- FS_OPT_LAST_DECODE_KERNEL) = range(10)
+ FS_OPT_LAST_DECODE_KERNEL, FS_OPT_LAST_PREFILL_ITEMS) = range(11)
 
 
 class fs_geometry_t(ctypes.Structure):

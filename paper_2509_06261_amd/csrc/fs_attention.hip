@@ -1010,6 +1010,7 @@ int fs_pool_get_option(fs_pool* p, int option, int64_t* value) {
     case FS_OPT_LAST_PREFILL_KERNEL: *value = o.last_prefill; return FS_OK;
     case FS_OPT_DECODE_WORK_LIST: *value = o.decode_list; return FS_OK;
     case FS_OPT_LAST_DECODE_KERNEL: *value = o.last_decode; return FS_OK;
+    case FS_OPT_LAST_PREFILL_ITEMS: *value = o.last_items; return FS_OK;
     default: break;
   }
   set_error("fs_pool_get_option: unknown option");

@@ -39,6 +39,7 @@ struct Options {
   bool prefill_pipe = false;    // FS_OPT_PREFILL_PIPELINED
   bool prefill_deq = true;      // FS_OPT_PREFILL_STAGED_DEQUANT
   int64_t last_prefill = 0;     // FS_OPT_LAST_PREFILL_KERNEL (read-only)
+  int64_t last_items = 0;       // FS_OPT_LAST_PREFILL_ITEMS (read-only)
   bool decode_list = false;     // FS_OPT_DECODE_WORK_LIST
   int64_t last_decode = 0;      // FS_OPT_LAST_DECODE_KERNEL (read-only)
   hipEvent_t ev0 = nullptr, ev1 = nullptr;  // around the latest timed attention kernel

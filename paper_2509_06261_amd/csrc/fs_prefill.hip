@@ -2293,10 +2293,12 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     A.n_batches = 1;
     const uint64_t work = (uint64_t)n_rows * (uint64_t)g.n_kv_heads;
     p->opt.last_prefill = 1 << 18;
+    p->opt.last_items = 0;
     e = launch_generic_prefill(A, q_offsets, (int)n_rows, (int)std::min<uint64_t>(work, (uint64_t)p->n_cu * 8), s);
     if (e != hipSuccess) return device_error(e, "prefill launch (generic kernel)");
     return FS_OK;
   }
+  p->opt.last_items = ncb | (kv_shift << 8);
   // waves per SIMD: the 16-column kernel runs two, the wider wave-level ones one
   const int wps = ncb == 1 ? mfma_wgs_per_cu(g.head_dim) : 1;
   // workgroup kernels: 16 blocks = 8 waves x 2 (default) or 4 x 4, 4 sub-tiles per step, one workgroup per compute unit
@@ -2381,8 +2383,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return device_error(e, "prefill LDS attribute");
     const bool deq_used = deq && (g.kv_dtype == FS_KV_INT8 || g.kv_dtype == FS_KV_INT4);
-    p->opt.last_prefill = (kv_shift ? kSmallBlocks : std::min(ncb, 16)) | (nw << 8) | ((int64_t)deq_used << 16) |
-                          ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17) | ((int64_t)kv_shift << 19) | ((int64_t)(ncb == 24 ? 1 : ncb == 32 ? 2 : 0) << 21);
+    p->opt.last_prefill = (kv_shift ? kSmallBlocks : std::min(ncb, 16)) | (nw << 8) | ((int64_t)deq_used << 16) | ((int64_t)(nw == 4 && p->opt.prefill_pipe) << 17);
     hipLaunchKernelGGL(kern, dim3(n_wg), dim3(nw * 64), smem, s, P);
   } else if (ncb == 1) {
     p->opt.last_prefill = 1;

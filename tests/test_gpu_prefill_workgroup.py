@@ -223,10 +223,14 @@ def test_small_launches(dtype, head_dim, kv_heads, group):
         par.close()
 
 
-def _groups(kernel):
-    """log2 of the groups of waves that the launch may deal contexts to; the kernel is that of the small launches."""
-    assert kernel & ~(3 << 19) == (8 | 8 << 8), kernel
-    return kernel >> 19 & 3
+def _groups(pool):
+    """log2 of the groups of waves that the latest launch may deal contexts to; the kernel is that of the small launches."""
+    import paper_2509_06261_amd as fs
+
+    assert fs.fs_pool_get_option(pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
+    items = fs.fs_pool_get_option(pool, fs.FS_OPT_LAST_PREFILL_ITEMS)
+    assert items & 255 == (4 if items >> 8 == 2 else 8), items
+    return items >> 8
 
 
 @pytest.mark.parametrize("dtype", [FP16, FP8, INT8, INT4])
@@ -236,7 +240,6 @@ def test_context_groups(dtype, head_dim, kv_heads, group, n_new, shift):
     """Small launches behind long contexts: two and four groups of waves per context (items of 8 and 4 blocks), sequences
     of less than a step, a group without tokens, ragged items."""
     import gpu_harness
-    import paper_2509_06261_amd as fs
 
     lens = np.array([1500 if shift == 2 else 2060, 1111, 40, 260], np.int32)
     wl = Workload("pfgrp", 160 * KiB, 160 * 600 * KiB, [ModelSpec("m", dtype, kv_heads, head_dim, 1, kv_heads * group, lens, tag=50, src_f32=dtype == INT4)], "shuffle")
@@ -244,7 +247,7 @@ def test_context_groups(dtype, head_dim, kv_heads, group, n_new, shift):
     try:
         par.gw.populate([[0]])
         print(par.prefill_and_check(0, 0, np.array(n_new, np.int32)))
-        assert _groups(fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)) == shift
+        assert _groups(par.gw.pool) == shift
     finally:
         par.close()
 
@@ -273,8 +276,7 @@ def test_several_table_segments_of_odd_blocks(dtype, T, shift, monkeypatch):
         assert p.gw.T[p.gw.model_ids[0]] == T
         p.gw.populate([[0]])
         print(p.prefill_and_check(0, 0, np.array(n_new, np.int32)))
-        ran = fs.fs_pool_get_option(p.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)
-        assert _groups(ran) == shift if shift else ran & 0xffff == (16 | 8 << 8)
+        assert _groups(p.gw.pool) == shift if shift else fs.fs_pool_get_option(p.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) & 0xffff == (16 | 8 << 8)
     finally:
         p.close()
 
@@ -302,7 +304,7 @@ def test_contexts_are_dealt_to_groups_by_their_lengths():
             table, lens = gw.tables[0].repeat(n_seq, 1), gw.seq_lens[0].repeat(n_seq)
             out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
             fs.fs_prefill_attention(gw.pool, gw.model_ids[0], 0, H * group, 0.1, q, table, lens, torch.from_numpy(off).cuda(), off, out, lse, ws)
-            assert fs.fs_decode_status(ws) == 0 and _groups(fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)) == groups
+            assert fs.fs_decode_status(ws) == 0 and _groups(gw.pool) == groups
             got.append(out.float())
         # (values of N(0, 1) averaged: below 4, so two results each within 2^-11 of a weight's rounding and the output's)
         diff = (got[0] - got[1]).abs().max().item()
@@ -341,7 +343,7 @@ def test_short_contexts_behind_a_wide_table(dtype, head_dim, kv_heads, lens, n_n
         for table in (narrow, wide):
             out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
             fs.fs_prefill_attention(gw.pool, m, 0, kv_heads * group, 0.1, q, table, gw.seq_lens[0], torch.from_numpy(off).cuda(), off, out, lse, ws)
-            assert fs.fs_decode_status(ws) == 0 and fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) & 0xffff == (8 | 8 << 8)
+            assert fs.fs_decode_status(ws) == 0 and fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (8 | 8 << 8)
             got.append((out, lse))
         assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
         assert bool(got[0][0].ne(0).any(-1).all())
@@ -371,7 +373,7 @@ def test_infinite_value_with_context_groups(head_dim, kv_heads, length, shift):
         def run():
             out, lse = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda")
             fs.fs_prefill_attention(gw.pool, m, 0, kv_heads * group, 0.1, q, gw.tables[0], gw.seq_lens[0], torch.from_numpy(off).cuda(), off, out, lse, ws)
-            assert fs.fs_decode_status(ws) == 0 and _groups(fs.fs_pool_get_option(gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL)) == shift
+            assert fs.fs_decode_status(ws) == 0 and _groups(gw.pool) == shift
             return out, lse
 
         out0, lse0 = run()
@@ -405,7 +407,8 @@ def test_large_launches_at_head_dim_64(dtype, group, lens, seqs):
     try:
         par.gw.populate([[0]])
         print("T", par.gw.T, par.prefill_and_check(0, 0, lens, seqs=np.array(seqs)))
-        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (16 | 8 << 8 | (2 if dtype == FP16 else 1) << 21)
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_KERNEL) == (16 | 8 << 8)
+        assert fs.fs_pool_get_option(par.gw.pool, fs.FS_OPT_LAST_PREFILL_ITEMS) == (32 if dtype == FP16 else 24)
     finally:
         par.close()
 

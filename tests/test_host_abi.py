@@ -248,7 +248,7 @@ def test_pool_options_are_per_pool_and_range_checked():
         defaults = {fs.FS_OPT_DECODE_KERNEL: 0, fs.FS_OPT_SPLIT_BYTES: 0, fs.FS_OPT_KERNEL_TIMING: 0,
                     fs.FS_OPT_PREFILL_COLUMN_BLOCKS: 0, fs.FS_OPT_PREFILL_WAVES: 0, fs.FS_OPT_PREFILL_PIPELINED: 0,
                     fs.FS_OPT_PREFILL_STAGED_DEQUANT: 1, fs.FS_OPT_LAST_PREFILL_KERNEL: 0, fs.FS_OPT_DECODE_WORK_LIST: 0,
-                    fs.FS_OPT_LAST_DECODE_KERNEL: 0}
+                    fs.FS_OPT_LAST_DECODE_KERNEL: 0, fs.FS_OPT_LAST_PREFILL_ITEMS: 0}
         for opt, v in defaults.items():
             assert fs.fs_pool_get_option(a, opt) == v
         assert fs.fs_pool_set_option(a, fs.FS_OPT_DECODE_KERNEL, 2) == fs.FS_OK
@@ -264,7 +264,7 @@ def test_pool_options_are_per_pool_and_range_checked():
         for opt, bad in ((fs.FS_OPT_DECODE_KERNEL, 3), (fs.FS_OPT_DECODE_KERNEL, -1), (fs.FS_OPT_SPLIT_BYTES, 100),
                          (fs.FS_OPT_SPLIT_BYTES, 1 << 31), (fs.FS_OPT_PREFILL_COLUMN_BLOCKS, 8),
                          (fs.FS_OPT_PREFILL_COLUMN_BLOCKS, 3), (fs.FS_OPT_PREFILL_WAVES, 2),
-                         (fs.FS_OPT_LAST_PREFILL_KERNEL, 1), (fs.FS_OPT_LAST_DECODE_KERNEL, 1), (99, 0)):
+                         (fs.FS_OPT_LAST_PREFILL_KERNEL, 1), (fs.FS_OPT_LAST_DECODE_KERNEL, 1), (fs.FS_OPT_LAST_PREFILL_ITEMS, 1), (99, 0)):
             assert fs.fs_pool_set_option(a, opt, bad) == fs.FS_ERR_INVALID, (opt, bad)
         with pytest.raises(fs.FsError):
             fs.fs_pool_get_option(a, 99)
