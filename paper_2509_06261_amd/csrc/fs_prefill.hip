@@ -1912,135 +1912,110 @@ __device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_
   if (threadIdx.x == 0) P.header[kHdrStatus] = *s_flags;
 }
 
-// What a workgroup knows of the launch, and where its shared memory is.
-struct WgLaunch {
-  uint8_t* smem;           // two stages
-  uint64_t* s_tab;         // block-address table
-  uint32_t* s_ctl;         // kWgCtlBytes
-  uint32_t* header;        // where a block-table entry outside the pool is reported
-  const uint32_t* tf;      // first query tile of the k-th sequence
-  SeqList list;            // (listed)
-  uint32_t total;          // work items
-  bool listed, direct;
-  int wave, lane;
-};
-
-// The workgroup's work items.
-template <int DT, int NW, int NCB, int SUBS, bool PIPE, bool DEQ, int HD, bool SUM32, bool GROUPS>
-__device__ __forceinline__ void run_items(const PrefillArgs& P, const WgLaunch& W
-#ifdef FS_TIMELINE
-                                          , uint64_t& tl_items
-#endif
-) {
-  const DevBatch& B = P.b;
-  const uint32_t H = (uint32_t)B.g.H;
-  // direct: consecutive items, which stream the same keys and values, on one XCD (workgroups are dealt to the XCDs in
-  // turn); workgroup b takes items (b % 8) per + b / 8, + slots, ... of its XCD's share
-  const uint32_t per = (W.total + 7) / 8, slots = gridDim.x >> 3;  // (the host launches a multiple of eight)
-  uint32_t u = blockIdx.x >> 3;
-  ItemDraw d{0u, 0u};
-  SeqHeld held;
-  uint32_t turn = 0;
-  if (W.wave == 0 && !W.direct) d = first_draw(P.header, blockIdx.x >> 3, W.lane);
-  for (;;) {
-#ifdef FS_TIMELINE
-    const uint64_t tl_top = wall_clock64();
-#endif
-    uint32_t item;
-    if (W.direct) {
-      item = P.by_tile ? 8 * u + (blockIdx.x & 7) : (blockIdx.x & 7) * per + u;
-      if (u >= per || item >= W.total) break;
-      u += slots;
-    } else {
-      if (W.wave == 0) {  // one wave draws for the workgroup
-        const bool ok = next_item(d, P.header, W.total, (uint32_t)P.chunk_shift, W.lane, item);
-        if (W.lane == 0) W.s_ctl[turn] = ok ? item : 0xffffffffu;
-      }
-      __syncthreads();
-      // (an LDS load is not uniform to the compiler; the next draw writes the other word, the one after it lies behind
-      // a barrier that every wave passes with this item in hand)
-      item = __builtin_amdgcn_readfirstlane(W.s_ctl[turn]);
-      turn ^= 1;
-      if (item == 0xffffffffu) break;
-    }
-    int seq, head, qt;
-    const int found = P.by_tile ? fs::decode_item_by_tile(W.tf, B.n_seq, item, H, seq, head, qt) : decode_item(P, W.tf, item, H, seq, head, qt);
-    if (!__builtin_amdgcn_readfirstlane(found)) continue;  // (uniform, so that what lives across items stays scalar)
-    uint32_t unused = 0;
-    seq = __builtin_amdgcn_readfirstlane(W.listed ? W.list.seq[seq] : seq);
-    SeqShape shape = W.listed ? W.list.shape[seq] : seq_shape(P, seq, unused);
-    shape.len = __builtin_amdgcn_readfirstlane(shape.len);
-    shape.n_new = __builtin_amdgcn_readfirstlane(shape.n_new);
-    shape.q0 = __builtin_amdgcn_readfirstlane(shape.q0);
-    // (the same in every lane; said so, the item's addresses and bounds live in scalar registers: FP16 needs no
-    // scratch any more, and 64 prompts of 512 - 4096 tokens run 4232 -> 4126 us)
-    head = __builtin_amdgcn_readfirstlane(head);
-    qt = __builtin_amdgcn_readfirstlane(qt);
-#ifdef FS_TIMELINE
-    const uint64_t tl_begin = wall_clock64();
-#endif
-    if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, W.smem, W.s_tab, W.wave);
-    else prefill_item_wg<DT, NW, NCB, SUBS, DEQ, HD, SUM32, GROUPS>(P, W.header, seq, shape, head, qt, W.smem, W.s_tab, W.wave, held);
-#ifdef FS_TIMELINE
-    ++tl_items;
-    if (threadIdx.x == 0 && item < kPfTimelineItems) {
-      uint64_t* row = P.timeline + 8 * (kPfTimelineGroups + item);
-      row[0] = tl_begin;
-      row[1] = wall_clock64();
-      row[2] = ((uint64_t)seq << 32) | ((uint64_t)head << 20) | (uint64_t)qt;
-      row[3] = (uint64_t)blockIdx.x | ((tl_begin - tl_top) << 32);
-    }
-#endif
-  }
-}
-
 // WPC = workgroups per compute unit the kernel is built for.  GROUPS: the groups' items, or -- where the scan finds no context
 // long enough -- those of the small launches' kernel, one block per wave.
 template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false, bool GROUPS = false>
 __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
   extern __shared__ uint64_t smem64[];
   const DevBatch& B = P.b;
-  WgLaunch W;
-  W.smem = reinterpret_cast<uint8_t*>(smem64);
-  W.s_tab = reinterpret_cast<uint64_t*>(W.smem + 2 * stage_bytes(SUBS, HD));
-  W.s_ctl = reinterpret_cast<uint32_t*>(W.smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8);
-  W.lane = threadIdx.x & 63;
-  W.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint8_t* smem = reinterpret_cast<uint8_t*>(smem64);
+  uint64_t* s_tab = reinterpret_cast<uint64_t*>(smem + 2 * stage_bytes(SUBS, HD));
+  uint32_t* s_ctl = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t H = (uint32_t)B.g.H;
-  uint32_t* s_tf = reinterpret_cast<uint32_t*>(W.smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
-  W.direct = GROUPS || (!PIPE && P.direct);  // (uniform)
-  W.header = W.direct ? P.header + kHdrIgnored - kHdrStatus : P.header;
-  W.tf = P.tile_first;
-  W.list = seq_list(s_tf, B.n_seq);
-  W.listed = GROUPS || (!PIPE && P.tf_cache == 2);  // (uniform; always so in a direct launch)
-  if (W.listed) {
-    W.total = __builtin_amdgcn_readfirstlane(scan_sequences<GROUPS>(P, W.list, reinterpret_cast<uint32_t*>(W.smem), W.s_ctl)) * H;
-    W.tf = W.list.tf;
+  uint32_t* s_tf = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
+  const bool direct = GROUPS || (!PIPE && P.direct);  // (uniform)
+  uint32_t* const header = direct ? P.header + kHdrIgnored - kHdrStatus : P.header;
+  const uint32_t* tf = P.tile_first;
+  const SeqList list = seq_list(s_tf, B.n_seq);
+  uint32_t total;
+  const bool listed = GROUPS || (!PIPE && P.tf_cache == 2);  // (uniform; always so in a direct launch)
+  if (listed) {
+    total = __builtin_amdgcn_readfirstlane(scan_sequences<GROUPS>(P, list, reinterpret_cast<uint32_t*>(smem), s_ctl)) * H;
+    tf = list.tf;
   } else {
-    W.total = P.tile_first[B.n_seq] * H;
+    total = P.tile_first[B.n_seq] * H;
     if (P.tf_cache) {  // (uniform)
       for (int i = threadIdx.x; i <= B.n_seq; i += NW * 64) s_tf[i] = P.tile_first[i];
       __syncthreads();
-      W.tf = s_tf;
+      tf = s_tf;
     }
   }
 #ifdef FS_TIMELINE
   const uint64_t tl_start = wall_clock64();
   uint64_t tl_items = 0;
-#define FS_TL_ITEMS , tl_items
-#else
-#define FS_TL_ITEMS
 #endif
+  // the workgroup's work items
+  auto items = [&](auto ncb_c, auto groups_c) __attribute__((always_inline)) {
+    // direct: consecutive items, which stream the same keys and values, on one XCD (workgroups are dealt to the XCDs in
+    // turn); workgroup b takes items (b % 8) per + b / 8, + slots, ... of its XCD's share
+    const uint32_t per = (total + 7) / 8, slots = gridDim.x >> 3;  // (the host launches a multiple of eight)
+    uint32_t u = blockIdx.x >> 3;
+    ItemDraw d{0u, 0u};
+    SeqHeld held;
+    uint32_t turn = 0;
+    if (wave == 0 && !direct) d = first_draw(P.header, blockIdx.x >> 3, lane);
+    for (;;) {
+#ifdef FS_TIMELINE
+      const uint64_t tl_top = wall_clock64();
+#endif
+      uint32_t item;
+      if (direct) {
+        item = P.by_tile ? 8 * u + (blockIdx.x & 7) : (blockIdx.x & 7) * per + u;
+        if (u >= per || item >= total) break;
+        u += slots;
+      } else {
+        if (wave == 0) {  // one wave draws for the workgroup
+          const bool ok = next_item(d, P.header, total, (uint32_t)P.chunk_shift, lane, item);
+          if (lane == 0) s_ctl[turn] = ok ? item : 0xffffffffu;
+        }
+        __syncthreads();
+        // (an LDS load is not uniform to the compiler; the next draw writes the other word, the one after it lies behind
+        // a barrier that every wave passes with this item in hand)
+        item = __builtin_amdgcn_readfirstlane(s_ctl[turn]);
+        turn ^= 1;
+        if (item == 0xffffffffu) break;
+      }
+      int seq, head, qt;
+      const int found = P.by_tile ? fs::decode_item_by_tile(tf, B.n_seq, item, H, seq, head, qt) : decode_item(P, tf, item, H, seq, head, qt);
+      if (!__builtin_amdgcn_readfirstlane(found)) continue;  // (uniform, so that what lives across items stays scalar)
+      uint32_t unused = 0;
+      seq = __builtin_amdgcn_readfirstlane(listed ? list.seq[seq] : seq);
+      SeqShape shape = listed ? list.shape[seq] : seq_shape(P, seq, unused);
+      shape.len = __builtin_amdgcn_readfirstlane(shape.len);
+      shape.n_new = __builtin_amdgcn_readfirstlane(shape.n_new);
+      shape.q0 = __builtin_amdgcn_readfirstlane(shape.q0);
+      // (the same in every lane; said so, the item's addresses and bounds live in scalar registers: FP16 needs no
+      // scratch any more, and 64 prompts of 512 - 4096 tokens run 4232 -> 4126 us)
+      head = __builtin_amdgcn_readfirstlane(head);
+      qt = __builtin_amdgcn_readfirstlane(qt);
+#ifdef FS_TIMELINE
+      const uint64_t tl_begin = wall_clock64();
+#endif
+      if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
+      else prefill_item_wg<DT, NW, decltype(ncb_c)::value, SUBS, DEQ, HD, SUM32, decltype(groups_c)::value>(P, header, seq, shape, head, qt, smem, s_tab, wave, held);
+#ifdef FS_TIMELINE
+      ++tl_items;
+      if (threadIdx.x == 0 && item < kPfTimelineItems) {
+        uint64_t* row = P.timeline + 8 * (kPfTimelineGroups + item);
+        row[0] = tl_begin;
+        row[1] = wall_clock64();
+        row[2] = ((uint64_t)seq << 32) | ((uint64_t)head << 20) | (uint64_t)qt;
+        row[3] = (uint64_t)blockIdx.x | ((tl_begin - tl_top) << 32);
+      }
+#endif
+    }
+  };
   if constexpr (GROUPS) {
-    if (__builtin_amdgcn_readfirstlane(W.s_ctl[0])) run_items<DT, NW, NCB, SUBS, PIPE, DEQ, HD, SUM32, true>(P, W FS_TL_ITEMS);
-    else run_items<DT, NW, 1, SUBS, PIPE, DEQ, HD, SUM32, false>(P, W FS_TL_ITEMS);
+    if (__builtin_amdgcn_readfirstlane(s_ctl[0])) items(std::integral_constant<int, NCB>{}, std::true_type{});
+    else items(std::integral_constant<int, 1>{}, std::false_type{});
   } else {
-    run_items<DT, NW, NCB, SUBS, PIPE, DEQ, HD, SUM32, false>(P, W FS_TL_ITEMS);
+    items(std::integral_constant<int, NCB>{}, std::false_type{});
   }
-#undef FS_TL_ITEMS
-  if (W.direct) {
-    const uint32_t last = W.total ? W.total - 1 : 0u, per = (W.total + 7) / 8, slots = gridDim.x >> 3, n = W.total ? per : 1u;
-    if (blockIdx.x == (P.by_tile ? last % gridDim.x : (last % n % slots) * 8 + last / n)) direct_status<NW * 64>(P, reinterpret_cast<uint32_t*>(W.smem));
+  if (direct) {
+    const uint32_t last = total ? total - 1 : 0u, per = (total + 7) / 8, slots = gridDim.x >> 3, n = total ? per : 1u;
+    if (blockIdx.x == (P.by_tile ? last % gridDim.x : (last % n % slots) * 8 + last / n)) direct_status<NW * 64>(P, reinterpret_cast<uint32_t*>(smem));
   }
 #ifdef FS_TIMELINE
   if (threadIdx.x == 0 && blockIdx.x < kPfTimelineGroups) {

@@ -72,7 +72,7 @@ def test_calls_run_on_the_current_stream(kind, native, monkeypatch):
         torch.cuda.synchronize()
         side = torch.cuda.Stream()
         with torch.cuda.stream(side):
-            torch.cuda._sleep(20_000_000)  # several milliseconds
+            torch.cuda._sleep(100_000_000)  # some 50 milliseconds
             bring()
             call()
         assert not side.query()  # (the call did not wait for the stream)
