@@ -18,9 +18,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 FLAGS += os.environ.get("FS_EXTRA_HIPCC_FLAGS", "").split()  # experiments only
-# The prefill kernels keep MFMA accumulators and results in vector registers (no AccVGPR operands): their softmax
-# reads every S^T tile with the vector ALU, which cannot address AccVGPRs.
-FILE_FLAGS = {"fs_prefill.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# The MFMA kernels keep accumulators and results in vector registers (no AccVGPR operands): their softmax reads every
+# S^T tile with the vector ALU, which cannot address AccVGPRs.  (Decode at head_dim 256, the only shape there with more
+# than 256 registers: 60 INT8 sequences of 500 - 9000 tokens, 4 KV heads, 146.7 us without the flag, 141.4 with it.)
+FILE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("fs_prefill.hip", "fs_attention_mfma.hip")}
 
 
 TIMELINE_LIB = os.path.join(_DIR, "libfineserve_timeline.so")

@@ -34,12 +34,12 @@ struct DevBatch {
   // per byte), small ones at the end (the waves finish within one small item of each other).  tier_seq[t] = n_seq
   // where a tier is unused.
   int32_t tier_seq[kTierSteps];
-  // Runs one turn of the MFMA kernel's tile ring covers (4 per tile, 1 / 2 / 2 / 3 tiles for FP16 / FP8 / INT8 /
-  // INT4): the kernel works in whole turns, so items are whole turns long (their surplus tiles would be computed
+  // Runs one turn of the MFMA kernel's tile ring covers (4 per tile, 1 tile for FP16, 2 for the others at
+  // head_dim 128): the kernel works in whole turns, so items are whole turns long (their surplus tiles would be computed
   // and masked, which the formats bound by the vector ALU cannot afford on small items).
   int32_t ring_runs;
   int32_t R;
-  uint32_t r_magic;      // ceil(2^32 / R): run / R == umulhi(run, r_magic) while run * R < 2^32
+  uint32_t r_magic;      // ceil(2^32 / R), 0 for R = 1: run / R == umulhi(run, r_magic) while run * R < 2^32
   uint32_t n_blocks;     // blocks of this model's size the pool holds: valid table entries are 0 .. n_blocks - 1
 };
 
@@ -121,10 +121,11 @@ struct MultiArgs {
 constexpr int mfma_wgs_per_cu(int head_dim) { return head_dim == 256 ? 1 : 2; }
 
 // 32-token tiles the MFMA decode kernel keeps in flight per wave: about 16 KiB of K/V rows (32 KiB at head_dim
-// 256, where half as many waves run).  The host sizes work items in whole turns of this ring.
+// 256, where half as many waves run; INT4 at head_dim 128 half of it: a third tile costs 50 registers and gains nothing).
+// The host sizes work items in whole turns of this ring.
 constexpr int ring_tiles(int kv_dtype, int head_dim) {
   const bool f16 = kv_dtype == FS_KV_FP16, i4 = kv_dtype == FS_KV_INT4;
-  return head_dim <= 64 ? (f16 ? 2 : 4) : head_dim == 128 ? (f16 ? 1 : i4 ? 3 : 2) : (f16 ? 1 : i4 ? 4 : 2);
+  return head_dim <= 64 ? (f16 ? 2 : 4) : head_dim == 128 ? (f16 ? 1 : 2) : (f16 ? 1 : i4 ? 4 : 2);
 }
 
 // Runs of 8 token slots that a sequence of `len` tokens occupies (MFMA kernel's unit of work).
@@ -223,6 +224,48 @@ __device__ __host__ inline RunGeom run_geom(const ItemCtx& X, int vr) {
   L.hi_u = 8 < X.len_u - L.tok0 ? 8 : X.len_u - L.tok0;
   L.k_rel = k - X.k0;
   return L;
+}
+
+// The same in two steps, of which the first is the same for all lanes of a tile that begins at run vb (scalar arithmetic on
+// the device).  The two products of a lane's own division cost as much as eight plain instructions, and three look-ups per tile
+// made them a fifth of a 4-bit tile's work.  The integer formats take this form above head_dim 64; FP16 and FP8, which wait for
+// memory, keep the lane's own division: its shorter chain and fewer scalar registers show in the smallest calls (eight FP16
+// sequences of up to 256 tokens at head_dim 64: 6.45 us, 6.6 in two steps).
+struct TileGeom {
+  int k, r0;  // block and run within the block of the tile's first run (of the item's last run where vb lies past it)
+  int last;   // the tile's runs past this one lie past the item's end
+};
+__device__ __host__ inline TileGeom tile_geom(const ItemCtx& X, int vb) {
+  const int vc = vb < X.v_end - 1 ? vb : X.v_end - 1;
+  TileGeom t;
+  t.k = div_runs(vc, X.R, X.r_magic);
+  t.r0 = vc - t.k * X.R;
+  t.last = X.v_end - 1 - vc;
+  return t;
+}
+
+// Run vb + i, i = 0 .. 3.  x = r0 + i is at most R + 2, so that the quotient x / R is a comparison where R > 2 and a shift
+// where R is 1 or 2.
+__device__ __host__ inline RunGeom run_geom(const ItemCtx& X, const TileGeom& t, int vb, int i) {
+  const int x = t.r0 + (i < t.last ? i : t.last);
+  const int near = X.R > 2 ? X.R : 0x7fffffff, shift = X.R > 2 ? 31 : X.R - 1;
+  const int q = (x >> shift) + (x >= near ? 1 : 0), k = t.k + q;
+  const int r8 = 8 * (x - (q & 3) * (X.R & 0xffff));  // (the MFMA kernels' blocks hold less than 2^16 runs)
+  RunGeom L;
+  L.start = r8 < X.T - 8 ? r8 : X.T - 8;
+  L.lo = r8 - L.start;
+  L.tok0 = vb + i < X.v_end ? k * X.T + L.start : 0x3fffffff;
+  L.hi = 8 < X.len - L.tok0 ? 8 : X.len - L.tok0;
+  L.hi_u = 8 < X.len_u - L.tok0 ? 8 : X.len_u - L.tok0;
+  L.k_rel = k - X.k0;
+  return L;
+}
+
+// Whether every slot of the tile's four runs holds a token of the first `len` that no other run holds: none of them
+// shifted back, none past the item's end.
+__device__ __host__ inline bool tile_interior(const ItemCtx& X, const TileGeom& t, int len) {
+  const bool in_block = X.T == 8 * X.R || t.r0 + 3 < X.R - 1;
+  return in_block && t.last >= 3 && 8 * (t.r0 + 4) <= len - t.k * X.T;
 }
 
 // Split `chunk` of a sequence of `len` (clamped) tokens as a decode work item: its runs [v0, v1) and the blocks

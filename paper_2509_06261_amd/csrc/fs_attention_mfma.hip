@@ -139,9 +139,7 @@ template <int DT, int HD>
 __device__ __forceinline__ void output_row(const StateT<HD>& st, int r, float Z, float v_static, float (&o)[HD / 16]) {
 #pragma unroll
   for (int e = 0; e < HD / 16; ++e) {
-    // integer formats: undo the 2^-24 of the subnormal encoding (and the 16 of INT4's odd code positions)
-    const float f = DT == FS_KV_INT8 ? kTwo24 : (DT == FS_KV_INT4 ? ((e & 1) ? kTwo20 : kTwo24) : 1.0f);
-    o[e] = st.acc[e][r] * f;
+    o[e] = column_value<DT, true>(st.acc, e, r);
     if constexpr (Fmt<DT, HD>::kParBytes != 0) o[e] += Z;
     o[e] *= v_static;
   }
@@ -151,7 +149,7 @@ __device__ __forceinline__ void output_row(const StateT<HD>& st, int r, float Z,
 // workgroup: read from memory here they would be one more round trip in front of every item's stores).
 template <int DT, int GP, int HD>
 __device__ __forceinline__ void finish_item(const MultiArgs& A, const ItemPlan& P, StateT<HD>& st, const uint64_t* part_off) {
-  constexpr int NE = HD / 16;  // output columns NE c .. NE c + NE - 1 are this lane's
+  constexpr int NE = HD / 16;  // output columns of this lane (column_of)
   const int b = P.b, seq = P.seq, head = P.head;
   const DevBatch& B = A.b[b];
   int lane = threadIdx.x & 63;
@@ -185,20 +183,20 @@ __device__ __forceinline__ void finish_item(const MultiArgs& A, const ItemPlan& 
           const half2v hv = {(_Float16)(o[2 * q] * inv), (_Float16)(o[2 * q + 1] * inv)};
           w[q] = h2u(hv);
         }
-        _Float16* orow = B.out + ((int64_t)seq * B.n_q + qh) * HD + NE * c;
+        _Float16* orow = B.out + ((int64_t)seq * B.n_q + qh) * HD;
         if constexpr (NE == 4) {
-          *reinterpret_cast<u32x2*>(orow) = u32x2{w[0], w[1]};
+          *reinterpret_cast<u32x2*>(orow + column_of<DT, HD>(c, 0)) = u32x2{w[0], w[1]};
         } else {
 #pragma unroll
           for (int q = 0; q < NE / 8; ++q)
-            reinterpret_cast<u32x4*>(orow)[q] = u32x4{w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
+            *reinterpret_cast<u32x4*>(orow + column_of<DT, HD>(c, 8 * q)) = u32x4{w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
         }
         if (c == 0 && B.lse) B.lse[(int64_t)seq * B.n_q + qh] = (M + __builtin_amdgcn_logf(L)) * kLn2;
       } else {
         float* pr = A.partials + part_base + (uint64_t)h * (HD + 2);
         // (a row starts at a multiple of 8 bytes: part_stride and HD + 2 are even)
 #pragma unroll
-        for (int e = 0; e < NE; e += 2) *reinterpret_cast<float2*>(pr + NE * c + e) = float2{o[e], o[e + 1]};
+        for (int e = 0; e < NE; e += 2) *reinterpret_cast<float2*>(pr + column_of<DT, HD>(c, e)) = float2{o[e], o[e + 1]};
         if (c == 0) {
           pr[HD] = M * kLn2;  // partial records keep the reference in natural-log units
           pr[HD + 1] = L;
@@ -228,7 +226,7 @@ __device__ __forceinline__ void leave_records(const MultiArgs& A, const ItemPlan
       float o[NE];
       output_row<DT, HD>(st, r, Z, v_static, o);
 #pragma unroll
-      for (int e = 0; e < NE; e += 2) *reinterpret_cast<float2*>(pr + NE * c + e) = float2{o[e], o[e + 1]};
+      for (int e = 0; e < NE; e += 2) *reinterpret_cast<float2*>(pr + column_of<DT, HD>(c, e)) = float2{o[e], o[e + 1]};
       if (c == 0) *reinterpret_cast<float2*>(pr + HD) = float2{M * kLn2, L};
     }
   }

@@ -66,6 +66,7 @@ struct Fmt {
   static constexpr int kVRegs = DT == FS_KV_INT4 ? 4 * kVWords : kNE / 2;
   static constexpr int kParBytes = DT == FS_KV_INT8 ? 2 : (DT == FS_KV_INT4 ? 4 : 0);
   static constexpr int kRing = ring_tiles(DT, HD);
+  static constexpr bool kScalarWalk = kParBytes != 0 && HD > 64;  // look-ups of runs by way of the tile's place (tile_geom)
 };
 
 template <int BYTES>
@@ -81,6 +82,10 @@ struct KVec<8> {
 // Measured on the four-model pool: the hint helps loads that cover whole 128-byte lines per instruction (the V
 // rows: + 1.2 % on the kernel) and costs where an instruction takes half a line of each of 16 rows (the K operand
 // pattern: - 0.3 %, and - 2.5 % with both), so V rows carry it and K rows do not.
+// The rows of the integer formats begin anywhere in a line (their tiles are padded to 16 bytes only), so that two
+// instructions share a line: with the hint the second one fetches it again (86 INT8 sequences of 2381 - 7152 tokens, 8 KV heads:
+// 165 us without, 182 with it; FP8, whose rows are whole lines, 134 and 126).  The wide INT4 loads (wide_v) take four
+// neighbouring rows per instruction and gain by it again (48 sequences of 4000 - 6000 tokens, 8 KV heads: 58 us, 62 without).
 #ifndef FS_NT_K
 #define FS_NT_K 0
 #endif
@@ -97,6 +102,17 @@ __device__ __forceinline__ uint32_t h2u(half2v h) { return __builtin_bit_cast(ui
 __device__ __forceinline__ half2v u2h(uint32_t u) { return __builtin_bit_cast(half2v, u); }
 __device__ __forceinline__ float f16lo(uint32_t w) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xFFFF)); }
 __device__ __forceinline__ float f16hi(uint32_t w) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16)); }
+
+// value of lane I of the own 16-lane row, broadcast to the whole row (DPP row_newbcast)
+template <int I>
+__device__ __forceinline__ float row_bcast(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x150 + I, 0xF, 0xF, false));
+}
+
+template <int... Is, typename F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, Is...>, F&& f) {
+  (f(std::integral_constant<int, Is>{}), ...);
+}
 
 // ---- 8 stored elements -> 4 registers of packed fp16 -----------------------------------------
 // FP16 and FP8 convert to their exact fp16 values, register p holding elements (2p, 2p+1).
@@ -142,19 +158,26 @@ struct Tile {
   typename KVec<Fmt<DT, HD>::kKLane>::type k[2][Fmt<DT, HD>::kKLoads];
   uint32_t v[8][Fmt<DT, HD>::kVWords];
   // INT8/INT4 per-token parameters.  GP == 16: one register; lanes c < 8 hold the K parameters of token c of
-  // the lane's run, lanes c >= 8 the V ones.  GP == 4: those of the lane's own two tokens, K K V V.
-  uint32_t par[GP == 16 ? 1 : 4];
+  // the lane's run, lanes c >= 8 the V ones.  GP == 4: those of the lane's own two tokens, K K V V (INT8: two tokens a register).
+  uint32_t par[GP == 16 ? 1 : DT == FS_KV_INT4 ? 4 : 2];
 };
+// Parameters of two neighbouring slots, read together: aligned to one slot's.
+typedef uint32_t par_u32 __attribute__((aligned(2)));
+typedef uint32_t par_u32x2 __attribute__((ext_vector_type(2), aligned(4)));
 
-// Run vr of an item (run_geom, fs_attention.h) with the head-chunk address of its block.
+// Run i of the tile that begins at run vb of an item (run_geom, fs_attention.h) with the head-chunk address of its block.
 struct RunLoc {
   gptr base;
   int start, lo, hi, hi_u;
   int tok0;  // token index of the run's slot 0 (a huge value for a run past the item's end: no column reaches it)
 };
 
-__device__ __forceinline__ RunLoc locate(const ItemCtx& X, int vr) {
-  const RunGeom r = run_geom(X, vr);
+// SCALAR: by way of the tile's place (tile_geom).
+template <bool SCALAR = false>
+__device__ __forceinline__ RunLoc locate(const ItemCtx& X, int vb, int i) {
+  RunGeom r;
+  if constexpr (SCALAR) r = run_geom(X, tile_geom(X, vb), vb, i);
+  else r = run_geom(X, vb + i);
   RunLoc L;
   L.start = r.start;
   L.lo = r.lo;
@@ -170,7 +193,7 @@ __device__ __forceinline__ void issue_k(const ItemCtx& X, int vb, int j, int c, 
   using F = Fmt<DT, HD>;
   typedef typename KVec<F::kKLane>::type kvec;
   // row m = c of S^T tile u is slot 4u + (c & 3) of run c >> 2
-  const RunLoc L = locate(X, vb + (c >> 2));
+  const RunLoc L = locate<F::kScalarWalk>(X, vb, c >> 2);
   const gptr p = L.base + (uint32_t)((L.start + (c & 3)) * F::kRowBytes) + F::kKLane * j;
 #pragma unroll
   for (int u = 0; u < 2; ++u)
@@ -179,39 +202,77 @@ __device__ __forceinline__ void issue_k(const ItemCtx& X, int vb, int j, int c, 
       t.k[u][s] = stream_load<FS_NT_K>(reinterpret_cast<const FS_GLOBAL kvec*>(p + u * 4 * F::kRowBytes + 4 * F::kKLane * s));
 }
 
+// INT4 at head_dim 128: a lane's four bytes of a row are a quarter of what a load can carry, and eight such loads touch every
+// line two or three times.  So lane (j, c) loads sixteen bytes (chunk c % 4) of two rows of the run, c / 4 and c / 4 + 4, and
+// the lanes of equal c % 4 exchange their words when the tile's turn comes (transpose_banks).  256 sequences of 1024 - 8192
+// tokens, 8 KV heads: 306 us with narrow loads, 260 with these.
+// FP16 at head_dim 256: a lane's share of a row is 32 bytes, and two loads of neighbouring sixteen leave every line half used
+// by each; so lane c loads the chunks c and c + 16.
+template <int DT, int HD>
+constexpr bool wide_v() { return (DT == FS_KV_INT4 && HD == 128) || (DT == FS_KV_FP16 && HD == 256); }
+template <int DT, int HD>
+constexpr bool nt_v() { return FS_NT_V && (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3); }
+// The output column that accumulator e of lane (j, c) holds: neighbours for e in steps of four, eight where HD > 64.
+template <int DT, int HD>
+__device__ __forceinline__ int column_of(int c, int e) {
+  if constexpr (wide_v<DT, HD>()) return DT == FS_KV_INT4 ? 8 * (4 * (c & 3) + (c >> 2)) + e : 128 * (e >> 3) + 8 * c + (e & 7);
+  return HD / 16 * c + e;
+}
+
+// v[i], i = 4 u + q: word q of what lane (j, c) loaded, of row 4 u + c / 4.  Afterwards: word c / 4 of row i.
+// (DPP row shifts by one and two banks of four lanes; the banks that a mask leaves out keep theirs.)
+__device__ __forceinline__ void transpose_banks(uint32_t (&v)[8][1]) {
+#pragma unroll
+  for (int u = 0; u < 8; u += 4) {
+    uint32_t a[4];
+#pragma unroll
+    for (int q = 0; q < 4; q += 2) {
+      const uint32_t x = v[u + q][0], y = v[u + q + 1][0];
+      a[q] = __builtin_amdgcn_update_dpp(x, y, 0x114, 0xF, 0xA, false);      // odd banks: y of the bank before
+      a[q + 1] = __builtin_amdgcn_update_dpp(y, x, 0x104, 0xF, 0x5, false);  // even banks: x of the bank behind
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      v[u + q][0] = __builtin_amdgcn_update_dpp(a[q], a[q + 2], 0x118, 0xF, 0xC, false);
+      v[u + q + 2][0] = __builtin_amdgcn_update_dpp(a[q + 2], a[q], 0x108, 0xF, 0x3, false);
+    }
+  }
+}
+
 template <int DT, int HD>
 __device__ __forceinline__ void load_v_row(gptr p, uint32_t (&v)[Fmt<DT, HD>::kVWords]) {
   constexpr int kVBytes = Fmt<DT, HD>::kVBytes;
   if constexpr (kVBytes == 32) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const u32x4 x = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL u32x4*>(p) + h);
+      const u32x4 x = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL u32x4*>(p) + h);
       v[4 * h + 0] = x[0];
       v[4 * h + 1] = x[1];
       v[4 * h + 2] = x[2];
       v[4 * h + 3] = x[3];
     }
   } else if constexpr (kVBytes == 16) {
-    const u32x4 x = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL u32x4*>(p));
+    const u32x4 x = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL u32x4*>(p));
     v[0] = x[0];
     v[1] = x[1];
     v[2] = x[2];
     v[3] = x[3];
   } else if constexpr (kVBytes == 8) {
-    const u32x2 x = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL u32x2*>(p));
+    const u32x2 x = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL u32x2*>(p));
     v[0] = x[0];
     v[1] = x[1];
   } else if constexpr (kVBytes == 4) {
-    v[0] = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL uint32_t*>(p));
+    v[0] = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL uint32_t*>(p));
   } else {
-    v[0] = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL uint16_t*>(p));
+    v[0] = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL uint16_t*>(p));
   }
 }
 
-template <int DT, int GP, int HD>
+// WIDE: see wide_v.
+template <int DT, int GP, int HD, bool WIDE = false>
 __device__ __forceinline__ void issue_v(const ItemCtx& X, const DevGeom& g, int vb, int j, int c, Tile<DT, GP, HD>& t) {
   using F = Fmt<DT, HD>;
-  const RunLoc L = locate(X, vb + j);
+  const RunLoc L = locate<F::kScalarWalk>(X, vb, j);
   if constexpr (F::kParBytes != 0) {  // parameters first: the softmax needs them before the V rows
     const gptr pk = L.base + 2u * g.kv_tile;
     if constexpr (GP == 16) {
@@ -222,21 +283,40 @@ __device__ __forceinline__ void issue_v(const ItemCtx& X, const DevGeom& g, int 
       const gptr p = pk + (uint32_t)((L.start + 2 * (c >> 2)) * F::kParBytes);  // slots 2 (c >> 2), + 1 of the run
       const gptr q = p + g.par_tile;
       if constexpr (F::kParBytes == 2) {
-        t.par[0] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(p);
-        t.par[1] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(p + 2);
-        t.par[2] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(q);
-        t.par[3] = *reinterpret_cast<const FS_GLOBAL uint16_t*>(q + 2);
+        t.par[0] = *reinterpret_cast<const FS_GLOBAL par_u32*>(p);
+        t.par[1] = *reinterpret_cast<const FS_GLOBAL par_u32*>(q);
       } else {
-        t.par[0] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(p);
-        t.par[1] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(p + 4);
-        t.par[2] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(q);
-        t.par[3] = *reinterpret_cast<const FS_GLOBAL uint32_t*>(q + 4);
+        const par_u32x2 k = *reinterpret_cast<const FS_GLOBAL par_u32x2*>(p), v = *reinterpret_cast<const FS_GLOBAL par_u32x2*>(q);
+        t.par[0] = k[0];
+        t.par[1] = k[1];
+        t.par[2] = v[0];
+        t.par[3] = v[1];
       }
     }
   }
-  const gptr p0 = L.base + g.kv_tile + (uint32_t)(L.start * F::kRowBytes) + c * F::kVBytes;
+  if constexpr (WIDE && DT == FS_KV_FP16) {
+    const gptr p = L.base + g.kv_tile + (uint32_t)(L.start * F::kRowBytes) + 16 * c;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) load_v_row<DT, HD>(p0 + i * F::kRowBytes, t.v[i]);
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const u32x4 x = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL u32x4*>(p + i * F::kRowBytes + 256 * h));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t.v[i][4 * h + q] = x[q];
+      }
+  } else if constexpr (WIDE) {
+    const gptr p = L.base + g.kv_tile + (uint32_t)((L.start + (c >> 2)) * F::kRowBytes) + 16 * (c & 3);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const u32x4 x = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL u32x4*>(p + u * 4 * F::kRowBytes));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t.v[4 * u + q][0] = x[q];
+    }
+  } else {
+    const gptr p0 = L.base + g.kv_tile + (uint32_t)(L.start * F::kRowBytes) + c * F::kVBytes;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) load_v_row<DT, HD>(p0 + i * F::kRowBytes, t.v[i]);
+  }
 }
 
 // The Q operand (B of S^T = K Q^T) of lane (j, c) for k-step ks: 8 halves of q[head c] in the d order
@@ -322,6 +402,71 @@ __device__ __forceinline__ void k_operands(const typename KVec<Fmt<DT, HD>::kKLa
   }
 }
 
+// The B operands of P V from one lane's share of the eight rows of a run: op(e, b) for every output column e, halves
+// (2q, 2q + 1) of b[q] = the column's elements of slots 2q, 2q + 1.  Two rows' bytes are paired first and only then spread to
+// halves: a 4-bit tile takes 32 instructions like that (48 with SUM_ODD off) and 72 with every word spread by itself, an 8-bit
+// one 48 and 80, an FP8 one 16 pairings for 32.
+// INT4: an odd column's elements are 16-fold; with SUM_ODD each also holds the even column's element below it (the stored
+// byte, 16 odd + even, is exact as a subnormal), and whoever reads the accumulators takes the even column's off
+// (column_value).
+template <int DT, int HD, bool SUM_ODD, typename F>
+__device__ __forceinline__ void v_columns(const uint32_t (&v)[8][Fmt<DT, HD>::kVWords], F&& op) {
+  constexpr int NE = Fmt<DT, HD>::kNE;
+  if constexpr (DT == FS_KV_FP16) {
+    static_for(std::make_integer_sequence<int, NE>{}, [&](auto E) {
+      constexpr int e = decltype(E)::value;
+      u32x4 b;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[q] = __builtin_amdgcn_perm(v[2 * q + 1][e >> 1], v[2 * q][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+      op(E, b);
+    });
+  } else if constexpr (DT == FS_KV_INT8) {
+    uint32_t u[8][Fmt<DT, HD>::kVWords];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int w = 0; w < Fmt<DT, HD>::kVWords; ++w) u[i][w] = v[i][w] ^ 0x80808080u;
+    static_for(std::make_integer_sequence<int, NE>{}, [&](auto E) {
+      constexpr int e = decltype(E)::value;
+      u32x4 b;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[q] = __builtin_amdgcn_perm(u[2 * q + 1][e >> 2], u[2 * q][e >> 2], 0x0C040C00u + 0x00010001u * (e & 3));
+      op(E, b);
+    });
+  } else {  // two columns at a time: they share a byte (INT4) or a conversion's source word (FP8)
+    static_for(std::make_integer_sequence<int, NE / 2>{}, [&](auto H) {
+      constexpr int e = 2 * decltype(H)::value;
+      u32x4 b0, b1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (DT == FS_KV_FP8_E4M3) {
+          const uint32_t x = __builtin_amdgcn_perm(v[2 * q + 1][e >> 2], v[2 * q][e >> 2], (e & 2) ? 0x07030602u : 0x05010400u);
+          b0[q] = fp8x2_lo(x);
+          b1[q] = fp8x2_hi(x);
+        } else {
+          const uint32_t x = __builtin_amdgcn_perm(v[2 * q + 1][e >> 3], v[2 * q][e >> 3], 0x0C040C00u + 0x00010001u * ((e & 7) >> 1));
+          b0[q] = x & 0x000F000Fu;
+          b1[q] = SUM_ODD ? x : x & 0x00F000F0u;
+        }
+      }
+      op(std::integral_constant<int, e>{}, b0);
+      op(std::integral_constant<int, e + 1>{}, b1);
+    });
+  }
+}
+
+// Column e of an accumulator row whose columns v_columns' operands made: the sum over the stored values (codes, for the
+// integer formats).
+template <int DT, bool SUM_ODD, int NE>
+__device__ __forceinline__ float column_value(const float4v (&acc)[NE], int e, int r) {
+  // integer formats: undo the 2^-24 of the subnormal encoding (and the 16 of INT4's odd code positions)
+  if constexpr (DT == FS_KV_INT4) {
+    if (e & 1) return (SUM_ODD ? acc[e][r] - acc[e - 1][r] : acc[e][r]) * kTwo20;
+    return acc[e][r] * kTwo24;
+  }
+  return DT == FS_KV_INT8 ? acc[e][r] * kTwo24 : acc[e][r];
+}
+
 // One lane's elements of a V row -> packed-fp16 registers (layout note above).
 template <int DT, int HD = 128>
 __device__ __forceinline__ void v_unpack(const uint32_t (&v)[Fmt<DT, HD>::kVWords], uint32_t (&x)[Fmt<DT, HD>::kVRegs]) {
@@ -347,17 +492,6 @@ __device__ __forceinline__ void v_unpack(const uint32_t (&v)[Fmt<DT, HD>::kVWord
       for (int q = 0; q < 4; ++q) x[4 * w + q] = r[q];
     }
   }
-}
-
-// value of lane I of the own 16-lane row, broadcast to the whole row (DPP row_newbcast)
-template <int I>
-__device__ __forceinline__ float row_bcast(float x) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x150 + I, 0xF, 0xF, false));
-}
-
-template <int... Is, typename F>
-__device__ __forceinline__ void static_for(std::integer_sequence<int, Is...>, F&& f) {
-  (f(std::integral_constant<int, Is>{}), ...);
 }
 
 // Per-wave online-softmax state.  acc[e] is the 16x16 output tile of d columns {kNE c' + e}: lane (j', c')
@@ -419,6 +553,10 @@ __device__ __forceinline__ void move_reference(StateT<HD>& st, float tmax, int j
 #pragma unroll
     for (int e = 0; e < HD / 16; ++e) st.acc[e][r] *= cr;
   }
+  // Opaque as whole tuples: the compiler otherwise joins this path and the usual one element by element and copies the
+  // accumulators on every tile to put them together again (32 moves a tile in the INT4 loop).
+#pragma unroll
+  for (int e = 0; e < HD / 16; ++e) asm volatile("" : "+v"(st.acc[e]));
   st.m = m_new;
 }
 
@@ -433,13 +571,24 @@ __device__ __forceinline__ void move_reference(StateT<HD>& st, float tmax, int j
 // (j, c) takes head c % 4 and slots 2 (c / 4), + 1 of run j: it fetches those two logits from lane (j, c % 4)
 // (DPP row shifts), loads the parameters of its own two tokens itself, and hands its packed pair of P back to
 // lanes c < 4 (DPP again), which assemble the A operand.  A quarter of the exponentials, no broadcasts.
-template <int DT, int GP, int HD>
+// DECODE: the V rows were loaded wide where that pays (wide_v), and odd columns hold the even ones below them (SUM_ODD of
+// v_columns).
+template <int DT, int GP, int HD, bool DECODE>
 __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t, const float4v (&s)[2], int vb, int j, int c,
                                            float qsum, float alpha, StateT<HD>& st) {
   using F = Fmt<DT, HD>;
-  const RunLoc L = locate(X, vb + j);
-  const uint32_t n_ok = (uint32_t)max(L.hi - L.lo, 0);   // slot i of the run is live iff (unsigned)(i - lo) < n_ok
-  const bool partial = !__all(L.lo == 0 && L.hi == 8);   // wave-uniform
+  RunGeom L;
+  bool partial;  // wave-uniform
+  if constexpr (F::kScalarWalk) {  // (no look-up for an interior tile)
+    const TileGeom tg = tile_geom(X, vb);
+    partial = !__all(tile_interior(X, tg, X.len));
+    L = RunGeom{};
+    if (partial) L = run_geom(X, tg, vb, j);
+  } else {
+    L = run_geom(X, vb + j);
+    partial = !__all(L.lo == 0 && L.hi == 8);
+  }
+  const uint32_t n_ok = (uint32_t)max(L.hi - L.lo, 0);  // of a partial tile: slot i of the run is live iff (unsigned)(i - lo) < n_ok
   if (partial) {
     if constexpr (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3) {
       // slots past the sequence's end may hold NaN/Inf bit patterns; 0 * NaN would poison the MFMA
@@ -462,7 +611,7 @@ __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t
         pa = alpha * kTwo24 * sc;
         pb = -alpha * sc * zp;
       } else {      // V: p' = p * sc, zero-point term -p * sc * zp
-        const bool ok = (c & 7) >= L.lo && (c & 7) < L.hi_u;  // a slot past the sequence may hold any bit pattern
+        const bool ok = !partial || ((c & 7) >= L.lo && (c & 7) < L.hi_u);  // a slot past the sequence may hold any bit pattern
         pa = ok ? sc : 0.f;
         pb = ok ? -sc * zp : 0.f;
       }
@@ -528,7 +677,7 @@ __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t
     if constexpr (F::kParBytes != 0) {
       // logit = alpha * sc * (2^24 * S_raw - zp * qsum)     (qsum: of this lane's head)
       const float a24 = alpha * kTwo24, aq = -alpha * qsum;
-      const float s0 = f16lo(t.par[0]), s1 = f16lo(t.par[1]);
+      const float s0 = f16lo(t.par[0]), s1 = DT == FS_KV_INT4 ? f16lo(t.par[1]) : f16hi(t.par[0]);
       const float z0 = DT == FS_KV_INT4 ? f16hi(t.par[0]) : 128.0f, z1 = DT == FS_KV_INT4 ? f16hi(t.par[1]) : 128.0f;
       x0 = fmaf(y0, s0 * a24, (s0 * z0) * aq);
       x1 = fmaf(y1, s1 * a24, (s1 * z1) * aq);
@@ -548,11 +697,15 @@ __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t
     float p0 = e0, p1 = e1;
     if constexpr (F::kParBytes != 0) {
       // p' = p * sc, zero-point term -p' * zp
-      float s0 = f16lo(t.par[2]), s1 = f16lo(t.par[3]);
-      const float z0 = DT == FS_KV_INT4 ? f16hi(t.par[2]) : 128.0f, z1 = DT == FS_KV_INT4 ? f16hi(t.par[3]) : 128.0f;
-      if (partial) {  // a dead slot's scale may be any bit pattern
+      float s0 = f16lo(t.par[DT == FS_KV_INT4 ? 2 : 1]), s1 = DT == FS_KV_INT4 ? f16lo(t.par[3]) : f16hi(t.par[1]);
+      float z0 = DT == FS_KV_INT4 ? f16hi(t.par[2]) : 128.0f, z1 = DT == FS_KV_INT4 ? f16hi(t.par[3]) : 128.0f;
+      if (partial) {  // a dead slot's parameters may be any bit pattern
         s0 = ok0 ? s0 : 0.f;
         s1 = ok1 ? s1 : 0.f;
+        if constexpr (DT == FS_KV_INT4) {
+          z0 = ok0 ? z0 : 0.f;
+          z1 = ok1 ? z1 : 0.f;
+        }
       }
       p0 = e0 * s0;
       p1 = e1 * s1;
@@ -567,19 +720,8 @@ __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t
     pk[3] = from_shl<12>(pp);
   }
   // ---- V rows of the run -> B operands (8x8 in-register transpose) and out += P V ----
-  uint32_t vx[8][F::kVRegs];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v_unpack<DT, HD>(t.v[i], vx[i]);
-#pragma unroll
-  for (int e = 0; e < F::kNE; ++e) {
-    // element e of the lane's share: INT4 word e / 8 holds codes (p, p + 4) of its eight in register p
-    const int reg = DT == FS_KV_INT4 ? 4 * (e >> 3) + (e & 3) : (e >> 1);
-    const uint32_t sel = (DT == FS_KV_INT4 ? ((e >> 2) & 1) : (e & 1)) ? 0x07060302u : 0x05040100u;
-    u32x4 b;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) b[q] = __builtin_amdgcn_perm(vx[2 * q + 1][reg], vx[2 * q][reg], sel);
-    st.acc[e] = mfma(pk, b, st.acc[e]);
-  }
+  if constexpr (DECODE && wide_v<DT, HD>() && DT == FS_KV_INT4) transpose_banks(t.v);
+  v_columns<DT, HD, DECODE>(t.v, [&](auto E, const u32x4& b) { st.acc[decltype(E)::value] = mfma(pk, b, st.acc[decltype(E)::value]); });
 }
 
 // Head-chunk addresses of blocks k0 .. k0 + nb - 1 of a sequence into this wave's LDS table: every lane of
@@ -606,7 +748,7 @@ __device__ __forceinline__ void fill_table(uint64_t* s_ptr, const int32_t* table
 // never used.  With refills that depend on a condition the compiler cannot know how many loads are outstanding behind
 // the one it needs and waits for all of them, the ones just issued included, which exposes the full memory latency on
 // every tile.
-// PEEL (decode): the last turn is a second copy of the step without any refill.  Then nothing is requested that no
+// PEEL (decode, with the V loads and columns that softmax_pv's DECODE names): the last turn is a second copy of the step without any refill.  Then nothing is requested that no
 // one will read (a ring of rows per item), and nothing is in flight when the caller goes on to write the item's
 // result: that code reuses the tiles' registers and otherwise waits for those loads to land (a per-item timeline
 // showed 4 us per item between the last tile and the end of the output, 4 % of the mixed launch and 14 % of a short
@@ -621,7 +763,7 @@ __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g,
   static_for(std::make_integer_sequence<int, NBUF>{}, [&](auto Bi) {
     constexpr int bi = decltype(Bi)::value;
     issue_k<DT, GP, HD>(X, v0 + bi * 4, j, c, t[bi]);
-    issue_v<DT, GP, HD>(X, g, v0 + bi * 4, j, c, t[bi]);
+    issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, g, v0 + bi * 4, j, c, t[bi]);
   });
   // One turn of the ring: every slot's tile is consumed and replaced by the tile NBUF further on.
   // (not for INT4, nor INT8 at head_dim 64: with the second copy of the step their tile loops spill registers)
@@ -635,8 +777,8 @@ __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g,
       float4v s[2];
       qk_tile<DT, GP, HD>(t[bi], qb, s);
       issue_k<DT, GP, HD>(X, vb_next, j, c, t[bi]);
-      softmax_pv<DT, GP, HD>(X, t[bi], s, vb, j, c, qsum, alpha, st);
-      issue_v<DT, GP, HD>(X, g, vb_next, j, c, t[bi]);
+      softmax_pv<DT, GP, HD, PEEL>(X, t[bi], s, vb, j, c, qsum, alpha, st);
+      issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, g, vb_next, j, c, t[bi]);
     });
   }
   // the last turn: the 1 .. NBUF tiles that are left, no refills (slots past the last tile hold rows nobody needs)
@@ -646,7 +788,7 @@ __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g,
       if (bi == 0 || k0 + bi < n_tiles) {  // wave-uniform
         float4v s[2];
         qk_tile<DT, GP, HD>(t[bi], qb, s);
-        softmax_pv<DT, GP, HD>(X, t[bi], s, v0 + (k0 + bi) * 4, j, c, qsum, alpha, st);
+        softmax_pv<DT, GP, HD, PEEL>(X, t[bi], s, v0 + (k0 + bi) * 4, j, c, qsum, alpha, st);
       }
     });
   }

@@ -318,7 +318,7 @@ __device__ __forceinline__ void wide_tile(const ItemCtx& X, const DevGeom& g, Ti
   }
   issue_k<DT, 16>(X, vb_next, j, c, t);
 
-  const RunLoc L = locate(X, vb + j);  // X.len == X.len_u here: L.hi == L.hi_u
+  const RunLoc L = locate(X, vb, j);  // X.len == X.len_u here: L.hi == L.hi_u
   const bool interior = __all(L.lo == 0 && L.tok0 + 8 <= first_pos + 1);  // wave-uniform
   // per-token dequantization factors, prepared by the lane that loaded the token's parameters, broadcast once
   float ka[8], kb[8], va[8], vb2[8];
@@ -1474,7 +1474,7 @@ __device__ __forceinline__ bool make_logits(const float4v (&s)[NCB][2], const ui
                                             const float (&qsum)[NCB], const int (&len_cb)[NCB], float alpha, int first_pos,
                                             int vb, int lane, int c, const WideState<NCB>& st, Logits<DT, NCB>& out) {
   using F = Fmt<DT>;
-  const RunLoc L = locate(X, vb + (lane >> 4));
+  const RunLoc L = locate(X, vb, lane >> 4);
   const bool interior = __all(L.lo == 0 && L.tok0 + 8 <= first_pos + 1);  // wave-uniform
   float ka[8], kb[8];
   if constexpr (F::kParBytes != 0) {
@@ -1609,7 +1609,7 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
     issue_v<DT, 16>(X, g, v0 + 4 * w, j, c, t);
     stage_k<DT, kD>(smem, w, lane, t);
     {
-      const int live = locate(X, v0 + 4 * w + j).hi_u;
+      const int live = locate(X, v0 + 4 * w, j).hi_u;
       stage_v<DT, SUBS, kD>(smem, w, lane, !__all(live >= 8), live, t);
     }
     __syncthreads();
@@ -1724,7 +1724,7 @@ __device__ void prefill_item_wgp(const PrefillArgs& P, int seq, int head, int qt
       uint8_t* next = smem + (uint32_t)((i + 1) & 1) * stage_bytes(SUBS);
       stage_k<DT, kD>(next, w, lane, t);
       {
-        const int live = locate(X, vb_next + j).hi_u;
+        const int live = locate(X, vb_next, j).hi_u;
         stage_v<DT, SUBS, kD>(next, w, lane, !__all(live >= 8), live, t);
       }
       __syncthreads();

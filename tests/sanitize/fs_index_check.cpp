@@ -107,10 +107,19 @@ void check_batch(const fs::DevBatch& B, const std::vector<int32_t>& lens) {
         ++g_tiles;
         const int vb = r.v0 + 4 * tile;
         const bool consumed = tile < turns * ring;
+        int whole_runs = 0;
         for (int lane = 0; lane < 64; ++lane) {
           const int j = lane >> 4, c = lane & 15;
           // K operand rows: run c / 4 of the tile, slots 4 u + c % 4
           const fs::RunGeom Lk = fs::run_geom(X, vb + (c >> 2));
+          // (the look-up in two steps says the same, and which tiles need no masks)
+          const fs::TileGeom tg = fs::tile_geom(X, vb);
+          for (int i = 0; i < 4; ++i) {
+            const fs::RunGeom a = fs::run_geom(X, vb + i), b = fs::run_geom(X, tg, vb, i);
+            CHECK(a.k_rel == b.k_rel && a.start == b.start && a.lo == b.lo && a.hi == b.hi && a.hi_u == b.hi_u && a.tok0 == b.tok0);
+            if (lane == 0) whole_runs += a.lo == 0 && a.hi == 8;
+          }
+          if (lane == 0) CHECK(fs::tile_interior(X, tg, len) == (whole_runs == 4));
           CHECK(Lk.k_rel >= 0 && Lk.k_rel < r.nb);
           CHECK(Lk.start >= 0 && Lk.start + 8 <= g.T);
           for (int u = 0; u < 2; ++u)
