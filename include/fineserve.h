@@ -256,7 +256,9 @@ int fs_decode_status(const void* workspace, void* stream);
  *            host memory (sizes the launch; the kernels read the device copy, and clamp every row index into
  *            n_rows, so a mismatch cannot make them leave the buffers)
  *   workspace: device memory of fs_prefill_workspace_bytes(n_seq) bytes, 256-byte aligned, owned by the caller,
- *            in use until the stream has passed the call.  fs_decode_status(workspace, stream) afterwards: bit 0
+ *            in use until the stream has passed the call (65 MiB of it hold partial results of work items that several
+ *            workgroups share; a workspace that ends before them, 8 KiB + 4 n_seq bytes, is accepted and such launches take
+ *            longer).  fs_decode_status(workspace, stream) afterwards: bit 0
  *            set if a length or a chunk size was out of range (clamped), bit 2 (value 4) if a block-table entry
  *            named no block of the pool (read as block 0; the affected rows are meaningless).
  * At most 16 query heads per KV head (FS_ERR_INVALID otherwise).  head_dim 64, 128 and 256 with at least 8 tokens per

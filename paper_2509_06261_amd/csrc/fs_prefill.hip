@@ -49,6 +49,8 @@ struct PrefillArgs {
   int32_t group_len;         // ... in launches with a sequence of at least this many tokens (see scan_sequences)
   int32_t by_tile;           // workgroup kernels: 1 = items in the order of decode_item_by_tile
   int32_t direct;            // workgroup kernels: 1 = no preparation ran and no tickets are drawn (see "Direct launches")
+  int32_t plan_items;        // workgroup kernel with split items: places for items in the plan (a multiple of eight, see SplitPlan)
+  uint8_t* pieces;           // ... its counters and partial results in the workspace (see "Split items")
 #ifdef FS_TIMELINE
   uint64_t* timeline;        // (timeline build) clock readings of the workgroup kernels, at the end of the workspace
 #endif
@@ -1242,6 +1244,102 @@ __device__ __forceinline__ void merge_groups(const PrefillArgs& P, WgState<NCB, 
   __syncthreads();  // (the next item's first stage goes where the partial sums are)
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// Split items.  In a launch of few items per compute unit the longest context, or the second round of a few items, decides:
+// four FP8 chunks of 512 tokens behind 4700 - 14700 (256 items, one per unit) took 382 us, what 115 steps take although the mean is
+// 76; now 320 (988 TFLOP/s: with no unit idle the chip's power bounds a step, 4.0 us against 3.3).  Such a launch lays its items' steps (128 tokens each) one after the other and cuts the row into equal ranges, one per
+// workgroup (SplitPlan): an item that a cut divides is worked on in pieces by neighbouring workgroups, each of which leaves its
+// accumulators, references and sums (fp32, as they stand in the registers) in the workspace and counts; whoever counts
+// last adds the pieces up, in the order of the context whoever that is, and writes the rows.  Nobody waits for anybody.
+// A counter is a 64-bit word in the workspace that nothing clears before the launch: the count stands behind a
+// 48-bit mark without which the word reads as zero, and the last piece of an item takes the mark away again.
+// ---------------------------------------------------------------------------------------------------------
+static_assert(kSplitGroups <= 512, "a thread for every workgroup's whole items");  // (their pieces have a place: two each)
+constexpr uint32_t kPieceBytes = 8 * (16 * 1024 + 2 * 128);  // 8 waves of 16 accumulator tiles and 2 x 16 references and sums
+constexpr uint64_t kPieceMark = 0x9d3c5af16e870000ull;
+constexpr uint64_t kPiecesBytes = 8ull * kSplitGroups + 2ull * kSplitGroups * kPieceBytes;
+struct Piece {
+  int step = 0, end = 0x7fffffff;  // of the item's steps
+  uint32_t first = 0, n = 1;       // the first workgroup with a piece of this item, and how many have one
+  uint32_t own = 0;                // which of them this is
+  uint32_t* s_count = nullptr;     // a word of LDS
+};
+// The first piece of an item lies at the end of its workgroup's range, all others at the beginning of theirs.
+__device__ __forceinline__ uint8_t* piece_at(const PrefillArgs& P, const Piece& p, uint32_t k) {
+  return P.pieces + 8ull * kSplitGroups + (uint64_t)piece_place(p.first, k) * kPieceBytes;
+}
+// How many pieces of the item that begins in workgroup `at` have been left, this one included.
+__device__ __forceinline__ uint32_t count_piece(const PrefillArgs& P, uint32_t at, uint32_t n) {
+  unsigned long long* word = reinterpret_cast<unsigned long long*>(P.pieces) + at;
+  unsigned long long old = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
+  uint32_t count;
+  do {  // (as many rounds as other pieces of the item are being counted)
+    count = (old & ~0xffffull) == kPieceMark ? (uint32_t)(old & 0xffff) + 1 : 1;
+    next = count == n ? 0ull : kPieceMark | count;
+  } while (!__hip_atomic_compare_exchange_strong(word, &old, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  return count;
+}
+// Leaves the workgroup's piece; true: it was the last, and st holds the whole item (the sum in the lanes j = 0).  Every wave
+// takes part; the result is uniform.
+template <int NW, int NCB, int HD>
+__device__ __forceinline__ bool merge_pieces(const PrefillArgs& P, const Piece& p, WgState<NCB, HD>& st, int w, int lane) {
+  constexpr int NE = HD / 16, N = NCB * NE;
+  static_assert(NW * (N * 1024 + NCB * 128) <= (int)kPieceBytes, "a piece has room");
+  const int j = lane >> 4, c = lane & 15;
+  auto acc_at = [&](uint32_t k) { return reinterpret_cast<float4v*>(piece_at(P, p, k)) + w * N * 64 + lane; };
+  auto ml_at = [&](uint32_t k) { return reinterpret_cast<float2*>(piece_at(P, p, k) + NW * N * 1024) + w * NCB * 16 + c; };
+  {
+    float4v* const acc = acc_at(p.own);
+    float2* const ml = ml_at(p.own);
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      const float l = over_column(st.l[cb], [](float a, float b) { return a + b; });
+      if (j == 0) ml[cb * 16] = float2{st.m[cb], l};
+#pragma unroll
+      for (int e = 0; e < NE; ++e) acc[(cb * NE + e) * 64] = st.acc[cb][e];
+    }
+  }
+  __syncthreads();  // (orders the waves' stores before the fence of the one that counts, and its second fence before their loads)
+  if (threadIdx.x == 0) {
+    __threadfence();
+    *p.s_count = count_piece(P, p.first, p.n);
+    __threadfence();
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*p.s_count) != p.n) return false;  // (the next piece's count lies behind barriers)
+  float M[NCB];
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) {
+    M[cb] = ml_at(0)[cb * 16].x;
+    for (uint32_t k = 1; k < p.n; ++k) M[cb] = fmaxf(M[cb], ml_at(k)[cb * 16].x);
+    st.l[cb] = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) st.acc[cb][e] = float4v{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll 1
+  for (uint32_t k = 0; k < p.n; ++k) {
+    const float4v* const acc = acc_at(k);
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      const float2 ml = ml_at(k)[cb * 16];
+      const float f = __builtin_amdgcn_exp2f(ml.x - M[cb]);
+      st.l[cb] += f * ml.y;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const float4v x = acc[(cb * NE + e) * 64];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st.acc[cb][e][r] += f * x[r];
+      }
+    }
+  }
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) {
+    st.m[cb] = M[cb];
+    if (j != 0) st.l[cb] = 0.f;
+  }
+  return true;
+}
+
 // smem: two stages, then the workgroup's block-address table.
 // DEQ (INT8 / INT4 only): the staging waves dequantize, the tile code is the FP16 one.
 // header: where a block-table entry outside the pool is reported.
@@ -1252,9 +1350,9 @@ struct SeqHeld {
   int seq = -1;
   bool table = false;  // the address table holds all blocks of the sequence
 };
-template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD, bool SUM32, bool GROUPS>
+template <int DT, int NW, int NCB, int SUBS, bool DEQ, int HD, bool SUM32, bool GROUPS, bool SPLIT = false>
 __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq, const SeqShape& shape, int head, int qt,
-                                uint8_t* smem, uint64_t* s_tab, int w, SeqHeld& S) {
+                                uint8_t* smem, uint64_t* s_tab, int w, SeqHeld& S, const Piece& piece = Piece{}) {
   static_assert(NW == SUBS || NW == 2 * SUBS, "staging roles");
 #ifdef FS_TIMELINE
   uint64_t tl_ph[5] = {(uint64_t)wall_clock64(), 0, 0, 0, 0};
@@ -1292,6 +1390,8 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   const int tok_c = c / G, hg_c = c - tok_c * G;
 
   const int len_u = len - n_new + r0_wg + n_tok_wg;  // tokens that the workgroup's last query sees
+  // (SPLIT) where the piece ends
+  const int end_u = SPLIT && piece.end < (len_u + 32 * SUBS - 1) / (32 * SUBS) ? 32 * SUBS * piece.end : len_u;
   TokenCtx X;
   X.ptr = s_tab;
   X.base_off = (uint64_t)head * g.head_chunk;
@@ -1320,14 +1420,15 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
   const int32_t* table = B.tables + (int64_t)seq * B.max_blocks;
   const int w_end = n_tok > 0 ? first_pos + n_tok : 0;  // tokens this wave's last query sees
   constexpr bool kCut = SUM32 && DT == FS_KV_FP16;  // (see wg_tile)
-  int t0 = 0;  // (and what is counted from it: multiples of 32)
+  int t0 = SPLIT ? 32 * SUBS * piece.step : 0;  // (and what is counted from it: multiples of 32)
+  if (SPLIT && t0 > 0) S.table = false;
   do {
-    const int n = min(len_u - t0, P.seg_tokens), k0 = t0 / g.T;
+    const int n = min(end_u - t0, P.seg_tokens), k0 = t0 / g.T;
     X.rel0 = t0 - k0 * g.T;
     X.last = n - 1;
     if (!S.table) {  // (uniform)
       // the previous segment's (or item's) last barrier lies behind every use of the old table
-      S.table = len <= P.seg_tokens;  // one segment (t0 = 0): all of the sequence's blocks, for its next items
+      S.table = len <= P.seg_tokens && (!SPLIT || t0 == 0);  // one segment (t0 = 0): all of the sequence's blocks, for its next items
       const int nb = (X.rel0 + (S.table ? len : n) - 1) / g.T + 1;
       for (int i = threadIdx.x; i < nb; i += NW * 64)
         s_tab[i] = reinterpret_cast<uint64_t>(B.layer_base + (uint64_t)checked_block(table[k0 + i], B.n_blocks, header) * g.block_budget);
@@ -1398,11 +1499,17 @@ __device__ void prefill_item_wg(const PrefillArgs& P, uint32_t* header, int seq,
       if (more) stage_to(next, tb_next);
       __syncthreads();  // (also after the last step: the next staging overwrites what other waves may still read)
     }
-  } while (next_segment(t0, len_u, P.seg_tokens));
+  } while (next_segment(t0, end_u, P.seg_tokens));
 #ifdef FS_TIMELINE
   tl_ph[3] = wall_clock64();
 #endif
   const float v_static = DT == FS_KV_FP8_E4M3 ? B.v_scale[head] : 1.0f;
+  if constexpr (SPLIT) {
+    if (piece.n > 1) {  // (uniform)
+      S.table = false;
+      if (!merge_pieces<NW, NCB, HD>(P, piece, st, w, lane)) return;
+    }
+  }
   if constexpr (GROUPS) {
     merge_groups<CDT, NW, NCB, HD>(P, st, smem, w, lane, head, shape.q0 + r0, n_tok, v_static);
     return;
@@ -1894,6 +2001,110 @@ __device__ __forceinline__ uint32_t scan_sequences(const PrefillArgs& P, const S
   return L.tf[n];
 }
 
+// The plan of a launch with split items, in LDS: item i of the plan's order (XCD by XCD, an XCD's items in the order of a direct
+// launch) has steps cum[i] .. cum[i + 1], workgroup k of that order the steps cut[k] .. cut[k + 1].
+struct SplitPlan {
+  uint32_t* cum;  // [plan_items + 1]
+  uint32_t* cut;  // [workgroups + 1]
+  uint16_t* order;     // [plan_items] whole items: an XCD's items by their steps, most first ...
+  bool sorted = false; // ... where it has more of them than workgroups
+  uint32_t turns = 1;  // sequences whose tiles are dealt one from each in turn (see plan_item)
+};
+constexpr uint32_t split_plan_bytes(uint32_t plan_items) { return (plan_items + 1 + kSplitGroups + 1) * 4 + plan_items * 2; }
+// Lays the plan (n = 8 per items, n <= plan_items, n > 0); false: the items stay whole, each workgroup taking its XCD's in turn.
+// That is so where a range has fewer than eight steps, and where the busiest workgroup would not end late enough after the
+// mean: a cut costs its two workgroups an item's start (1.5 steps) and a piece written and read again (2), and workgroups that
+// read the same context out of step share fewer of its lines in their L2.  Where the sequences bring the same number of tiles, no
+// more than an XCD has workgroups, the plan goes through the sequences tile by tile, and the ranges of a sequence's tiles begin
+// at (nearly) the same of its steps: a sixteenth is enough there, a quarter elsewhere.
+// us, FP16 / FP8 / INT4, 8 heads x 4: 5 chunks of 512 behind 3500 (320 items) 270 -> 217 / 245 -> 197 / 271 -> 212, 6 behind 7500 513 ->
+// 460 / 459 -> 398 / 513 -> 439, 8 of 256 behind 4000 - 12000 364 -> 328 / 318 -> 281 / 359 -> 308.  Cut wherever a sixteenth was to be
+// gained, one prompt of 6000 tokens took 340 -> 393 / 302 -> 362 / 335 -> 389, two of 1875 and 2625 140 -> 155 / 128 -> 148 / 141 -> 156.
+// Whole items are dealt by their steps, most first, there and back over the workgroups (item_rank, snake), against the ticket queue
+// behind a preparation launch: one prompt of 3000 140 -> 111 / 130 -> 100 / 143 -> 110; those two 141 -> 134 / 129 -> 125 / 142 -> 133
+// (157 / 150 / 157 in the queue's order); 12 chunks of 300 behind 500 - 15000 694 -> 539 / 613 -> 464 / 689 -> 518; 40 of 64 behind
+// 250 - 1100 79 -> 62 / 74 -> 59 / 79 -> 61; prompts of three and four items per unit, and what is no longer than a round, the same
+// within 0.6 %.
+__device__ __forceinline__ SplitPlan split_plan(const SeqList& list, int n_seq, int plan_items) {  // (behind the list of sequences)
+  uint32_t* const w = list.tf + 5 * n_seq + 1;
+  return SplitPlan{w + kSplitGroups + 1, w, reinterpret_cast<uint16_t*>(w + kSplitGroups + 1 + plan_items + 1)};
+}
+template <int NT>
+__device__ __forceinline__ bool lay_plan(const PrefillArgs& P, SplitPlan& plan, const SeqList& list, uint32_t* s_tmp, uint32_t total,
+                                         int step_tokens, int ncb, int nw) {
+  const uint32_t per = (total + 7) / 8, n = 8 * per, groups = gridDim.x, slots = groups >> 3;
+  const int q_wg = P.tpt * ncb * nw;
+  if (threadIdx.x == 0) plan.cum[0] = 0, s_tmp[0] = 0, s_tmp[1] = 0;
+  __syncthreads();
+  const uint32_t tiles = list.tf[1];
+  for (int k = threadIdx.x; k < P.b.n_seq; k += NT)
+    if (list.tf[k + 1] - list.tf[k] != tiles) s_tmp[1] = 1;
+  __syncthreads();
+  const bool even = P.by_tile && P.b.g.H % 8 == 0 && s_tmp[1] == 0 && tiles * (uint32_t)(P.b.g.H / 8) <= slots;  // (uniform)
+  for (uint32_t i = threadIdx.x; i < n; i += NT) {
+    const uint32_t item = plan_item(P.by_tile, i, per, 1);
+    uint32_t steps = 0;
+    int seq, head, qt;
+    if (item < total && (P.by_tile ? fs::decode_item_by_tile(list.tf, P.b.n_seq, item, (uint32_t)P.b.g.H, seq, head, qt)
+                                   : fs::decode_item(list.tf, P.b.n_seq, item, (uint32_t)P.b.g.H, seq, head, qt))) {
+      const SeqShape s = list.shape[list.seq[seq]];
+      steps = (uint32_t)(((int64_t)s.len - s.n_new + min((qt + 1) * q_wg, s.n_new) + step_tokens - 1) / step_tokens);
+    }
+    plan.cum[i + 1] = steps;
+  }
+  __syncthreads();
+  plan.sorted = per > slots;
+  if (plan.sorted) {  // (uniform)
+    for (uint32_t i = threadIdx.x; i < n; i += NT) {
+      const uint32_t x = i / per;
+      plan.order[x * per + item_rank(plan.cum + x * per + 1, per, i - x * per)] = (uint16_t)(i - x * per);
+    }
+    __syncthreads();
+  }
+  // what whole items would take the busiest workgroup, an item's start among it
+  uint32_t busy = 0;
+  if (threadIdx.x < groups)
+    for (uint32_t u = threadIdx.x >> 3; u - u % slots < per; u += slots) {
+      const uint32_t v = snake(u, slots);
+      if (v < per) busy += plan.cum[(threadIdx.x & 7) * per + (plan.sorted ? plan.order[(threadIdx.x & 7) * per + v] : v) + 1] + 1;
+    }
+  if (busy) atomicMax(s_tmp, busy);
+  if (even) {  // (a thread has at most kSplitItems items of a workgroup each: n <= 4 * 256, NT = 512)
+    plan.turns = (uint32_t)P.b.n_seq;
+    uint32_t mine[2 * kSplitItems];
+    uint32_t k = 0;
+    for (uint32_t i = threadIdx.x; i < n && k < 2 * kSplitItems; i += NT, ++k) {
+      const uint32_t x = i / per, u = i - x * per;
+      mine[k] = plan.cum[x * per + dealt(u, per, plan.turns) + 1];
+    }
+    __syncthreads();
+    k = 0;
+    for (uint32_t i = threadIdx.x; i < n && k < 2 * kSplitItems; i += NT, ++k) plan.cum[i + 1] = mine[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {  // inclusive sums: each lane its run of items
+    const uint32_t run = (n + 63) / 64, a = min(threadIdx.x * run, n), b = min(a + run, n);
+    uint32_t sum = 0;
+    for (uint32_t i = a; i < b; ++i) sum += plan.cum[i + 1];
+    uint32_t incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t up = __shfl_up(incl, off, 64);
+      if ((int)threadIdx.x >= off) incl += up;
+    }
+    uint32_t at = incl - sum;
+    for (uint32_t i = a; i < b; ++i) plan.cum[i + 1] = at += plan.cum[i + 1];
+  }
+  __syncthreads();
+  const uint32_t steps = plan.cum[n], mean = steps / groups;
+  if (mean < kSplitLeast || s_tmp[0] <= mean + mean / (even ? 16 : 4) + 6) return false;
+  for (uint32_t k = threadIdx.x; k <= groups; k += NT) {
+    plan.cut[k] = plan_cut(plan.cum, n, groups, k);
+  }
+  __syncthreads();
+  return true;
+}
+
 template <int NT>
 __device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_flags) {
   const DevBatch& B = P.b;
@@ -1914,7 +2125,7 @@ __device__ __forceinline__ void direct_status(const PrefillArgs& P, uint32_t* s_
 
 // WPC = workgroups per compute unit the kernel is built for.  GROUPS: the groups' items, or -- where the scan finds no context
 // long enough -- those of the small launches' kernel, one block per wave.
-template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false, bool GROUPS = false>
+template <int DT, int NW, int NCB, int SUBS, int WPC, bool PIPE = false, bool DEQ = false, int HD = kD, bool SUM32 = false, bool GROUPS = false, bool SPLIT = false>
 __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P) {
   extern __shared__ uint64_t smem64[];
   const DevBatch& B = P.b;
@@ -1925,12 +2136,12 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t H = (uint32_t)B.g.H;
   uint32_t* s_tf = reinterpret_cast<uint32_t*>(smem + 2 * stage_bytes(SUBS, HD) + (size_t)P.table_entries * 8 + kWgCtlBytes);
-  const bool direct = GROUPS || (!PIPE && P.direct);  // (uniform)
+  const bool direct = GROUPS || SPLIT || (!PIPE && P.direct);  // (uniform)
   uint32_t* const header = direct ? P.header + kHdrIgnored - kHdrStatus : P.header;
   const uint32_t* tf = P.tile_first;
   const SeqList list = seq_list(s_tf, B.n_seq);
   uint32_t total;
-  const bool listed = GROUPS || (!PIPE && P.tf_cache == 2);  // (uniform; always so in a direct launch)
+  const bool listed = GROUPS || SPLIT || (!PIPE && P.tf_cache == 2);  // (uniform; always so in a direct launch)
   if (listed) {
     total = __builtin_amdgcn_readfirstlane(scan_sequences<GROUPS>(P, list, reinterpret_cast<uint32_t*>(smem), s_ctl)) * H;
     tf = list.tf;
@@ -1955,16 +2166,57 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
     ItemDraw d{0u, 0u};
     SeqHeld held;
     uint32_t turn = 0;
+    Piece piece;
+    // (SPLIT) the workgroup's range of steps, and the item that its next step belongs to
+    uint32_t at = 0, end = 0, i_plan = 0, me = 0;
+    SplitPlan plan = split_plan(list, B.n_seq, P.plan_items);
+    bool split = false;
+    if constexpr (SPLIT) {
+      if (per > 0 && 8 * per <= (uint32_t)P.plan_items)
+        split = __builtin_amdgcn_readfirstlane(lay_plan<NW * 64>(P, plan, list, reinterpret_cast<uint32_t*>(smem), total, 32 * SUBS, NCB, NW));
+      __syncthreads();  // (the first stage goes where its scratch word is)
+      if (split) {
+        me = (blockIdx.x & 7) * slots + (blockIdx.x >> 3);
+        at = __builtin_amdgcn_readfirstlane(plan.cut[me]);
+        end = __builtin_amdgcn_readfirstlane(plan.cut[me + 1]);
+        i_plan = __builtin_amdgcn_readfirstlane(item_of_step(plan.cum, 8 * per, at));
+      }
+      piece.s_count = s_ctl + 2;
+    }
     if (wave == 0 && !direct) d = first_draw(P.header, blockIdx.x >> 3, lane);
     for (;;) {
 #ifdef FS_TIMELINE
       const uint64_t tl_top = wall_clock64();
 #endif
       uint32_t item;
-      if (direct) {
-        item = P.by_tile ? 8 * u + (blockIdx.x & 7) : (blockIdx.x & 7) * per + u;
-        if (u >= per || item >= total) break;
-        u += slots;
+      if (SPLIT && split) {
+        if (at >= end) break;
+        const uint32_t from = __builtin_amdgcn_readfirstlane(plan.cum[i_plan]), to = __builtin_amdgcn_readfirstlane(plan.cum[i_plan + 1]);
+        item = plan_item(P.by_tile, i_plan, per, plan.turns);
+        ++i_plan;
+        if (to <= at) continue;  // (an item without steps)
+        piece.step = (int)(at - from);
+        piece.end = (int)(min(to, end) - from);
+        uint32_t last;
+        piece_owners(plan.cut, me, from, to, piece.first, last);
+        piece.first = __builtin_amdgcn_readfirstlane(piece.first);
+        piece.n = __builtin_amdgcn_readfirstlane(last) - piece.first + 1;
+        piece.own = me - piece.first;
+        at = min(to, end);
+      } else if (direct) {
+        if constexpr (SPLIT) {  // (whoever had the longest item of one round has the shortest of the next)
+          if (u - u % slots >= per) break;
+          uint32_t v = snake(u, slots);
+          u += slots;
+          if (v >= per) continue;
+          if (plan.sorted) v = __builtin_amdgcn_readfirstlane((uint32_t)plan.order[(blockIdx.x & 7) * per + v]);
+          item = P.by_tile ? 8 * v + (blockIdx.x & 7) : (blockIdx.x & 7) * per + v;
+          if (item >= total) continue;
+        } else {
+          item = P.by_tile ? 8 * u + (blockIdx.x & 7) : (blockIdx.x & 7) * per + u;
+          if (u >= per || item >= total) break;
+          u += slots;
+        }
       } else {
         if (wave == 0) {  // one wave draws for the workgroup
           const bool ok = next_item(d, P.header, total, (uint32_t)P.chunk_shift, lane, item);
@@ -1994,7 +2246,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
       const uint64_t tl_begin = wall_clock64();
 #endif
       if constexpr (PIPE) prefill_item_wgp<DT>(P, seq, head, qt, smem, s_tab, wave);
-      else prefill_item_wg<DT, NW, decltype(ncb_c)::value, SUBS, DEQ, HD, SUM32, decltype(groups_c)::value>(P, header, seq, shape, head, qt, smem, s_tab, wave, held);
+      else prefill_item_wg<DT, NW, decltype(ncb_c)::value, SUBS, DEQ, HD, SUM32, decltype(groups_c)::value, SPLIT>(P, header, seq, shape, head, qt, smem, s_tab, wave, held, piece);
 #ifdef FS_TIMELINE
       ++tl_items;
       if (threadIdx.x == 0 && item < kPfTimelineItems) {
@@ -2067,14 +2319,16 @@ extern "C" uint64_t fs_prefill_timeline_bytes(uint64_t* group_rows, uint64_t* it
 }
 #endif
 
-uint64_t fs_prefill_workspace_bytes(int n_seq) {
-  if (n_seq < 1) return 0;
+// The workspace: header and first tiles, which every launch needs, then the pieces of split items; a workspace that ends before
+// these is served as well, with whole items.  (Timeline build: the readings lie at the end, and it has to be all there.)
+static uint64_t pieces_at(int n_seq) { return align256(kHeaderBytes + 4ull * ((uint64_t)n_seq + 1)); }
 #ifdef FS_TIMELINE
-  return align256(kHeaderBytes + 4ull * ((uint64_t)n_seq + 1)) + kPfTimelineBytes;
+uint64_t fs_prefill_workspace_bytes(int n_seq) { return n_seq < 1 ? 0 : align256(pieces_at(n_seq) + kPiecesBytes) + kPfTimelineBytes; }
+static uint64_t least_workspace_bytes(int n_seq) { return fs_prefill_workspace_bytes(n_seq); }
 #else
-  return align256(kHeaderBytes + 4ull * ((uint64_t)n_seq + 1));
+uint64_t fs_prefill_workspace_bytes(int n_seq) { return n_seq < 1 ? 0 : pieces_at(n_seq) + kPiecesBytes; }
+static uint64_t least_workspace_bytes(int n_seq) { return pieces_at(n_seq); }
 #endif
-}
 
 int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads, float sm_scale, const void* q,
                          const int32_t* block_tables, const int32_t* seq_lens, const int32_t* q_offsets,
@@ -2189,7 +2443,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     set_error("prefill attention: FP8 model has no scales (fs_model_set_fp8_scales)");
     return FS_ERR_INVALID;
   }
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < fs_prefill_workspace_bytes(n_seq)) {
+  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < least_workspace_bytes(n_seq)) {
     set_error("prefill attention: workspace missing, not 256-byte aligned or too small (see fs_prefill_workspace_bytes)");
     return workspace && !((uintptr_t)workspace & 255) ? FS_ERR_NOMEM : FS_ERR_INVALID;
   }
@@ -2227,7 +2481,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   P.header = (uint32_t*)workspace;
   P.tile_first = (uint32_t*)((uint8_t*)workspace + kHeaderBytes);
 #ifdef FS_TIMELINE
-  P.timeline = (uint64_t*)((uint8_t*)workspace + align256(kHeaderBytes + 4ull * ((uint64_t)n_seq + 1)));
+  P.timeline = (uint64_t*)((uint8_t*)workspace + fs_prefill_workspace_bytes(n_seq) - kPfTimelineBytes);
 #endif
   P.tpt = tpt;
   P.ncb = ncb;
@@ -2254,6 +2508,22 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   P.tf_cache = !wg || generic ? 0 : (nw == 8 || d256) && n_seq <= nw * 64 ? 2 : (uint64_t)n_seq + 1 <= 4096;
   // no more items than compute units: a direct launch (see "Direct launches")
   P.direct = P.tf_cache == 2 && items <= (uint64_t)p->n_cu;
+  // Split items: up to four of 16 blocks per compute unit (the queue deals more as evenly: 3 prompts of 2000 - 6000 tokens, 3.8 per
+  // unit, 509 us with either), where the tables can hold eight steps (the workgroups, who see the lengths, decide: see lay_plan) and the
+  // workspace has room for the pieces.
+  const bool deq_on = p->opt.prefill_deq || g.kv_dtype == FS_KV_FP16 || g.kv_dtype == FS_KV_FP8_E4M3;
+  const uint32_t split_groups = std::min<uint32_t>(kSplitGroups, (uint32_t)p->n_cu & ~7u);
+  const int64_t capacity = std::min<int64_t>((int64_t)max_blocks * g.tokens_per_block, 0x7fffffff);
+  bool split = P.tf_cache == 2 && g.head_dim == kD && nw == 8 && ncb == 16 && !ncb_env && large && deq_on && split_groups >= 8 &&
+               items <= kSplitItems * (uint64_t)p->n_cu && capacity >= 128 * (int64_t)kSplitLeast &&
+               (uint64_t)(capacity / 128 + 2) * items < (1ull << 31) &&  // (sums of steps)
+               workspace_bytes >= fs_prefill_workspace_bytes(n_seq);
+  P.plan_items = (int32_t)((items + 7) / 8 * 8);
+  P.pieces = (uint8_t*)workspace + pieces_at(n_seq);
+  const size_t smem_split = 2 * (size_t)stage_bytes(4, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes + seq_list_bytes(n_seq) +
+                            split_plan_bytes((uint32_t)P.plan_items);
+  if (smem_split > 160 * 1024) split = false;
+  if (split) P.direct = 1;
   hipError_t e = hipSuccess;
   if (!P.direct) {
     hipLaunchKernelGGL(prefill_prep_kernel, dim3(1), dim3(kPrepThreads), 0, s, P);
@@ -2278,7 +2548,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   const int wps = ncb == 1 ? mfma_wgs_per_cu(g.head_dim) : 1;
   // workgroup kernels: 16 blocks = 8 waves x 2 (default) or 4 x 4, 4 sub-tiles per step, one workgroup per compute unit
   const int subs = d256 ? 2 : 4, wpc = 1;
-  const int n_wg = P.direct ? (int)((items + 7) / 8 * 8) : wg ? (int)std::min<uint64_t>((uint64_t)p->n_cu * wpc, std::max<uint64_t>(items, 1))
+  const int n_wg = split ? (int)split_groups : P.direct ? (int)((items + 7) / 8 * 8) : wg ? (int)std::min<uint64_t>((uint64_t)p->n_cu * wpc, std::max<uint64_t>(items, 1))
                       : (int)std::min<uint64_t>((uint64_t)p->n_cu * wps, std::max<uint64_t>((items + kWaves - 1) / kWaves, 1));
   // (The other kernels, and other numbers of heads:) consecutive items -- the query tiles of one (sequence, head), which stream
   // the same K/V -- go to one XCD in chunks of 128 (a head of 8192 tokens in one piece: measured + 1.4 % over chunks of 32 on long prompts), of
@@ -2296,7 +2566,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // 21045 -> 21929 / 21370 -> 21957.
   P.by_tile = wg && (g.n_kv_heads % 8 == 0 || g.n_kv_heads == 4 || (g.n_kv_heads <= 2 && items <= 20 * (uint64_t)p->n_cu));
   if (P.by_tile) P.chunk_shift = 0;
-  const size_t smem = wg ? 2 * (size_t)stage_bytes(subs, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes +
+  const size_t smem = split ? smem_split : wg ? 2 * (size_t)stage_bytes(subs, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes +
                                (P.tf_cache == 2 ? seq_list_bytes(n_seq) : P.tf_cache ? (((size_t)n_seq + 1) * 4 + 15) / 16 * 16 : 0)
                          : (size_t)kWaves * P.table_entries * sizeof(uint64_t);
   if (wg) {
@@ -2347,6 +2617,15 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
         default: kern = FS_WG64(FS_KV_INT4, 3); break;
       }
 #undef FS_WG64
+    } else if (split) {
+#define FS_WGS(DT, DEQ) prefill_wg_kernel<DT, 8, 2, 4, 1, false, DEQ, kD, false, false, true>
+      switch (g.kv_dtype) {
+        case FS_KV_FP16: kern = FS_WGS(FS_KV_FP16, false); break;
+        case FS_KV_FP8_E4M3: kern = FS_WGS(FS_KV_FP8_E4M3, false); break;
+        case FS_KV_INT8: kern = FS_WGS(FS_KV_INT8, true); break;
+        default: kern = FS_WGS(FS_KV_INT4, true); break;
+      }
+#undef FS_WGS
     } else switch (g.kv_dtype) {
       case FS_KV_FP16: kern = large ? FS_WG(FS_KV_FP16) : prefill_wg_kernel<FS_KV_FP16, 8, 2, 4, 1, false, false, kD, true>; break;
       case FS_KV_FP8_E4M3: kern = large ? FS_WG(FS_KV_FP8_E4M3) : prefill_wg_kernel<FS_KV_FP8_E4M3, 8, 2, 4, 1, false, false, kD, true>; break;

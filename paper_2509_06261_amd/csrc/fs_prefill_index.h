@@ -46,6 +46,57 @@ __device__ __host__ inline bool decode_item_by_tile(const uint32_t* tf, int n_se
   return true;
 }
 
+// ---- Launches whose items are split (see "Split items" in fs_prefill.hip): the items' steps in a row, cut into equal ranges ----
+constexpr uint32_t kSplitGroups = 256;  // most workgroups of such a launch
+constexpr uint32_t kSplitLeast = 8;     // fewest steps of a range
+constexpr uint32_t kSplitItems = 4;     // most items per compute unit of a launch with split items
+// Place u of an XCD's `per` items when `turns` sequences of per / turns items each are dealt one item from each in turn.
+__device__ __host__ inline uint32_t dealt(uint32_t u, uint32_t per, uint32_t turns) { return u % turns * (per / turns) + u / turns; }
+// Place i of the plan's order, an XCD's items one after the other (per each): which item of the launch that is.
+__device__ __host__ inline uint32_t plan_item(bool by_tile, uint32_t i, uint32_t per, uint32_t turns) {
+  const uint32_t x = i / per, u = dealt(i - x * per, per, turns);
+  return by_tile ? 8 * u + x : x * per + u;
+}
+// How many of an XCD's `per` items stand before its u-th one by their steps, most first.
+__device__ __host__ inline uint32_t item_rank(const uint32_t* steps, uint32_t per, uint32_t u) {
+  const uint32_t mine = steps[u];
+  uint32_t rank = 0;
+  for (uint32_t v = 0; v < per; ++v) rank += steps[v] > mine || (steps[v] == mine && v < u);
+  return rank;
+}
+// Whole items, dealt to `slots` workgroups there and back: the place that follows from a workgroup's u-th one (u = its own
+// index, then + slots).
+__device__ __host__ inline uint32_t snake(uint32_t u, uint32_t slots) {
+  const uint32_t round = u / slots, k = u - round * slots;
+  return round & 1 ? u - k + (slots - 1 - k) : u;
+}
+// The last of n items that begins at or before step p: the one with that step, where p is a step of the launch.
+__device__ __host__ inline uint32_t item_of_step(const uint32_t* cum, uint32_t n, uint32_t p) {
+  uint32_t lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi + 1) >> 1;
+    if (cum[mid] <= p) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+// Where the range of workgroup k begins.  A cut less than two steps from an end of its item moves there; ranges of
+// kSplitLeast steps keep four at least.
+__device__ __host__ inline uint32_t plan_cut(const uint32_t* cum, uint32_t n, uint32_t groups, uint32_t k) {
+  const uint32_t steps = cum[n], p = (uint32_t)((uint64_t)steps * k / groups);
+  if (k == 0 || k >= groups) return p;
+  const uint32_t i = item_of_step(cum, n, p);
+  return p - cum[i] < 2 ? cum[i] : cum[i + 1] - p < 2 ? cum[i + 1] : p;
+}
+// The workgroups first .. last with a piece of the item of steps from .. to, of which workgroup `me` has one.
+__device__ __host__ inline void piece_owners(const uint32_t* cut, uint32_t me, uint32_t from, uint32_t to, uint32_t& first, uint32_t& last) {
+  first = last = me;
+  while (cut[first] > from) --first;     // (cut[0] = 0)
+  while (cut[last + 1] < to) ++last;     // (the last cut: all steps)
+}
+// An item's first piece is the last of its workgroup's range, the others are the first of theirs: two places a workgroup.
+__device__ __host__ inline uint32_t piece_place(uint32_t first, uint32_t k) { return 2 * (first + k) + (k ? 0 : 1); }
+
 // Runs of 8 token slots streamed per refill of a wave's block-address table (a multiple of 4, about 500 blocks),
 // and the table's entries: the blocks such a segment can touch.
 __device__ __host__ inline int32_t prefill_seg_runs(int R) {

@@ -676,6 +676,65 @@ void prefill_order_by_tile(int rounds) {
   }
 }
 
+// Launches with split items: the plan's places are the launch's items one to one, the workgroups' ranges hold every step of
+// every item once, all workgroups with a piece of an item name the same ones, a piece's place is nobody else's.
+void prefill_split_plan(int rounds) {
+  for (int round = 0; round < rounds; ++round) {
+    const uint32_t groups = round % 3 ? fs::kSplitGroups : 8 * (1 + (uint32_t)(rnd() % 32)), total = 1 + (uint32_t)(rnd() % (4 * groups));
+    const uint32_t turns = 1 + (uint32_t)(round % 4 ? rnd() % 12 : 0), per = ((total + 7) / 8 + turns - 1) / turns * turns, n = 8 * per, slots = groups / 8;
+    std::vector<uint32_t> whole(per, 0);  // whole items: every place once
+    for (uint32_t k = 0; k < slots; ++k)
+      for (uint32_t u = k; u - u % slots < per; u += slots)
+        if (fs::snake(u, slots) < per) CHECK(!whole[fs::snake(u, slots)]++);
+    for (uint32_t u = 0; u < per; ++u) CHECK(whole[u] == 1);
+    std::vector<uint32_t> steps(per), by_rank(per, 0);
+    for (uint32_t u = 0; u < per; ++u) steps[u] = (uint32_t)(rnd() % 9);
+    for (uint32_t u = 0; u < per; ++u) {
+      const uint32_t r = fs::item_rank(steps.data(), per, u);
+      CHECK(r < per && !by_rank[r]++);
+    }
+    const uint32_t most = 1 + (uint32_t)(rnd() % (round % 5 ? 200 : 20000));
+    const bool by_tile = rnd() & 1;
+    std::vector<uint32_t> cum(n + 1, 0), cut(groups + 1), seen(n, 0);
+    for (uint32_t i = 0; i < n; ++i) {
+      const uint32_t item = fs::plan_item(by_tile, i, per, turns);
+      CHECK(item < n && !seen[item]);
+      seen[item] = 1;
+      cum[i + 1] = cum[i] + (item < total ? 1 + (uint32_t)(rnd() % most) : 0);
+    }
+    if (cum[n] / groups < fs::kSplitLeast) continue;
+    for (uint32_t k = 0; k <= groups; ++k) cut[k] = fs::plan_cut(cum.data(), n, groups, k);
+    CHECK(cut[0] == 0 && cut[groups] == cum[n]);
+    std::vector<uint32_t> done(n, 0), pieces(n, 0), counter(groups, 0), place(2 * groups, 0);
+    for (uint32_t k = 0; k < groups; ++k) {
+      CHECK(cut[k + 1] >= cut[k] + 4);
+      uint32_t at = cut[k], i = fs::item_of_step(cum.data(), n, at);
+      while (at < cut[k + 1]) {
+        CHECK(i < n);
+        const uint32_t from = cum[i], to = cum[i + 1], end = std::min(to, cut[k + 1]);
+        if (to <= at) { ++i; continue; }
+        CHECK(at >= from);
+        uint32_t first, last;
+        fs::piece_owners(cut.data(), k, from, to, first, last);
+        CHECK(first <= k && k <= last && last < groups);
+        CHECK((first == k) == (at == from) && (last == k) == (end == to));
+        done[i] += end - at;
+        ++pieces[i];
+        if (last > first) {
+          const uint32_t at_place = fs::piece_place(first, k - first);
+          CHECK(at_place < 2 * groups && !place[at_place]);
+          place[at_place] = 1;
+          if (k == first) CHECK(!counter[first]++);
+          if (k == last) CHECK(pieces[i] == last - first + 1);
+        }
+        at = end;
+        ++i;
+      }
+    }
+    for (uint32_t i = 0; i < n; ++i) CHECK(done[i] == cum[i + 1] - cum[i]);
+  }
+}
+
 // The workgroup prefill kernels' walk by tokens: every row of every sub-tile of a context is its token's place, the last
 // token's past a segment's end, and no look-up leaves the segment's table.
 void prefill_token_walk(int rounds) {
@@ -744,6 +803,7 @@ int main() {
   prefill_longest_contexts();
   prefill_token_walk(240);
   prefill_order_by_tile(60);
+  prefill_split_plan(300);
   run(600);
   direct_order();
   direct_rule();
