@@ -1,0 +1,50 @@
+"""What the built library's own device code has to hold, read from its disassembly (no GPU needed)."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{kernel name: its instructions in order} of libfineserve.so."""
+    lib = os.path.join(ROOT, "paper_2509_06261_amd", "libfineserve.so")
+    if not os.path.exists(OBJDUMP) or not os.path.exists(lib):
+        pytest.skip("llvm-objdump or the built library not found")
+    tmp = tmp_path_factory.mktemp("device_code")
+    lib = shutil.copy(lib, tmp)
+    subprocess.run([OBJDUMP, "--offloading", lib], check=True, cwd=tmp, stdout=subprocess.DEVNULL)
+    found = {}
+    for name in sorted(os.listdir(tmp)):
+        if not name.endswith("gfx950"):
+            continue
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", os.path.join(tmp, name)], check=True,
+                              stdout=subprocess.PIPE, text=True).stdout
+        for part in re.split(r"^<", text, flags=re.M)[1:]:
+            head, _, body = part.partition(">:")
+            found[head] = [line.split("//")[0].strip() for line in body.splitlines() if line.strip()]
+    assert found
+    return found
+
+
+def test_pieces_are_complete_before_they_are_counted(kernels):
+    """Prefill kernels with split items: a wave's stores of its piece go to where all XCDs see them (sc1, agent scope), the
+    wave waits for its own stores before the barrier in front of the count (a barrier waits for none), and the pieces are read
+    from there as well; or the piece is written back and invalidated as a whole by every wave."""
+    split = {k: v for k, v in kernels.items() if "prefill_wg_kernel" in k and any("cmpswap_x2" in i for i in v)}
+    assert len(split) == 4  # one for each format
+    for name, code in split.items():
+        count = next(i for i, x in enumerate(code) if "cmpswap_x2" in x)
+        before = max(i for i in range(count) if code[i] == "s_barrier")
+        stores = [i for i in range(before) if code[i].startswith("global_store")][-32:]
+        wait = code[stores[-1] + 1 : before]
+        assert any(x.startswith("s_waitcnt vmcnt(0)") for x in wait), name
+        assert all(code[i].endswith(" sc1") for i in stores) or "buffer_wbl2 sc1" in wait, name
+        after = min(i for i in range(count, len(code)) if code[i] == "s_barrier")
+        loads = [i for i in range(after, len(code)) if code[i].startswith("global_load")][:32]
+        assert all(code[i].endswith(" sc1") for i in loads) or "buffer_inv sc1" in code[after : loads[0]], name
