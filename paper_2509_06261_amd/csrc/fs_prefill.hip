@@ -2593,7 +2593,11 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // end matters: 12 prompts (5 items per unit) 322 -> 314 / 324 -> 323, six FP8 ones of 11000 - 16000 (20) 4116 -> 3993 / 4151 -> 4001;
   // two of 7000 and 8000 (4) 568 -> 575 / 562 -> 575; but 48 of 500 - 3500 (23) 1105 -> 1120 / 1112 -> 1124 and 24 of 14000 - 16000 (87)
   // 21045 -> 21929 / 21370 -> 21957.
-  P.by_tile = wg && (g.n_kv_heads % 8 == 0 || g.n_kv_heads == 4 || (g.n_kv_heads <= 2 && items <= 20 * (uint64_t)p->n_cu));
+  // Launches that may split items take this order with any number of heads: head by head, the XCD with the longest contexts ended
+  // long after the others, and whole items stay on their XCD there.  us, head by head -> by tile: 60 chunks of 16 behind 200 - 4000, 12
+  // heads 239 -> 180, FP8 with 10 heads 189 -> 144; 12 prompts of 300 - 1500, 5 heads 75 -> 64; eight chunks of 1024 behind 976, 5 heads
+  // 105 -> 110 (all three in the queue, behind a preparation launch: 192, 155, 86 and 142).
+  P.by_tile = wg && (split || g.n_kv_heads % 8 == 0 || g.n_kv_heads == 4 || (g.n_kv_heads <= 2 && items <= 20 * (uint64_t)p->n_cu));
   if (P.by_tile) P.chunk_shift = 0;
   const size_t smem = split ? smem_split : wg ? 2 * (size_t)stage_bytes(subs, g.head_dim) + (size_t)P.table_entries * 8 + kWgCtlBytes +
                                (P.tf_cache == 2 ? seq_list_bytes(n_seq) : P.tf_cache ? (((size_t)n_seq + 1) * 4 + 15) / 16 * 16 : 0)
