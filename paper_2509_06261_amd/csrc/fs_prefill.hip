@@ -2025,25 +2025,29 @@ __device__ __forceinline__ uint32_t scan_sequences(const PrefillArgs& P, const S
 struct SplitPlan {
   uint32_t* cum;  // [plan_items + 1]
   uint32_t* cut;  // [workgroups + 1]
-  uint16_t* order;     // [plan_items] whole items: an XCD's items by their steps, most first ...
+  uint16_t* order;     // [8][kSplitItems][workgroups / 8] whole items: XCD, round, workgroup of the XCD -> the XCD's item (0xffff: none) ...
   bool sorted = false; // ... where it has more of them than workgroups
   uint32_t turns = 1;  // sequences whose tiles are dealt one from each in turn (see plan_item)
 };
-constexpr uint32_t split_plan_bytes(uint32_t plan_items) { return (plan_items + 1 + kSplitGroups + 1) * 4 + plan_items * 2; }
+constexpr uint32_t split_plan_bytes(uint32_t plan_items) { return (plan_items + 1 + kSplitGroups + 1) * 4 + kSplitItems * kSplitGroups * 2; }
 // Lays the plan (n = 8 per items, n <= plan_items, n > 0); false: the items stay whole, each workgroup taking its XCD's in turn.
 // That is so where a range has fewer than eight steps, and where the busiest workgroup would not end late enough after the
-// mean: a cut costs its two workgroups an item's start (1.5 steps) and a piece written and read again (2), and workgroups that
-// read the same context out of step share fewer of its lines in their L2.  Where the sequences bring the same number of tiles, no
-// more than an XCD has workgroups, the plan goes through the sequences tile by tile, and the ranges of a sequence's tiles begin
-// at (nearly) the same of its steps: a sixteenth is enough there, a quarter elsewhere.
-// us, FP16 / FP8 / INT4, 8 heads x 4: 5 chunks of 512 behind 3500 (320 items) 270 -> 217 / 245 -> 197 / 271 -> 212, 6 behind 7500 513 ->
-// 460 / 459 -> 398 / 513 -> 439, 8 of 256 behind 4000 - 12000 364 -> 328 / 318 -> 281 / 359 -> 308.  Cut wherever a sixteenth was to be
-// gained, one prompt of 6000 tokens took 340 -> 393 / 302 -> 362 / 335 -> 389, two of 1875 and 2625 140 -> 155 / 128 -> 148 / 141 -> 156.
-// Whole items are dealt by their steps, most first, there and back over the workgroups (item_rank, snake), against the ticket queue
-// behind a preparation launch: one prompt of 3000 140 -> 111 / 130 -> 100 / 143 -> 110; those two 141 -> 134 / 129 -> 125 / 142 -> 133
-// (157 / 150 / 157 in the queue's order); 12 chunks of 300 behind 500 - 15000 694 -> 539 / 613 -> 464 / 689 -> 518; 40 of 64 behind
-// 250 - 1100 79 -> 62 / 74 -> 59 / 79 -> 61; prompts of three and four items per unit, and what is no longer than a round, the same
-// within 0.6 %.
+// mean.  Both count an item's start as two steps (kItemStart): ranges of steps alone held more items where contexts are short, and
+// 128 chunks of 16 behind 100 - 3000 took 238 us if cut, 207 with starts counted, 165 whole.  A cut costs its two workgroups an item's
+// start and a piece written and read again (six steps in all), and workgroups that read the same context out of step share fewer of
+// its lines in their L2.  Where the sequences bring one tile each, or the same number and no more than an XCD has workgroups (the plan
+// then goes through the sequences tile by tile, and the ranges of a sequence's tiles begin at nearly the same of its steps), a
+// sixteenth more is enough; a quarter elsewhere.  Forced to either side, whole -> cut, us by the busiest workgroup over the mean, FP16 /
+// FP8 / INT4, 8 heads x 4: chunks of 16 behind 4000: 40 (68 over 42 steps) 186 -> 145 / 170 -> 127 / 182 -> 136, 80 (102 / 85) 285 -> 260 / 258 ->
+// 230 / 277 -> 245, 88 (102 / 93) 291 -> 293 / 261 -> 257 / 279 -> 273, 128 (136 / 136) 388 -> 394 / 346 -> 353 / 371 -> 376; of 64 behind 1000 - 9000:
+// 40 (72 / 52) 311 -> 282 / 255 -> 233 / 275 -> 242, 72 (107 / 93) 493 -> 494 / 401 -> 407 / 430 -> 419, 88 (127 / 114) 589 -> 600 / 483 -> 495 / 507 ->
+// 515; of 512: 4 behind 1500 - 6000 (45 / 30) 171 -> 146 / 156 -> 136 / 170 -> 143, 6 behind 1500 (32 / 25) 129 -> 126 / 119 -> 116 / 128 -> 124; one
+// prompt of 5000 tokens (62 / 55) 244 -> 249 / 224 -> 226 / 242 -> 243, of 4000 (34 / 32) 152 -> 192 / 136 -> 185 / 149 -> 193 (steps alone).
+// Whole items are dealt by their steps, most first, the first two rounds there and back over an XCD's workgroups and the others to
+// whoever has least so far (item_rank, snake, load_rank).  Against the ticket queue behind a preparation launch, us: one prompt of 3000
+// 138 -> 104 / 128 -> 95 / 140 -> 102; 12 chunks of 300 behind 100 - 16000 705 -> 537 / 594 -> 450 / 664 -> 491; 40 of 64 behind 300 - 1200 79 ->
+// 59 / 74 -> 56 / 78 -> 57; three prompts of 1200 - 2000 121 -> 99 (FP16), eight of 256 - 1000 71 -> 66 (FP8); three and four items per unit
+// the same within 2 %.  A launch of an item per unit whose contexts are alike pays the plan's first look, 1 us of 55 - 75.
 __device__ __forceinline__ SplitPlan split_plan(const SeqList& list, int n_seq, int plan_items) {  // (behind the list of sequences)
   uint32_t* const w = list.tf + 5 * n_seq + 1;
   return SplitPlan{w + kSplitGroups + 1, w, reinterpret_cast<uint16_t*>(w + kSplitGroups + 1 + plan_items + 1)};
@@ -2051,17 +2055,43 @@ __device__ __forceinline__ SplitPlan split_plan(const SeqList& list, int n_seq, 
 template <int NT>
 __device__ __forceinline__ bool lay_plan(const PrefillArgs& P, SplitPlan& plan, const SeqList& list, uint32_t* s_tmp, uint32_t total,
                                          int step_tokens, int ncb, int nw) {
+  // Wave x lays XCD x's part; a lane has its items `lane` and, of more than 64, `lane + 64`.
+  static_assert(NT == 512 && kSplitItems * kSplitGroups / 8 <= 128, "a wave for every XCD, two items a lane");
+  const uint32_t lane = threadIdx.x & 63, x = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t per = (total + 7) / 8, n = 8 * per, groups = gridDim.x, slots = groups >> 3;
-  const int q_wg = P.tpt * ncb * nw;
-  if (threadIdx.x == 0) plan.cum[0] = 0, s_tmp[0] = 0, s_tmp[1] = 0;
-  __syncthreads();
+  const int q_wg = P.tpt * ncb * nw, halves = per > 64 ? 2 : 1;
+  uint32_t* const cum = plan.cum + x * per + 1;
+  auto settle = [] {  // (a wave's LDS operations complete in order; this keeps the compiler from turning them round)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // the sequences: whether they bring the same number of tiles, and the tokens that the query tiles of one head see
   const uint32_t tiles = list.tf[1];
-  for (int k = threadIdx.x; k < P.b.n_seq; k += NT)
-    if (list.tf[k + 1] - list.tf[k] != tiles) s_tmp[1] = 1;
-  __syncthreads();
-  const bool even = P.by_tile && P.b.g.H % 8 == 0 && s_tmp[1] == 0 && tiles * (uint32_t)(P.b.g.H / 8) <= slots;  // (uniform)
-  for (uint32_t i = threadIdx.x; i < n; i += NT) {
-    const uint32_t item = plan_item(P.by_tile, i, per, 1);
+  bool same = true;
+  float seen = 0.f;
+  for (int k = lane; k < P.b.n_seq; k += 64) {
+    const uint32_t t = list.tf[k + 1] - list.tf[k];
+    const SeqShape s = list.shape[list.seq[k]];
+    same = same && t == tiles;
+    if (t > 0) seen += (float)t * ((float)(s.len - s.n_new) + 0.5f * (float)(t - 1) * (float)q_wg) + (float)s.n_new;
+  }
+  const bool rows = P.by_tile && P.b.g.H % 8 == 0 && tiles * (uint32_t)(P.b.g.H / 8) <= slots;
+  const bool even = __all(same) && (tiles == 1 || rows);  // (uniform)
+  auto worth = [&](uint32_t mean, uint32_t busy) { return busy > mean + mean / (even ? 16 : 4) + 6; };
+  plan.sorted = per > slots;
+  if (!plan.sorted) {
+    // An item a workgroup at most: none takes longer than the longest sequence's last tile, and the mean is known from below: enough
+    // for the launches whose items are all alike.
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) seen += __shfl_xor(seen, off, 64);
+    const float mean = (0.9999f * seen * (float)P.b.g.H / (float)step_tokens + (float)(kItemStart * total)) / (float)groups;
+    if (!worth((uint32_t)mean, (uint32_t)((list.shape[list.seq[0]].len - 1) / step_tokens + 1) + kItemStart)) return false;
+  }
+  uint32_t sum = 0, busy = 0;
+#pragma unroll 1
+  for (int h = 0; h < halves; ++h) {
+    const uint32_t u = lane + 64 * h, item = u < per ? plan_item(P.by_tile, x * per + u, per, 1) : total;
     uint32_t steps = 0;
     int seq, head, qt;
     if (item < total && (P.by_tile ? fs::decode_item_by_tile(list.tf, P.b.n_seq, item, (uint32_t)P.b.g.H, seq, head, qt)
@@ -2069,57 +2099,85 @@ __device__ __forceinline__ bool lay_plan(const PrefillArgs& P, SplitPlan& plan, 
       const SeqShape s = list.shape[list.seq[seq]];
       steps = (uint32_t)(((int64_t)s.len - s.n_new + min((qt + 1) * q_wg, s.n_new) + step_tokens - 1) / step_tokens);
     }
-    plan.cum[i + 1] = steps;
+    if (steps) steps += kItemStart;
+    if (u < per) cum[u] = steps;
+    sum += steps;
+    busy = max(busy, steps);
   }
-  __syncthreads();
-  plan.sorted = per > slots;
-  if (plan.sorted) {  // (uniform)
-    for (uint32_t i = threadIdx.x; i < n; i += NT) {
-      const uint32_t x = i / per;
-      plan.order[x * per + item_rank(plan.cum + x * per + 1, per, i - x * per)] = (uint16_t)(i - x * per);
-    }
-    __syncthreads();
-  }
+  settle();
   // what whole items would take the busiest workgroup, an item's start among it
-  uint32_t busy = 0;
-  if (threadIdx.x < groups)
-    for (uint32_t u = threadIdx.x >> 3; u - u % slots < per; u += slots) {
-      const uint32_t v = snake(u, slots);
-      if (v < per) busy += plan.cum[(threadIdx.x & 7) * per + (plan.sorted ? plan.order[(threadIdx.x & 7) * per + v] : v) + 1] + 1;
+  if (plan.sorted) {  // (uniform)
+    uint32_t* const by_rank = s_tmp + 32 + x * 256;  // [128] steps, [128] items, [64] loads behind all of them
+    uint32_t* const load = s_tmp + 32 + 8 * 256 + x * 64;
+    bool falling = true;  // (so are one sequence's tiles, and sequences of one tile each)
+    for (int h = 0; h < halves; ++h) {
+      const uint32_t u = lane + 64 * h;
+      if (u + 1 < per) falling = falling && cum[u] >= cum[u + 1];
     }
-  if (busy) atomicMax(s_tmp, busy);
-  if (even) {  // (a thread has at most kSplitItems items of a workgroup each: n <= 4 * 256, NT = 512)
-    plan.turns = (uint32_t)P.b.n_seq;
-    uint32_t mine[2 * kSplitItems];
-    uint32_t k = 0;
-    for (uint32_t i = threadIdx.x; i < n && k < 2 * kSplitItems; i += NT, ++k) {
-      const uint32_t x = i / per, u = i - x * per;
-      mine[k] = plan.cum[x * per + dealt(u, per, plan.turns) + 1];
+    falling = __all(falling);
+#pragma unroll 1
+    for (int h = 0; h < halves; ++h) {
+      const uint32_t u = lane + 64 * h;
+      if (u >= per) continue;
+      const uint32_t rank = falling ? u : item_rank(cum, per, u);
+      by_rank[rank] = cum[u];
+      by_rank[128 + rank] = u;
     }
-    __syncthreads();
-    k = 0;
-    for (uint32_t i = threadIdx.x; i < n && k < 2 * kSplitItems; i += NT, ++k) plan.cum[i + 1] = mine[k];
+    settle();
+    busy = 0;
+#pragma unroll 1
+    for (uint32_t first = 0; first < per; first += slots) {
+      load[lane] = busy;
+      settle();
+      // the first two rounds there and back, the others to whoever has least so far
+      const uint32_t k = lane < slots ? lane : slots - 1;
+      const uint32_t at = first < 2 * slots ? snake(first + k, slots) : first + load_rank(load, slots, k);
+      if (lane < slots) {
+        const bool has = at < per;
+        plan.order[(x * kSplitItems + first / slots) * slots + lane] = has ? (uint16_t)by_rank[128 + at] : (uint16_t)0xffff;
+        if (has) busy += by_rank[at];
+      }
+      settle();
+    }
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    sum += __shfl_xor(sum, off, 64);
+    busy = max(busy, (uint32_t)__shfl_xor(busy, off, 64));
+  }
+  if (lane == 0) s_tmp[x] = sum, s_tmp[8 + x] = busy;
   __syncthreads();
-  if (threadIdx.x < 64) {  // inclusive sums: each lane its run of items
-    const uint32_t run = (n + 63) / 64, a = min(threadIdx.x * run, n), b = min(a + run, n);
-    uint32_t sum = 0;
-    for (uint32_t i = a; i < b; ++i) sum += plan.cum[i + 1];
-    uint32_t incl = sum;
+  uint32_t steps = 0, before = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < 8; ++k) {
+    before += k < x ? s_tmp[k] : 0u;
+    steps += s_tmp[k];
+    busy = max(busy, s_tmp[8 + k]);
+  }
+  const uint32_t mean = steps / groups;
+  if (mean < kSplitLeast || !worth(mean, busy)) return false;
+  // running sums, the XCD's first step in front of them
+  if (even && rows) plan.turns = (uint32_t)P.b.n_seq;
+  uint32_t mine[2] = {0, 0};
+  for (int h = 0; h < halves; ++h) {
+    const uint32_t u = lane + 64 * h;
+    if (u < per) mine[h] = cum[dealt(u, per, plan.turns)];
+  }
+  settle();
+  for (int h = 0; h < halves; ++h) {
+    const uint32_t u = lane + 64 * h;
+    uint32_t incl = mine[h];
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const uint32_t up = __shfl_up(incl, off, 64);
-      if ((int)threadIdx.x >= off) incl += up;
+      if ((int)lane >= off) incl += up;
     }
-    uint32_t at = incl - sum;
-    for (uint32_t i = a; i < b; ++i) plan.cum[i + 1] = at += plan.cum[i + 1];
+    if (u < per) cum[u] = before + incl;
+    before += __shfl(incl, 63, 64);
   }
+  if (threadIdx.x == 0) plan.cum[0] = 0;
   __syncthreads();
-  const uint32_t steps = plan.cum[n], mean = steps / groups;
-  if (mean < kSplitLeast || s_tmp[0] <= mean + mean / (even ? 16 : 4) + 6) return false;
-  for (uint32_t k = threadIdx.x; k <= groups; k += NT) {
-    plan.cut[k] = plan_cut(plan.cum, n, groups, k);
-  }
+  for (uint32_t k = threadIdx.x; k <= groups; k += NT) plan.cut[k] = plan_cut(plan.cum, n, groups, k);
   __syncthreads();
   return true;
 }
@@ -2224,8 +2282,8 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
         item = plan_item(P.by_tile, i_plan, per, plan.turns);
         ++i_plan;
         if (to <= at) continue;  // (an item without steps)
-        piece.step = (int)(at - from);
-        piece.end = (int)(min(to, end) - from);
+        piece.step = at > from ? (int)(at - from - kItemStart) : 0;
+        piece.end = (int)(min(to, end) - from - kItemStart);
         uint32_t last;
         piece_owners(plan.cut, me, from, to, piece.first, last);
         piece.first = __builtin_amdgcn_readfirstlane(piece.first);
@@ -2235,10 +2293,9 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
       } else if (direct) {
         if constexpr (SPLIT) {  // (whoever had the longest item of one round has the shortest of the next)
           if (u - u % slots >= per) break;
-          uint32_t v = snake(u, slots);
+          const uint32_t v = plan.sorted ? __builtin_amdgcn_readfirstlane((uint32_t)plan.order[(blockIdx.x & 7) * kSplitItems * slots + u]) : u;
           u += slots;
           if (v >= per) continue;
-          if (plan.sorted) v = __builtin_amdgcn_readfirstlane((uint32_t)plan.order[(blockIdx.x & 7) * per + v]);
           item = P.by_tile ? 8 * v + (blockIdx.x & 7) : (blockIdx.x & 7) * per + v;
           if (item >= total) continue;
         } else {
@@ -2544,8 +2601,8 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   const uint32_t split_groups = std::min<uint32_t>(kSplitGroups, (uint32_t)p->n_cu & ~7u);
   const int64_t capacity = std::min<int64_t>((int64_t)max_blocks * g.tokens_per_block, 0x7fffffff);
   bool split = P.tf_cache == 2 && g.head_dim == kD && nw == 8 && ncb == 16 && !ncb_env && large && deq_on && split_groups >= 8 &&
-               items <= kSplitItems * (uint64_t)p->n_cu && capacity >= 128 * (int64_t)kSplitLeast &&
-               (uint64_t)(capacity / 128 + 2) * items < (1ull << 31) &&  // (sums of steps)
+               items <= kSplitItems * (uint64_t)split_groups && capacity >= 128 * (int64_t)kSplitLeast &&
+               (uint64_t)(capacity / 128 + 2 + kItemStart) * items < (1ull << 31) &&  // (sums of steps)
                workspace_bytes >= fs_prefill_workspace_bytes(n_seq);
   P.plan_items = (int32_t)((items + 7) / 8 * 8);
   P.pieces = (uint8_t*)workspace + pieces_at(n_seq);

@@ -49,6 +49,7 @@ __device__ __host__ inline bool decode_item_by_tile(const uint32_t* tf, int n_se
 // ---- Launches whose items are split (see "Split items" in fs_prefill.hip): the items' steps in a row, cut into equal ranges ----
 constexpr uint32_t kSplitGroups = 256;  // most workgroups of such a launch
 constexpr uint32_t kSplitLeast = 8;     // fewest steps of a range
+constexpr uint32_t kItemStart = 2;      // steps that an item's start is worth
 constexpr uint32_t kSplitItems = 4;     // most items per compute unit of a launch with split items
 // Place u of an XCD's `per` items when `turns` sequences of per / turns items each are dealt one item from each in turn.
 __device__ __host__ inline uint32_t dealt(uint32_t u, uint32_t per, uint32_t turns) { return u % turns * (per / turns) + u / turns; }
@@ -61,6 +62,7 @@ __device__ __host__ inline uint32_t plan_item(bool by_tile, uint32_t i, uint32_t
 __device__ __host__ inline uint32_t item_rank(const uint32_t* steps, uint32_t per, uint32_t u) {
   const uint32_t mine = steps[u];
   uint32_t rank = 0;
+#pragma unroll 8
   for (uint32_t v = 0; v < per; ++v) rank += steps[v] > mine || (steps[v] == mine && v < u);
   return rank;
 }
@@ -69,6 +71,14 @@ __device__ __host__ inline uint32_t item_rank(const uint32_t* steps, uint32_t pe
 __device__ __host__ inline uint32_t snake(uint32_t u, uint32_t slots) {
   const uint32_t round = u / slots, k = u - round * slots;
   return round & 1 ? u - k + (slots - 1 - k) : u;
+}
+// How many of an XCD's `slots` workgroups come before its k-th one by what they have, least first.
+__device__ __host__ inline uint32_t load_rank(const uint32_t* load, uint32_t slots, uint32_t k) {
+  const uint32_t mine = load[k];
+  uint32_t rank = 0;
+#pragma unroll 8
+  for (uint32_t i = 0; i < slots; ++i) rank += load[i] < mine || (load[i] == mine && i < k);
+  return rank;
 }
 // The last of n items that begins at or before step p: the one with that step, where p is a step of the launch.
 __device__ __host__ inline uint32_t item_of_step(const uint32_t* cum, uint32_t n, uint32_t p) {
@@ -86,7 +96,7 @@ __device__ __host__ inline uint32_t plan_cut(const uint32_t* cum, uint32_t n, ui
   const uint32_t steps = cum[n], p = (uint32_t)((uint64_t)steps * k / groups);
   if (k == 0 || k >= groups) return p;
   const uint32_t i = item_of_step(cum, n, p);
-  return p - cum[i] < 2 ? cum[i] : cum[i + 1] - p < 2 ? cum[i + 1] : p;
+  return p - cum[i] < kItemStart + 2 ? cum[i] : cum[i + 1] - p < 2 ? cum[i + 1] : p;
 }
 // The workgroups first .. last with a piece of the item of steps from .. to, of which workgroup `me` has one.
 __device__ __host__ inline void piece_owners(const uint32_t* cut, uint32_t me, uint32_t from, uint32_t to, uint32_t& first, uint32_t& last) {

@@ -735,6 +735,45 @@ void prefill_split_plan(int rounds) {
   }
 }
 
+// Steps and items' starts in one row: a cut lies between items or leaves each side two steps at least, and what the workgroups take of
+// an item are its steps, once.  Whole items of the later rounds: every workgroup of an XCD gets one.
+void prefill_split_starts(int rounds) {
+  for (int round = 0; round < rounds; ++round) {
+    const uint32_t groups = fs::kSplitGroups, n = 8 * (1 + (uint32_t)(rnd() % 128)), most = 1 + (uint32_t)(rnd() % (round % 3 ? 60 : 3000));
+    std::vector<uint32_t> steps(n), cum(n + 1, 0), done(n, 0);
+    for (uint32_t i = 0; i < n; ++i) {
+      steps[i] = rnd() % 8 ? 1 + (uint32_t)(rnd() % most) : 0;
+      cum[i + 1] = cum[i] + (steps[i] ? steps[i] + fs::kItemStart : 0);
+    }
+    if (cum[n] / groups >= fs::kSplitLeast) {
+      uint32_t at = 0;
+      for (uint32_t k = 0; k < groups; ++k) {
+        const uint32_t end = fs::plan_cut(cum.data(), n, groups, k + 1);
+        CHECK(end >= at + 4);
+        for (uint32_t i = fs::item_of_step(cum.data(), n, at); at < end; ++i) {
+          CHECK(i < n);
+          const uint32_t from = cum[i], to = cum[i + 1];
+          if (to <= at) continue;
+          const uint32_t last = std::min(to, end), a = at > from ? at - from - fs::kItemStart : 0, b = last - from - fs::kItemStart;
+          CHECK((at == from || a >= 2) && b <= steps[i] && a < b && (last == to || b >= 2) && done[i] == a);
+          CHECK(at == from || steps[i] - a >= 2);
+          done[i] = b;
+          at = last;
+        }
+      }
+      CHECK(done == steps);
+    }
+    const uint32_t slots = 1 + (uint32_t)(rnd() % 32);
+    std::vector<uint32_t> load(slots), taken(slots, 0);
+    for (uint32_t k = 0; k < slots; ++k) load[k] = (uint32_t)(rnd() % 9);
+    for (uint32_t k = 0; k < slots; ++k) {
+      const uint32_t r = fs::load_rank(load.data(), slots, k);
+      CHECK(r < slots && !taken[r]++);
+      for (uint32_t i = 0; i < slots; ++i) CHECK(load[i] >= load[k] || fs::load_rank(load.data(), slots, i) < r);
+    }
+  }
+}
+
 // The workgroup prefill kernels' walk by tokens: every row of every sub-tile of a context is its token's place, the last
 // token's past a segment's end, and no look-up leaves the segment's table.
 void prefill_token_walk(int rounds) {
@@ -804,6 +843,7 @@ int main() {
   prefill_token_walk(240);
   prefill_order_by_tile(60);
   prefill_split_plan(300);
+  prefill_split_starts(300);
   run(600);
   direct_order();
   direct_rule();
