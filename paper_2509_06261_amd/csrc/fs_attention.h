@@ -227,10 +227,11 @@ __device__ __host__ inline RunGeom run_geom(const ItemCtx& X, int vr) {
 }
 
 // The same in two steps, of which the first is the same for all lanes of a tile that begins at run vb (scalar arithmetic on
-// the device).  The two products of a lane's own division cost as much as eight plain instructions, and three look-ups per tile
-// made them a fifth of a 4-bit tile's work.  The integer formats take this form above head_dim 64; FP16 and FP8, which wait for
-// memory, keep the lane's own division: its shorter chain and fewer scalar registers show in the smallest calls (eight FP16
-// sequences of up to 256 tokens at head_dim 64: 6.45 us, 6.6 in two steps).
+// the device).  The kernels keep the lane's own division, whose two products cost as much as eight plain instructions: it is the
+// shorter chain and takes fewer scalar registers (the direct decode kernel at head_dim 128 holds 13 in vector registers with this
+// form for the integer formats, 2 without).  us, two steps -> own division: eight INT4 sequences of up to 256 tokens, 8 KV heads x 4 of
+// 128, 9.4 -> 8.7; 128 of 1000 - 6000 100 -> 95, at head_dim 256 144 -> 140; four INT8 ones of 50 - 600 10.5 -> 9.7; one FP16 of 100 7.2 ->
+// 7.1.
 struct TileGeom {
   int k, r0;  // block and run within the block of the tile's first run (of the item's last run where vb lies past it)
   int last;   // the tile's runs past this one lie past the item's end

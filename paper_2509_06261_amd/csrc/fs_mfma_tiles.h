@@ -66,7 +66,6 @@ struct Fmt {
   static constexpr int kVRegs = DT == FS_KV_INT4 ? 4 * kVWords : kNE / 2;
   static constexpr int kParBytes = DT == FS_KV_INT8 ? 2 : (DT == FS_KV_INT4 ? 4 : 0);
   static constexpr int kRing = ring_tiles(DT, HD);
-  static constexpr bool kScalarWalk = kParBytes != 0 && HD > 64;  // look-ups of runs by way of the tile's place (tile_geom)
 };
 
 template <int BYTES>
@@ -172,12 +171,8 @@ struct RunLoc {
   int tok0;  // token index of the run's slot 0 (a huge value for a run past the item's end: no column reaches it)
 };
 
-// SCALAR: by way of the tile's place (tile_geom).
-template <bool SCALAR = false>
 __device__ __forceinline__ RunLoc locate(const ItemCtx& X, int vb, int i) {
-  RunGeom r;
-  if constexpr (SCALAR) r = run_geom(X, tile_geom(X, vb), vb, i);
-  else r = run_geom(X, vb + i);
+  const RunGeom r = run_geom(X, vb + i);
   RunLoc L;
   L.start = r.start;
   L.lo = r.lo;
@@ -193,7 +188,7 @@ __device__ __forceinline__ void issue_k(const ItemCtx& X, int vb, int j, int c, 
   using F = Fmt<DT, HD>;
   typedef typename KVec<F::kKLane>::type kvec;
   // row m = c of S^T tile u is slot 4u + (c & 3) of run c >> 2
-  const RunLoc L = locate<F::kScalarWalk>(X, vb, c >> 2);
+  const RunLoc L = locate(X, vb, c >> 2);
   const gptr p = L.base + (uint32_t)((L.start + (c & 3)) * F::kRowBytes) + F::kKLane * j;
 #pragma unroll
   for (int u = 0; u < 2; ++u)
@@ -272,7 +267,7 @@ __device__ __forceinline__ void load_v_row(gptr p, uint32_t (&v)[Fmt<DT, HD>::kV
 template <int DT, int GP, int HD, bool WIDE = false>
 __device__ __forceinline__ void issue_v(const ItemCtx& X, const DevGeom& g, int vb, int j, int c, Tile<DT, GP, HD>& t) {
   using F = Fmt<DT, HD>;
-  const RunLoc L = locate<F::kScalarWalk>(X, vb, j);
+  const RunLoc L = locate(X, vb, j);
   if constexpr (F::kParBytes != 0) {  // parameters first: the softmax needs them before the V rows
     const gptr pk = L.base + 2u * g.kv_tile;
     if constexpr (GP == 16) {
@@ -577,17 +572,8 @@ template <int DT, int GP, int HD, bool DECODE>
 __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t, const float4v (&s)[2], int vb, int j, int c,
                                            float qsum, float alpha, StateT<HD>& st) {
   using F = Fmt<DT, HD>;
-  RunGeom L;
-  bool partial;  // wave-uniform
-  if constexpr (F::kScalarWalk) {  // (no look-up for an interior tile)
-    const TileGeom tg = tile_geom(X, vb);
-    partial = !__all(tile_interior(X, tg, X.len));
-    L = RunGeom{};
-    if (partial) L = run_geom(X, tg, vb, j);
-  } else {
-    L = run_geom(X, vb + j);
-    partial = !__all(L.lo == 0 && L.hi == 8);
-  }
+  const RunGeom L = run_geom(X, vb + j);
+  const bool partial = !__all(L.lo == 0 && L.hi == 8);  // wave-uniform
   const uint32_t n_ok = (uint32_t)max(L.hi - L.lo, 0);  // of a partial tile: slot i of the run is live iff (unsigned)(i - lo) < n_ok
   if (partial) {
     if constexpr (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3) {
@@ -757,13 +743,16 @@ __device__ __forceinline__ void fill_table(uint64_t* s_ptr, const int32_t* table
 template <int DT, int GP, int HD = 128, bool PEEL = false>
 __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g, int v0, const u32x4 (&qb)[HD / 32], float qsum,
                                              float alpha, StateT<HD>& st, int j, int c) {
+  // (opaque: with few scalar registers left the compiler reads them from the arguments again for every tile and waits)
+  DevGeom own = g;
+  if constexpr (PEEL) asm volatile("" : "+s"(own.kv_tile), "+s"(own.par_tile));
   constexpr int NBUF = Fmt<DT, HD>::kRing;
   const int n_tiles = (X.v_end - v0 + 3) >> 2;
   Tile<DT, GP, HD> t[NBUF];
   static_for(std::make_integer_sequence<int, NBUF>{}, [&](auto Bi) {
     constexpr int bi = decltype(Bi)::value;
     issue_k<DT, GP, HD>(X, v0 + bi * 4, j, c, t[bi]);
-    issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, g, v0 + bi * 4, j, c, t[bi]);
+    issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, own, v0 + bi * 4, j, c, t[bi]);
   });
   // One turn of the ring: every slot's tile is consumed and replaced by the tile NBUF further on.
   // (not for INT4, nor INT8 at head_dim 64: with the second copy of the step their tile loops spill registers)
@@ -778,7 +767,7 @@ __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g,
       qk_tile<DT, GP, HD>(t[bi], qb, s);
       issue_k<DT, GP, HD>(X, vb_next, j, c, t[bi]);
       softmax_pv<DT, GP, HD, PEEL>(X, t[bi], s, vb, j, c, qsum, alpha, st);
-      issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, g, vb_next, j, c, t[bi]);
+      issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, own, vb_next, j, c, t[bi]);
     });
   }
   // the last turn: the 1 .. NBUF tiles that are left, no refills (slots past the last tile hold rows nobody needs)
