@@ -22,10 +22,11 @@ FLAGS += os.environ.get("FS_EXTRA_HIPCC_FLAGS", "").split()  # experiments only
 # S^T tile with the vector ALU, which cannot address AccVGPRs.  (Decode at head_dim 256, the only shape there with more
 # than 256 registers: 60 INT8 sequences of 500 - 9000 tokens, 4 KV heads, 146.7 us without the flag, 141.4 with it.)
 FILE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("fs_prefill.hip", "fs_attention_mfma.hip")}
-# Loops begin at a cache line of instructions, so that code elsewhere in a kernel does not shift them: a change in what runs
-# once, at the launch's end, moved the FP8 prefill loop by 20 bytes and cost it 1.5 - 2 % (24 prompts of 512 - 4096 tokens 1298 ->
-# 1323 us; aligned 1299).
-FILE_FLAGS["fs_prefill.hip"].append("-falign-loops=64")
+# Loops begin at half a line of the instruction cache, so that code elsewhere in a kernel does not shift them: a change in what
+# runs once, at the launch's end, moved the FP8 prefill loop by 20 bytes and cost it 1.5 - 2 % (24 prompts of 512 - 4096 tokens 1298 ->
+# 1323 us; aligned 1298).  Whole lines cost the smallest calls of the 16-column kernel 4 % (one INT8 prompt of 60 tokens at head_dim
+# 64 16.9 -> 17.6 us).
+FILE_FLAGS["fs_prefill.hip"].append("-falign-loops=32")
 
 
 TIMELINE_LIB = os.path.join(_DIR, "libfineserve_timeline.so")
