@@ -139,7 +139,7 @@ template <int DT, int HD>
 __device__ __forceinline__ void output_row(const StateT<HD>& st, int r, float Z, float v_static, float (&o)[HD / 16]) {
 #pragma unroll
   for (int e = 0; e < HD / 16; ++e) {
-    o[e] = column_value<DT, true>(st.acc, e, r);
+    o[e] = column_value<DT>(st.acc, e, r);
     if constexpr (Fmt<DT, HD>::kParBytes != 0) o[e] += Z;
     o[e] *= v_static;
   }

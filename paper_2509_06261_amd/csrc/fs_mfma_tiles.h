@@ -399,12 +399,11 @@ __device__ __forceinline__ void k_operands(const typename KVec<Fmt<DT, HD>::kKLa
 
 // The B operands of P V from one lane's share of the eight rows of a run: op(e, b) for every output column e, halves
 // (2q, 2q + 1) of b[q] = the column's elements of slots 2q, 2q + 1.  Two rows' bytes are paired first and only then spread to
-// halves: a 4-bit tile takes 32 instructions like that (48 with SUM_ODD off) and 72 with every word spread by itself, an 8-bit
-// one 48 and 80, an FP8 one 16 pairings for 32.
-// INT4: an odd column's elements are 16-fold; with SUM_ODD each also holds the even column's element below it (the stored
-// byte, 16 odd + even, is exact as a subnormal), and whoever reads the accumulators takes the even column's off
-// (column_value).
-template <int DT, int HD, bool SUM_ODD, typename F>
+// halves: a 4-bit tile takes 48 instructions like that and 72 with every word spread by itself, an 8-bit one 48 and 80, an FP8 one
+// 16 pairings for 32.
+// INT4: an odd column's elements are 16-fold.  (Left in the stored byte, 16 odd + even, for whoever reads the accumulators to take
+// the even column's sum off, they cost 32 instructions and 0.5 - 2 % less time, but an infinite weight then made NaN of Inf.)
+template <int DT, int HD, typename F>
 __device__ __forceinline__ void v_columns(const uint32_t (&v)[8][Fmt<DT, HD>::kVWords], F&& op) {
   constexpr int NE = Fmt<DT, HD>::kNE;
   if constexpr (DT == FS_KV_FP16) {
@@ -441,7 +440,7 @@ __device__ __forceinline__ void v_columns(const uint32_t (&v)[8][Fmt<DT, HD>::kV
         } else {
           const uint32_t x = __builtin_amdgcn_perm(v[2 * q + 1][e >> 3], v[2 * q][e >> 3], 0x0C040C00u + 0x00010001u * ((e & 7) >> 1));
           b0[q] = x & 0x000F000Fu;
-          b1[q] = SUM_ODD ? x : x & 0x00F000F0u;
+          b1[q] = x & 0x00F000F0u;
         }
       }
       op(std::integral_constant<int, e>{}, b0);
@@ -452,14 +451,10 @@ __device__ __forceinline__ void v_columns(const uint32_t (&v)[8][Fmt<DT, HD>::kV
 
 // Column e of an accumulator row whose columns v_columns' operands made: the sum over the stored values (codes, for the
 // integer formats).
-template <int DT, bool SUM_ODD, int NE>
+template <int DT, int NE>
 __device__ __forceinline__ float column_value(const float4v (&acc)[NE], int e, int r) {
   // integer formats: undo the 2^-24 of the subnormal encoding (and the 16 of INT4's odd code positions)
-  if constexpr (DT == FS_KV_INT4) {
-    if (e & 1) return (SUM_ODD ? acc[e][r] - acc[e - 1][r] : acc[e][r]) * kTwo20;
-    return acc[e][r] * kTwo24;
-  }
-  return DT == FS_KV_INT8 ? acc[e][r] * kTwo24 : acc[e][r];
+  return DT == FS_KV_INT8 ? acc[e][r] * kTwo24 : DT == FS_KV_INT4 ? acc[e][r] * ((e & 1) ? kTwo20 : kTwo24) : acc[e][r];
 }
 
 // One lane's elements of a V row -> packed-fp16 registers (layout note above).
@@ -566,8 +561,7 @@ __device__ __forceinline__ void move_reference(StateT<HD>& st, float tmax, int j
 // (j, c) takes head c % 4 and slots 2 (c / 4), + 1 of run j: it fetches those two logits from lane (j, c % 4)
 // (DPP row shifts), loads the parameters of its own two tokens itself, and hands its packed pair of P back to
 // lanes c < 4 (DPP again), which assemble the A operand.  A quarter of the exponentials, no broadcasts.
-// DECODE: the V rows were loaded wide where that pays (wide_v), and odd columns hold the even ones below them (SUM_ODD of
-// v_columns).
+// DECODE: the V rows were loaded wide where that pays (wide_v).
 template <int DT, int GP, int HD, bool DECODE>
 __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t, const float4v (&s)[2], int vb, int j, int c,
                                            float qsum, float alpha, StateT<HD>& st) {
@@ -707,7 +701,7 @@ __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t
   }
   // ---- V rows of the run -> B operands (8x8 in-register transpose) and out += P V ----
   if constexpr (DECODE && wide_v<DT, HD>() && DT == FS_KV_INT4) transpose_banks(t.v);
-  v_columns<DT, HD, DECODE>(t.v, [&](auto E, const u32x4& b) { st.acc[decltype(E)::value] = mfma(pk, b, st.acc[decltype(E)::value]); });
+  v_columns<DT, HD>(t.v, [&](auto E, const u32x4& b) { st.acc[decltype(E)::value] = mfma(pk, b, st.acc[decltype(E)::value]); });
 }
 
 // Head-chunk addresses of blocks k0 .. k0 + nb - 1 of a sequence into this wave's LDS table: every lane of
@@ -734,9 +728,9 @@ __device__ __forceinline__ void fill_table(uint64_t* s_ptr, const int32_t* table
 // never used.  With refills that depend on a condition the compiler cannot know how many loads are outstanding behind
 // the one it needs and waits for all of them, the ones just issued included, which exposes the full memory latency on
 // every tile.
-// PEEL (decode, with the V loads and columns that softmax_pv's DECODE names): the last turn is a second copy of the step without any refill.  Then nothing is requested that no
-// one will read (a ring of rows per item), and nothing is in flight when the caller goes on to write the item's
-// result: that code reuses the tiles' registers and otherwise waits for those loads to land (a per-item timeline
+// PEEL (decode, with the V loads that softmax_pv's DECODE names): the last turn is a second copy of the step without any
+// refill.  Then nothing is requested that no one will read (a ring of rows per item), and nothing is in flight when the
+// caller goes on to write the item's result: that code reuses the tiles' registers and otherwise waits for those loads to land (a per-item timeline
 // showed 4 us per item between the last tile and the end of the output, 4 % of the mixed launch and 14 % of a short
 // one).  Without PEEL every turn refills, the last one past the item's end (runs mapped onto the last run, never used),
 // and the tile count is rounded up to whole turns of masked tiles.
