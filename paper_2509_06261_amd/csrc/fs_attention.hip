@@ -437,7 +437,7 @@ int make_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, void* worksp
   A.n_batches = n_batches;
   const uint64_t split_bytes = launch_split_bytes(p, batches, n_batches);
   int64_t seq_total = 0, qrows = 0;
-  uint64_t part_floats = 0;
+  uint64_t part_floats = 0, launch_bytes = 0;
   for (int i = 0; i < n_batches; ++i) {
     const fs_batch_t& b = batches[i];
     if (b.model < 0 || b.model >= kMaxModels || !p->models[b.model].in_use) {
@@ -492,9 +492,10 @@ int make_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, void* worksp
     B.n_blocks = (uint32_t)(p->pool_bytes / g.block_budget);
     // size tiers: first sequence of tiers 1.., by the share of the batch's KV bytes that lies in front of it
     for (int t = 0; t < kTierSteps; ++t) B.tier_seq[t] = b.n_seq;
+    uint64_t batch_bytes = 0;
+    for (int s = 0; s < b.n_seq; ++s) batch_bytes += head_bytes(b, g, s);
+    launch_bytes += batch_bytes * (uint64_t)g.n_kv_heads;
     if (tiers) {
-      uint64_t batch_bytes = 0;
-      for (int s = 0; s < b.n_seq; ++s) batch_bytes += head_bytes(b, g, s);
       uint64_t before = 0;
       int t = 0;
       for (int s = 0; s < b.n_seq && t < kTierSteps; ++s) {
@@ -533,6 +534,8 @@ int make_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, void* worksp
   A.n_seq_total = (int32_t)seq_total;
   A.n_qrows_total = (int32_t)qrows;
   A.part_capacity = part_floats;
+  // (the line: 256 MB of memory-side cache, see wide_v)
+  for (int i = 0; i < n_batches; ++i) A.b[i].stream_v = launch_bytes > (256ull << 20);
   const uint64_t off_items = kHeaderBytes;
   const uint64_t off_list = align256(off_items + 4ull * (uint64_t)(seq_total + 1));
   const uint64_t off_part = align256(off_list + 32ull * plan.ub_items);

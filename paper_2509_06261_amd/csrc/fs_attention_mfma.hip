@@ -112,6 +112,9 @@ __device__ __forceinline__ void stream_item(const MultiArgs& A, const ItemPlan& 
   st.l = 0.f;
   st.zc = 0.f;
 
+  if constexpr (DT == FS_KV_INT8 && HD == 64) {
+    if (B.stream_v) return stream_tiles<DT, GP, HD, true, true>(X, g, P.v0, qb, qsum, alpha, st, j, c);
+  }
   stream_tiles<DT, GP, HD, true>(X, g, P.v0, qb, qsum, alpha, st, j, c);
 }
 
@@ -511,7 +514,8 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_ker
   const uint8_t* head_base = B.layer_base + (uint64_t)P.head * B.g.head_chunk;
   const int G = B.G;
   float* rec = s_rec + wave * G * (HD + 2);
-  float* part = A.partials + D.part_off[P.b] + (uint64_t)item.rec * (uint64_t)B.part_stride;
+  auto record = [&] { return A.partials + D.part_off[P.b] + (uint64_t)item.rec * (uint64_t)A.b[P.b].part_stride; };
+  float* part = record();
   DirectRange r{P.chunk * B.chunk_runs, 0};
   bool whole = false;
   // one turn per segment of the item (see direct_segment_end): nearly always one
@@ -553,6 +557,12 @@ __global__ __launch_bounds__(kThreads, mfma_wgs_per_cu(HD)) void mfma_direct_ker
     }
     __syncthreads();
     const bool last = end == r.v1;
+    // (Above head_dim 64 the record's place is looked up here: kept over the tiles it pushes out their scalars.  At 64 the smallest
+    // calls are faster with it looked up in front: one sequence of 100 tokens 6.05 us, 6.15 like this.)
+    if constexpr (HD > 64) {
+      asm volatile("" : "+s"(P.b));
+      part = record();
+    }
     if (turn == 0 && last) merge_records<HD, false>(A, P, s_rec, whole, part, nullptr, nullptr);
     else merge_records<HD, true>(A, P, s_rec, false, part, turn ? s_before[turn & 1] : nullptr, last ? nullptr : s_before[(turn + 1) & 1]);
     if (last) return;

@@ -200,17 +200,20 @@ __device__ __forceinline__ void issue_k(const ItemCtx& X, int vb, int j, int c, 
 // INT4 at head_dim 128: a lane's four bytes of a row are a quarter of what a load can carry, and eight such loads touch every
 // line two or three times.  So lane (j, c) loads sixteen bytes (chunk c % 4) of two rows of the run, c / 4 and c / 4 + 4, and
 // the lanes of equal c % 4 exchange their words when the tile's turn comes (transpose_banks).  256 sequences of 1024 - 8192
-// tokens, 8 KV heads: 306 us with narrow loads, 260 with these.
+// tokens, 8 KV heads: 309 us with narrow loads, 278 with these (and the paired spreading of v_columns).
+// INT8 at head_dim 64 has rows of the same 64 bytes.  With the streaming hint 128 sequences of 1000 - 6000 tokens, 8 KV heads (473 MB),
+// take 84 us, without it 98, and with narrow loads 92 and 98; below what the memory-side cache holds (256 MB) calls are faster
+// without: 32 of 500 - 3000, 4 KV heads, 18.4 with it, 16.8 without (narrow loads 19.9 and 16.7).
 // FP16 at head_dim 256: a lane's share of a row is 32 bytes, and two loads of neighbouring sixteen leave every line half used
 // by each; so lane c loads the chunks c and c + 16.
 template <int DT, int HD>
-constexpr bool wide_v() { return (DT == FS_KV_INT4 && HD == 128) || (DT == FS_KV_FP16 && HD == 256); }
+constexpr bool wide_v() { return (DT == FS_KV_INT4 && HD == 128) || (DT == FS_KV_INT8 && HD == 64) || (DT == FS_KV_FP16 && HD == 256); }
 template <int DT, int HD>
 constexpr bool nt_v() { return FS_NT_V && (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3); }
 // The output column that accumulator e of lane (j, c) holds: neighbours for e in steps of four, eight where HD > 64.
 template <int DT, int HD>
 __device__ __forceinline__ int column_of(int c, int e) {
-  if constexpr (wide_v<DT, HD>()) return DT == FS_KV_INT4 ? 8 * (4 * (c & 3) + (c >> 2)) + e : 128 * (e >> 3) + 8 * c + (e & 7);
+  if constexpr (wide_v<DT, HD>()) return DT != FS_KV_FP16 ? HD / 16 * (4 * (c & 3) + (c >> 2)) + e : 128 * (e >> 3) + 8 * c + (e & 7);
   return HD / 16 * c + e;
 }
 
@@ -263,8 +266,8 @@ __device__ __forceinline__ void load_v_row(gptr p, uint32_t (&v)[Fmt<DT, HD>::kV
   }
 }
 
-// WIDE: see wide_v.
-template <int DT, int GP, int HD, bool WIDE = false>
+// WIDE, STREAM: see wide_v.
+template <int DT, int GP, int HD, bool WIDE = false, bool STREAM = false>
 __device__ __forceinline__ void issue_v(const ItemCtx& X, const DevGeom& g, int vb, int j, int c, Tile<DT, GP, HD>& t) {
   using F = Fmt<DT, HD>;
   const RunLoc L = locate(X, vb, j);
@@ -300,10 +303,10 @@ __device__ __forceinline__ void issue_v(const ItemCtx& X, const DevGeom& g, int 
         for (int q = 0; q < 4; ++q) t.v[i][4 * h + q] = x[q];
       }
   } else if constexpr (WIDE) {
-    const gptr p = L.base + g.kv_tile + (uint32_t)((L.start + (c >> 2)) * F::kRowBytes) + 16 * (c & 3);
+    const FS_GLOBAL u32x4* const p = reinterpret_cast<const FS_GLOBAL u32x4*>(L.base + g.kv_tile + (uint32_t)((L.start + (c >> 2)) * F::kRowBytes) + 16 * (c & 3));
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const u32x4 x = stream_load<FS_NT_V>(reinterpret_cast<const FS_GLOBAL u32x4*>(p + u * 4 * F::kRowBytes));
+      const u32x4 x = stream_load<FS_NT_V && (DT == FS_KV_INT4 || STREAM)>(p + u * F::kRowBytes / 4);
 #pragma unroll
       for (int q = 0; q < 4; ++q) t.v[4 * u + q][0] = x[q];
     }
@@ -700,7 +703,7 @@ __device__ __forceinline__ void softmax_pv(const ItemCtx& X, Tile<DT, GP, HD>& t
     pk[3] = from_shl<12>(pp);
   }
   // ---- V rows of the run -> B operands (8x8 in-register transpose) and out += P V ----
-  if constexpr (DECODE && wide_v<DT, HD>() && DT == FS_KV_INT4) transpose_banks(t.v);
+  if constexpr (DECODE && wide_v<DT, HD>() && DT != FS_KV_FP16) transpose_banks(t.v);
   v_columns<DT, HD>(t.v, [&](auto E, const u32x4& b) { st.acc[decltype(E)::value] = mfma(pk, b, st.acc[decltype(E)::value]); });
 }
 
@@ -734,7 +737,7 @@ __device__ __forceinline__ void fill_table(uint64_t* s_ptr, const int32_t* table
 // showed 4 us per item between the last tile and the end of the output, 4 % of the mixed launch and 14 % of a short
 // one).  Without PEEL every turn refills, the last one past the item's end (runs mapped onto the last run, never used),
 // and the tile count is rounded up to whole turns of masked tiles.
-template <int DT, int GP, int HD = 128, bool PEEL = false>
+template <int DT, int GP, int HD = 128, bool PEEL = false, bool STREAM = false>
 __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g, int v0, const u32x4 (&qb)[HD / 32], float qsum,
                                              float alpha, StateT<HD>& st, int j, int c) {
   // (opaque: with few scalar registers left the compiler reads them from the arguments again for every tile and waits)
@@ -746,7 +749,7 @@ __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g,
   static_for(std::make_integer_sequence<int, NBUF>{}, [&](auto Bi) {
     constexpr int bi = decltype(Bi)::value;
     issue_k<DT, GP, HD>(X, v0 + bi * 4, j, c, t[bi]);
-    issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, own, v0 + bi * 4, j, c, t[bi]);
+    issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>(), STREAM>(X, own, v0 + bi * 4, j, c, t[bi]);
   });
   // One turn of the ring: every slot's tile is consumed and replaced by the tile NBUF further on.
   // (not for INT4, nor INT8 at head_dim 64: with the second copy of the step their tile loops spill registers)
@@ -761,7 +764,7 @@ __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g,
       qk_tile<DT, GP, HD>(t[bi], qb, s);
       issue_k<DT, GP, HD>(X, vb_next, j, c, t[bi]);
       softmax_pv<DT, GP, HD, PEEL>(X, t[bi], s, vb, j, c, qsum, alpha, st);
-      issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>()>(X, own, vb_next, j, c, t[bi]);
+      issue_v<DT, GP, HD, PEEL && wide_v<DT, HD>(), STREAM>(X, own, vb_next, j, c, t[bi]);
     });
   }
   // the last turn: the 1 .. NBUF tiles that are left, no refills (slots past the last tile hold rows nobody needs)
