@@ -256,11 +256,13 @@ int fs_decode_status(const void* workspace, void* stream);
  *            host memory (sizes the launch; the kernels read the device copy, and clamp every row index into
  *            n_rows, so a mismatch cannot make them leave the buffers)
  *   workspace: device memory of fs_prefill_workspace_bytes(n_seq) bytes, 256-byte aligned, owned by the caller,
- *            in use until the stream has passed the call (65 MiB of it hold partial results of work items that several
- *            workgroups share; a workspace that ends before them, 8 KiB + 4 n_seq bytes, is accepted and such launches take
- *            longer).  fs_decode_status(workspace, stream) afterwards: bit 0
- *            set if a length or a chunk size was out of range (clamped), bit 2 (value 4) if a block-table entry
- *            named no block of the pool (read as block 0; the affected rows are meaningless).
+ *            in use until the stream has passed the call.  65 MiB of it hold partial results of work items that several
+ *            workgroups share: launches at head_dim 128 of one to four work items per compute unit, at most 512 sequences.
+ *            A workspace of fs_prefill_least_workspace_bytes(n_seq) bytes ends before them and is accepted for every
+ *            call; such launches then keep their items whole, which takes longer and rounds their rows differently.
+ *            fs_decode_status(workspace, stream) afterwards: bit 0 set if a length or a chunk size was out of range
+ *            (clamped), bit 2 (value 4) if a block-table entry named no block of the pool (read as block 0; the
+ *            affected rows are meaningless).
  * At most 16 query heads per KV head (FS_ERR_INVALID otherwise).  head_dim 64, 128 and 256 with at least 8 tokens per
  * block run on the MFMA kernels: the workgroup kernel, which shares unpacked K/V between the waves of a workgroup, or,
  * for head_dim 64 launches of very few items and most head_dim 256 launches of FP8 and integer formats, the 16-column
@@ -271,6 +273,7 @@ int fs_decode_status(const void* workspace, void* stream);
  * chunk whose columns share an MFMA with one of them (up to 31 tokens ahead) may come out as NaN too.
  * Asynchronous on `stream`; no allocation, no host synchronisation. */
 uint64_t fs_prefill_workspace_bytes(int n_seq);
+uint64_t fs_prefill_least_workspace_bytes(int n_seq);
 int fs_prefill_attention(fs_pool* pool, fs_model_t model, int layer, int n_q_heads, float sm_scale, const void* q,
                          const int32_t* block_tables, const int32_t* seq_lens, const int32_t* q_offsets,
                          const int32_t* q_offsets_host, int n_seq, int max_blocks, void* out, float* lse,

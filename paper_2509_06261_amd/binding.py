@@ -29,7 +29,7 @@ EXPORTS = ["fs_pool_create", "fs_pool_destroy", "fs_pool_base", "fs_model_regist
            "fs_pool_stats", "fs_pool_dump", "fs_model_dump_live", "fs_kv_append", "fs_kv_append_multi", "fs_decode_step_multi",
            "fs_decode_workspace_bytes",
            "fs_decode_attention", "fs_decode_attention_multi", "fs_decode_attention_multi_static", "fs_decode_status", "fs_prefill_workspace_bytes",
-           "fs_prefill_attention", "fs_sched_select_batch", "fs_sched_place_models", "fs_model_stats", "fs_pool_set_option",
+           "fs_prefill_least_workspace_bytes", "fs_prefill_attention", "fs_sched_select_batch", "fs_sched_place_models", "fs_model_stats", "fs_pool_set_option",
            "fs_pool_get_option", "fs_pool_last_attention_kernel_ms", "fs_last_error"]
 
 (FS_OPT_DECODE_KERNEL, FS_OPT_SPLIT_BYTES, FS_OPT_KERNEL_TIMING, FS_OPT_PREFILL_COLUMN_BLOCKS, FS_OPT_PREFILL_WAVES,
@@ -106,6 +106,7 @@ def _load():
         "fs_decode_attention_multi_static": (i32, [vp, ctypes.POINTER(fs_batch_t), i32, vp, vp]),
         "fs_decode_status": (i32, [vp, vp]),
         "fs_prefill_workspace_bytes": (u64, [i32]),
+        "fs_prefill_least_workspace_bytes": (u64, [i32]),
         "fs_prefill_attention": (i32, [vp, i32, i32, i32, ctypes.c_float, vp, vp, vp, vp, vp, i32, i32, vp, vp, vp, u64, vp]),
         "fs_sched_select_batch": (i32, [vp, i32, vp, ctypes.c_double, vp, vp, vp, vp]),
         "fs_sched_place_models": (i32, [vp, vp, i32, vp, i32, vp]),
@@ -428,6 +429,10 @@ def fs_decode_status(workspace, stream=None) -> int:
 
 def fs_prefill_workspace_bytes(n_seq: int) -> int:
     return _L.fs_prefill_workspace_bytes(n_seq)
+
+
+def fs_prefill_least_workspace_bytes(n_seq: int) -> int:
+    return _L.fs_prefill_least_workspace_bytes(n_seq)
 
 
 def fs_prefill_attention(pool, model, layer, n_q_heads, sm_scale, q, block_tables, seq_lens, q_offsets, q_offsets_host,

@@ -733,10 +733,10 @@ __device__ __forceinline__ void fill_table(uint64_t* s_ptr, const int32_t* table
 // every tile.
 // PEEL (decode, with the V loads that softmax_pv's DECODE names): the last turn is a second copy of the step without any
 // refill.  Then nothing is requested that no one will read (a ring of rows per item), and nothing is in flight when the
-// caller goes on to write the item's result: that code reuses the tiles' registers and otherwise waits for those loads to land (a per-item timeline
-// showed 4 us per item between the last tile and the end of the output, 4 % of the mixed launch and 14 % of a short
-// one).  Without PEEL every turn refills, the last one past the item's end (runs mapped onto the last run, never used),
-// and the tile count is rounded up to whole turns of masked tiles.
+// caller goes on to write the item's result: that code reuses the tiles' registers and otherwise waits for those loads to
+// land (a per-item timeline showed 4 us per item between the last tile and the end of the output, 4 % of the mixed launch
+// and 14 % of a short one).  Without PEEL every turn refills, the last one past the item's end (runs mapped onto the last
+// run, never used), and the tile count is rounded up to whole turns of masked tiles.
 template <int DT, int GP, int HD = 128, bool PEEL = false, bool STREAM = false>
 __device__ __forceinline__ void stream_tiles(const ItemCtx& X, const DevGeom& g, int v0, const u32x4 (&qb)[HD / 32], float qsum,
                                              float alpha, StateT<HD>& st, int j, int c) {

@@ -1246,11 +1246,13 @@ __device__ __forceinline__ void merge_groups(const PrefillArgs& P, WgState<NCB, 
 
 // ---------------------------------------------------------------------------------------------------------
 // Split items.  In a launch of few items per compute unit the longest context, or the second round of a few items, decides:
-// four FP8 chunks of 512 tokens behind 4700 - 14700 (256 items, one per unit) took 382 us, what 115 steps take although the mean is
-// 76; now 320 (988 TFLOP/s: with no unit idle the chip's power bounds a step, 4.0 us against 3.3).  Such a launch lays its items' steps (128 tokens each) one after the other and cuts the row into equal ranges, one per
-// workgroup (SplitPlan): an item that a cut divides is worked on in pieces by neighbouring workgroups, each of which leaves its
+// four FP8 chunks of 512 tokens behind 4700 - 14700 (256 items, one per unit) took 383 us, what 115 steps take although the mean
+// is 76; now 300 (with no unit idle the chip's power bounds a step, 3.8 us against 3.3).  Such a launch lays its items' steps
+// (128 tokens each, and two for an item's start) one after the other and cuts the row into equal ranges, one per workgroup
+// (SplitPlan): an item that a cut divides is worked on in pieces by neighbouring workgroups, each of which leaves its
 // accumulators, references and sums (fp32, as they stand in the registers) in the workspace and counts; whoever counts
 // last adds the pieces up, in the order of the context whoever that is, and writes the rows.  Nobody waits for anybody.
+// (One workgroup reads all pieces of an item, 1.5 us each; a piece stands for eight steps of 3 us or more that others took.)
 // A counter is a 64-bit word in the workspace that nothing clears before the launch: the count stands behind a
 // 48-bit mark without which the word reads as zero, and the last piece of an item takes the mark away again.
 // ---------------------------------------------------------------------------------------------------------
@@ -2410,10 +2412,10 @@ extern "C" uint64_t fs_prefill_timeline_bytes(uint64_t* group_rows, uint64_t* it
 static uint64_t pieces_at(int n_seq) { return align256(kHeaderBytes + 4ull * ((uint64_t)n_seq + 1)); }
 #ifdef FS_TIMELINE
 uint64_t fs_prefill_workspace_bytes(int n_seq) { return n_seq < 1 ? 0 : align256(pieces_at(n_seq) + kPiecesBytes) + kPfTimelineBytes; }
-static uint64_t least_workspace_bytes(int n_seq) { return fs_prefill_workspace_bytes(n_seq); }
+uint64_t fs_prefill_least_workspace_bytes(int n_seq) { return fs_prefill_workspace_bytes(n_seq); }
 #else
 uint64_t fs_prefill_workspace_bytes(int n_seq) { return n_seq < 1 ? 0 : pieces_at(n_seq) + kPiecesBytes; }
-static uint64_t least_workspace_bytes(int n_seq) { return pieces_at(n_seq); }
+uint64_t fs_prefill_least_workspace_bytes(int n_seq) { return n_seq < 1 ? 0 : pieces_at(n_seq); }
 #endif
 
 int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads, float sm_scale, const void* q,
@@ -2529,7 +2531,7 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
     set_error("prefill attention: FP8 model has no scales (fs_model_set_fp8_scales)");
     return FS_ERR_INVALID;
   }
-  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < least_workspace_bytes(n_seq)) {
+  if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < fs_prefill_least_workspace_bytes(n_seq)) {
     set_error("prefill attention: workspace missing, not 256-byte aligned or too small (see fs_prefill_workspace_bytes)");
     return workspace && !((uintptr_t)workspace & 255) ? FS_ERR_NOMEM : FS_ERR_INVALID;
   }
@@ -2595,8 +2597,8 @@ int fs_prefill_attention(fs_pool* p, fs_model_t model, int layer, int n_q_heads,
   // no more items than compute units: a direct launch (see "Direct launches")
   P.direct = P.tf_cache == 2 && items <= (uint64_t)p->n_cu;
   // Split items: up to four of 16 blocks per compute unit (the queue deals more as evenly: 3 prompts of 2000 - 6000 tokens, 3.8 per
-  // unit, 509 us with either), where the tables can hold eight steps (the workgroups, who see the lengths, decide: see lay_plan) and the
-  // workspace has room for the pieces.
+  // unit, 509 us with either), where the tables can hold eight steps (the workgroups, who see the lengths, decide: see lay_plan)
+  // and the workspace has room for the pieces.
   const bool deq_on = p->opt.prefill_deq || g.kv_dtype == FS_KV_FP16 || g.kv_dtype == FS_KV_FP8_E4M3;
   const uint32_t split_groups = std::min<uint32_t>(kSplitGroups, (uint32_t)p->n_cu & ~7u);
   const int64_t capacity = std::min<int64_t>((int64_t)max_blocks * g.tokens_per_block, 0x7fffffff);
