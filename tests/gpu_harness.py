@@ -6,6 +6,8 @@ applied to source rows regenerated on the host by fs_inputs.gen, placed by its o
 """
 from __future__ import annotations
 
+import os
+
 import numpy as np
 
 import oracle
@@ -14,6 +16,7 @@ from fs_inputs import gen, workloads
 TOL_FP16 = 2e-3   # max-abs, FP16 KV (benchmark definition)
 TOL_QUANT = 4e-3  # max-abs, FP8 / INT8 / INT4 KV
 TOL_LSE = 1e-3
+THREADS = min(16, int(os.environ.get("OMP_NUM_THREADS") or 8))  # of the oracle, whose results do not depend on it
 
 
 def prefill_lse_tolerance(sm_scale, head_dim, staged_dequant):
@@ -129,7 +132,7 @@ class Parity:
             del mem1
         q = gen.normal_q(self.wl.seed, s.tag, layer, seqs, s.n_q_heads, s.head_dim)
         scale = 1.0 / np.sqrt(s.head_dim) if sm_scale is None else sm_scale
-        out, lse = oracle.decode_attention(mem0, g, layer, s.n_q_heads, scale, q, ctab, lens, ks, vs, n_threads=8)
+        out, lse = oracle.decode_attention(mem0, g, layer, s.n_q_heads, scale, q, ctab, lens, ks, vs, n_threads=THREADS)
         return dict(real_blocks=real_blocks, mem=mem0, written=written, out=out, lse=lse, q=q, ctab=ctab, lens=lens, ks=ks,
                     vs=vs, layer=layer)
 
@@ -167,7 +170,7 @@ class Parity:
         sub_off = np.concatenate([[0], np.cumsum(n_new[seqs])]).astype(np.int32)
         o_out, o_lse = oracle.prefill_attention(ref["mem"], self.ogeom[k], layer, s.n_q_heads, scale,
                                                 q[rows], ref["ctab"], ref["lens"], sub_off, ref["ks"], ref["vs"],
-                                                n_threads=8)
+                                                n_threads=THREADS)
         tol = TOL_FP16 if s.kv_dtype == workloads.FP16 else TOL_QUANT
         # Rows early in a prompt average few values: outputs reach |4| where rounding the result to fp16 alone costs
         # up to |ref| * 2^-11 (decode outputs, averages over hundreds of tokens, stay below 1).  That share is
@@ -239,7 +242,7 @@ class Parity:
         sub_off = np.concatenate([[0], np.cumsum(n_new)]).astype(np.int32)
         o_out, o_lse = oracle.prefill_attention(ref["mem"], self.ogeom[k], layer, s.n_q_heads, scale,
                                                 np.concatenate(q_rows), np.stack(ctab), np.asarray(o_lens, np.int32),
-                                                sub_off, ref["ks"], ref["vs"], n_threads=8)
+                                                sub_off, ref["ks"], ref["vs"], n_threads=THREADS)
         rows = torch.from_numpy(np.concatenate(where)).to(dev)
         out = out_d[rows].cpu().numpy().astype(np.float64)
         lse = lse_d[rows].cpu().numpy().astype(np.float64)
