@@ -41,7 +41,7 @@ struct DevBatch {
   int32_t R;
   uint32_t r_magic;      // ceil(2^32 / R), 0 for R = 1: run / R == umulhi(run, r_magic) while run * R < 2^32
   uint32_t n_blocks;     // blocks of this model's size the pool holds: valid table entries are 0 .. n_blocks - 1
-  int32_t stream_v;      // decode: 1 = the launch reads more than the memory-side cache holds (see wide_v)
+  int32_t stream_v;      // decode: 1 = INT8 V rows carry the streaming hint (see FS_NT_V and wide_v)
 };
 
 // Workspace header words (uint32 unless noted).

@@ -534,8 +534,12 @@ int make_plan(fs_pool* p, const fs_batch_t* batches, int n_batches, void* worksp
   A.n_seq_total = (int32_t)seq_total;
   A.n_qrows_total = (int32_t)qrows;
   A.part_capacity = part_floats;
-  // (the line: 256 MB of memory-side cache, see wide_v)
-  for (int i = 0; i < n_batches; ++i) A.b[i].stream_v = launch_bytes > (256ull << 20);
+  // (the line: 256 MB of memory-side cache, see wide_v; from head_dim 128 on also rows that are whole lines, see FS_NT_V)
+  for (int i = 0; i < n_batches; ++i) {
+    DevBatch& B = A.b[i];
+    const bool whole_lines = (((uint64_t)B.layer_base | B.g.block_budget | B.g.head_chunk | B.g.kv_tile) & 127) == 0;
+    B.stream_v = launch_bytes > (256ull << 20) && (B.g.D == 64 || whole_lines);
+  }
   const uint64_t off_items = kHeaderBytes;
   const uint64_t off_list = align256(off_items + 4ull * (uint64_t)(seq_total + 1));
   const uint64_t off_part = align256(off_list + 32ull * plan.ub_items);

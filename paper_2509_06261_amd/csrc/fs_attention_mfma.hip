@@ -112,7 +112,7 @@ __device__ __forceinline__ void stream_item(const MultiArgs& A, const ItemPlan& 
   st.l = 0.f;
   st.zc = 0.f;
 
-  if constexpr (DT == FS_KV_INT8 && HD == 64) {
+  if constexpr (DT == FS_KV_INT8) {
     if (B.stream_v) return stream_tiles<DT, GP, HD, true, true>(X, g, P.v0, qb, qsum, alpha, st, j, c);
   }
   stream_tiles<DT, GP, HD, true>(X, g, P.v0, qb, qsum, alpha, st, j, c);

@@ -81,10 +81,14 @@ struct KVec<8> {
 // Measured on the four-model pool: the hint helps loads that cover whole 128-byte lines per instruction (the V
 // rows: + 1.2 % on the kernel) and costs where an instruction takes half a line of each of 16 rows (the K operand
 // pattern: - 0.3 %, and - 2.5 % with both), so V rows carry it and K rows do not.
-// The rows of the integer formats begin anywhere in a line (their tiles are padded to 16 bytes only), so that two
-// instructions share a line: with the hint the second one fetches it again (86 INT8 sequences of 2381 - 7152 tokens, 8 KV heads:
-// 165 us without, 182 with it; FP8, whose rows are whole lines, 134 and 126).  The wide INT4 loads (wide_v) take four
-// neighbouring rows per instruction and gain by it again (48 sequences of 4000 - 6000 tokens, 8 KV heads: 58 us, 62 without).
+// The rows of the integer formats begin anywhere in a line (their tiles are padded to 16 bytes only) unless the bytes of a head's chunk
+// happen to be whole lines.  Where two instructions share a line, the hint makes the second one fetch it again; where the memory-side
+// cache (256 MB) holds what the launch reads, it keeps the next step from finding it there.  So INT8 carries it from head_dim 128 on in
+// launches of more than 256 MB over whole lines (DevBatch::stream_v picks a copy of the tile loop, STREAM below).  8 KV heads of 128,
+// us without / with it: 64 sequences of 3000 - 6000 tokens 114 / 97 and 128 of 4000 - 8000 285 / 257 over whole lines (31 tokens a block),
+// 114 / 119 and 286 / 306 over split ones (15 tokens); 32 of 500 - 3000 (115 MB) 30.0 / 30.6 and 31.2 / 35.7.
+// FP8 rows are whole lines always: 86 sequences of 2381 - 7152 tokens 134 / 126.  The wide INT4 loads (wide_v) take four
+// neighbouring rows per instruction and gain by it at any alignment (48 sequences of 4000 - 6000 tokens, 8 KV heads: 62 / 58).
 #ifndef FS_NT_K
 #define FS_NT_K 0
 #endif
@@ -208,8 +212,8 @@ __device__ __forceinline__ void issue_k(const ItemCtx& X, int vb, int j, int c, 
 // by each; so lane c loads the chunks c and c + 16.
 template <int DT, int HD>
 constexpr bool wide_v() { return (DT == FS_KV_INT4 && HD == 128) || (DT == FS_KV_INT8 && HD == 64) || (DT == FS_KV_FP16 && HD == 256); }
-template <int DT, int HD>
-constexpr bool nt_v() { return FS_NT_V && (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3); }
+template <int DT, int HD, bool STREAM = false>
+constexpr bool nt_v() { return FS_NT_V && (DT == FS_KV_FP16 || DT == FS_KV_FP8_E4M3 || STREAM); }
 // The output column that accumulator e of lane (j, c) holds: neighbours for e in steps of four, eight where HD > 64.
 template <int DT, int HD>
 __device__ __forceinline__ int column_of(int c, int e) {
@@ -237,32 +241,32 @@ __device__ __forceinline__ void transpose_banks(uint32_t (&v)[8][1]) {
   }
 }
 
-template <int DT, int HD>
+template <int DT, int HD, bool STREAM = false>
 __device__ __forceinline__ void load_v_row(gptr p, uint32_t (&v)[Fmt<DT, HD>::kVWords]) {
   constexpr int kVBytes = Fmt<DT, HD>::kVBytes;
   if constexpr (kVBytes == 32) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const u32x4 x = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL u32x4*>(p) + h);
+      const u32x4 x = stream_load<nt_v<DT, HD, STREAM>()>(reinterpret_cast<const FS_GLOBAL u32x4*>(p) + h);
       v[4 * h + 0] = x[0];
       v[4 * h + 1] = x[1];
       v[4 * h + 2] = x[2];
       v[4 * h + 3] = x[3];
     }
   } else if constexpr (kVBytes == 16) {
-    const u32x4 x = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL u32x4*>(p));
+    const u32x4 x = stream_load<nt_v<DT, HD, STREAM>()>(reinterpret_cast<const FS_GLOBAL u32x4*>(p));
     v[0] = x[0];
     v[1] = x[1];
     v[2] = x[2];
     v[3] = x[3];
   } else if constexpr (kVBytes == 8) {
-    const u32x2 x = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL u32x2*>(p));
+    const u32x2 x = stream_load<nt_v<DT, HD, STREAM>()>(reinterpret_cast<const FS_GLOBAL u32x2*>(p));
     v[0] = x[0];
     v[1] = x[1];
   } else if constexpr (kVBytes == 4) {
-    v[0] = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL uint32_t*>(p));
+    v[0] = stream_load<nt_v<DT, HD, STREAM>()>(reinterpret_cast<const FS_GLOBAL uint32_t*>(p));
   } else {
-    v[0] = stream_load<nt_v<DT, HD>()>(reinterpret_cast<const FS_GLOBAL uint16_t*>(p));
+    v[0] = stream_load<nt_v<DT, HD, STREAM>()>(reinterpret_cast<const FS_GLOBAL uint16_t*>(p));
   }
 }
 
@@ -313,7 +317,7 @@ __device__ __forceinline__ void issue_v(const ItemCtx& X, const DevGeom& g, int 
   } else {
     const gptr p0 = L.base + g.kv_tile + (uint32_t)(L.start * F::kRowBytes) + c * F::kVBytes;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) load_v_row<DT, HD>(p0 + i * F::kRowBytes, t.v[i]);
+    for (int i = 0; i < 8; ++i) load_v_row<DT, HD, STREAM>(p0 + i * F::kRowBytes, t.v[i]);
   }
 }
 

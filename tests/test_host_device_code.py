@@ -49,7 +49,7 @@ def test_decode_and_column_kernels_hold_their_scalars(code_objects):
             name = re.search(r"^\s+\.name:\s+(\S+)", kernel, flags=re.M)
             spills[name.group(1)] = (int(re.search(r"\.sgpr_spill_count:\s+(\d+)", kernel).group(1)),
                                      int(re.search(r"\.vgpr_spill_count:\s+(\d+)", kernel).group(1)))
-    most = {"mfma_direct_kernelILi64E": 8, "mfma_direct_kernelILi128E": 2, "mfma_direct_kernelILi256E": 8, "mfma_attention_kernelILi64E": 0,
+    most = {"mfma_direct_kernelILi64E": 8, "mfma_direct_kernelILi128E": 4, "mfma_direct_kernelILi256E": 8, "mfma_attention_kernelILi64E": 0,
             "mfma_attention_kernelILi128E": 0, "mfma_attention_kernelILi256E": 0, "prefill_kernelILi64E": 28, "prefill_kernelILi128E": 28,
             "prefill_kernelILi256E": 28}
     for key, limit in most.items():
