@@ -2029,6 +2029,7 @@ struct SplitPlan {
   uint32_t* cut;  // [workgroups + 1]
   uint16_t* order;     // [8][kSplitItems][workgroups / 8] whole items: XCD, round, workgroup of the XCD -> the XCD's item (0xffff: none) ...
   bool sorted = false; // ... where it has more of them than workgroups
+  bool weighed = false;  // steps are those of weighed() (some tiles have all their waves, others less)
   uint32_t turns = 1;  // sequences whose tiles are dealt one from each in turn (see plan_item)
 };
 constexpr uint32_t split_plan_bytes(uint32_t plan_items) { return (plan_items + 1 + kSplitGroups + 1) * 4 + kSplitItems * kSplitGroups * 2; }
@@ -2045,8 +2046,15 @@ constexpr uint32_t split_plan_bytes(uint32_t plan_items) { return (plan_items + 
 // 40 (72 / 52) 311 -> 282 / 255 -> 233 / 275 -> 242, 72 (107 / 93) 493 -> 494 / 401 -> 407 / 430 -> 419, 88 (127 / 114) 589 -> 600 / 483 -> 495 / 507 ->
 // 515; of 512: 4 behind 1500 - 6000 (45 / 30) 171 -> 146 / 156 -> 136 / 170 -> 143, 6 behind 1500 (32 / 25) 129 -> 126 / 119 -> 116 / 128 -> 124; one
 // prompt of 5000 tokens (62 / 55) 244 -> 249 / 224 -> 226 / 242 -> 243, of 4000 (34 / 32) 152 -> 192 / 136 -> 185 / 149 -> 193 (steps alone).
-// Whole items are dealt by their steps, most first, the first two rounds there and back over an XCD's workgroups and the others to
-// whoever has least so far (item_rank, snake, load_rank).  Against the ticket queue behind a preparation launch, us: one prompt of 3000
+// A last tile's waves without tokens leave the others more of their SIMDs: where tiles differ in that, its steps weigh less (live_sixths;
+// 32 chunks behind 4000, us of 26 - 32 / 40 / 48 / 64 tokens: FP16 106 - 113 / 141 / 150 / 169, FP8 91 at 32, 121 / 137 at 48 and 64).
+// Whole items are dealt the first two rounds there and back over an XCD's workgroups and the others to whoever has least so far
+// (snake, load_rank).  Where a sequence's tiles see mostly the same tokens, in their order: tiles of one sequence run side by side and find
+// its lines in the XCD's L2.  Elsewhere -- prompts, whose tiles see from none to all -- by their steps, most first (item_rank).
+// us, queue / by steps / by weighed steps / in order: chunks of 154, FP16, 24 behind 689 - 1054 94 / 111 / 103 / 88, 33 130 / 146 / 131 / 118, 33
+// behind 1500 - 2500 252 / 268 / 257 / 229; of 100, 60 behind 600 - 1100 153 / 160 / 160 / 154; of 512, 16 behind 600 - 1500 170 / 160 / 160 /
+// 155; prompts, five of 600 - 2000, 131 / 121 / 121 / 138.
+// Against the ticket queue behind a preparation launch, us: one prompt of 3000
 // 138 -> 104 / 128 -> 95 / 140 -> 102; 12 chunks of 300 behind 100 - 16000 705 -> 537 / 594 -> 450 / 664 -> 491; 40 of 64 behind 300 - 1200 79 ->
 // 59 / 74 -> 56 / 78 -> 57; three prompts of 1200 - 2000 121 -> 99 (FP16), eight of 256 - 1000 71 -> 66 (FP8); three and four items per unit
 // the same within 2 %.  A launch of an item per unit whose contexts are alike pays the plan's first look, 1 us of 55 - 75.
@@ -2071,13 +2079,31 @@ __device__ __forceinline__ bool lay_plan(const PrefillArgs& P, SplitPlan& plan, 
   // the sequences: whether they bring the same number of tiles, and the tokens that the query tiles of one head see
   const uint32_t tiles = list.tf[1];
   bool same = true;
-  float seen = 0.f;
+  bool full = false;  // some tile has all its waves
+  float seen = 0.f, light = 0.f, behind = 0.f;  // (light: what waves without tokens take off that; behind: of it, before the new tokens)
+  auto sixths = [&](int n_new, int qt) {
+    const int tokens = min(n_new - qt * q_wg, q_wg), own = P.tpt * ncb;
+    return live_sixths((uint32_t)((tokens + own - 1) / own), (uint32_t)nw);
+  };
   for (int k = lane; k < P.b.n_seq; k += 64) {
     const uint32_t t = list.tf[k + 1] - list.tf[k];
     const SeqShape s = list.shape[list.seq[k]];
     same = same && t == tiles;
-    if (t > 0) seen += (float)t * ((float)(s.len - s.n_new) + 0.5f * (float)(t - 1) * (float)q_wg) + (float)s.n_new;
+    if (t > 0) {
+      const uint32_t w = sixths(s.n_new, (int)t - 1);
+      full = full || t > 1 || w == 6;
+      seen += (float)t * ((float)(s.len - s.n_new) + 0.5f * (float)(t - 1) * (float)q_wg) + (float)s.n_new;
+      behind += (float)t * (float)(s.len - s.n_new);
+      light += (float)s.len * (float)(6 - w) * (1.f / 6.f);
+    }
   }
+  plan.weighed = __any(full);  // (uniform; else all steps are short alike)
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    seen += __shfl_xor(seen, off, 64);
+    behind += __shfl_xor(behind, off, 64);
+  }
+  const bool shared = 2.f * behind >= seen;  // (uniform) a sequence's tiles see mostly the same tokens
   const bool rows = P.by_tile && P.b.g.H % 8 == 0 && tiles * (uint32_t)(P.b.g.H / 8) <= slots;
   const bool even = __all(same) && (tiles == 1 || rows);  // (uniform)
   auto worth = [&](uint32_t mean, uint32_t busy) { return busy > mean + mean / (even ? 16 : 4) + 6; };
@@ -2085,8 +2111,11 @@ __device__ __forceinline__ bool lay_plan(const PrefillArgs& P, SplitPlan& plan, 
   if (!plan.sorted) {
     // An item a workgroup at most: none takes longer than the longest sequence's last tile, and the mean is known from below: enough
     // for the launches whose items are all alike.
+    if (plan.weighed) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) seen += __shfl_xor(seen, off, 64);
+      for (int off = 32; off > 0; off >>= 1) light += __shfl_xor(light, off, 64);
+      seen -= light;
+    }
     const float mean = (0.9999f * seen * (float)P.b.g.H / (float)step_tokens + (float)(kItemStart * total)) / (float)groups;
     if (!worth((uint32_t)mean, (uint32_t)((list.shape[list.seq[0]].len - 1) / step_tokens + 1) + kItemStart)) return false;
   }
@@ -2100,6 +2129,7 @@ __device__ __forceinline__ bool lay_plan(const PrefillArgs& P, SplitPlan& plan, 
                                    : fs::decode_item(list.tf, P.b.n_seq, item, (uint32_t)P.b.g.H, seq, head, qt))) {
       const SeqShape s = list.shape[list.seq[seq]];
       steps = (uint32_t)(((int64_t)s.len - s.n_new + min((qt + 1) * q_wg, s.n_new) + step_tokens - 1) / step_tokens);
+      if (plan.weighed) steps = weighed(steps, sixths(s.n_new, qt));
     }
     if (steps) steps += kItemStart;
     if (u < per) cum[u] = steps;
@@ -2116,7 +2146,7 @@ __device__ __forceinline__ bool lay_plan(const PrefillArgs& P, SplitPlan& plan, 
       const uint32_t u = lane + 64 * h;
       if (u + 1 < per) falling = falling && cum[u] >= cum[u + 1];
     }
-    falling = __all(falling);
+    falling = shared || __all(falling);
 #pragma unroll 1
     for (int h = 0; h < halves; ++h) {
       const uint32_t u = lane + 64 * h;
@@ -2285,7 +2315,7 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
         ++i_plan;
         if (to <= at) continue;  // (an item without steps)
         piece.step = at > from ? (int)(at - from - kItemStart) : 0;
-        piece.end = (int)(min(to, end) - from - kItemStart);
+        piece.end = to <= end ? 0x7fffffff : (int)(end - from - kItemStart);
         uint32_t last;
         piece_owners(plan.cut, me, from, to, piece.first, last);
         piece.first = __builtin_amdgcn_readfirstlane(piece.first);
@@ -2330,6 +2360,14 @@ __global__ __launch_bounds__(NW * 64, WPC) void prefill_wg_kernel(PrefillArgs P)
       // scratch any more, and 64 prompts of 512 - 4096 tokens run 4232 -> 4126 us)
       head = __builtin_amdgcn_readfirstlane(head);
       qt = __builtin_amdgcn_readfirstlane(qt);
+      if constexpr (SPLIT) {
+        if (split && plan.weighed) {  // (steps of the plan -> steps of the item; the next piece's step comes of the same number)
+          const int own = P.tpt * NCB, tokens = min(shape.n_new - qt * own * NW, own * NW);
+          const uint32_t w = live_sixths((uint32_t)((tokens + own - 1) / own), NW);
+          piece.step = (int)step_at((uint32_t)piece.step, w);
+          if (piece.end != 0x7fffffff) piece.end = (int)step_at((uint32_t)piece.end, w);
+        }
+      }
 #ifdef FS_TIMELINE
       const uint64_t tl_begin = wall_clock64();
 #endif

@@ -51,6 +51,11 @@ constexpr uint32_t kSplitGroups = 256;  // most workgroups of such a launch
 constexpr uint32_t kSplitLeast = 8;     // fewest steps of a range
 constexpr uint32_t kItemStart = 2;      // steps that an item's start is worth
 constexpr uint32_t kSplitItems = 4;     // most items per compute unit of a launch with split items
+// What a step takes where only `live` of a workgroup's `waves` waves (two on each SIMD) have query tokens, in sixths of a step of all.
+__device__ __host__ inline uint32_t live_sixths(uint32_t live, uint32_t waves) { return 2 * live <= waves ? 4 : 4 * live <= 3 * waves ? 5 : 6; }
+// An item's steps in such time, and the step that place x of them stands for: none of a piece's two or more gets lost.
+__device__ __host__ inline uint32_t weighed(uint32_t steps, uint32_t sixths) { return steps - steps * (6 - sixths) / 6; }
+__device__ __host__ inline uint32_t step_at(uint32_t x, uint32_t sixths) { return x * 6 / sixths; }
 // Place u of an XCD's `per` items when `turns` sequences of per / turns items each are dealt one item from each in turn.
 __device__ __host__ inline uint32_t dealt(uint32_t u, uint32_t per, uint32_t turns) { return u % turns * (per / turns) + u / turns; }
 // Place i of the plan's order, an XCD's items one after the other (per each): which item of the launch that is.

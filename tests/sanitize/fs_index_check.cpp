@@ -774,6 +774,20 @@ void prefill_split_starts(int rounds) {
   }
 }
 
+// Items whose steps weigh less: places stand for the item's steps in order, and two places at either end are a step at least.
+void prefill_weighed_steps() {
+  for (uint32_t live = 1; live <= 8; ++live) {
+    const uint32_t w = fs::live_sixths(live, 8);
+    CHECK(w >= 4 && w <= 6 && (live < 8 || w == 6) && (live == 1 || w >= fs::live_sixths(live - 1, 8)));
+    for (uint32_t steps = 1; steps < 3000; ++steps) {
+      const uint32_t places = fs::weighed(steps, w);
+      CHECK(places >= 1 && places <= steps && 6 * places >= w * steps);
+      for (uint32_t x = 2; x + 2 <= places; ++x) CHECK(fs::step_at(x, w) > fs::step_at(x - 1, w) && fs::step_at(x, w) < steps);
+    }
+    CHECK(fs::weighed(1u << 25, w) <= 1u << 25 && fs::step_at(fs::weighed(1u << 25, w), w) >= 1u << 25);
+  }
+}
+
 // The workgroup prefill kernels' walk by tokens: every row of every sub-tile of a context is its token's place, the last
 // token's past a segment's end, and no look-up leaves the segment's table.
 void prefill_token_walk(int rounds) {
@@ -844,6 +858,7 @@ int main() {
   prefill_order_by_tile(60);
   prefill_split_plan(300);
   prefill_split_starts(300);
+  prefill_weighed_steps();
   run(600);
   direct_order();
   direct_rule();

@@ -24,6 +24,8 @@ SHAPES = {
     "two-kv-heads": (2, 4, 24, [900, 1100, 1500, 2300, 3000, 3500, 4100, 6000], [900, 1000, 1024, 1000, 1100, 1024, 1024, 1024], [0, 2]),
     "four-kv-heads": (4, 4, 12, [900, 1100, 1500, 2300, 3000, 3500, 4100, 6000], [500, 512, 512, 600, 512, 512, 500, 512], [0, 3]),
     "five-kv-heads": (5, 2, 16, [1100, 1500, 2300, 3000, 3500, 4100, 6000], [1000, 1024, 1000, 1100, 1024, 1300, 1324], [0]),
+    # last tiles of 26 and 36 tokens (four and five waves of eight with tokens, whose steps weigh less), cut like the whole ones
+    "light": (8, 4, 16, [9000, 8100] + [1500] * 10, [154, 164] + [154] * 10, [0, 1]),
     "multi-head": (40, 1, 15, [400, 900, 1500, 5000], [300, 256, 600, 700], [0, 1]),
 }
 
@@ -71,7 +73,7 @@ class Watched:
 
 @pytest.mark.parametrize("shape,dtype", [("even", FP8), ("even", INT4), ("segments", FP16), ("segments", INT8), ("diagonals", FP16),
                                          ("diagonals", INT4), ("three-heads", INT8), ("one-kv-head", FP8), ("two-kv-heads", INT4),
-                                         ("four-kv-heads", FP16), ("five-kv-heads", INT8), ("multi-head", INT4)])
+                                         ("four-kv-heads", FP16), ("five-kv-heads", INT8), ("multi-head", INT4), ("light", FP16), ("light", INT8)])
 def test_pieces_against_the_oracle(shape, dtype):
     import gpu_harness
 
